@@ -102,17 +102,20 @@ hipError_t launch_pixel_scalars(float* sx, float* sy, int W, int H, hipStream_t 
 }
 
 // ------------------------------------------------------------------------------------------
-// pack: one workgroup per environment.  Each wave takes whole z layers: the layer's material bytes
-// are prefetched into registers one layer ahead, go through LDS and leave again as the batch's own
-// copy.  Grids of one word per row (X, Y <= 64, X a multiple of 4): lane j turns x row j into bits
-// dword by dword (non-zero bytes -> nibble with a carry trick and one dot product), and the y rows
-// are the 64x64 bit transpose of the x rows, done across lanes without memory.  Other grids: lane r
-// gathers row r cell by cell.  Rows leave as one coalesced store per 64 rows.
-// A layer of air (no byte set) skips LDS and the transpose: its rows are written as zero words.
+// pack: one workgroup per environment, whole z layers per wave.  Two kernels, chosen by the host (launch_pack):
+//   pack_kernel      grids of one word per row whose layers are whole 16-byte pieces at aligned addresses: a layer is
+//                    prefetched into registers one layer ahead, goes through LDS and leaves again as the batch's
+//                    own copy; lane j turns x row j into bits dword by dword.
+//   pack_any_kernel  every other size and alignment: a layer becomes a plain bit string in LDS (bit c = cell c of the
+//                    layer) as it arrives, and the rows are cut out of that string at any bit offset.
+// In both the y rows are the 64x64 bit transposes of the x rows, done across lanes without memory, and rows leave as
+// one coalesced store per 64 rows.  A layer of air (no byte set) is written as zero rows without more work.
 // ------------------------------------------------------------------------------------------
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kPackThreads = 256;
+constexpr int kPackAnyWaves = 16;       // most waves of a pack_any_kernel workgroup
+constexpr int kPackAnyPieces = 3;       // 16-byte pieces of a layer each of its lanes keeps in flight
 
 // Colour table entry (a6): round-to-nearest(palette value * face intensity) per channel as two
 // separately rounded float32 operations (multiply, then add 0.5), floor, clamp to 255; r | g<<8 | b<<16.
@@ -130,26 +133,26 @@ __device__ __forceinline__ uint32_t shade_entry(const uint8_t* rgb, float intens
     return packed;
 }
 
-// 1 if the byte is non-zero (one v_min_u32; written as asm because the compiler otherwise expands the
-// idiom into a compare and a select)
-__device__ __forceinline__ uint32_t nonzero(uint32_t byte)
+// The environment's palette: private copy, and the colour table lut[face][material].
+__device__ __forceinline__ void pack_palette(const uint8_t* pal_src, uint8_t* pal_dst, uint32_t* lut_dst, int env,
+                                             int materials_plus_one, const Intensities& I, int threads)
 {
-    uint32_t r;
-    asm("v_min_u32 %0, 1, %1" : "=v"(r) : "v"(byte));
-    return r;
+    const uint8_t* ps = pal_src + (size_t)env * materials_plus_one * 3;
+    uint8_t* pd = pal_dst + (size_t)env * materials_plus_one * 3;
+    uint32_t* lut = lut_dst + (size_t)env * kNumFaces * materials_plus_one;
+    if (ps != pd)
+        for (int i = threadIdx.x; i < materials_plus_one * 3; i += threads) pd[i] = ps[i];
+    for (int i = threadIdx.x; i < kNumFaces * materials_plus_one; i += threads) {
+        const int face = i / materials_plus_one, m = i - face * materials_plus_one;
+        lut[i] = shade_entry(ps + 3 * m, I.v[face]);
+    }
 }
 
-// Bits of `count` cells starting at `cell`, `stride` bytes apart: bit b = (cell[b*stride] != 0).
-__device__ __forceinline__ uint64_t gather_row_bits(const uint8_t* cell, int stride, int count)
+// The non-zero bytes of a dword as four bits (carry trick, then one dot product with weights 1,2,4,8).
+__device__ __forceinline__ uint32_t nonzero_nibble(uint32_t x)
 {
-    uint32_t lo = 0, hi = 0;
-    const int n_lo = min(count, 32);
-    // unrolled so that the LDS reads of several cells are in flight together
-#pragma unroll 8
-    for (int b = 0; b < n_lo; ++b) lo |= nonzero(cell[b * stride]) << b;
-#pragma unroll 8
-    for (int b = 32; b < count; ++b) hi |= nonzero(cell[b * stride]) << (b - 32);
-    return ((uint64_t)hi << 32) | lo;
+    const uint32_t flags = ((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) >> 7) & 0x01010101u;
+    return __builtin_amdgcn_udot4(flags, 0x08040201u, 0u, false);
 }
 
 // 64x64 bit-matrix transpose across the wave: on entry lane j holds row j, on return lane i holds
@@ -206,187 +209,200 @@ __device__ __forceinline__ void report_height(const HeightFeedback& fb, int top)
 // kPackPrefetch = dwords of the next layer each lane keeps in flight: 8 covers layers up to 2 KiB (40x40), 16
 // layers up to 4 KiB (64x64); the deeper variant costs registers, so small layers keep the shallow one.  (Two
 // layers in flight per wave change nothing, four are slower: the kernel moves its bytes at the rate of a plain
-// device copy as it is.)
-// kFastPath = the host has checked that layers are prefetched, 16-byte aligned and one word per row: the other
-// paths are then not compiled into the kernel (they cost it a third of its registers, and with them two of its
-// eight waves per SIMD).
-template <int kPackPrefetch, bool kFastPath>
+// device copy as it is.)  Other sizes and alignments have a kernel of their own: with their code in this one it
+// needed a third more registers, and lost two of its eight waves per SIMD.
+template <int kPackPrefetch>
 __global__ __launch_bounds__(kPackThreads) void pack_kernel(const uint8_t* __restrict__ src, uint8_t* __restrict__ vox_dst,
                                                             uint64_t* __restrict__ bits_dst, int32_t* __restrict__ ztop_dst,
-                                                            GridLayout g, int vec_ok, const uint8_t* __restrict__ pal_src,
+                                                            GridLayout g, const uint8_t* __restrict__ pal_src,
                                                             uint8_t* __restrict__ pal_dst, uint32_t* __restrict__ lut_dst,
                                                             int materials_plus_one, Intensities I, HeightFeedback heights)
 {
-    extern __shared__ __align__(16) uint8_t layer_lds[];   // one layer per wave, padded to 16 bytes
+    extern __shared__ __align__(16) uint8_t layer_lds[];   // one layer per wave
     __shared__ int top_lds;
     const int env = blockIdx.x;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int waves = kPackThreads / 64;
     const int X = g.X, Y = g.Y, Z = g.Z;
     const int XY = X * Y;
-    const int layer_stride = (XY + 15) & ~15;
-    uint8_t* mine = layer_lds + (size_t)wave * layer_stride;
+    uint8_t* mine = layer_lds + (size_t)wave * XY;
     const size_t env_vox = (size_t)env * XY * Z;
     const bool copy = (src != vox_dst);
     uint64_t* xrows = bits_dst + (size_t)env * g.env_words;
     uint64_t* yrows = xrows + g.xrow_words;
     int top = 0;
-    const int n4 = XY >> 2;
-    const bool prefetch = kFastPath || (vec_ok && n4 <= kPackPrefetch * 64);
-    const bool quick = kFastPath || (g.fast && (X & 3) == 0 && XY >= 8 * Y);     // the x rows (8 B each) fit over the layer in LDS
-    const bool wide = kFastPath || vec_ok == 2;     // layers and pointers are 16-byte aligned: four dwords per access
     const int n16 = XY >> 4;
-    uint32_t pre[kPackPrefetch];
+    u32x4 pre[kPackPrefetch / 4];
     auto fetch_layer = [&](int k) {
-        const uint8_t* layer = src + env_vox + (size_t)k * XY;
-        if (wide) {
-            const u32x4* s16 = reinterpret_cast<const u32x4*>(layer);
+        const u32x4* s16 = reinterpret_cast<const u32x4*>(src + env_vox + (size_t)k * XY);
 #pragma unroll
-            for (int u = 0; u < kPackPrefetch / 4; ++u) {
-                u32x4 v = { 0u, 0u, 0u, 0u };
-                if (u * 64 + lane < n16) v = __builtin_nontemporal_load(&s16[u * 64 + lane]);
-                pre[4 * u] = v.x; pre[4 * u + 1] = v.y; pre[4 * u + 2] = v.z; pre[4 * u + 3] = v.w;
-            }
-        } else {
-            const uint32_t* s4 = reinterpret_cast<const uint32_t*>(layer);
-#pragma unroll
-            for (int u = 0; u < kPackPrefetch; ++u) pre[u] = (u * 64 + lane) < n4 ? __builtin_nontemporal_load(&s4[u * 64 + lane]) : 0u;
+        for (int u = 0; u < kPackPrefetch / 4; ++u) {
+            u32x4 v = { 0u, 0u, 0u, 0u };
+            if (u * 64 + lane < n16) v = __builtin_nontemporal_load(&s16[u * 64 + lane]);
+            pre[u] = v;
         }
     };
-    if (prefetch && wave < Z) fetch_layer(wave);
+    if (wave < Z) fetch_layer(wave);
 
     // (after the first layers have been requested, so that the palette's trip to memory runs beside theirs)
-    if (pal_src) {
-        // the environment's palette: private copy, and the colour table lut[face][material]
-        const uint8_t* ps = pal_src + (size_t)blockIdx.x * materials_plus_one * 3;
-        uint8_t* pd = pal_dst + (size_t)blockIdx.x * materials_plus_one * 3;
-        uint32_t* lut = lut_dst + (size_t)blockIdx.x * kNumFaces * materials_plus_one;
-        if (ps != pd)
-            for (int i = threadIdx.x; i < materials_plus_one * 3; i += kPackThreads) pd[i] = ps[i];
-        for (int i = threadIdx.x; i < kNumFaces * materials_plus_one; i += kPackThreads) {
-            const int face = i / materials_plus_one, m = i - face * materials_plus_one;
-            lut[i] = shade_entry(ps + 3 * m, I.v[face]);
-        }
-    }
+    if (pal_src) pack_palette(pal_src, pal_dst, lut_dst, env, materials_plus_one, I, kPackThreads);
     if (threadIdx.x == 0) top_lds = 0;
     __syncthreads();
 
-    // the rows of layer k from its bytes in this wave's LDS slot
-    auto rows_from_lds = [&](int k) {
+    for (int k = wave; k < Z; k += waves) {
+        // The private material copy is only ever read at voxels whose occupancy bit is set (the hit
+        // voxel of a ray), so a layer without any solid voxel is not copied: its old bytes stay behind
+        // bits that are all zero.
+        uint32_t any = 0;
+#pragma unroll
+        for (int u = 0; u < kPackPrefetch / 4; ++u) any |= pre[u].x | pre[u].y | pre[u].z | pre[u].w;
+        if (__ballot(any != 0) == 0) {
+            // a layer of air: its rows are zero words, and neither LDS nor the transpose is needed for that
+            if (k + waves < Z) fetch_layer(k + waves);
+            if (lane < Y) xrows[(size_t)k * Y + lane] = 0ull;
+            if (lane < X) yrows[(size_t)k * X + lane] = 0ull;
+            continue;
+        }
+        top = k + 1;
+        u32x4* d16 = reinterpret_cast<u32x4*>(vox_dst + env_vox + (size_t)k * XY);
+        u32x4* m16 = reinterpret_cast<u32x4*>(mine);
+#pragma unroll
+        for (int u = 0; u < kPackPrefetch / 4; ++u) {
+            const int b = u * 64 + lane;
+            if (b < n16) {
+                m16[b] = pre[u];
+                if (copy) __builtin_nontemporal_store(pre[u], &d16[b]);
+            }
+        }
+        // the next layer is requested as soon as the registers are free, and arrives while this one is packed
+        if (k + waves < Z) fetch_layer(k + waves);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        uint64_t seen = 0;
-        if (quick) {
-            // One word per row, X a multiple of 4.  x rows: lane j reads its row as dwords; the non-zero
-            // bytes of a dword become a nibble (carry trick + one dot product with weights 1,2,4,8).
-            uint32_t lo = 0, hi = 0;
-            const uint32_t* rowp = reinterpret_cast<const uint32_t*>(mine + min(lane, Y - 1) * X);
+        uint32_t lo = 0, hi = 0;
+        const uint32_t* rowp = reinterpret_cast<const uint32_t*>(mine + min(lane, Y - 1) * X);
 #pragma unroll
-            for (int w4 = 0; w4 < 16; ++w4) {
-                if (w4 * 4 < X) {
-                    const uint32_t x = rowp[w4];
-                    const uint32_t flags = ((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) >> 7) & 0x01010101u;
-                    const uint32_t nib = __builtin_amdgcn_udot4(flags, 0x08040201u, 0u, false);
-                    if (w4 < 8) lo |= nib << (4 * w4); else hi |= nib << (4 * (w4 - 8));
-                }
-            }
-            const uint64_t xbits = ((uint64_t)hi << 32) | lo;
-            seen = xbits;
-            if (lane < Y) xrows[(size_t)k * Y + lane] = xbits;
-            // y rows = the transpose of the 64x64 bit matrix whose row j is lane j's x row
-            const uint64_t ybits = transpose_bits_across_lanes(lane < Y ? xbits : 0ull, lane);
-            if (lane < X) yrows[(size_t)k * X + lane] = ybits;
-        } else {
-            // x rows: row (k*Y + j), word w holds cells i = 64w .. 64w+63
-            for (int j0 = 0; j0 < Y; j0 += 64) {
-                const int j = min(j0 + lane, Y - 1);
-                for (int w = 0; w < g.rowwords_x; ++w) {
-                    const uint64_t bits = gather_row_bits(mine + j * X + w * 64, 1, min(64, X - w * 64));
-                    seen |= bits;
-                    if (j0 + lane < Y) xrows[((size_t)k * Y + j) * g.rowwords_x + w] = bits;
-                }
-            }
-            // y rows: row (k*X + i), word w holds cells j = 64w .. 64w+63
-            for (int i0 = 0; i0 < X; i0 += 64) {
-                const int i = min(i0 + lane, X - 1);
-                for (int w = 0; w < g.rowwords_y; ++w) {
-                    const uint64_t bits = gather_row_bits(mine + (w * 64) * X + i, X, min(64, Y - w * 64));
-                    if (i0 + lane < X) yrows[((size_t)k * X + i) * g.rowwords_y + w] = bits;
-                }
+        for (int w4 = 0; w4 < 16; ++w4) {
+            if (w4 * 4 < X) {
+                const uint32_t nib = nonzero_nibble(rowp[w4]);
+                if (w4 < 8) lo |= nib << (4 * w4); else hi |= nib << (4 * (w4 - 8));
             }
         }
-        if (__ballot(seen != 0) != 0) top = k + 1;
+        const uint64_t xbits = ((uint64_t)hi << 32) | lo;
+        if (lane < Y) xrows[(size_t)k * Y + lane] = xbits;
+        // y rows = the transpose of the 64x64 bit matrix whose row j is lane j's x row
+        const uint64_t ybits = transpose_bits_across_lanes(lane < Y ? xbits : 0ull, lane);
+        if (lane < X) yrows[(size_t)k * X + lane] = ybits;
         __builtin_amdgcn_wave_barrier();
-    };
+    }
+    if (lane == 0) atomicMax(&top_lds, top);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        ztop_dst[env] = top_lds;
+        report_height(heights, top_lds);
+    }
+}
 
-    if (prefetch) {
-        for (int k = wave; k < Z; k += waves) {
-            uint8_t* ldst = vox_dst + env_vox + (size_t)k * XY;
-            // The private material copy is only ever read at voxels whose occupancy bit is set (the hit
-            // voxel of a ray), so a layer without any solid voxel is not copied: its old bytes stay behind
-            // bits that are all zero.
-            uint32_t any = 0;
+// 16 bytes at any address (one unaligned vector access)
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+
+// Any grid size, any alignment.  What bounds it is memory, as for pack_kernel; a wave keeps 3 KiB in flight and the
+// workgroup holds as many waves as the world has layers (up to 16), so that a CU with a single environment still has
+// 48 KiB on its way.  A lane turns its 16 bytes into 16 bits where they arrive (the
+// bytes never see LDS), and a row of the layer, wherever it starts in the bit string, costs two funnel shifts.
+// The kernel before this one gathered rows cell by cell out of a byte copy in LDS (three instructions per
+// cell and direction, four waves per environment).
+__global__ __launch_bounds__(kPackAnyWaves * 64) __attribute__((amdgpu_waves_per_eu(8, 8))) void pack_any_kernel(const uint8_t* __restrict__ src, uint8_t* __restrict__ vox_dst,
+                                                                      uint64_t* __restrict__ bits_dst, int32_t* __restrict__ ztop_dst,
+                                                                      GridLayout g, const uint8_t* __restrict__ pal_src,
+                                                                      uint8_t* __restrict__ pal_dst, uint32_t* __restrict__ lut_dst,
+                                                                      int materials_plus_one, Intensities I, HeightFeedback heights,
+                                                                      int bits_bytes, int waves)
+{
+    extern __shared__ __align__(16) uint8_t bits_lds[];     // per wave: the bit string of one layer and two dwords more
+    __shared__ int top_lds;
+    const int env = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int X = g.X, Y = g.Y, Z = g.Z;
+    const int XY = X * Y, wx = g.rowwords_x, wy = g.rowwords_y;
+    uint16_t* string16 = reinterpret_cast<uint16_t*>(bits_lds + (size_t)wave * bits_bytes);
+    const uint32_t* string32 = reinterpret_cast<const uint32_t*>(string16);
+    const size_t env_vox = (size_t)env * XY * Z;
+    const bool copy = (src != vox_dst);
+    uint64_t* xrows = bits_dst + (size_t)env * g.env_words;
+    uint64_t* yrows = xrows + g.xrow_words;
+    if (pal_src) pack_palette(pal_src, pal_dst, lut_dst, env, materials_plus_one, I, waves * 64);
+    if (threadIdx.x == 0) top_lds = 0;
+    __syncthreads();
+
+    // word w of x row j, from the bit string (bits beyond the row's end cleared)
+    auto row_word = [&](int j, int w) -> uint64_t {
+        const uint32_t at = (uint32_t)(j * X + 64 * w), d = at >> 5;
+        const uint32_t lo = __builtin_amdgcn_alignbit(string32[d + 1], string32[d], at);
+        const uint32_t hi = __builtin_amdgcn_alignbit(string32[d + 2], string32[d + 1], at);
+        const uint64_t both = ((uint64_t)hi << 32) | lo;
+        const int n = X - 64 * w;
+        return n >= 64 ? both : both & ((1ull << n) - 1ull);
+    };
+    int top = 0;
+    for (int k = wave; k < Z; k += waves) {
+        const uint8_t* layer = src + env_vox + (size_t)k * XY;
+        uint8_t* dst = vox_dst + env_vox + (size_t)k * XY;
+        uint64_t seen = 0;
+        if (XY >= 16) {
+            const int pieces = (XY + 15) >> 4;
+            for (int b0 = 0; b0 < pieces; b0 += 64 * kPackAnyPieces) {
+                u32x4 v[kPackAnyPieces];
 #pragma unroll
-            for (int u = 0; u < kPackPrefetch; ++u) any |= pre[u];
-            const bool solid = __ballot(any != 0) != 0;
-            if (!solid && quick) {
-                // a layer of air: its rows are zero words, and neither LDS nor the transpose is needed for that
-                if (k + waves < Z) fetch_layer(k + waves);
-                if (lane < Y) xrows[(size_t)k * Y + lane] = 0ull;
-                if (lane < X) yrows[(size_t)k * X + lane] = 0ull;
-                continue;
-            }
-            const bool store_copy = copy && solid;
-            if (wide) {
-                u32x4* d16 = reinterpret_cast<u32x4*>(ldst);
-                u32x4* m16 = reinterpret_cast<u32x4*>(mine);
+                for (int u = 0; u < kPackAnyPieces; ++u) {
+                    // the last piece is read 16 bytes from the layer's end (and shifted down below)
+                    const int b = b0 + u * 64 + lane;
+                    v[u] = u32x4{ 0u, 0u, 0u, 0u };
+                    if (b < pieces) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(layer + min(b * 16, XY - 16)));
+                }
 #pragma unroll
-                for (int u = 0; u < kPackPrefetch / 4; ++u) {
-                    const int b = u * 64 + lane;
-                    if (b < n16) {
-                        const u32x4 v = { pre[4 * u], pre[4 * u + 1], pre[4 * u + 2], pre[4 * u + 3] };
-                        m16[b] = v;
-                        if (store_copy) __builtin_nontemporal_store(v, &d16[b]);
+                for (int u = 0; u < kPackAnyPieces; ++u) {
+                    const int b = b0 + u * 64 + lane, at = min(b * 16, XY - 16);
+                    const uint32_t bits = nonzero_nibble(v[u].x) | (nonzero_nibble(v[u].y) << 4) | (nonzero_nibble(v[u].z) << 8) |
+                                          (nonzero_nibble(v[u].w) << 12);
+                    const uint64_t some = __ballot(bits != 0);
+                    seen |= some;
+                    if (b < pieces) {
+                        string16[b] = (uint16_t)(bits >> (b * 16 - at));
+                        // (the material copy is only read at solid voxels: 64 pieces that are all air are not copied)
+                        if (copy && some) __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4_any*>(dst + at));
                     }
                 }
-            } else {
-                uint32_t* d4 = reinterpret_cast<uint32_t*>(ldst);
-                uint32_t* m4 = reinterpret_cast<uint32_t*>(mine);
-#pragma unroll
-                for (int u = 0; u < kPackPrefetch; ++u) {
-                    const int b = u * 64 + lane;
-                    if (b < n4) {
-                        m4[b] = pre[u];
-                        if (store_copy) __builtin_nontemporal_store(pre[u], &d4[b]);
-                    }
-                }
             }
-            // the next layer is requested as soon as the registers are free, and arrives while this one is packed
-            if (k + waves < Z) fetch_layer(k + waves);
-            rows_from_lds(k);
-        }
-    } else {
-        for (int k = wave; k < Z; k += waves) {
-            const uint8_t* lsrc = src + env_vox + (size_t)k * XY;
-            uint8_t* ldst = vox_dst + env_vox + (size_t)k * XY;
-            if (vec_ok) {
-                const uint32_t* s4 = reinterpret_cast<const uint32_t*>(lsrc);
-                uint32_t* d4 = reinterpret_cast<uint32_t*>(ldst);
-                uint32_t* m4 = reinterpret_cast<uint32_t*>(mine);
-                for (int b = lane; b < n4; b += 64) {
-                    uint32_t v = s4[b];
-                    m4[b] = v;
-                    if (copy) d4[b] = v;
-                }
-            } else {
-                for (int b = lane; b < XY; b += 64) {
-                    uint8_t m = lsrc[b];
-                    mine[b] = m;
-                    if (copy) ldst[b] = m;
-                }
+        } else {
+            uint32_t bits = 0;
+            for (int c = 0; c < XY; ++c) {
+                const uint8_t m = layer[c];
+                bits |= (m != 0 ? 1u : 0u) << c;
+                if (copy && lane == 0) dst[c] = m;
             }
-            rows_from_lds(k);
+            seen = bits;
+            if (lane == 0) string16[0] = (uint16_t)bits;
         }
+        if (seen == 0) {
+            for (int r = lane; r < Y * wx; r += 64) xrows[(size_t)k * Y * wx + r] = 0ull;
+            for (int r = lane; r < X * wy; r += 64) yrows[(size_t)k * X * wy + r] = 0ull;
+            continue;
+        }
+        top = k + 1;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // blocks of 64 rows x 64 cells: the x-row words as they are, the y-row words as the block's transpose
+        for (int jb = 0; jb < wy; ++jb) {
+            const int j = jb * 64 + lane;
+            for (int w = 0; w < wx; ++w) {
+                const uint64_t xbits = j < Y ? row_word(j, w) : 0ull;
+                if (j < Y) xrows[((size_t)k * Y + j) * wx + w] = xbits;
+                const uint64_t ybits = transpose_bits_across_lanes(xbits, lane);
+                const int i = w * 64 + lane;
+                if (i < X) yrows[((size_t)k * X + i) * wy + jb] = ybits;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
     }
     if (lane == 0) atomicMax(&top_lds, top);
     __syncthreads();
@@ -410,25 +426,23 @@ hipError_t launch_pack(const uint8_t* src, uint8_t* vox_dst, uint64_t* bits_dst,
     Intensities I;
     for (int f = 0; f < kNumFaces; ++f) I.v[f] = intensity[f];
     const size_t XY = (size_t)g.X * g.Y;
-    const size_t lds = pack_lds_bytes(g);
-    // 0: byte access; 1: dword access; 2: 16-byte access to the layers (sizes and both pointers aligned)
-    int vec_ok = (XY % 4 == 0) && ((reinterpret_cast<uintptr_t>(src) & 3) == 0) &&
-                 ((reinterpret_cast<uintptr_t>(vox_dst) & 3) == 0);
-    if (vec_ok && XY % 16 == 0 && ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(vox_dst)) & 15) == 0)
-        vec_ok = 2;
-    const int X = g.X, Y = g.Y;
-    const bool quick = g.fast && (X & 3) == 0 && XY >= (size_t)8 * Y;
-    const bool deep = XY / 4 > 8 * 64;
-    const bool fast_path = vec_ok == 2 && quick && XY / 4 <= (size_t)(deep ? 16 : 8) * 64;
-#define MV_LAUNCH_PACK(PREFETCH, FASTPATH)                                                                              \
-    hipLaunchKernelGGL((pack_kernel<PREFETCH, FASTPATH>), dim3(count), dim3(kPackThreads), lds, stream, src, vox_dst,    \
-                       bits_dst, ztop_dst, g, vec_ok, pal_src, pal_dst, lut_dst, materials_plus_one, I, heights)
-    if (!deep) {
-        if (fast_path) MV_LAUNCH_PACK(8, true); else MV_LAUNCH_PACK(8, false);
-    } else {
-        if (fast_path) MV_LAUNCH_PACK(16, true); else MV_LAUNCH_PACK(16, false);
-    }
+    const bool aligned = XY % 16 == 0 && ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(vox_dst)) & 15) == 0;
+    // (fast grids hold at most 64 x 64 cells, 4 KiB, per layer: sixteen dwords per lane; rows are read as dwords)
+    if (g.fast && aligned && (g.X & 3) == 0) {
+        const size_t lds = pack_lds_bytes(g);
+#define MV_LAUNCH_PACK(PREFETCH)                                                                                          \
+    hipLaunchKernelGGL(pack_kernel<PREFETCH>, dim3(count), dim3(kPackThreads), lds, stream, src, vox_dst, bits_dst,        \
+                       ztop_dst, g, pal_src, pal_dst, lut_dst, materials_plus_one, I, heights)
+        if (XY / 4 <= 8 * 64) MV_LAUNCH_PACK(8); else MV_LAUNCH_PACK(16);
 #undef MV_LAUNCH_PACK
+    } else {
+        int waves = g.Z < kPackAnyWaves ? g.Z : kPackAnyWaves;
+        if (waves < 4) waves = 4;
+        // per wave: the layer's bit string, and the two dwords behind its last one that a row's last word may read
+        const int bits_bytes = (int)(((XY + 31) / 32) * 4 + 8);
+        hipLaunchKernelGGL(pack_any_kernel, dim3(count), dim3(waves * 64), (size_t)waves * bits_bytes, stream, src, vox_dst,
+                           bits_dst, ztop_dst, g, pal_src, pal_dst, lut_dst, materials_plus_one, I, heights, bits_bytes, waves);
+    }
     return hipGetLastError();
 }
 
@@ -1571,12 +1585,10 @@ hipError_t prepare_kernels()
 #undef MV_SET
     // the pack kernel also has a few static words of LDS: its dynamic share must leave room for them
     const int pack_limit = (int)(kLdsBudget - kPackStaticLds);
-#define MV_SET(N, F)                                                                                              \
-    if (e == hipSuccess)                                                                                          \
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&pack_kernel<N, F>),                                \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, pack_limit)
-    MV_SET(8, false); MV_SET(8, true); MV_SET(16, false); MV_SET(16, true);
-#undef MV_SET
+    const void* pack_kernels[] = { reinterpret_cast<const void*>(&pack_kernel<8>), reinterpret_cast<const void*>(&pack_kernel<16>),
+                                   reinterpret_cast<const void*>(&pack_any_kernel) };
+    for (const void* k : pack_kernels)
+        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, pack_limit);
     if (e == hipSuccess && device >= 0 && device < kMaxDevices) done[device].store(true, std::memory_order_release);
     return e;
 }

@@ -1459,6 +1459,49 @@ def test_pack_kernel_bit_exact(lib, grid):
         check(vox2)
 
 
+@pytest.mark.parametrize("grid", [(3, 5, 2), (15, 1, 3), (4, 4, 5), (17, 1, 1), (31, 33, 4), (64, 65, 3), (65, 64, 3), (96, 96, 5),
+                                  (127, 129, 2), (41, 39, 17), (40, 40, 3), (200, 200, 1)])
+@pytest.mark.parametrize("offset", [0, 1, 4])
+def test_pack_of_any_size_and_alignment(lib, grid, offset):
+    """The pack kernel for sizes and source addresses that are not whole 16-byte pieces: bit rows and tops against
+    NumPy, and the private material copy against a render that reads the caller's array in place."""
+    rng = np.random.default_rng(31)
+    N, M = 3, 6
+    X, Y, Z = grid
+    vox, pal = synth.random_world(rng, N, grid, 0.2, M)
+    vox[1, Z // 2:] = 0
+    vox[2, :, Y // 2:] = 0                                        # pieces of a layer that are all air
+    store = torch.zeros(vox.size + 16, dtype=torch.uint8, device="cuda")
+    src = store[offset:offset + vox.size].view(vox.shape)
+    src.copy_(torch.from_numpy(vox))
+    pal_d = torch.from_numpy(pal).cuda()
+    cams = synth.random_cameras(rng, 2 * N, grid)
+    cams_d = torch.from_numpy(cams).cuda()
+    images = []
+    for borrow in (False, True):
+        batch = binding.Batch(N, 2, grid, M, 40, 24)
+        batch.upload_worlds(src, pal_d, stream=_stream(), borrow=borrow)
+        batch.set_cameras(cams_d, stream=_stream())
+        out = [torch.zeros((2 * N, 24, 40) + tail, dtype=t, device="cuda")
+               for tail, t in (((3,), torch.uint8), ((), torch.float32), ((), torch.uint8), ((), torch.int32), ((), torch.uint8))]
+        batch.render(*out, stream=_stream())
+        torch.cuda.synchronize()
+        images.append([o.cpu().numpy() for o in out])
+        for env in range(N):
+            xp, xw, yp, yw, tp = batch.debug_occupancy(env)
+            occ = vox[env] != 0
+            want_x = np.packbits(np.pad(occ, ((0, 0), (0, 0), (0, xw * 64 - X))), axis=-1, bitorder="little")
+            np.testing.assert_array_equal(_read_device(xp, Z * Y * xw * 8).reshape(Z, Y, xw * 8), want_x)
+            want_y = np.packbits(np.pad(occ.transpose(0, 2, 1), ((0, 0), (0, 0), (0, yw * 64 - Y))), axis=-1, bitorder="little")
+            np.testing.assert_array_equal(_read_device(yp, Z * X * yw * 8).reshape(Z, X, yw * 8), want_y)
+            layers = np.nonzero(occ.any(axis=(1, 2)))[0]
+            assert int(_read_device(tp, 4).view(np.int32)[0]) == (int(layers.max()) + 1 if layers.size else 0)
+        batch.close()
+    for a, b in zip(*images):
+        np.testing.assert_array_equal(a, b)
+    assert bytes(store[:offset].cpu().numpy()) + bytes(store[offset + vox.size:].cpu().numpy()) == bytes(16)
+
+
 def test_camera_records_match_the_oracle(lib, orc):
     rng = np.random.default_rng(23)
     N, A = 64, 4
