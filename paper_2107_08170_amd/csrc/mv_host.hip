@@ -228,6 +228,13 @@ static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::Gri
     p.blocks_per_xcd = (uint32_t)per_xcd;
     p.sky_packed = (uint32_t)cfg.sky_rgb[0] | ((uint32_t)cfg.sky_rgb[1] << 8) | ((uint32_t)cfg.sky_rgb[2] << 16);
     p.max_steps = p.g.X + p.g.Y + p.g.Z + 3;
+    p.by_blocks_per_obs = mv::make_divider((uint32_t)p.blocks_per_obs);
+    p.by_blocks_per_obs_tail = mv::make_divider((uint32_t)p.blocks_per_obs_tail);
+    p.by_agents = mv::make_divider((uint32_t)p.A);
+    p.by_tiles_x = mv::make_divider((uint32_t)p.tiles_x);
+    p.by_threads = mv::make_divider((uint32_t)p.threads);
+    p.by_x = mv::make_divider((uint32_t)layout.X);
+    p.by_plane = mv::make_divider((uint32_t)(layout.X * layout.Y));
     return MV_OK;
 }
 
@@ -505,7 +512,7 @@ int mv_set_cameras(mv_batch* b, const float* cams, const int32_t* self_voxel, in
         d_self = self_voxel ? b->d_self : nullptr;
     }
     MV_HIP(mv::launch_cameras(d_cams, d_self, b->d_rec, b->num_obs, b->tan_half_x, b->tan_half_y,
-                              b->cfg.grid_x * b->cfg.grid_y, stream));
+                              b->layout, stream));
     b->cameras_set = true;
     return MV_OK;
 }
@@ -892,7 +899,7 @@ extern "C" int mv_render_worlds_noalloc(const mv_config* cfg, const uint8_t* vox
     // the render reads the material of a hit voxel from `voxels` directly
     MV_HIP(mv::launch_pack(voxels, const_cast<uint8_t*>(voxels), d_bits, d_ztop, cfg->num_envs, layout, palette,
                            const_cast<uint8_t*>(palette), d_lut, mp1, intensity, no_feedback, stream));
-    MV_HIP(mv::launch_cameras(cams, self_voxel, d_rec, (int)NA, tan_half_x, tan_half_y, cfg->grid_x * cfg->grid_y, stream));
+    MV_HIP(mv::launch_cameras(cams, self_voxel, d_rec, (int)NA, tan_half_x, tan_half_y, layout, stream));
 
     mv::RenderParams p{};
     p.staged_layers = cfg->grid_z;            // no height feedback without a batch object: stage every layer

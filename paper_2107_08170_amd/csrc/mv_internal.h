@@ -8,12 +8,20 @@
 namespace mv {
 
 // One camera, 64 bytes: position, forward axis, right axis scaled by tan(hfov/2), up axis scaled
-// by tan(hfov/2)*H/W, and the two voxels of the camera's own body (-1 = none).
+// by tan(hfov/2)*H/W, the two voxels of the camera's own body (-1 = none), where the camera stands, and the z layer
+// nearest to it.
 struct alignas(64) CameraRecord {
     float   P[3], F[3], R[3], U[3];
     int32_t self_lo, self_hi;
-    int32_t pad[2];
+    int32_t place;                        // one of the values below
+    int32_t layer;                        // floor(P_z) clamped to the grid
 };
+constexpr int kPlaceInGrid = 0;           // inside the grid's box or on its boundary
+constexpr int kPlaceOutside = 1;          // outside it, no coordinate beyond kNearOutside
+constexpr int kPlaceFarOutside = 2;       // further away, or a position that is not a number
+// So near, the point where a ray enters the grid is good to a small fraction of a voxel in float32 (the spacing of
+// float32 numbers at 4096 is 5e-4), which the row scan from that point relies on.
+constexpr float kNearOutside = 4096.0f;
 static_assert(sizeof(CameraRecord) == 64, "camera record must be 64 bytes");
 
 // A wave renders a tile of kTileW x kTileH = 64 pixels.  8 x 8 keeps the rays of a wave most alike; 16 x 4 would
@@ -50,6 +58,26 @@ struct HeightFeedback {
     int32_t* host_max;      // device-visible address of the pinned host word
 };
 
+// n / d for 0 <= n < 2^31 as one 32 x 32 -> 64-bit product and a shift: with s = ceil(log2 d) and
+// mul = ceil(2^(31+s) / d), which is at most 2^32 - 1 (2^31 if d is a power of two), the product exceeds n * 2^(31+s) / d
+// by less than n < 2^31 <= 2^(31+s) / d, so its floor is exact.  Four scalar instructions; the compiler's division by a
+// run-time value is about twenty, through the reciprocal unit of the vector pipeline.  (Every wave of the render kernel
+// makes four divisions before its first tile and four more for a camera with a body, next to about twelve tiles of 210
+// instructions: a step of 1024 x 4 cameras with bodies 158.2 -> 154.3 us.)
+struct Divider {
+    uint32_t mul, shift;
+#if defined(__HIPCC__)
+    __host__ __device__
+#endif
+    uint32_t quotient(uint32_t n) const { return (uint32_t)(((uint64_t)n * mul) >> shift); }
+};
+inline Divider make_divider(uint32_t d)
+{
+    uint32_t s = 0;
+    while ((1ull << s) < d) ++s;
+    return Divider{ (uint32_t)(((1ull << (31 + s)) + d - 1) / d), 31 + s };
+}
+
 struct RenderParams {
     const uint64_t*     bits;             // [N][env_words]
     const int32_t*      ztop;             // [N] 1 + highest solid layer (0 = empty world)
@@ -78,6 +106,7 @@ struct RenderParams {
     uint32_t sky_packed;
     int32_t max_steps;
     int32_t threads;                      // workgroup size (multiple of 64)
+    Divider by_blocks_per_obs, by_blocks_per_obs_tail, by_agents, by_tiles_x, by_threads, by_x, by_plane;
     int32_t staged_layers;                // row-scan grids: layers 0 .. staged_layers-1 of the bit rows go to LDS
     int32_t coarse_after;                 // < 0: no coarse level; else the ordinary turns a ray makes before it uses it
     HeightFeedback heights;
@@ -110,7 +139,7 @@ hipError_t launch_move_voxels(const int32_t* env, const int32_t* from_voxel, con
                               int num_envs, int voxels_per_env, int num_materials, const GridLayout& g,
                               const HeightFeedback& heights, hipStream_t stream);
 hipError_t launch_cameras(const float* cams, const int32_t* self_voxel, CameraRecord* rec, int num_obs,
-                          double tan_half_x, double tan_half_y, int plane_voxels, hipStream_t stream);
+                          double tan_half_x, double tan_half_y, const GridLayout& g, hipStream_t stream);
 struct BarParams {
     int32_t x, y, width, height;
     uint32_t fill_packed, empty_packed;   // r | g<<8 | b<<16

@@ -518,7 +518,7 @@ hipError_t launch_move_voxels(const int32_t* env, const int32_t* from_voxel, con
 // ------------------------------------------------------------------------------------------
 __global__ void camera_kernel(const float* __restrict__ cams, const int32_t* __restrict__ self_voxel,
                               CameraRecord* __restrict__ rec, int num_obs, double tan_half_x, double tan_half_y,
-                              int plane_voxels)
+                              int X, int Y, int Z)
 {
     int o = blockIdx.x * blockDim.x + threadIdx.x;
     if (o >= num_obs) return;
@@ -534,16 +534,21 @@ __global__ void camera_kernel(const float* __restrict__ cams, const int32_t* __r
     r.U[0] = (float)(tan_half_y * (-sp * cy)); r.U[1] = (float)(tan_half_y * (-sp * sy)); r.U[2] = (float)(tan_half_y * cp);
     int s = self_voxel ? self_voxel[o] : -1;
     r.self_lo = s >= 0 ? s : -1;
-    r.self_hi = s >= 0 ? s + plane_voxels : -1;
-    r.pad[0] = r.pad[1] = 0;
+    r.self_hi = s >= 0 ? s + X * Y : -1;
+    // where the camera stands, once here instead of in every workgroup that renders for it
+    const bool in_grid = r.P[0] >= 0.0f && r.P[0] <= (float)X && r.P[1] >= 0.0f && r.P[1] <= (float)Y &&
+                         r.P[2] >= 0.0f && r.P[2] <= (float)Z;
+    const bool near = fabsf(r.P[0]) <= kNearOutside && fabsf(r.P[1]) <= kNearOutside && fabsf(r.P[2]) <= kNearOutside;
+    r.place = in_grid ? kPlaceInGrid : (near ? kPlaceOutside : kPlaceFarOutside);
+    r.layer = min(max((int)floorf(r.P[2]), 0), Z - 1);
     rec[o] = r;
 }
 
 hipError_t launch_cameras(const float* cams, const int32_t* self_voxel, CameraRecord* rec, int num_obs,
-                          double tan_half_x, double tan_half_y, int plane_voxels, hipStream_t stream)
+                          double tan_half_x, double tan_half_y, const GridLayout& g, hipStream_t stream)
 {
     hipLaunchKernelGGL(camera_kernel, dim3((num_obs + 127) / 128), dim3(128), 0, stream, cams, self_voxel, rec,
-                       num_obs, tan_half_x, tan_half_y, plane_voxels);
+                       num_obs, tan_half_x, tan_half_y, g.X, g.Y, g.Z);
     return hipGetLastError();
 }
 
@@ -564,6 +569,12 @@ __device__ __forceinline__ float safe_rcp(float d)
     return __builtin_amdgcn_fmed3f(__builtin_amdgcn_rcpf(d), -kBig, kBig);
 }
 
+// a value all lanes share, as a scalar
+__device__ __forceinline__ float uniform(float v)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v)));
+}
+
 // Constants of one scan class of one camera.  A class is (dominant horizontal axis, direction along it,
 // direction along the other horizontal axis, vertical direction): class = 8*(y dominant) + 4*(u negative) +
 // 2*(v negative) + (z negative), so a ray picks every direction-dependent constant with one record load
@@ -574,12 +585,13 @@ __device__ __forceinline__ float safe_rcp(float d)
 struct alignas(16) ScanClass {
     float Pu;           // camera coordinate along u (mirrored for negative u)
     float uexit;        // U - Pu: distance to the far side of the grid along u
-    float dist_v;       // distance from the camera to the first v plane in this direction (>= 0)
-    float nv_max;       // v planes between the camera cell and the grid boundary in this direction
-    float zero[2];      // 0, 0: where a ray's two crossing counters start (the z counterparts of the two values
-                        // above depend on the image row: RowRecord holds them)
     float Pu_err;       // what rounding took from the mirrored coordinate: (U - P) - Pu exactly, 0 if not mirrored
     int   addr0;        // LDS byte address of the camera's row in this class's row array
+    float zero[2];      // 0, 0: where a ray's two crossing counters start (beside two values that are dead by then: the
+                        // counters keep the registers they were loaded into)
+    float dist_v;       // distance from the camera to the first v plane in this direction (>= 0)
+    float nv_max;       // v planes between the camera cell and the grid boundary in this direction
+                        // (the z counterparts of these two depend on the image row: RowRecord holds them)
     int   i0;           // camera cell along u (mirrored)
     int   um1;          // U - 1
     // voxel index of the hit = idx0 + cell*stride_u + n_v*stride_v + n_z*stride_z, evaluated with three fused
@@ -619,7 +631,7 @@ struct alignas(16) PairClass {
 static_assert(sizeof(ScanClass) + sizeof(PairClass) <= kClassStride, "class slot too small");
 
 // Plain 3D-DDA through the x rows (any row width), in LDS or in global memory.  Used for grids wider than 64
-// voxels, for cameras outside the grid, and for workgroups whose world is taller than the layers staged.  Crossing parameters are t = n*|1/d| + t_first (one fused op, error relative
+// voxels, for cameras far outside the grid, and for workgroups whose world is taller than the layers staged.  Crossing parameters are t = n*|1/d| + t_first (one fused op, error relative
 // to t itself) rather than accumulated.
 // self_lo / self_hi: voxels this camera must not see (-1 = none); callers that have already removed the body
 // from their copy of the rows pass -1.
@@ -771,6 +783,64 @@ __device__ __forceinline__ int mad24s(int a, int b_uniform, int c)
     return r;
 }
 
+// A camera outside the grid, for the tracers below: its rays start where they enter the box [0,X]x[0,Y]x[0,top].
+struct OutsideCamera {
+    float P[3];
+    float dz;           // vertical component of the ray
+    int X, Y, top;      // top: layers that may hold a solid voxel, at least 1
+};
+
+// Where such a ray enters the box: the same slab test, entry cells and first crossings as trace_generic.
+struct BoxEntry {
+    bool misses;
+    float t;            // parameter of the entry point, >= 0
+    int face;           // face code of a voxel found in the entry cell
+    int j, k;           // entry cell along v and along z
+    float t0_v, t0_z;   // parameters of the first v and z crossing
+    float left_v, left_z;   // planes between the entry cell and the far side of the box along v and z
+};
+
+__device__ __forceinline__ BoxEntry enter_box(const OutsideCamera& o, float dx, float dy, bool xm, float rcp_z)
+{
+    const float kInf = __builtin_inff();
+    const float d[3] = { dx, dy, o.dz };
+    const float rcp[3] = { safe_rcp(dx + 0.0f), safe_rcp(dy + 0.0f), rcp_z };
+    const int dim[3] = { o.X, o.Y, o.top };
+    float t_near = -kInf, t_far = kInf;
+    int axis = -1;
+    // (a direction that is not a number misses, so that every comparison below means what it says)
+    bool dead = !(fabsf(dx) + fabsf(dy) + fabsf(o.dz) < kBig);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float lo = (0.0f - o.P[a]) * rcp[a], hi = ((float)dim[a] - o.P[a]) * rcp[a];
+        const bool zero = d[a] == 0.0f;
+        const float ta = zero ? -kInf : fminf(lo, hi), tb = zero ? kInf : fmaxf(lo, hi);
+        dead |= zero && (o.P[a] < 0.0f || o.P[a] > (float)dim[a]);
+        if (ta > t_near) { t_near = ta; axis = a; }
+        t_far = fminf(t_far, tb);
+    }
+    BoxEntry e;
+    e.misses = dead || t_near > t_far || t_far < 0.0f;
+    e.t = fmaxf(t_near, 0.0f);
+    if (!(t_near > 0.0f)) axis = -1;
+    const float d_axis = axis == 0 ? dx : (axis == 1 ? dy : o.dz);
+    e.face = axis < 0 ? 6 : 2 * axis + (d_axis > 0.0f ? 0 : 1);
+    auto along = [&](int a, float da, float pa, float ra, int n, int& cell, float& first, float& left) {
+        const bool neg = da < 0.0f;
+        int c = (int)fminf(fmaxf(floorf(fmaf(e.t, da, pa)), 0.0f), (float)(n - 1));
+        if (a == axis) c = neg ? n - 1 : 0;
+        cell = c;
+        // (not before the entry point: what a ray crosses later it must also reach later, or the run of cells of its
+        // first row would end before it begins)
+        first = da == 0.0f ? kBig : fmaxf(((float)(neg ? c : c + 1) - pa) * ra, e.t);
+        left = (float)(neg ? c : n - 1 - c);
+    };
+    if (xm) along(1, dy, o.P[1], rcp[1], o.Y, e.j, e.t0_v, e.left_v);
+    else    along(0, dx, o.P[0], rcp[0], o.X, e.j, e.t0_v, e.left_v);
+    along(2, o.dz, o.P[2], rcp_z, o.top, e.k, e.t0_z, e.left_z);
+    return e;
+}
+
 // Row-scan traversal: DDA over the (v,z) rows the ray passes through, one 64-bit shift per row.
 // The loop has one exit (row holds a solid cell in range, or the ray leaves the grid).  It ends for
 // every input: each turn advances n_v or n_z, the crossing parameters n*dt + t0 never decrease, and
@@ -781,9 +851,18 @@ __device__ __forceinline__ int mad24s(int a, int b_uniform, int c)
 // t_end, which puts the last cell of the run at U at most (U only through rounding at the far boundary);
 // with U <= 63 that still is a valid bit position of an always-empty cell, and the clamp to U - 1 that
 // 64-cell rows need is left out.
-template <bool kNarrow, bool kCoarse>
-__device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float dy, const RowRecord& rr, int fine_turns)
+// kOutside: the ray starts where it enters the grid's box instead of in the camera's cell (see enter_box), and the
+// class records hold row and voxel index of cell (0,0,0) of the class's array instead of the camera's.  The row loop
+// is the same one; a ray that misses the box leaves it in its first turn.  No crossing parameter lies before the entry
+// point, so the runs of cells are monotone here as well.  Bound by instruction issue like the inside scan (about ninety
+// instructions more per ray, for the entry); the per-cell tracer over rows in device memory, which took these cameras
+// before and still takes far ones, spends a dependent memory access per cell (256 x 4 cameras around 40x40x16 worlds at
+// 128x72, upload + cameras + render: 286 -> 82 us).
+template <bool kNarrow, bool kCoarse, bool kOutside = false>
+__device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float dy, const RowRecord& rr, int fine_turns,
+                                          const OutsideCamera* from_outside = nullptr)
 {
+    static_assert(!(kCoarse && kOutside), "the coarse level starts from the camera's own pair of rows");
     const bool xm = fabsf(dx) >= fabsf(dy);
     const float du = xm ? dx : dy;
     const float dv = xm ? dy : dx;
@@ -809,10 +888,25 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     const float dt_v = fabsf(rcp_v), dt_z = fabsf(rcp_z);
     // first crossing on an axis: the distance to the first plane in the ray's direction times |1/d| (along z: from
     // the image row's record, see RowRecord)
-    const float t0_v = c.dist_v * dt_v;
-    const float t0_z = rr.t0_z;
-    // leaving the grid: same n*dt + t0 expression as the crossings, so the comparison below is exact
-    const float t_end = vmin3(c.uexit * inv_u, fmaf(c.nv_max, dt_v, t0_v), rr.tend_z);
+    float t0_v, t0_z, t_end;
+    BoxEntry in{};
+    if constexpr (kOutside) {
+        in = enter_box(*from_outside, dx, dy, xm, rcp_z);
+        if (__ballot(!in.misses) == 0) return Hit{ -1, 0, 0.0f };        // no ray of the tile meets the box
+        t0_v = in.t0_v; t0_z = in.t0_z;
+        t_end = vmax(vmin3(c.uexit * inv_u, fmaf(in.left_v, dt_v, t0_v), fmaf(in.left_z, dt_z, t0_z)), in.t);
+        // the record's address and index are those of cell (0,0,0)
+        const int V = xm ? from_outside->Y : from_outside->X;
+        c.addr0 += 8 * (in.k * V + in.j);
+        c.idx0 += (float)((in.k * from_outside->Y) * from_outside->X + in.j * (xm ? from_outside->X : 1));
+        c.i0 = min(max((int)fmaf(in.t, dua, c.Pu), 0), c.um1);
+        if (in.misses) t0_v = t0_z = t_end = 0.0f;
+    } else {
+        t0_v = c.dist_v * dt_v;
+        t0_z = rr.t0_z;
+        // leaving the grid: same n*dt + t0 expression as the crossings, so the comparison below is exact
+        t_end = vmin3(c.uexit * inv_u, fmaf(c.nv_max, dt_v, t0_v), rr.tend_z);
+    }
 
     // crossings made so far along v and z (without sign; the directions sit in the class), and the parameters
     // of the next ones: t_v = n_v*dt_v + t0_v, t_z likewise
@@ -832,6 +926,7 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     // The next row is requested as soon as its address is known, at the end of the turn before (render -1 %).
     uint64_t row = 0;
     if constexpr (!kCoarse) row = *(lds_u64_ptr)(uintptr_t)addr;
+    if constexpr (kOutside) row = in.misses ? 0ull : row;
     int i_a = c.i0, i_b;
     if constexpr (kCoarse) {
         // Coarse level: after `fine_turns` ordinary turns a ray first looks at the PAIR of rows it is in (the OR of
@@ -1032,8 +1127,14 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     const float iu_f = (float)iu;
     const float t_u = ((iu_f - c.Pu) - c.Pu_err) * inv_u;
     const int face_vz = via_z ? c.face_z : c.face_v;
-    const int face = along_row ? c.face_u : face_vz;
-    const float t = along_row ? t_u : t_in;
+    int face = along_row ? c.face_u : face_vz;
+    float t = along_row ? t_u : t_in;
+    if constexpr (kOutside) {
+        // the voxel the ray meets as it enters the box
+        const bool at_entry = !along_row && n_v + n_z == 0.0f;
+        face = at_entry ? in.face : face;
+        t = at_entry ? in.t : t;
+    }
     // voxel index: the class record holds the index of (mirrored cell 0, camera's v cell, camera's layer)
     // and the signed index steps per cell along u and per crossing along v and z
     const int idx = (int)fmaf(n_z, c.stride_z, fmaf(n_v, c.stride_v, fmaf(iu_f, c.stride_u, c.idx0)));
@@ -1075,16 +1176,18 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     const uint32_t body = (uint32_t)p.obs_body_per_xcd * (uint32_t)p.blocks_per_obs;
     int obs, part, tiles_per_block, strips;
     if (seq < body) {
-        obs = (int)(xcd * (uint32_t)p.obs_per_xcd + seq / (uint32_t)p.blocks_per_obs);
-        part = (int)(seq % (uint32_t)p.blocks_per_obs);
+        const uint32_t local = p.by_blocks_per_obs.quotient(seq);
+        obs = (int)(xcd * (uint32_t)p.obs_per_xcd + local);
+        part = (int)(seq - local * (uint32_t)p.blocks_per_obs);
         tiles_per_block = p.tiles_per_block;
         strips = p.blocks_per_obs;
     } else {
         const uint32_t s2 = seq - body;
-        const uint32_t local = (uint32_t)p.obs_body_per_xcd + s2 / (uint32_t)p.blocks_per_obs_tail;
+        const uint32_t t = p.by_blocks_per_obs_tail.quotient(s2);
+        const uint32_t local = (uint32_t)p.obs_body_per_xcd + t;
         if (local >= (uint32_t)p.obs_per_xcd) return;
         obs = (int)(xcd * (uint32_t)p.obs_per_xcd + local);
-        part = (int)(s2 % (uint32_t)p.blocks_per_obs_tail);
+        part = (int)(s2 - t * (uint32_t)p.blocks_per_obs_tail);
         tiles_per_block = p.tiles_per_block_tail;
         strips = p.blocks_per_obs_tail;
     }
@@ -1092,8 +1195,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     // The hardware deals an XCD's consecutive workgroups to its four shader engines in turn: with an even
     // number of strips per observation the same engines would always get the top strips (mostly sky, the
     // slow ones).  Rotating the strips by a hash of the observation index breaks that pairing.
-    if ((strips & 1) == 0) part = (int)(((uint32_t)part + (((uint32_t)obs * 2654435761u) >> 16)) % (uint32_t)strips);
-    const int env = obs / p.A;
+    if ((strips & 1) == 0) {
+        const uint32_t turned = (uint32_t)part + (((uint32_t)obs * 2654435761u) >> 16);
+        const uint32_t whole = (seq < body ? p.by_blocks_per_obs : p.by_blocks_per_obs_tail).quotient(turned);
+        part = (int)(turned - whole * (uint32_t)strips);
+    }
+    const int env = (int)p.by_agents.quotient((uint32_t)obs);
     if (p.active && p.active[env] == 0) return;         // finished episode: its frame is never drawn
     const GridLayout& g = p.g;
     const int X = g.X, Y = g.Y, Z = g.Z;
@@ -1114,11 +1221,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     const float Fx = recp->F[0], Fy = recp->F[1], Fz = recp->F[2];
     const float Rx = recp->R[0], Ry = recp->R[1], Rz = recp->R[2];
     const float Ux = recp->U[0], Uy = recp->U[1], Uz = recp->U[2];
-    const int self_lo = recp->self_lo, self_hi = recp->self_hi;
+    const int self_lo = recp->self_lo;
 
-    const bool origin_in_grid = P[0] >= 0.0f && P[0] <= (float)X && P[1] >= 0.0f && P[1] <= (float)Y &&
-                                P[2] >= 0.0f && P[2] <= (float)Z;
-    const int k0 = min(max((int)floorf(P[2]), 0), Z - 1);
+    const int place = recp->place, k0 = recp->layer;
+    const bool origin_in_grid = place == kPlaceInGrid;
     // Layers the rays of this camera can reach.  Above the highest solid layer of the environment a rising
     // ray can only miss, so the grid is cut there.  A camera that is itself above every solid sits, for the
     // row scan, in one tall empty layer that reaches from the top of the solids upwards: its layer index is
@@ -1140,6 +1246,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         staged = min(staged, max(tallest + 1, 1));
     }
     const bool use_rows = FAST && origin_in_grid && zlim <= staged;
+    // A camera outside the grid scans rows from where its rays enter it; far outside, and for positions that are not
+    // numbers, cell by cell.
+    const bool outside_rows = FAST && place == kPlaceOutside && max(ztop, 1) <= staged;
+    const bool stage_rows = use_rows || outside_rows;
     const int sxw = staged * Y, syw = staged * X;          // words of one staged x / y row array
     if (FAST && origin_in_grid && !use_rows && threadIdx.x == 0 && p.heights.device_max) {
         atomicMax(p.heights.device_max, ztop);
@@ -1158,7 +1268,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         const uint32_t first_lut = gl[min(tid, lut_n - 1)];
         const uint64_t* gb = p.bits + (size_t)env * g.env_words;
         if (FAST) {
-            if (use_rows) {
+            if (stage_rows) {
                 // arrays: [x rows][x rows mirrored][y rows][y rows mirrored], layers 0 .. staged-1 of each
                 uint64_t* ax = lds_rows;
                 uint64_t* axm = ax + sxw;
@@ -1208,31 +1318,32 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     // once, instead of being tested for at every step.  The thread that staged a word (word index modulo the
     // workgroup size) clears the body's bit in it straight after its own stores (one wave's LDS operations
     // keep their order), so the barrier below is the only one the staging needs.
-    if (self_lo >= 0) {
+    if (self_lo >= 0 && self_lo < X * Y * Z) {
+        const int k = (int)p.by_plane.quotient((uint32_t)self_lo), rem = self_lo - k * X * Y;
+        const int j = (int)p.by_x.quotient((uint32_t)rem), i = rem - j * X;
+        auto staged_by_me = [&](int w) { return (int)threadIdx.x == w - (int)p.by_threads.quotient((uint32_t)w) * threads; };
 #pragma unroll
-        for (int part = 0; part < 2; ++part) {
-            const int sv_ = part == 0 ? self_lo : self_hi;
-            if (sv_ >= 0 && sv_ < X * Y * Z) {
-                const int k = sv_ / (X * Y), rem = sv_ - k * X * Y, j = rem / X, i = rem - j * X;
-                if (FAST) {
-                    if (use_rows && k < staged) {
-                        uint64_t* ax = lds_rows;
-                        uint64_t* axm = ax + sxw;
-                        uint64_t* ay = axm + sxw;
-                        uint64_t* aym = ay + syw;
-                        if ((int)threadIdx.x == (k * Y + j) % threads) {
-                            ax[k * Y + j] &= ~(1ull << i);
-                            axm[k * Y + j] &= ~(1ull << (X - 1 - i));
-                        }
-                        if ((int)threadIdx.x == (k * X + i) % threads) {
-                            ay[k * X + i] &= ~(1ull << j);
-                            aym[k * X + i] &= ~(1ull << (Y - 1 - j));
-                        }
+        for (int up = 0; up < 2; ++up) {            // the voxel itself and the one above it
+            const int kb = k + up;
+            if (kb >= Z) continue;
+            if (FAST) {
+                if (stage_rows && kb < staged) {
+                    uint64_t* ax = lds_rows;
+                    uint64_t* axm = ax + sxw;
+                    uint64_t* ay = axm + sxw;
+                    uint64_t* aym = ay + syw;
+                    if (staged_by_me(kb * Y + j)) {
+                        ax[kb * Y + j] &= ~(1ull << i);
+                        axm[kb * Y + j] &= ~(1ull << (X - 1 - i));
                     }
-                } else {
-                    const int w = (k * Y + j) * g.rowwords_x + (i >> 6);
-                    if ((int)threadIdx.x == w % threads) lds_rows[w] &= ~(1ull << (i & 63));
+                    if (staged_by_me(kb * X + i)) {
+                        ay[kb * X + i] &= ~(1ull << j);
+                        aym[kb * X + i] &= ~(1ull << (Y - 1 - j));
+                    }
                 }
+            } else {
+                const int w = (kb * Y + j) * g.rowwords_x + (i >> 6);
+                if (staged_by_me(w)) lds_rows[w] &= ~(1ull << (i & 63));
             }
         }
     }
@@ -1240,7 +1351,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     const int vpx = (Y + 1) / 2, vpy = (X + 1) / 2;         // pairs per layer of the x / y arrays
     const int pxw = staged * vpx, pyw = staged * vpy;
     const uint32_t off_pairs = off_rows + 16u * (uint32_t)(sxw + syw);
-    if (use_rows && threadIdx.x >= 64 && threadIdx.x < 64 + kScanClasses) {
+    if (stage_rows && threadIdx.x >= 64 && threadIdx.x < 64 + kScanClasses) {
         const int q = threadIdx.x - 64;
         const bool xmaj = q < 8, neg = q & 4, vneg = q & 2, zneg = q & 1;
         const int U = xmaj ? X : Y, V = xmaj ? Y : X;
@@ -1266,7 +1377,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         c.nv_max = (float)(vneg ? j0 : V - 1 - j0);
         c.zero[0] = c.zero[1] = 0.0f;
         const uint32_t array_off = off_rows + 8u * (uint32_t)(xmaj ? (neg ? sxw : 0) : 2 * sxw + (neg ? syw : 0));
-        c.addr0 = (int)(lds_base + array_off + 8u * (uint32_t)(kc * V + j0));
+        // (for cameras outside: of cell (0,0,0), each ray adds its own entry cell)
+        const int j_row = outside_rows ? 0 : j0, k_row = outside_rows ? 0 : kc;
+        c.addr0 = (int)(lds_base + array_off + 8u * (uint32_t)(k_row * V + j_row));
         c.sv = vneg ? -8 : 8;
         c.sz = zneg ? -8 * V : 8 * V;
         c.um1 = U - 1;
@@ -1278,7 +1391,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         c.stride_u = (float)(neg ? -su : su);
         c.stride_v = (float)(vneg ? -sv_idx : sv_idx);
         c.stride_z = (float)(zneg ? -X * Y : X * Y);
-        c.idx0 = (float)(kc * X * Y + j0 * sv_idx + (neg ? (U - 1) * su : 0));
+        c.idx0 = (float)(k_row * X * Y + j_row * sv_idx + (neg ? (U - 1) * su : 0));
         *reinterpret_cast<ScanClass*>(lds + off_classes + q * kClassStride) = c;
         if (COARSE) {
             const int VP = xmaj ? vpx : vpy;
@@ -1394,17 +1507,33 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     // traced in the previous trip, then traces its own tile, and only then shades and stores the previous
     // one, so that the global fetch hides behind a whole traversal.  (The request is issued in the trip that
     // consumes it: a value still in flight across the loop's back edge would be waited for there.)
-    // The loop exists twice: once with the row scan alone (the common case), once with the other tracers,
-    // so that the values only those need are not kept in registers through the common loop.
-    auto run_tiles = [&](auto rows_only_tag, auto narrow_tag) {
+    // The loop exists once for each of: the row scan alone (the common case), the row scan of cameras outside, the other
+    // tracers, so that the values only one of them needs are not kept in registers through the others' loops.
+    auto run_tiles = [&](auto rows_only_tag, auto narrow_tag, auto outside_tag) {
         constexpr bool kRowsOnly = decltype(rows_only_tag)::value;
+        constexpr bool kOutside = decltype(outside_tag)::value;
+        // What only the rarer loops need of the camera is read again for them (through a pointer the compiler cannot
+        // match with the first read): kept in scalar registers from the prologue on, it costs the common loop spills.
+        float Pc[3] = { 0.0f, 0.0f, 0.0f }, Fcz = 0.0f, Ucz = 0.0f;
+        int body_lo = -1, body_hi = -1, top = 0;
+        bool inside = true;
+        if constexpr (!kRowsOnly || kOutside) {
+            const CameraRecord* again = p.rec + obs;
+            const int32_t* tops = p.ztop;
+            asm volatile("" : "+s"(again), "+s"(tops));
+            Pc[0] = uniform(again->P[0]); Pc[1] = uniform(again->P[1]); Pc[2] = uniform(again->P[2]);
+            Fcz = uniform(again->F[2]); Ucz = uniform(again->U[2]);         // R_z = 0: no roll
+            body_lo = __builtin_amdgcn_readfirstlane(again->self_lo); body_hi = __builtin_amdgcn_readfirstlane(again->self_hi);
+            top = __builtin_amdgcn_readfirstlane(tops[env]);
+            inside = __builtin_amdgcn_readfirstlane(again->place) == kPlaceInGrid;
+        }
         constexpr bool kNarrow = decltype(narrow_tag)::value;
         int pend_idx = -1, pend_face = 255;
         float pend_t = 0.0f;
         uint32_t pend_pix = 0;
         bool pend_active = false, pending = false;
         // tile coordinates are carried along instead of divided out of the tile index every trip
-        int ty = (tile_begin + wave) / p.tiles_x, tx = (tile_begin + wave) - ty * p.tiles_x - waves;
+        int ty = (int)p.by_tiles_x.quotient((uint32_t)(tile_begin + wave)), tx = (tile_begin + wave) - ty * p.tiles_x - waves;
         for (int tile = tile_begin + wave; tile < tile_end; tile += waves) {
             // lanes without a hit (idx -1 = 0xffffffff) read the last voxel and drop it later: no branch
             const uint8_t pend_material = vox_env[min((uint32_t)pend_idx, last_voxel)];
@@ -1435,22 +1564,25 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             float d[3];
             d[0] = fmaf(rr.sy, Ux, fmaf(sx, Rx, Fx));
             d[1] = fmaf(rr.sy, Uy, fmaf(sx, Ry, Fy));
-            if (!kRowsOnly) d[2] = fmaf(rr.sy, Uz, fmaf(sx, Rz, Fz));
+            if (!kRowsOnly || kOutside) d[2] = fmaf(rr.sy, Ucz, Fcz);
 
             // a5: traversal
             Hit h;
-            if (kRowsOnly) {
+            if constexpr (kOutside) {
+                const OutsideCamera from{ { Pc[0], Pc[1], Pc[2] }, d[2], X, Y, max(top, 1) };
+                h = trace_rows<kNarrow, false, true>(lds_base + off_classes, d[0], d[1], rr, -1, &from);
+            } else if (kRowsOnly) {
                 h = trace_rows<kNarrow, COARSE>(lds_base + off_classes, d[0], d[1], rr, p.coarse_after);
             } else if (use_rows) {
                 h.idx = cam_idx; h.face = 6; h.t = 0.0f;
             } else if (FAST) {
-                // cameras outside the grid, and worlds taller than the staged layers: the x rows in global
+                // cameras far outside the grid, and worlds taller than the staged layers: the x rows in global
                 // memory, own body skipped by index
                 h = trace_generic(reinterpret_cast<const uint32_t*>(p.bits + (size_t)env * g.env_words), 2 * g.rowwords_x,
-                                  P, d, X, Y, Z, origin_in_grid, p.max_steps, self_lo, self_hi);
+                                  Pc, d, X, Y, Z, inside, p.max_steps, body_lo, body_hi);
             } else {
-                h = trace_generic(reinterpret_cast<const uint32_t*>(lds_rows), 2 * g.rowwords_x, P, d, X, Y, Z,
-                                  origin_in_grid, p.max_steps, -1, -1);
+                h = trace_generic(reinterpret_cast<const uint32_t*>(lds_rows), 2 * g.rowwords_x, Pc, d, X, Y, Z,
+                                  inside, p.max_steps, -1, -1);
             }
 
             if (pending) shade_and_store(pend_idx, pend_face, pend_t, pend_material, pend_pix, pend_active, rows_only_tag);
@@ -1466,11 +1598,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     };
     __builtin_amdgcn_s_setprio(0);
     if (use_rows && cam_idx < 0) {
-        if (X < 64 && Y < 64) run_tiles(std::true_type{}, std::true_type{});
-        else run_tiles(std::true_type{}, std::false_type{});
-    } else {
-        run_tiles(std::false_type{}, std::false_type{});
+        if (X < 64 && Y < 64) run_tiles(std::true_type{}, std::true_type{}, std::false_type{});
+        else run_tiles(std::true_type{}, std::false_type{}, std::false_type{});
+        return;
     }
+    if (FAST && !use_rows && stage_rows) { run_tiles(std::true_type{}, std::false_type{}, std::true_type{}); return; }
+    run_tiles(std::false_type{}, std::false_type{}, std::false_type{});
 }
 
 // ------------------------------------------------------------------------------------------

@@ -778,6 +778,51 @@ def test_rays_that_reach_the_far_end_of_a_row(lib, orc, grid):
     assert (ref.hit_index >= 0).any() and (ref.hit_index < 0).any()
 
 
+@pytest.mark.parametrize("grid", [(1, 1, 1), (5, 7, 3), (63, 20, 9), (64, 64, 8), (20, 64, 12), (40, 40, 16)])
+def test_cameras_outside_scan_rows_from_where_rays_enter(lib, orc, grid):
+    """Cameras in front of every side of the grid, above it, at its edges and corners, on the continuation of voxel
+    planes and of the boundary planes, with axis-parallel, vertical and oblique views: the entry face, entry cell and
+    every later hit follow the oracle, with and without an own body, for worlds with nothing in their upper layers (the
+    box is cut there), empty ones and full ones, and for every staged layer count.  Distances up to 150 voxels: there two
+    roundings of the entry parameter, 150 * 2^-22 voxels, still lie within the oracle's tie margin of 1e-4."""
+    rng = np.random.default_rng(grid[0] * 10007 + grid[1] * 101 + grid[2])
+    N, A, M = 8, 12, 7
+    spec = _mini_spec(N, A, grid, 40, 24, M)
+    X, Y, Z = grid
+    vox, pal = synth.random_world(rng, N, grid, 0.1, M)
+    vox[1] = 0
+    vox[2] = 3
+    vox[3:, (Z + 1) // 2:] = 0
+    cams = np.zeros((N * A, 5), np.float32)
+    dim = np.array(grid, np.float64)
+    for o in range(N * A):
+        side, far = o % 6, float(rng.choice([0.25, 1.0, 7.3, 150.0]))
+        pos = rng.uniform(0.05, 0.95, 3) * dim
+        if rng.random() < 0.4:
+            pos = np.floor(pos) + rng.choice([0.0, 0.5], 3)
+        if rng.random() < 0.3:
+            a = int(rng.integers(0, 3))
+            pos[a] = rng.choice([-2.5, 0.0, dim[a], dim[a] + 1.0])
+        axis, sign = side // 2, 1 - 2 * (side % 2)
+        pos[axis] = -far if sign > 0 else dim[axis] + far
+        aim = rng.uniform(0.2, 0.8, 3) * dim - pos
+        yaw, pitch = np.arctan2(aim[1], aim[0]), np.arctan2(aim[2], np.hypot(aim[0], aim[1]))
+        if rng.random() < 0.4:
+            yaw = (0.0, np.pi, np.pi / 2, -np.pi / 2)[side] if side < 4 else 0.0
+            pitch = 0.0 if side < 4 else sign * np.pi / 2
+        cams[o] = (*pos, yaw, pitch)
+    selfv = rng.integers(-1, X * Y * Z, size=N * A).astype(np.int32)
+    for hfov, body in ((1.2, None), (0.3, selfv), (2.5, None)):
+        hfov = float(np.float32(hfov))
+        ob = _oracle_for(orc, spec, vox, pal, cams, body, hfov_rad=hfov)
+        ref = ob.render()
+        run = _gpu_for(spec, vox, pal, cams, body, hfov_rad=hfov)
+        for layers in (0, Z, 1):            # as the worlds need, all, and too few (cell by cell where a world is taller)
+            run.batch.debug_set_staged_layers(layers)
+            run.render()
+            _pixelwise_rule(run.numpy(), ref, f"outside, grid {grid}, fov {hfov}, layers {layers}")
+
+
 def test_largest_grid_the_lds_plan_takes(lib, orc):
     grid = (128, 128, 32)                   # 64 KiB of occupancy bits
     rng = np.random.default_rng(8)
@@ -1175,8 +1220,8 @@ def test_step_replays_from_a_hip_graph(lib, orc):
 @pytest.mark.parametrize("name", ["wide", "outside", "odd"])
 def test_slow_paths_on_mid_size_batches(lib, orc, name):
     """Every pixel against the oracle on batches of hundreds of observations for the paths the five workloads
-    never take: grids wider than 64 voxels (per-cell tracer over rows on chip), cameras outside the grid (per-cell
-    tracer over rows in device memory), and an image that is not made of whole 8x8 tiles (clamped tiles, byte
+    never take: grids wider than 64 voxels (per-cell tracer over rows on chip), cameras outside the grid (row scan
+    from where a ray enters it), and an image that is not made of whole 8x8 tiles (clamped tiles, byte
     stores) -- several workgroups per compute unit, tail strips and the XCD mapping included."""
     wl = synth.generate_extra(name)
     spec = wl.spec
