@@ -172,6 +172,7 @@ static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::Gri
     p.g = layout;
     p.voxels_per_env = layout.X * layout.Y * layout.Z;
     p.threads = plan.threads;
+    p.window = plan.window ? 1 : 0;
     p.W = cfg.width; p.H = cfg.height; p.A = cfg.agents_per_env;
     p.materials_plus_one = (cfg.num_materials + 1);
     p.tiles_x = (p.W + mv::kTileW - 1) / mv::kTileW;
@@ -530,7 +531,7 @@ int mv_render_batch(mv_batch* b, uint8_t* rgb, float* depth, uint8_t* aux_materi
     DeviceScope scope(b->cfg.device);
     if (!scope.ok()) return fail(MV_ERR_HIP, "mv_render_batch: cannot select device %d", b->cfg.device);
 
-    // How many layers of a row-scan grid to stage: as many as the tallest world the kernels have reported
+    // How many layers to stage: as many as the tallest world the kernels have reported
     // so far (read without synchronising: a value that is out of date costs speed, never correctness -- a
     // workgroup whose world is taller than what was staged traces through global memory and reports it),
     // all of them before the first report.
@@ -538,7 +539,7 @@ int mv_render_batch(mv_batch* b, uint8_t* rgb, float* depth, uint8_t* aux_materi
     // know: it stages every layer (unless the caller fixed the number), so that a replay never falls back to the
     // slow path because the worlds grew after the capture.
     int staged = b->cfg.grid_z;
-    if (b->layout.fast) {
+    {
         bool capturing = false;
         if (hip_stream) {
             hipStreamCaptureStatus status = hipStreamCaptureStatusNone;

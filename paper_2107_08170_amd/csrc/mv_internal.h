@@ -107,7 +107,8 @@ struct RenderParams {
     int32_t max_steps;
     int32_t threads;                      // workgroup size (multiple of 64)
     Divider by_blocks_per_obs, by_blocks_per_obs_tail, by_agents, by_tiles_x, by_threads, by_x, by_plane;
-    int32_t staged_layers;                // row-scan grids: layers 0 .. staged_layers-1 of the bit rows go to LDS
+    int32_t staged_layers;                // layers 0 .. staged_layers-1 of the bit rows go to LDS
+    int32_t window;                       // grids wider than 64 voxels: x and y rows are staged for the window scan
     int32_t coarse_after;                 // < 0: no coarse level; else the ordinary turns a ray makes before it uses it
     HeightFeedback heights;
 };
@@ -118,8 +119,9 @@ GridLayout make_layout(int X, int Y, int Z);
 struct LdsPlan {
     size_t bytes;         // dynamic LDS per workgroup
     int    threads;       // workgroup size that keeps a CU busy with that much LDS
+    bool   window;        // a grid wider than 64 voxels whose x and y rows fit (else: all x rows, traced cell by cell)
 };
-// staged_layers: how many z layers of a row-scan grid the workgroup keeps in LDS (1..Z; ignored for other grids);
+// staged_layers: how many z layers the workgroup keeps in LDS (1..Z; ignored by the per-cell tracer's plan);
 // coarse: with the pair-of-rows arrays of the optional coarse level
 LdsPlan plan_lds(const GridLayout& g, int W, int H, int materials_plus_one, int staged_layers, bool coarse);
 

@@ -45,14 +45,17 @@ static size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
 
 // LDS map (bytes):  [16 scan-class records, 112 B apart] | [sx: W floats][one RowRecord per image row] |
 //                   [colour table 7*(M+1) dwords] | bit rows
-// fast grids stage four row arrays (x, x mirrored, y, y mirrored) of `staged_layers` layers each; others stage
-// all x rows.  With the coarse level, four more arrays follow: the OR of each pair of neighbouring rows of a layer.
+// fast grids stage four row arrays (x, x mirrored, y, y mirrored) of `staged_layers` layers each.  With the coarse
+// level, four more arrays follow: the OR of each pair of neighbouring rows of a layer.
+// Grids wider than 64 voxels stage x and y rows of `staged_layers` layers for the window scan, which reads a row in
+// either direction (mirrored copies would leave room for half as many workgroups); where those do not fit, all x rows
+// for the per-cell tracer.
 struct LdsMap {
     uint32_t scalars, classes, lut, rows;
     uint32_t total;
 };
 
-static LdsMap lds_map(const GridLayout& g, int W, int H, int materials_plus_one, int staged_layers, bool coarse)
+static LdsMap lds_map(const GridLayout& g, int W, int H, int materials_plus_one, int staged_layers, bool coarse, bool window)
 {
     LdsMap m{};
     size_t off = 0;
@@ -61,7 +64,9 @@ static LdsMap lds_map(const GridLayout& g, int W, int H, int materials_plus_one,
     m.lut = (uint32_t)off;
     off = align16(off + (size_t)kNumFaces * materials_plus_one * 4);
     m.rows = (uint32_t)off;
-    off += g.fast ? 16 * (size_t)staged_layers * (size_t)(g.X + g.Y) : (size_t)g.xrow_words * 8;
+    if (g.fast) off += 16 * (size_t)staged_layers * (size_t)(g.X + g.Y);
+    else if (window) off += 8 * (size_t)staged_layers * ((size_t)g.Y * g.rowwords_x + (size_t)g.X * g.rowwords_y) + 16; // a window may end a dword behind its row
+    else off += (size_t)g.xrow_words * 8;
     if (g.fast && coarse) off += 16 * (size_t)staged_layers * (size_t)((g.X + 1) / 2 + (g.Y + 1) / 2);
     m.total = (uint32_t)off;
     return m;
@@ -70,8 +75,13 @@ static LdsMap lds_map(const GridLayout& g, int W, int H, int materials_plus_one,
 LdsPlan plan_lds(const GridLayout& g, int W, int H, int materials_plus_one, int staged_layers, bool coarse)
 {
     LdsPlan plan{};
-    const LdsMap m = lds_map(g, W, H, materials_plus_one, staged_layers, coarse);
-    if (m.total > kLdsBudget) return plan;                                  // bytes == 0: does not fit
+    plan.window = !g.fast;
+    LdsMap m = lds_map(g, W, H, materials_plus_one, staged_layers, coarse, plan.window);
+    if (plan.window && m.total > kLdsBudget) {
+        plan.window = false;
+        m = lds_map(g, W, H, materials_plus_one, staged_layers, coarse, false);
+    }
+    if (m.total > kLdsBudget) return LdsPlan{};                             // bytes == 0: does not fit
     plan.bytes = m.total;
     // as many waves per workgroup as fill the CU's wave slots with the workgroups its LDS can hold
     // (measured: 64x64x32 grids, two workgroups per CU: 1024 threads render 9 % faster than 512)
@@ -630,8 +640,8 @@ struct alignas(16) PairClass {
 };
 static_assert(sizeof(ScanClass) + sizeof(PairClass) <= kClassStride, "class slot too small");
 
-// Plain 3D-DDA through the x rows (any row width), in LDS or in global memory.  Used for grids wider than 64
-// voxels, for cameras far outside the grid, and for workgroups whose world is taller than the layers staged.  Crossing parameters are t = n*|1/d| + t_first (one fused op, error relative
+// Plain 3D-DDA through the x rows (any row width), in LDS or in global memory.  Used for grids whose x and y rows do not
+// both fit into LDS, for cameras far outside the grid, and for workgroups whose world is taller than the layers staged.  Crossing parameters are t = n*|1/d| + t_first (one fused op, error relative
 // to t itself) rather than accumulated.
 // self_lo / self_hi: voxels this camera must not see (-1 = none); callers that have already removed the body
 // from their copy of the rows pass -1.
@@ -1145,6 +1155,101 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     return h;
 }
 
+typedef __attribute__((address_space(3))) const uint32_t* lds_u32_ptr;
+
+// Row scan for grids of any width: the traversal of trace_rows, but a row is looked at through a window of 32 cells that
+// starts wherever the ray is (two dwords of the row and one funnel shift); a run of more than 32 cells takes several
+// windows.  There is one copy of the rows for both directions: for a ray that runs towards lower cells the window ends
+// where the ray is and is bit-reversed.  The record's address and index steps are those of rows of several words; `pad`
+// is -1 for mirrored classes, else 0.  Bits of a window beyond the row's ends belong to its neighbours in LDS and never
+// count: runs end at cell U - 1.  Ends for every input as trace_rows does; a window that does not reach the end of the run
+// advances it by 32 cells.  Bound by instruction issue, about five turns per ray instead of one per cell
+// (256 x 2 worlds of 96x96x16 at 128x72, upload + cameras + render: 184 -> 95 us).
+template <bool kOutside>
+__device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, float dy, const RowRecord& rr,
+                                             const OutsideCamera* from_outside = nullptr)
+{
+    const bool xm = fabsf(dx) >= fabsf(dy);
+    const float du = xm ? dx : dy;
+    const float dv = xm ? dy : dx;
+    uint32_t q = xm ? 0u : 1u;                      // the class index, as in trace_rows
+    q = __builtin_amdgcn_alignbit(q, __float_as_uint(du), 31);
+    q = __builtin_amdgcn_alignbit(q, __float_as_uint(dv + 0.0f), 31);
+    q = __builtin_amdgcn_alignbit(q, __float_as_uint(rr.rcp_z), 31);
+    ScanClass c;
+    {
+        lds_u32x4_ptr rec = (lds_u32x4_ptr)(uintptr_t)(classes_addr + q * (uint32_t)kClassStride);
+        u32x4* dst = reinterpret_cast<u32x4*>(&c);
+        dst[0] = rec[0]; dst[1] = rec[1]; dst[2] = rec[2]; dst[3] = rec[3]; dst[4] = rec[4];
+    }
+    const float dua = fabsf(du);
+    const float inv_u = safe_rcp(dua);
+    const float dt_v = fabsf(safe_rcp(dv)), dt_z = fabsf(rr.rcp_z);
+    float t0_v, t0_z, t_end;
+    BoxEntry in{};
+    if constexpr (kOutside) {
+        in = enter_box(*from_outside, dx, dy, xm, rr.rcp_z);
+        if (__ballot(!in.misses) == 0) return Hit{ -1, 0, 0.0f };
+        t0_v = in.t0_v; t0_z = in.t0_z;
+        t_end = vmax(vmin3(c.uexit * inv_u, fmaf(in.left_v, dt_v, t0_v), fmaf(in.left_z, dt_z, t0_z)), in.t);
+        const int V = xm ? from_outside->Y : from_outside->X;
+        c.addr0 += abs(c.sv) * (in.k * V + in.j);
+        c.idx0 += (float)((in.k * from_outside->Y) * from_outside->X + in.j * (xm ? from_outside->X : 1));
+        c.i0 = min(max((int)fmaf(in.t, dua, c.Pu), 0), c.um1);
+    } else {
+        t0_v = c.dist_v * dt_v;
+        t0_z = rr.t0_z;
+        t_end = vmin3(c.uexit * inv_u, fmaf(c.nv_max, dt_v, t0_v), rr.tend_z);
+    }
+    const int mirrored = c.pad;                     // -1 or 0
+    const int origin = mirrored & (c.um1 - 30);     // window of mirrored cell i: cells U-32-i .. U-1-i, else i .. i+31
+    float t_v = t0_v, t_z = t0_z, n_v = 0.0f, n_z = 0.0f;
+    uint32_t addr = (uint32_t)c.addr0, in_range = 0;
+    int i_from = c.i0, i_row = c.i0, i_last = c.i0;
+    for (bool go = !kOutside || !in.misses; go;) {
+        const float t_out = vmin3(t_v, t_z, t_end);
+        const int i_to = min((int)fmaf(t_out, dua, c.Pu), c.um1);
+        for (;;) {
+            const int first = (i_from ^ mirrored) + origin;
+            const lds_u32_ptr at = (lds_u32_ptr)(uintptr_t)(addr + (uint32_t)((first >> 5) * 4));
+            uint32_t cells = __builtin_amdgcn_alignbit(at[1], at[0], (uint32_t)first);
+            cells = mirrored ? __builtin_bitreverse32(cells) : cells;
+            i_last = min(i_to, i_from + 31);
+            in_range = cells << ((~i_last + i_from) & 31);
+            if ((in_range != 0) | (i_last == i_to)) break;
+            i_from = i_last + 1;
+        }
+        if ((in_range != 0) | !(t_out < t_end)) break;
+        const bool cv = t_v <= t_z;
+        const float one = cv ? 1.0f : 0.0f;
+        addr += (uint32_t)(cv ? c.sv : c.sz);
+        n_v += one;
+        n_z += 1.0f - one;
+        t_v = fmaf(n_v, dt_v, t0_v);
+        t_z = fmaf(n_z, dt_z, t0_z);
+        i_from = i_row = i_to;
+    }
+    // as in trace_rows; the hit cell is i_last - (31 - lowest bit)
+    const bool found = in_range != 0;
+    const int iu = i_last - 31 + (found ? __builtin_ctz(in_range) : 0);
+    const bool along_row = iu != i_row;
+    const float tv_last = fmaf(n_v - 1.0f, dt_v, t0_v);
+    const float tz_last = fmaf(n_z - 1.0f, dt_z, t0_z);
+    const bool via_z = tz_last >= tv_last;
+    const float t_in = vmax3(tv_last, tz_last, 0.0f);
+    const float iu_f = (float)iu;
+    const float t_u = ((iu_f - c.Pu) - c.Pu_err) * inv_u;
+    int face = along_row ? c.face_u : (via_z ? c.face_z : c.face_v);
+    float t = along_row ? t_u : t_in;
+    if constexpr (kOutside) {
+        const bool at_entry = !along_row && n_v + n_z == 0.0f;
+        face = at_entry ? in.face : face;
+        t = at_entry ? in.t : t;
+    }
+    const int idx = (int)fmaf(n_z, c.stride_z, fmaf(n_v, c.stride_v, fmaf(iu_f, c.stride_u, c.idx0)));
+    return Hit{ found ? idx : -1, face, t };
+}
+
 // colour of lane+1 within each group of four lanes (lane 3 of the group keeps its own): DPP
 // quad_perm [1,2,3,3]
 __device__ __forceinline__ uint32_t next_in_quad(uint32_t v)
@@ -1240,18 +1345,20 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     // tall the tallest world really is right now (it is exact: written by the pack and edit kernels earlier in the
     // stream), and nothing above that plus the one empty layer on top is worth copying.  A launch whose size was
     // fixed long before it runs (a replayed graph) thus stages only what today's worlds need.
-    int staged = FAST ? p.staged_layers : Z;
-    if (FAST && p.heights.device_max) {
+    const bool scans = FAST || p.window != 0;
+    int staged = scans ? p.staged_layers : Z;
+    if (scans && p.heights.device_max) {
         const int tallest = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.heights.device_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         staged = min(staged, max(tallest + 1, 1));
     }
-    const bool use_rows = FAST && origin_in_grid && zlim <= staged;
+    const bool use_rows = scans && origin_in_grid && zlim <= staged;
     // A camera outside the grid scans rows from where its rays enter it; far outside, and for positions that are not
     // numbers, cell by cell.
-    const bool outside_rows = FAST && place == kPlaceOutside && max(ztop, 1) <= staged;
+    const bool outside_rows = scans && place == kPlaceOutside && max(ztop, 1) <= staged;
     const bool stage_rows = use_rows || outside_rows;
-    const int sxw = staged * Y, syw = staged * X;          // words of one staged x / y row array
-    if (FAST && origin_in_grid && !use_rows && threadIdx.x == 0 && p.heights.device_max) {
+    const int wx = FAST ? 1 : g.rowwords_x, wy = FAST ? 1 : g.rowwords_y;
+    const int sxw = staged * Y * wx, syw = staged * X * wy;        // words of one staged x / y row array
+    if (scans && origin_in_grid && !use_rows && threadIdx.x == 0 && p.heights.device_max) {
         atomicMax(p.heights.device_max, ztop);
         __hip_atomic_fetch_max(p.heights.host_max, ztop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
@@ -1289,7 +1396,20 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
                 for (int base = 2 * threads; base < longest; base += 2 * threads) row_trip(base);
             }
         } else {
-            for (int w = tid; w < g.xrow_words; w += threads) lds_rows[w] = gb[w];
+            // x rows of the staged layers (all of them for the per-cell tracer), then y rows: word w is staged by thread
+            // w modulo the workgroup size; four loads in flight per thread
+            auto copy = [&](uint64_t* dst, const uint64_t* src, int n) {
+                for (int base = tid; base < n; base += 4 * threads) {
+                    uint64_t v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = src[min(base + u * threads, n - 1)];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (base + u * threads < n) dst[base + u * threads] = v[u];
+                }
+            };
+            if (stage_rows || !scans) copy(lds_rows, gb, sxw);
+            if (stage_rows) copy(lds_rows + sxw, gb + g.xrow_words, syw);
         }
         if (tid < p.W) lds_sx[tid] = first_sx;
         // image row records (see RowRecord); the z constants are those of the two vertical scan directions
@@ -1341,9 +1461,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
                         aym[kb * X + i] &= ~(1ull << (Y - 1 - j));
                     }
                 }
-            } else {
-                const int w = (kb * Y + j) * g.rowwords_x + (i >> 6);
+            } else if (kb < staged && (stage_rows || !scans)) {
+                const int w = (kb * Y + j) * wx + (i >> 6);
                 if (staged_by_me(w)) lds_rows[w] &= ~(1ull << (i & 63));
+                const int wv = (kb * X + i) * wy + (j >> 6);
+                if (stage_rows && staged_by_me(wv)) lds_rows[sxw + wv] &= ~(1ull << (j & 63));
             }
         }
     }
@@ -1359,7 +1481,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         ScanClass c;
         c.Pu = neg ? (float)U - pu : pu;
         c.Pu_err = 0.0f;
-        c.pad = 0;
+        c.pad = neg ? -1 : 0;
         if (neg) {                                         // exact error of the rounded difference (two-sum)
             const float a = (float)U, bneg = -pu;
             const float bb = __fsub_rn(c.Pu, a);
@@ -1376,12 +1498,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         c.dist_v = fabsf((float)(vneg ? j0 : j0 + 1) - pv);
         c.nv_max = (float)(vneg ? j0 : V - 1 - j0);
         c.zero[0] = c.zero[1] = 0.0f;
-        const uint32_t array_off = off_rows + 8u * (uint32_t)(xmaj ? (neg ? sxw : 0) : 2 * sxw + (neg ? syw : 0));
+        const uint32_t array_off = off_rows + 8u * (uint32_t)(FAST ? (xmaj ? (neg ? sxw : 0) : 2 * sxw + (neg ? syw : 0))
+                                                                   : (xmaj ? 0 : sxw));
+        const int row_bytes = 8 * (xmaj ? wx : wy);
         // (for cameras outside: of cell (0,0,0), each ray adds its own entry cell)
         const int j_row = outside_rows ? 0 : j0, k_row = outside_rows ? 0 : kc;
-        c.addr0 = (int)(lds_base + array_off + 8u * (uint32_t)(k_row * V + j_row));
-        c.sv = vneg ? -8 : 8;
-        c.sz = zneg ? -8 * V : 8 * V;
+        c.addr0 = (int)(lds_base + array_off) + row_bytes * (k_row * V + j_row);
+        c.sv = vneg ? -row_bytes : row_bytes;
+        c.sz = zneg ? -row_bytes * V : row_bytes * V;
         c.um1 = U - 1;
         c.face_u = 2 * (xmaj ? 0 : 1) + (neg ? 1 : 0);
         c.face_v = 2 * (xmaj ? 1 : 0) + (vneg ? 1 : 0);
@@ -1436,7 +1560,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     int cam_idx = -1;
     if (use_rows) {
         const int ic = min(max((int)floorf(P[0]), 0), X - 1), jc = min(max((int)floorf(P[1]), 0), Y - 1);
-        const uint32_t bit = (uint32_t)(lds_rows[kc * Y + jc] >> ic) & 1u;
+        const uint32_t bit = (uint32_t)(lds_rows[(kc * Y + jc) * wx + (FAST ? 0 : ic >> 6)] >> (ic & 63)) & 1u;
         if (__builtin_amdgcn_readfirstlane((int)bit)) cam_idx = (kc * Y + jc) * X + ic;
     }
 
@@ -1570,12 +1694,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             Hit h;
             if constexpr (kOutside) {
                 const OutsideCamera from{ { Pc[0], Pc[1], Pc[2] }, d[2], X, Y, max(top, 1) };
-                h = trace_rows<kNarrow, false, true>(lds_base + off_classes, d[0], d[1], rr, -1, &from);
-            } else if (kRowsOnly) {
-                h = trace_rows<kNarrow, COARSE>(lds_base + off_classes, d[0], d[1], rr, p.coarse_after);
+                if constexpr (FAST) h = trace_rows<kNarrow, false, true>(lds_base + off_classes, d[0], d[1], rr, -1, &from);
+                else h = trace_windows<true>(lds_base + off_classes, d[0], d[1], rr, &from);
+            } else if constexpr (kRowsOnly) {
+                if constexpr (FAST) h = trace_rows<kNarrow, COARSE>(lds_base + off_classes, d[0], d[1], rr, p.coarse_after);
+                else h = trace_windows<false>(lds_base + off_classes, d[0], d[1], rr);
             } else if (use_rows) {
                 h.idx = cam_idx; h.face = 6; h.t = 0.0f;
-            } else if (FAST) {
+            } else if (scans) {
                 // cameras far outside the grid, and worlds taller than the staged layers: the x rows in global
                 // memory, own body skipped by index
                 h = trace_generic(reinterpret_cast<const uint32_t*>(p.bits + (size_t)env * g.env_words), 2 * g.rowwords_x,
@@ -1598,11 +1724,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     };
     __builtin_amdgcn_s_setprio(0);
     if (use_rows && cam_idx < 0) {
-        if (X < 64 && Y < 64) run_tiles(std::true_type{}, std::true_type{}, std::false_type{});
+        if (FAST && X < 64 && Y < 64) run_tiles(std::true_type{}, std::true_type{}, std::false_type{});
         else run_tiles(std::true_type{}, std::false_type{}, std::false_type{});
         return;
     }
-    if (FAST && !use_rows && stage_rows) { run_tiles(std::true_type{}, std::false_type{}, std::true_type{}); return; }
+    if (!use_rows && stage_rows) { run_tiles(std::true_type{}, std::false_type{}, std::true_type{}); return; }
     run_tiles(std::false_type{}, std::false_type{}, std::false_type{});
 }
 

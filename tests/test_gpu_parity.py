@@ -778,7 +778,8 @@ def test_rays_that_reach_the_far_end_of_a_row(lib, orc, grid):
     assert (ref.hit_index >= 0).any() and (ref.hit_index < 0).any()
 
 
-@pytest.mark.parametrize("grid", [(1, 1, 1), (5, 7, 3), (63, 20, 9), (64, 64, 8), (20, 64, 12), (40, 40, 16)])
+@pytest.mark.parametrize("grid", [(1, 1, 1), (5, 7, 3), (63, 20, 9), (64, 64, 8), (20, 64, 12), (40, 40, 16),
+                                  (65, 9, 4), (9, 65, 4), (96, 96, 6), (70, 129, 3), (1, 200, 5)])
 def test_cameras_outside_scan_rows_from_where_rays_enter(lib, orc, grid):
     """Cameras in front of every side of the grid, above it, at its edges and corners, on the continuation of voxel
     planes and of the boundary planes, with axis-parallel, vertical and oblique views: the entry face, entry cell and
@@ -821,6 +822,43 @@ def test_cameras_outside_scan_rows_from_where_rays_enter(lib, orc, grid):
             run.batch.debug_set_staged_layers(layers)
             run.render()
             _pixelwise_rule(run.numpy(), ref, f"outside, grid {grid}, fov {hfov}, layers {layers}")
+
+
+@pytest.mark.parametrize("grid", [(65, 9, 4), (9, 65, 4), (95, 33, 3), (96, 96, 5), (97, 64, 4), (64, 127, 4), (128, 128, 4),
+                                  (129, 31, 3), (31, 191, 3), (300, 5, 2)])
+def test_windows_of_wide_rows(lib, orc, grid):
+    """Rows of more than one word, scanned through windows of 32 cells: runs of several windows in both directions, last
+    cells at every place within a dword, windows that reach over either end of a row."""
+    test_rays_that_reach_the_far_end_of_a_row(lib, orc, grid)
+
+
+@pytest.mark.parametrize("grid,layers", [((96, 80, 12), 0), ((96, 80, 12), 3), ((128, 128, 48), 0)])
+def test_wide_grids_with_bodies_tall_worlds_and_rows_that_do_not_fit(lib, orc, grid, layers):
+    """Wide grids with own bodies on either side of a word boundary, cameras in and above the solids and inside them; worlds
+    taller than the staged layers; and a grid whose x and y rows do not both fit into LDS (traced cell by cell)."""
+    rng = np.random.default_rng(sum(grid) + layers)
+    N, A, M = 2, 8, 9
+    spec = _mini_spec(N, A, grid, 48, 32, M)
+    X, Y, Z = grid
+    vox, pal = synth.random_world(rng, N, grid, 0.01, M)
+    vox[:, 0] = 3
+    cams = synth.random_cameras(rng, N * A, grid, margin=0.0)
+    cell = np.floor(np.minimum(cams[:, :3], np.array(grid) - 1)).astype(np.int64)
+    cell[::4, 0] = 63 + (np.arange(N * A)[::4] // 4) % 2            # bodies in cells 63 and 64 of their rows
+    cams[::4, 0] = cell[::4, 0] + 0.5
+    selfv = ((cell[:, 2] * Y + cell[:, 1]) * X + cell[:, 0]).astype(np.int32)
+    for o in range(N * A):                                          # every second camera stands in a solid body
+        if o % 2 == 0:
+            vox[o // A].reshape(-1)[selfv[o]] = 5
+    selfv[6::8] = -1                                                # some of them without knowing it
+    ob = _oracle_for(orc, spec, vox, pal, cams, selfv)
+    run = _gpu_for(spec, vox, pal, cams, selfv)
+    run.batch.debug_set_staged_layers(layers)
+    ref = ob.render(threads=4)
+    for _ in range(2):
+        run.render()
+        _pixelwise_rule(run.numpy(), ref, f"grid {grid}, layers {layers}")
+    assert (ref.face == 6).any() and (ref.hit_index >= 0).any()
 
 
 def test_largest_grid_the_lds_plan_takes(lib, orc):
@@ -1220,7 +1258,7 @@ def test_step_replays_from_a_hip_graph(lib, orc):
 @pytest.mark.parametrize("name", ["wide", "outside", "odd"])
 def test_slow_paths_on_mid_size_batches(lib, orc, name):
     """Every pixel against the oracle on batches of hundreds of observations for the paths the five workloads
-    never take: grids wider than 64 voxels (per-cell tracer over rows on chip), cameras outside the grid (row scan
+    never take: grids wider than 64 voxels (window scan), cameras outside the grid (row scan
     from where a ray enters it), and an image that is not made of whole 8x8 tiles (clamped tiles, byte
     stores) -- several workgroups per compute unit, tail strips and the XCD mapping included."""
     wl = synth.generate_extra(name)
