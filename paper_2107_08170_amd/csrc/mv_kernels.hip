@@ -1164,7 +1164,7 @@ typedef __attribute__((address_space(3))) const uint32_t* lds_u32_ptr;
 // is -1 for mirrored classes, else 0.  Bits of a window beyond the row's ends belong to its neighbours in LDS and never
 // count: runs end at cell U - 1.  Ends for every input as trace_rows does; a window that does not reach the end of the run
 // advances it by 32 cells.  Bound by instruction issue, about five turns per ray instead of one per cell
-// (256 x 2 worlds of 96x96x16 at 128x72, upload + cameras + render: 184 -> 95 us).
+// (256 x 2 worlds of 96x96x16 at 128x72, upload + cameras + render: 184 -> 82 us).
 template <bool kOutside>
 __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, float dy, const RowRecord& rr,
                                              const OutsideCamera* from_outside = nullptr)
@@ -1338,23 +1338,21 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     const int ztop = p.ztop[env];
     const int kc = min(k0, ztop);
     const int zlim = kc + 1 > ztop ? kc + 1 : ztop;
-    // Row scan: only if those layers were staged.  The launch stages as many layers as the tallest world
-    // the host has heard of; a taller one is traced through the rows in global memory, cell by cell, and
-    // says so, so that the next launch stages enough.
-    // Layers kept on chip: the launch reserved LDS for p.staged_layers of them; the batch's device word says how
-    // tall the tallest world really is right now (it is exact: written by the pack and edit kernels earlier in the
-    // stream), and nothing above that plus the one empty layer on top is worth copying.  A launch whose size was
-    // fixed long before it runs (a replayed graph) thus stages only what today's worlds need.
+    // Row scan: only if the launch reserved LDS for those layers (as many as the tallest world the host has heard of
+    // needs).  A taller world is traced through the rows in global memory, cell by cell, and says so, so that the next
+    // launch reserves enough.
     const bool scans = FAST || p.window != 0;
-    int staged = scans ? p.staged_layers : Z;
-    if (scans && p.heights.device_max) {
-        const int tallest = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.heights.device_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        staged = min(staged, max(tallest + 1, 1));
-    }
-    const bool use_rows = scans && origin_in_grid && zlim <= staged;
+    const bool use_rows = scans && origin_in_grid && zlim <= p.staged_layers;
     // A camera outside the grid scans rows from where its rays enter it; far outside, and for positions that are not
     // numbers, cell by cell.
-    const bool outside_rows = scans && place == kPlaceOutside && max(ztop, 1) <= staged;
+    const int solid_layers = max(ztop, 1);
+    const bool outside_rows = scans && place == kPlaceOutside && solid_layers <= p.staged_layers;
+    // Layers copied: those this environment's rays can reach, whatever the launch has room for.  So a launch whose size was
+    // fixed long before it runs (a replayed graph), or without knowledge of the worlds, copies no more than another.
+    // (Copying as many as the tallest world of the whole batch needs, read from its device word, or all of them where there
+    // is none, takes longer: 256 x 4 of 40x40x16 without a batch object 60.5 -> 56.8 us, with one 52.5 -> 52.2 us, 256 x 2
+    // of 96x96x16 94.7 -> 81.7 us.)
+    const int staged = __builtin_amdgcn_readfirstlane(!scans ? Z : (use_rows ? zlim : solid_layers));
     const bool stage_rows = use_rows || outside_rows;
     const int wx = FAST ? 1 : g.rowwords_x, wy = FAST ? 1 : g.rowwords_y;
     const int sxw = staged * Y * wx, syw = staged * X * wy;        // words of one staged x / y row array
