@@ -73,8 +73,7 @@ struct Divider {
 };
 inline Divider make_divider(uint32_t d)
 {
-    uint32_t s = 0;
-    while ((1ull << s) < d) ++s;
+    const uint32_t s = d > 1 ? 32 - (uint32_t)__builtin_clz(d - 1) : 0;
     return Divider{ (uint32_t)(((1ull << (31 + s)) + d - 1) / d), 31 + s };
 }
 
@@ -126,22 +125,31 @@ struct LdsPlan {
 LdsPlan plan_lds(const GridLayout& g, int W, int H, int materials_plus_one, int staged_layers, bool coarse);
 
 // Launchers (mv_kernels.hip).  All enqueue on `stream` and return hipGetLastError().
-hipError_t launch_pixel_scalars(float* sx, float* sy, int W, int H, hipStream_t stream);
+// Small work that runs behind another launch's workgroups, or in a launch of its own: camera records of num_obs cameras,
+// pixel scalars of a W x H image, active flags of num_done environments.  What a call has none of is 0.
+struct SideWork {
+    const float* cams; const int32_t* self_voxel; CameraRecord* rec;
+    int32_t num_obs, X, Y, Z;
+    double tan_half_x, tan_half_y;
+    float* sx; float* sy;
+    int32_t W, H;
+    const uint8_t* done; uint8_t* active;
+    int32_t num_done;
+};
+hipError_t launch_side(const SideWork& side, hipStream_t stream);
 // pal_src == nullptr keeps the palettes; otherwise [count][M+1][3] device bytes (may equal pal_dst)
 hipError_t launch_pack(const uint8_t* src, uint8_t* vox_dst, uint64_t* bits_dst, int32_t* ztop_dst, int count,
                        const GridLayout& g, const uint8_t* pal_src, uint8_t* pal_dst, uint32_t* lut_dst,
                        int materials_plus_one, const float intensity[kNumFaces], const HeightFeedback& heights,
-                       hipStream_t stream);
+                       const SideWork* side, hipStream_t stream);
 hipError_t launch_update_voxels(const int32_t* env, const int32_t* voxel_index, const uint8_t* material, int count,
                                 uint8_t* vox, uint64_t* bits, int32_t* ztop, int num_envs, int voxels_per_env,
-                                int num_materials, const GridLayout& g, const HeightFeedback& heights,
+                                int num_materials, const GridLayout& g, const HeightFeedback& heights, const SideWork* side,
                                 hipStream_t stream);
 hipError_t launch_move_voxels(const int32_t* env, const int32_t* from_voxel, const int32_t* to_voxel,
                               const uint8_t* material, int count, uint8_t* vox, uint64_t* bits, int32_t* ztop,
                               int num_envs, int voxels_per_env, int num_materials, const GridLayout& g,
                               const HeightFeedback& heights, hipStream_t stream);
-hipError_t launch_cameras(const float* cams, const int32_t* self_voxel, CameraRecord* rec, int num_obs,
-                          double tan_half_x, double tan_half_y, const GridLayout& g, hipStream_t stream);
 struct BarParams {
     int32_t x, y, width, height;
     uint32_t fill_packed, empty_packed;   // r | g<<8 | b<<16
@@ -161,8 +169,6 @@ struct OverlayParams {
 };
 hipError_t launch_overlay(uint8_t* rgb, const float* values, int values_per_obs, const uint8_t* active, int num_obs, int A,
                           int W, int H, const OverlayParams& overlay, hipStream_t stream);
-// active[i] = (done[i] == 0) for the n environments of a batch
-hipError_t launch_active_from_done(const uint8_t* done, uint8_t* active, int n, hipStream_t stream);
 // raises the dynamic-LDS limit of the render and pack kernels on the current device (cheap after the first call)
 hipError_t prepare_kernels();
 // dynamic LDS the pack kernel asks for: one z layer per wave

@@ -95,19 +95,65 @@ LdsPlan plan_lds(const GridLayout& g, int W, int H, int materials_plus_one, int 
 }
 
 // ------------------------------------------------------------------------------------------
-// pixel-centre scalars: sx[c] = (2c+1-W)/W, sy[r] = (H-2r-1)/H, one correctly rounded divide each
+// Work per camera, image row and column, and environment, microseconds in all: a launch of its own for each costs more
+// (about 4.7 us between two others, most of it start and end of the launch) than the work.  Calls that know several of
+// them at once run them together, in workgroups behind those of a launch the call makes anyway (SideWork).
+//   pixel-centre scalars: sx[c] = (2c+1-W)/W, sy[r] = (H-2r-1)/H, one correctly rounded divide each
+//   cameras: basis from yaw/pitch in float64, scaled, rounded once to float32.
+//     forward F = (cos p cos y, cos p sin y, sin p), right = (sin y, -cos y, 0),
+//     up = (-sin p cos y, -sin p sin y, cos p)
+//   active[n] = (done[n] == 0)
 // ------------------------------------------------------------------------------------------
-__global__ void pixel_scalars_kernel(float* __restrict__ sx, float* __restrict__ sy, int W, int H)
+constexpr int kSideThreads = 256;       // items a workgroup of any host kernel takes
+
+__device__ __forceinline__ void write_camera(const SideWork& s, int o)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < W) sx[i] = __fdiv_rn((float)(2 * i + 1 - W), (float)W);
-    if (i < H) sy[i] = __fdiv_rn((float)(H - 2 * i - 1), (float)H);
+    const float* c = s.cams + 5 * (size_t)o;
+    double yaw = (double)c[3], pitch = (double)c[4];
+    double sy, cy, sp, cp;
+    sincos(yaw, &sy, &cy);
+    sincos(pitch, &sp, &cp);
+    CameraRecord r;
+    r.P[0] = c[0]; r.P[1] = c[1]; r.P[2] = c[2];
+    r.F[0] = (float)(cp * cy); r.F[1] = (float)(cp * sy); r.F[2] = (float)sp;
+    r.R[0] = (float)(s.tan_half_x * sy); r.R[1] = (float)(s.tan_half_x * -cy); r.R[2] = (float)(s.tan_half_x * 0.0);
+    r.U[0] = (float)(s.tan_half_y * (-sp * cy)); r.U[1] = (float)(s.tan_half_y * (-sp * sy)); r.U[2] = (float)(s.tan_half_y * cp);
+    const int body = s.self_voxel ? s.self_voxel[o] : -1;
+    r.self_lo = body >= 0 ? body : -1;
+    r.self_hi = body >= 0 ? body + s.X * s.Y : -1;
+    // where the camera stands, once here instead of in every workgroup that renders for it
+    const bool in_grid = r.P[0] >= 0.0f && r.P[0] <= (float)s.X && r.P[1] >= 0.0f && r.P[1] <= (float)s.Y &&
+                         r.P[2] >= 0.0f && r.P[2] <= (float)s.Z;
+    const bool near = fabsf(r.P[0]) <= kNearOutside && fabsf(r.P[1]) <= kNearOutside && fabsf(r.P[2]) <= kNearOutside;
+    r.place = in_grid ? kPlaceInGrid : (near ? kPlaceOutside : kPlaceFarOutside);
+    r.layer = min(max((int)floorf(r.P[2]), 0), s.Z - 1);
+    s.rec[o] = r;
 }
 
-hipError_t launch_pixel_scalars(float* sx, float* sy, int W, int H, hipStream_t stream)
+// item `i` of every kind the call has (the counts of the others are 0)
+__device__ __forceinline__ void side_work(const SideWork& s, int i)
 {
-    int n = W > H ? W : H;
-    hipLaunchKernelGGL(pixel_scalars_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, sx, sy, W, H);
+    if (i < s.W) s.sx[i] = __fdiv_rn((float)(2 * i + 1 - s.W), (float)s.W);
+    if (i < s.H) s.sy[i] = __fdiv_rn((float)(s.H - 2 * i - 1), (float)s.H);
+    if (i < s.num_done) s.active[i] = s.done[i] == 0 ? 1 : 0;
+    if (i < s.num_obs) write_camera(s, i);
+}
+
+static int side_blocks(const SideWork& s)
+{
+    int n = s.num_obs;
+    if (s.W > n) n = s.W;
+    if (s.H > n) n = s.H;
+    if (s.num_done > n) n = s.num_done;
+    return (n + kSideThreads - 1) / kSideThreads;
+}
+
+__global__ void side_kernel(SideWork s) { side_work(s, blockIdx.x * blockDim.x + threadIdx.x); }
+
+hipError_t launch_side(const SideWork& side, hipStream_t stream)
+{
+    // (workgroups of 128 spread few cameras over more compute units)
+    hipLaunchKernelGGL(side_kernel, dim3(2 * side_blocks(side)), dim3(kSideThreads / 2), 0, stream, side);
     return hipGetLastError();
 }
 
@@ -221,16 +267,21 @@ __device__ __forceinline__ void report_height(const HeightFeedback& fb, int top)
 // layers in flight per wave change nothing, four are slower: the kernel moves its bytes at the rate of a plain
 // device copy as it is.)  Other sizes and alignments have a kernel of their own: with their code in this one it
 // needed a third more registers, and lost two of its eight waves per SIMD.
-template <int kPackPrefetch>
+template <int kPackPrefetch, bool kSide>
 __global__ __launch_bounds__(kPackThreads) void pack_kernel(const uint8_t* __restrict__ src, uint8_t* __restrict__ vox_dst,
                                                             uint64_t* __restrict__ bits_dst, int32_t* __restrict__ ztop_dst,
                                                             GridLayout g, const uint8_t* __restrict__ pal_src,
                                                             uint8_t* __restrict__ pal_dst, uint32_t* __restrict__ lut_dst,
-                                                            int materials_plus_one, Intensities I, HeightFeedback heights)
+                                                            int materials_plus_one, Intensities I, HeightFeedback heights,
+                                                            int count, SideWork side)
 {
     extern __shared__ __align__(16) uint8_t layer_lds[];   // one layer per wave
     __shared__ int top_lds;
     const int env = blockIdx.x;
+    if (kSide && env >= count) {
+        side_work(side, (env - count) * kSideThreads + (int)threadIdx.x);
+        return;
+    }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int waves = kPackThreads / 64;
     const int X = g.X, Y = g.Y, Z = g.Z;
@@ -321,16 +372,21 @@ typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 // bytes never see LDS), and a row of the layer, wherever it starts in the bit string, costs two funnel shifts.
 // The kernel before this one gathered rows cell by cell out of a byte copy in LDS (three instructions per
 // cell and direction, four waves per environment).
+template <bool kSide>
 __global__ __launch_bounds__(kPackAnyWaves * 64) __attribute__((amdgpu_waves_per_eu(8, 8))) void pack_any_kernel(const uint8_t* __restrict__ src, uint8_t* __restrict__ vox_dst,
                                                                       uint64_t* __restrict__ bits_dst, int32_t* __restrict__ ztop_dst,
                                                                       GridLayout g, const uint8_t* __restrict__ pal_src,
                                                                       uint8_t* __restrict__ pal_dst, uint32_t* __restrict__ lut_dst,
                                                                       int materials_plus_one, Intensities I, HeightFeedback heights,
-                                                                      int bits_bytes, int waves)
+                                                                      int bits_bytes, int waves, int count, SideWork side)
 {
     extern __shared__ __align__(16) uint8_t bits_lds[];     // per wave: the bit string of one layer and two dwords more
     __shared__ int top_lds;
     const int env = blockIdx.x;
+    if (kSide && env >= count) {
+        if (threadIdx.x < kSideThreads) side_work(side, (env - count) * kSideThreads + (int)threadIdx.x);
+        return;
+    }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int X = g.X, Y = g.Y, Z = g.Z;
     const int XY = X * Y, wx = g.rowwords_x, wy = g.rowwords_y;
@@ -431,8 +487,11 @@ size_t pack_lds_bytes(const GridLayout& g)
 hipError_t launch_pack(const uint8_t* src, uint8_t* vox_dst, uint64_t* bits_dst, int32_t* ztop_dst, int count,
                        const GridLayout& g, const uint8_t* pal_src, uint8_t* pal_dst, uint32_t* lut_dst,
                        int materials_plus_one, const float intensity[kNumFaces], const HeightFeedback& heights,
-                       hipStream_t stream)
+                       const SideWork* side, hipStream_t stream)
 {
+    static_assert(kPackThreads == kSideThreads, "a pack workgroup takes one workgroup's share of side work");
+    const SideWork no_side{};
+    const int blocks = count + (side ? side_blocks(*side) : 0);
     Intensities I;
     for (int f = 0; f < kNumFaces; ++f) I.v[f] = intensity[f];
     const size_t XY = (size_t)g.X * g.Y;
@@ -440,18 +499,25 @@ hipError_t launch_pack(const uint8_t* src, uint8_t* vox_dst, uint64_t* bits_dst,
     // (fast grids hold at most 64 x 64 cells, 4 KiB, per layer: sixteen dwords per lane; rows are read as dwords)
     if (g.fast && aligned && (g.X & 3) == 0) {
         const size_t lds = pack_lds_bytes(g);
-#define MV_LAUNCH_PACK(PREFETCH)                                                                                          \
-    hipLaunchKernelGGL(pack_kernel<PREFETCH>, dim3(count), dim3(kPackThreads), lds, stream, src, vox_dst, bits_dst,        \
-                       ztop_dst, g, pal_src, pal_dst, lut_dst, materials_plus_one, I, heights)
-        if (XY / 4 <= 8 * 64) MV_LAUNCH_PACK(8); else MV_LAUNCH_PACK(16);
+#define MV_LAUNCH_PACK(PREFETCH, SIDE)                                                                                    \
+    hipLaunchKernelGGL((pack_kernel<PREFETCH, SIDE>), dim3(blocks), dim3(kPackThreads), lds, stream, src, vox_dst,         \
+                       bits_dst, ztop_dst, g, pal_src, pal_dst, lut_dst, materials_plus_one, I, heights, count,             \
+                       side ? *side : no_side)
+        if (XY / 4 <= 8 * 64) { if (side) MV_LAUNCH_PACK(8, true); else MV_LAUNCH_PACK(8, false); }
+        else                  { if (side) MV_LAUNCH_PACK(16, true); else MV_LAUNCH_PACK(16, false); }
 #undef MV_LAUNCH_PACK
     } else {
+        // (at least kSideThreads threads: what a workgroup takes of the side work)
         int waves = g.Z < kPackAnyWaves ? g.Z : kPackAnyWaves;
-        if (waves < 4) waves = 4;
+        if (waves < kSideThreads / 64) waves = kSideThreads / 64;
         // per wave: the layer's bit string, and the two dwords behind its last one that a row's last word may read
         const int bits_bytes = (int)(((XY + 31) / 32) * 4 + 8);
-        hipLaunchKernelGGL(pack_any_kernel, dim3(count), dim3(waves * 64), (size_t)waves * bits_bytes, stream, src, vox_dst,
-                           bits_dst, ztop_dst, g, pal_src, pal_dst, lut_dst, materials_plus_one, I, heights, bits_bytes, waves);
+#define MV_LAUNCH_PACK_ANY(SIDE)                                                                                          \
+    hipLaunchKernelGGL(pack_any_kernel<SIDE>, dim3(blocks), dim3(waves * 64), (size_t)waves * bits_bytes, stream, src,      \
+                       vox_dst, bits_dst, ztop_dst, g, pal_src, pal_dst, lut_dst, materials_plus_one, I, heights,           \
+                       bits_bytes, waves, count, side ? *side : no_side)
+        if (side) MV_LAUNCH_PACK_ANY(true); else MV_LAUNCH_PACK_ANY(false);
+#undef MV_LAUNCH_PACK_ANY
     }
     return hipGetLastError();
 }
@@ -464,12 +530,17 @@ hipError_t launch_pack(const uint8_t* src, uint8_t* vox_dst, uint64_t* bits_dst,
 // stream order, those that fill one -- so an object that moves into the voxel another one leaves in the
 // same step ends up there whatever the order of the two edits in the list.
 // ------------------------------------------------------------------------------------------
-template <bool kFill>
+template <bool kFill, bool kSide>
 __global__ void update_voxels_kernel(const int32_t* __restrict__ env, const int32_t* __restrict__ voxel_index,
                                      const uint8_t* __restrict__ material, int count, uint8_t* __restrict__ vox,
                                      uint64_t* __restrict__ bits, int32_t* __restrict__ ztop, int num_envs,
-                                     int voxels_per_env, int num_materials, GridLayout g, HeightFeedback heights)
+                                     int voxels_per_env, int num_materials, GridLayout g, HeightFeedback heights,
+                                     int edit_blocks, SideWork side)
 {
+    if (kSide && (int)blockIdx.x >= edit_blocks) {
+        side_work(side, ((int)blockIdx.x - edit_blocks) * kSideThreads + (int)threadIdx.x);
+        return;
+    }
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= count) return;
     const int n = env[e], idx = voxel_index[e];
@@ -495,14 +566,26 @@ __global__ void update_voxels_kernel(const int32_t* __restrict__ env, const int3
     }
 }
 
+constexpr int kEditThreads = kSideThreads;
+
+// `side`, if any, runs in workgroups behind the first launch's
 hipError_t launch_update_voxels(const int32_t* env, const int32_t* voxel_index, const uint8_t* material, int count,
                                 uint8_t* vox, uint64_t* bits, int32_t* ztop, int num_envs, int voxels_per_env,
-                                int num_materials, const GridLayout& g, const HeightFeedback& heights, hipStream_t stream)
+                                int num_materials, const GridLayout& g, const HeightFeedback& heights, const SideWork* side,
+                                hipStream_t stream)
 {
-    hipLaunchKernelGGL(update_voxels_kernel<false>, dim3((count + 255) / 256), dim3(256), 0, stream, env, voxel_index,
-                       material, count, vox, bits, ztop, num_envs, voxels_per_env, num_materials, g, heights);
-    hipLaunchKernelGGL(update_voxels_kernel<true>, dim3((count + 255) / 256), dim3(256), 0, stream, env, voxel_index,
-                       material, count, vox, bits, ztop, num_envs, voxels_per_env, num_materials, g, heights);
+    const SideWork no_side{};
+    const int blocks = (count + kEditThreads - 1) / kEditThreads;
+    if (side)
+        hipLaunchKernelGGL((update_voxels_kernel<false, true>), dim3(blocks + side_blocks(*side)), dim3(kEditThreads), 0,
+                           stream, env, voxel_index, material, count, vox, bits, ztop, num_envs, voxels_per_env,
+                           num_materials, g, heights, blocks, *side);
+    else
+        hipLaunchKernelGGL((update_voxels_kernel<false, false>), dim3(blocks), dim3(kEditThreads), 0, stream, env, voxel_index,
+                           material, count, vox, bits, ztop, num_envs, voxels_per_env, num_materials, g, heights, blocks,
+                           no_side);
+    hipLaunchKernelGGL((update_voxels_kernel<true, false>), dim3(blocks), dim3(kEditThreads), 0, stream, env, voxel_index,
+                       material, count, vox, bits, ztop, num_envs, voxels_per_env, num_materials, g, heights, blocks, no_side);
     return hipGetLastError();
 }
 
@@ -513,52 +596,13 @@ hipError_t launch_move_voxels(const int32_t* env, const int32_t* from_voxel, con
                               int num_envs, int voxels_per_env, int num_materials, const GridLayout& g,
                               const HeightFeedback& heights, hipStream_t stream)
 {
-    hipLaunchKernelGGL(update_voxels_kernel<false>, dim3((count + 255) / 256), dim3(256), 0, stream, env, from_voxel,
+    const SideWork no_side{};
+    const int blocks = (count + kEditThreads - 1) / kEditThreads;
+    hipLaunchKernelGGL((update_voxels_kernel<false, false>), dim3(blocks), dim3(kEditThreads), 0, stream, env, from_voxel,
                        static_cast<const uint8_t*>(nullptr), count, vox, bits, ztop, num_envs, voxels_per_env, num_materials,
-                       g, heights);
-    hipLaunchKernelGGL(update_voxels_kernel<true>, dim3((count + 255) / 256), dim3(256), 0, stream, env, to_voxel,
-                       material, count, vox, bits, ztop, num_envs, voxels_per_env, num_materials, g, heights);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------
-// cameras: basis from yaw/pitch in float64, scaled, rounded once to float32.
-//   forward F = (cos p cos y, cos p sin y, sin p), right = (sin y, -cos y, 0),
-//   up = (-sin p cos y, -sin p sin y, cos p)
-// ------------------------------------------------------------------------------------------
-__global__ void camera_kernel(const float* __restrict__ cams, const int32_t* __restrict__ self_voxel,
-                              CameraRecord* __restrict__ rec, int num_obs, double tan_half_x, double tan_half_y,
-                              int X, int Y, int Z)
-{
-    int o = blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= num_obs) return;
-    const float* c = cams + 5 * (size_t)o;
-    double yaw = (double)c[3], pitch = (double)c[4];
-    double sy, cy, sp, cp;
-    sincos(yaw, &sy, &cy);
-    sincos(pitch, &sp, &cp);
-    CameraRecord r;
-    r.P[0] = c[0]; r.P[1] = c[1]; r.P[2] = c[2];
-    r.F[0] = (float)(cp * cy); r.F[1] = (float)(cp * sy); r.F[2] = (float)sp;
-    r.R[0] = (float)(tan_half_x * sy); r.R[1] = (float)(tan_half_x * -cy); r.R[2] = (float)(tan_half_x * 0.0);
-    r.U[0] = (float)(tan_half_y * (-sp * cy)); r.U[1] = (float)(tan_half_y * (-sp * sy)); r.U[2] = (float)(tan_half_y * cp);
-    int s = self_voxel ? self_voxel[o] : -1;
-    r.self_lo = s >= 0 ? s : -1;
-    r.self_hi = s >= 0 ? s + X * Y : -1;
-    // where the camera stands, once here instead of in every workgroup that renders for it
-    const bool in_grid = r.P[0] >= 0.0f && r.P[0] <= (float)X && r.P[1] >= 0.0f && r.P[1] <= (float)Y &&
-                         r.P[2] >= 0.0f && r.P[2] <= (float)Z;
-    const bool near = fabsf(r.P[0]) <= kNearOutside && fabsf(r.P[1]) <= kNearOutside && fabsf(r.P[2]) <= kNearOutside;
-    r.place = in_grid ? kPlaceInGrid : (near ? kPlaceOutside : kPlaceFarOutside);
-    r.layer = min(max((int)floorf(r.P[2]), 0), Z - 1);
-    rec[o] = r;
-}
-
-hipError_t launch_cameras(const float* cams, const int32_t* self_voxel, CameraRecord* rec, int num_obs,
-                          double tan_half_x, double tan_half_y, const GridLayout& g, hipStream_t stream)
-{
-    hipLaunchKernelGGL(camera_kernel, dim3((num_obs + 127) / 128), dim3(128), 0, stream, cams, self_voxel, rec,
-                       num_obs, tan_half_x, tan_half_y, g.X, g.Y, g.Z);
+                       g, heights, blocks, no_side);
+    hipLaunchKernelGGL((update_voxels_kernel<true, false>), dim3(blocks), dim3(kEditThreads), 0, stream, env, to_voxel,
+                       material, count, vox, bits, ztop, num_envs, voxels_per_env, num_materials, g, heights, blocks, no_side);
     return hipGetLastError();
 }
 
@@ -1802,18 +1846,6 @@ hipError_t launch_overlay(uint8_t* rgb, const float* values, int values_per_obs,
     return hipGetLastError();
 }
 
-__global__ void active_from_done_kernel(const uint8_t* __restrict__ done, uint8_t* __restrict__ active, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) active[i] = done[i] == 0 ? 1 : 0;
-}
-
-hipError_t launch_active_from_done(const uint8_t* done, uint8_t* active, int n, hipStream_t stream)
-{
-    hipLaunchKernelGGL(active_from_done_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, done, active, n);
-    return hipGetLastError();
-}
-
 template <bool AUX, bool PACKED, bool FAST, bool COARSE = false>
 static hipError_t set_lds_limit()
 {
@@ -1842,8 +1874,9 @@ hipError_t prepare_kernels()
 #undef MV_SET
     // the pack kernel also has a few static words of LDS: its dynamic share must leave room for them
     const int pack_limit = (int)(kLdsBudget - kPackStaticLds);
-    const void* pack_kernels[] = { reinterpret_cast<const void*>(&pack_kernel<8>), reinterpret_cast<const void*>(&pack_kernel<16>),
-                                   reinterpret_cast<const void*>(&pack_any_kernel) };
+    const void* pack_kernels[] = { reinterpret_cast<const void*>(&pack_kernel<8, false>), reinterpret_cast<const void*>(&pack_kernel<8, true>),
+                                   reinterpret_cast<const void*>(&pack_kernel<16, false>), reinterpret_cast<const void*>(&pack_kernel<16, true>),
+                                   reinterpret_cast<const void*>(&pack_any_kernel<false>), reinterpret_cast<const void*>(&pack_any_kernel<true>) };
     for (const void* k : pack_kernels)
         if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, pack_limit);
     if (e == hipSuccess && device >= 0 && device < kMaxDevices) done[device].store(true, std::memory_order_release);
