@@ -497,7 +497,11 @@ hipError_t launch_pack(const uint8_t* src, uint8_t* vox_dst, uint64_t* bits_dst,
     const size_t XY = (size_t)g.X * g.Y;
     const bool aligned = XY % 16 == 0 && ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(vox_dst)) & 15) == 0;
     // (fast grids hold at most 64 x 64 cells, 4 KiB, per layer: sixteen dwords per lane; rows are read as dwords)
-    if (g.fast && aligned && (g.X & 3) == 0) {
+    // Few worlds leave most of the chip idle: there the general kernel, a wave per layer instead of four layers one after
+    // the other per wave, is the faster one (40x40x16, us: 64 worlds 6.8 -> 5.2, 256 7.2 -> 5.9, 512 8.3 and 7.9, 1024 11.7
+    // and 14.3; 64x64x32: 64 worlds 11.8 -> 9.6, 256 13.7 -> 13.0, 512 21.5 and 21.9; 16x16x8 the same up to 512).
+    const bool few = count <= 256;
+    if (g.fast && aligned && (g.X & 3) == 0 && !few) {
         const size_t lds = pack_lds_bytes(g);
 #define MV_LAUNCH_PACK(PREFETCH, SIDE)                                                                                    \
     hipLaunchKernelGGL((pack_kernel<PREFETCH, SIDE>), dim3(blocks), dim3(kPackThreads), lds, stream, src, vox_dst,         \

@@ -1542,6 +1542,37 @@ def test_pack_kernel_bit_exact(lib, grid):
         check(vox2)
 
 
+@pytest.mark.parametrize("grid", [(4, 4, 3), (40, 40, 16), (64, 64, 5), (60, 28, 9), (64, 2, 4)])
+def test_pack_of_many_and_of_few_worlds_agree(lib, grid):
+    """Uploads of more than 256 worlds and of fewer take different pack kernels: same rows, tops and material bytes where
+    there is a solid voxel, for layers of air between solid ones, empty worlds and full ones."""
+    rng = np.random.default_rng(sum(grid))
+    N, half = 260, 130
+    X, Y, Z = grid
+    vox, pal = synth.random_world(rng, N, grid, 0.05, 9)
+    vox[::3, Z // 2] = 0
+    vox[1::7] = 0
+    vox[2::7] = 9
+    vd, pd = torch.from_numpy(vox).cuda(), torch.from_numpy(pal).cuda()
+    got = []
+    for parts in ((0, N),), ((0, half), (half, N)):
+        batch = binding.Batch(N, 1, grid, 9, 16, 8)
+        for a, b in parts:
+            batch.upload_worlds(vd[a:b], pd[a:b], first_env=a, stream=_stream())
+        batch.set_cameras(np.tile(np.array([X / 2, Y / 2, Z + 1.0, 0.3, -1.2], np.float32), (N, 1)), stream=_stream())
+        run = GpuRender(batch, 16, 8)
+        run.render()
+        xp, xw, yp, yw, tp = batch.debug_occupancy(0)
+        got.append((_read_device(xp, N * (Z * Y * xw + Z * X * yw) * 8), _read_device(tp, N * 4), run.numpy()))
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    np.testing.assert_array_equal(got[0][1], got[1][1])
+    np.testing.assert_array_equal(got[0][2].rgb, got[1][2].rgb)
+    np.testing.assert_array_equal(got[0][2].material, got[1][2].material)
+    want = np.packbits(np.pad(vox != 0, ((0, 0), (0, 0), (0, 0), (0, 64 - X))), axis=-1, bitorder="little")
+    rows = got[0][0].reshape(N, -1)[:, :Z * Y * 8].reshape(N, Z, Y, 8)
+    np.testing.assert_array_equal(rows, want)
+
+
 @pytest.mark.parametrize("grid", [(3, 5, 2), (15, 1, 3), (4, 4, 5), (17, 1, 1), (31, 33, 4), (64, 65, 3), (65, 64, 3), (96, 96, 5),
                                   (127, 129, 2), (41, 39, 17), (40, 40, 3), (200, 200, 1)])
 @pytest.mark.parametrize("offset", [0, 1, 4])
