@@ -55,6 +55,106 @@ private:
 
 }  // namespace
 
+// Host inputs of a call on their way to the GPU: they are copied into one of a batch's few pinned buffers, and the kernels
+// read them from there.  The call then neither waits for the stream nor makes copies of its own, which cost about 10 us
+// each, more than such a kernel takes to read its inputs over the link (64 x 2 cameras, an eighth of the worlds, moves and
+// cameras from host arrays and images fetched: a step 317 -> 249 us, of which the images take 150).  A buffer is taken again only when the launches of its
+// last use are over.
+class HostStaging {
+public:
+    // four buffers each of 64 KiB, 256 KiB and 1 MiB, made when first needed (pinning memory costs time by the page);
+    // above 1 MiB the copy engine's rate counts for more
+    static constexpr int kClasses = 3, kSlots = 4;
+    static constexpr size_t class_bytes(int c) { return (size_t)65536 << (2 * c); }
+    struct Part { const void* src; size_t bytes; const void* on_device; };      // on_device: out
+
+    // True: the parts are staged and may be reused by the caller; launch what reads them and call used().  False (too
+    // large, a stream that is being captured, no pinned memory): nothing happened, the caller copies and waits itself.
+    bool stage(Part* parts, int count, hipStream_t stream, hipError_t* err)
+    {
+        *err = hipSuccess;
+        size_t total = 0;
+        for (int i = 0; i < count; ++i) total += padded(parts[i].bytes);
+        int c = 0;
+        while (c < kClasses && total > class_bytes(c)) ++c;
+        if (c == kClasses) return false;
+        if (stream) {
+            hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(stream, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
+            if (status != hipStreamCaptureStatusNone) return false;
+        }
+        // a buffer that is free, else a new one, else the one used longest ago
+        Slot* free_slot = nullptr;
+        for (int i = 0; i < kSlots && !free_slot; ++i) {
+            Slot& s = slots_[c][i];
+            if (!s.memory) { if (!s.create(class_bytes(c))) return false; free_slot = &s; }
+            else if (!s.in_use || hipEventQuery(s.over) == hipSuccess) free_slot = &s;
+        }
+        (void)hipGetLastError();            // (a query's "not ready")
+        if (!free_slot) {
+            for (Slot& s : slots_[c])
+                if (!free_slot || s.order < free_slot->order) free_slot = &s;
+            *err = hipEventSynchronize(free_slot->over);
+            if (*err != hipSuccess) return true;
+        }
+        Slot& s = *free_slot;
+        s.in_use = false;
+        current_ = &s;
+        size_t at = 0;
+        for (int i = 0; i < count; ++i) {
+            std::memcpy(s.memory + at, parts[i].src, parts[i].bytes);
+            parts[i].on_device = s.device + at;
+            at += padded(parts[i].bytes);
+        }
+        return true;
+    }
+    // after the launches that read the parts staged last
+    hipError_t used(hipStream_t stream)
+    {
+        Slot& s = *current_;
+        s.order = ++uses_;
+        const hipError_t e = hipEventRecord(s.over, stream);
+        if (e != hipSuccess) (void)hipStreamSynchronize(stream);
+        else s.in_use = true;
+        return e;
+    }
+    void release()
+    {
+        for (auto& row : slots_)
+            for (Slot& s : row) s.destroy();
+    }
+
+private:
+    struct Slot {
+        uint8_t* memory = nullptr;
+        uint8_t* device = nullptr;
+        hipEvent_t over = nullptr;
+        bool in_use = false;
+        uint64_t order = 0;
+        bool create(size_t bytes)
+        {
+            if (hipHostMalloc((void**)&memory, bytes, hipHostMallocMapped) != hipSuccess) memory = nullptr;
+            if (memory && hipHostGetDevicePointer((void**)&device, memory, 0) == hipSuccess &&
+                hipEventCreateWithFlags(&over, hipEventDisableTiming) == hipSuccess)
+                return true;
+            (void)hipGetLastError();
+            over = nullptr;
+            destroy();
+            return false;
+        }
+        void destroy()
+        {
+            if (over) (void)hipEventDestroy(over);
+            if (memory) (void)hipHostFree(memory);
+            over = nullptr; memory = nullptr; in_use = false;
+        }
+    };
+    static size_t padded(size_t n) { return (n + 63) & ~(size_t)63; }
+    Slot slots_[kClasses][kSlots];
+    Slot* current_ = nullptr;
+    uint64_t uses_ = 0;
+};
+
 struct mv_batch {
     mv_config cfg{};
     int num_obs = 0;
@@ -87,6 +187,7 @@ struct mv_batch {
     int32_t* d_height = nullptr;
     int32_t* h_height = nullptr;          // pinned host memory
     int32_t* h_height_dev = nullptr;      // the same word as the device addresses it
+    HostStaging staging;
     int forced_layers = 0;                // debug override (0 = automatic)
     // the render's launch shape for `shaped_layers` staged layers: it follows from the configuration and that number
     mv::RenderParams shape{};
@@ -107,6 +208,7 @@ static void free_batch(mv_batch* b)
     (void)hipFree(b->d_overlay_values);
     (void)hipFree(b->d_height);
     if (b->h_height) (void)hipHostFree(b->h_height);
+    b->staging.release();
     delete b;
 }
 
@@ -208,7 +310,10 @@ static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::Gri
         if (mv::kLdsBudget / plan.bytes >= 4 && strips < 3) strips = 3;
         if (strips < 1) strips = 1;
         tpb = (int)((p.tiles_per_obs + strips - 1) / strips);
-        const int min_tpb = waves * 2;
+        // Two tiles per wave at least, or one where even that leaves compute units without a workgroup (4 observations of
+        // 128x72: 5.2 -> 4.4 us; 64 observations, 1152 workgroups of two tiles per wave: 8.6 us, of one 9.6).
+        const long long two_each = (long long)num_obs * ((p.tiles_per_obs + 2 * waves - 1) / (2 * waves));
+        const int min_tpb = two_each <= 256 ? waves : waves * 2;
         if (tpb < min_tpb) tpb = min_tpb;
         // The last twentieth (to tenth, see below) of every XCD's observations is cut into strips a third as long: the XCD's
         // work then ends with short workgroups (4096 x 2 observations, 3 strips of 48 tiles: tail strips of
@@ -370,17 +475,29 @@ int mv_upload_worlds(mv_batch* b, int32_t first_env, int32_t count, const uint8_
     if (!src_is_device) {
         const size_t n = (size_t)count * V;
         const uint8_t limit = (uint8_t)b->cfg.num_materials;
-        for (size_t i = 0; i < n; ++i)
+        uint8_t highest = 0;                // (no early way out: the compiler takes 16 and more bytes at a time)
+        for (size_t i = 0; i < n; ++i) highest = voxels[i] > highest ? voxels[i] : highest;
+        for (size_t i = 0; highest > limit && i < n; ++i)
             if (voxels[i] > limit)
                 return fail(MV_ERR_RANGE, "mv_upload_worlds: material id %d at voxel %zu exceeds num_materials %d",
                             (int)voxels[i], i, (int)limit);
-        MV_HIP(hipMemcpyAsync(vox_dst, voxels, n, hipMemcpyHostToDevice, stream));
-        if (palette) MV_HIP(hipMemcpyAsync(pal_dst, palette, (size_t)count * pal_bytes, hipMemcpyHostToDevice, stream));
-        // pageable host memory: make sure the runtime is done reading it before we return
-        MV_HIP(hipStreamSynchronize(stream));
-        MV_HIP(mv::launch_pack(vox_dst, vox_dst, bits_dst, ztop_dst, count, b->layout, palette ? pal_dst : nullptr,
-                               pal_dst, lut_dst, b->materials_plus_one, b->intensity,
-                               mv::HeightFeedback{ b->d_height, b->h_height_dev }, nullptr, stream));
+        HostStaging::Part parts[] = { { voxels, n, vox_dst }, { palette, (size_t)count * pal_bytes, pal_dst } };
+        hipError_t e = hipSuccess;
+        const bool staged = b->staging.stage(parts, palette ? 2 : 1, stream, &e);
+        MV_HIP(e);
+        if (!staged) {
+            MV_HIP(hipMemcpyAsync(vox_dst, voxels, n, hipMemcpyHostToDevice, stream));
+            if (palette) MV_HIP(hipMemcpyAsync(pal_dst, palette, (size_t)count * pal_bytes, hipMemcpyHostToDevice, stream));
+            // pageable host memory: make sure the runtime is done reading it before we return
+            MV_HIP(hipStreamSynchronize(stream));
+        }
+        const hipError_t launched = mv::launch_pack((const uint8_t*)parts[0].on_device, vox_dst, bits_dst, ztop_dst, count, b->layout,
+                                                    palette ? (const uint8_t*)parts[1].on_device : nullptr, pal_dst, lut_dst,
+                                                    b->materials_plus_one, b->intensity,
+                                                    mv::HeightFeedback{ b->d_height, b->h_height_dev }, nullptr, stream);
+        if (staged) e = b->staging.used(stream);
+        MV_HIP(launched);
+        MV_HIP(e);
     } else if (src_is_device == MV_SRC_DEVICE_BORROWED) {
         // source and destination of the material copy are the caller's array: nothing is copied
         MV_HIP(mv::launch_pack(voxels, const_cast<uint8_t*>(voxels), bits_dst, ztop_dst, count, b->layout, palette, pal_dst,
@@ -401,6 +518,33 @@ int mv_upload_worlds(mv_batch* b, int32_t first_env, int32_t count, const uint8_
     return MV_OK;
 }
 
+// The host arrays of an edit list, where the kernels can read them: staged, or (too many, or a stream that is being
+// captured) in the batch's device buffer, which only ever grows.  The parts' sizes are multiples of 4 n but for the last.
+static int edits_to_device(mv_batch* b, HostStaging::Part* parts, int count, size_t n, hipStream_t stream, bool* staged)
+{
+    hipError_t e = hipSuccess;
+    *staged = b->staging.stage(parts, count, stream, &e);
+    MV_HIP(e);
+    if (*staged) return MV_OK;
+    if (n > b->edits_capacity) {
+        size_t cap = b->edits_capacity ? b->edits_capacity : 4096;
+        while (cap < n) cap *= 2;
+        uint8_t* fresh = nullptr;
+        MV_HIP(hipMalloc((void**)&fresh, cap * 13));
+        MV_HIP(hipStreamSynchronize(stream));
+        (void)hipFree(b->d_edits);
+        b->d_edits = fresh;
+        b->edits_capacity = cap;
+    }
+    for (int i = 0; i < count; ++i) {
+        uint8_t* dst = b->d_edits + (size_t)i * 4 * b->edits_capacity;
+        MV_HIP(hipMemcpyAsync(dst, parts[i].src, parts[i].bytes, hipMemcpyHostToDevice, stream));
+        parts[i].on_device = dst;
+    }
+    MV_HIP(hipStreamSynchronize(stream));
+    return MV_OK;
+}
+
 int mv_update_voxels(mv_batch* b, int32_t count, const int32_t* env, const int32_t* voxel_index, const uint8_t* material,
                      int32_t src_is_device, void* hip_stream)
 {
@@ -415,6 +559,7 @@ int mv_update_voxels(mv_batch* b, int32_t count, const int32_t* env, const int32
     const int32_t* d_env = env;
     const int32_t* d_idx = voxel_index;
     const uint8_t* d_mat = material;
+    bool staged = false;
     if (!src_is_device) {
         for (int32_t e = 0; e < count; ++e) {
             if (env[e] < 0 || env[e] >= b->cfg.num_envs)
@@ -427,29 +572,19 @@ int mv_update_voxels(mv_batch* b, int32_t count, const int32_t* env, const int32
             if (!b->env_has_grid[env[e]])
                 return fail(MV_ERR_STATE, "mv_update_voxels: environment %d has no grid yet", env[e]);
         }
-        if ((size_t)count > b->edits_capacity) {
-            // the staging buffer only ever grows; steady-state steps do not allocate
-            size_t cap = b->edits_capacity ? b->edits_capacity : 4096;
-            while (cap < (size_t)count) cap *= 2;
-            uint8_t* fresh = nullptr;
-            MV_HIP(hipMalloc((void**)&fresh, cap * 13));
-            MV_HIP(hipStreamSynchronize(stream));
-            (void)hipFree(b->d_edits);
-            b->d_edits = fresh;
-            b->edits_capacity = cap;
-        }
-        int32_t* s_env = reinterpret_cast<int32_t*>(b->d_edits);
-        int32_t* s_idx = s_env + b->edits_capacity;
-        uint8_t* s_mat = reinterpret_cast<uint8_t*>(s_idx + b->edits_capacity);
-        MV_HIP(hipMemcpyAsync(s_env, env, (size_t)count * 4, hipMemcpyHostToDevice, stream));
-        MV_HIP(hipMemcpyAsync(s_idx, voxel_index, (size_t)count * 4, hipMemcpyHostToDevice, stream));
-        MV_HIP(hipMemcpyAsync(s_mat, material, (size_t)count, hipMemcpyHostToDevice, stream));
-        MV_HIP(hipStreamSynchronize(stream));
-        d_env = s_env; d_idx = s_idx; d_mat = s_mat;
+        const size_t n = (size_t)count;
+        HostStaging::Part parts[] = { { env, 4 * n, nullptr }, { voxel_index, 4 * n, nullptr }, { material, n, nullptr } };
+        const int rc = edits_to_device(b, parts, 3, n, stream, &staged);
+        if (rc != MV_OK) return rc;
+        d_env = (const int32_t*)parts[0].on_device; d_idx = (const int32_t*)parts[1].on_device;
+        d_mat = (const uint8_t*)parts[2].on_device;
     }
-    MV_HIP(mv::launch_update_voxels(d_env, d_idx, d_mat, count, b->d_vox, b->d_bits, b->d_ztop, b->cfg.num_envs,
-                                    b->voxels_per_env, b->cfg.num_materials, b->layout,
-                                    mv::HeightFeedback{ b->d_height, b->h_height_dev }, nullptr, stream));
+    const hipError_t launched = mv::launch_update_voxels(d_env, d_idx, d_mat, count, b->d_vox, b->d_bits, b->d_ztop, b->cfg.num_envs,
+                                                         b->voxels_per_env, b->cfg.num_materials, b->layout,
+                                                         mv::HeightFeedback{ b->d_height, b->h_height_dev }, nullptr, stream);
+    const hipError_t e = staged ? b->staging.used(stream) : hipSuccess;
+    MV_HIP(launched);
+    MV_HIP(e);
     return MV_OK;
 }
 
@@ -468,6 +603,7 @@ int mv_move_voxels(mv_batch* b, int32_t count, const int32_t* env, const int32_t
     const int32_t* d_from = from_voxel;
     const int32_t* d_to = to_voxel;
     const uint8_t* d_mat = material;
+    bool staged = false;
     if (!src_is_device) {
         for (int32_t e = 0; e < count; ++e) {
             if (env[e] < 0 || env[e] >= b->cfg.num_envs)
@@ -480,30 +616,20 @@ int mv_move_voxels(mv_batch* b, int32_t count, const int32_t* env, const int32_t
             if (!b->env_has_grid[env[e]])
                 return fail(MV_ERR_STATE, "mv_move_voxels: environment %d has no grid yet", env[e]);
         }
-        if ((size_t)count > b->edits_capacity) {
-            size_t cap = b->edits_capacity ? b->edits_capacity : 4096;
-            while (cap < (size_t)count) cap *= 2;
-            uint8_t* fresh = nullptr;
-            MV_HIP(hipMalloc((void**)&fresh, cap * 13));
-            MV_HIP(hipStreamSynchronize(stream));
-            (void)hipFree(b->d_edits);
-            b->d_edits = fresh;
-            b->edits_capacity = cap;
-        }
-        int32_t* s_env = reinterpret_cast<int32_t*>(b->d_edits);
-        int32_t* s_from = s_env + b->edits_capacity;
-        int32_t* s_to = s_from + b->edits_capacity;
-        uint8_t* s_mat = reinterpret_cast<uint8_t*>(s_to + b->edits_capacity);
-        MV_HIP(hipMemcpyAsync(s_env, env, (size_t)count * 4, hipMemcpyHostToDevice, stream));
-        MV_HIP(hipMemcpyAsync(s_from, from_voxel, (size_t)count * 4, hipMemcpyHostToDevice, stream));
-        MV_HIP(hipMemcpyAsync(s_to, to_voxel, (size_t)count * 4, hipMemcpyHostToDevice, stream));
-        MV_HIP(hipMemcpyAsync(s_mat, material, (size_t)count, hipMemcpyHostToDevice, stream));
-        MV_HIP(hipStreamSynchronize(stream));
-        d_env = s_env; d_from = s_from; d_to = s_to; d_mat = s_mat;
+        const size_t n = (size_t)count;
+        HostStaging::Part parts[] = { { env, 4 * n, nullptr }, { from_voxel, 4 * n, nullptr }, { to_voxel, 4 * n, nullptr },
+                                      { material, n, nullptr } };
+        const int rc = edits_to_device(b, parts, 4, n, stream, &staged);
+        if (rc != MV_OK) return rc;
+        d_env = (const int32_t*)parts[0].on_device; d_from = (const int32_t*)parts[1].on_device;
+        d_to = (const int32_t*)parts[2].on_device; d_mat = (const uint8_t*)parts[3].on_device;
     }
-    MV_HIP(mv::launch_move_voxels(d_env, d_from, d_to, d_mat, count, b->d_vox, b->d_bits, b->d_ztop, b->cfg.num_envs,
-                                  b->voxels_per_env, b->cfg.num_materials, b->layout,
-                                  mv::HeightFeedback{ b->d_height, b->h_height_dev }, stream));
+    const hipError_t launched = mv::launch_move_voxels(d_env, d_from, d_to, d_mat, count, b->d_vox, b->d_bits, b->d_ztop, b->cfg.num_envs,
+                                                       b->voxels_per_env, b->cfg.num_materials, b->layout,
+                                                       mv::HeightFeedback{ b->d_height, b->h_height_dev }, stream);
+    const hipError_t e = staged ? b->staging.used(stream) : hipSuccess;
+    MV_HIP(launched);
+    MV_HIP(e);
     return MV_OK;
 }
 
@@ -515,6 +641,7 @@ int mv_set_cameras(mv_batch* b, const float* cams, const int32_t* self_voxel, in
     hipStream_t stream = (hipStream_t)hip_stream;
     const float* d_cams = cams;
     const int32_t* d_self = self_voxel;
+    bool staged = false;
     if (!src_is_device) {
         const size_t n = (size_t)b->num_obs * 5;
         for (size_t i = 0; i < n; ++i)
@@ -523,13 +650,22 @@ int mv_set_cameras(mv_batch* b, const float* cams, const int32_t* self_voxel, in
             for (int o = 0; o < b->num_obs; ++o)
                 if (self_voxel[o] < -1 || self_voxel[o] >= b->voxels_per_env)
                     return fail(MV_ERR_RANGE, "mv_set_cameras: self_voxel[%d] = %d outside the grid", o, self_voxel[o]);
-        MV_HIP(hipMemcpyAsync(b->d_cams, cams, n * 4, hipMemcpyHostToDevice, stream));
-        if (self_voxel) MV_HIP(hipMemcpyAsync(b->d_self, self_voxel, (size_t)b->num_obs * 4, hipMemcpyHostToDevice, stream));
-        MV_HIP(hipStreamSynchronize(stream));
-        d_cams = b->d_cams;
-        d_self = self_voxel ? b->d_self : nullptr;
+        HostStaging::Part parts[] = { { cams, n * 4, b->d_cams }, { self_voxel, (size_t)b->num_obs * 4, b->d_self } };
+        hipError_t e = hipSuccess;
+        staged = b->staging.stage(parts, self_voxel ? 2 : 1, stream, &e);
+        MV_HIP(e);
+        if (!staged) {
+            MV_HIP(hipMemcpyAsync(b->d_cams, cams, n * 4, hipMemcpyHostToDevice, stream));
+            if (self_voxel) MV_HIP(hipMemcpyAsync(b->d_self, self_voxel, (size_t)b->num_obs * 4, hipMemcpyHostToDevice, stream));
+            MV_HIP(hipStreamSynchronize(stream));
+        }
+        d_cams = (const float*)parts[0].on_device;
+        d_self = self_voxel ? (const int32_t*)parts[1].on_device : nullptr;
     }
-    MV_HIP(mv::launch_side(camera_work(b, d_cams, d_self), stream));
+    const hipError_t launched = mv::launch_side(camera_work(b, d_cams, d_self), stream);
+    const hipError_t e = staged ? b->staging.used(stream) : hipSuccess;
+    MV_HIP(launched);
+    MV_HIP(e);
     b->cameras_set = true;
     return MV_OK;
 }

@@ -1542,6 +1542,49 @@ def test_pack_kernel_bit_exact(lib, grid):
         check(vox2)
 
 
+def test_host_arrays_may_be_reused_on_return(lib):
+    """Host inputs of every size class (up to 64 KiB, 256 KiB, 1 MiB and beyond), more calls in flight than there are
+    buffers, the caller's arrays overwritten straight after each call, two streams: the GPU's state is that of the same
+    calls with device arrays."""
+    rng = np.random.default_rng(5)
+    grid, M = (40, 40, 16), 9
+    V = grid[0] * grid[1] * grid[2]
+    side = torch.cuda.Stream()
+    for N in (2, 8, 30, 60):
+        vox, pal = synth.random_world(rng, N, grid, 0.1, M)
+        batches = [binding.Batch(N, 1, grid, M, 32, 24) for _ in range(2)]
+        runs = [GpuRender(b, 32, 24) for b in batches]
+        for b in batches:
+            b.upload_worlds(torch.from_numpy(vox).cuda(), torch.from_numpy(pal).cuda(), stream=_stream())
+        torch.cuda.synchronize()
+        for rep in range(7):
+            stream = _stream() if rep % 2 else side.cuda_stream
+            worlds, colours = synth.random_world(rng, N, grid, 0.02 * (rep + 1), M)
+            cells = np.stack([rng.permutation(V)[:3000 // N + 8] for _ in range(N)]).astype(np.int32)
+            env = np.repeat(np.arange(N, dtype=np.int32), cells.shape[1])
+            cells, mat = cells.reshape(-1), rng.integers(0, M + 1, cells.size).astype(np.uint8)
+            cams = synth.random_cameras(rng, N, grid)
+            body = rng.integers(-1, V // 2, N).astype(np.int32)
+            for i, b in enumerate(batches):
+                arrays = [a.copy() for a in (worlds, colours, env, cells, mat, cams, body)]
+                if i:
+                    arrays = [torch.from_numpy(a).cuda() for a in arrays]
+                    torch.cuda.synchronize()
+                w, c, e, v, m, k, s = arrays
+                for _ in range(3):
+                    b.upload_worlds(w, c, stream=stream)
+                b.update_voxels(e, v, m, stream=stream)
+                b.set_cameras(k, s, stream=stream)
+                for a in arrays if not i else ():
+                    a[:] = 1
+                torch.cuda.synchronize()
+        for r in runs:
+            r.render()
+        a, b = runs[0].numpy(), runs[1].numpy()
+        for x, y in ((a.rgb, b.rgb), (a.depth, b.depth), (a.hit_index, b.hit_index), (a.material, b.material)):
+            np.testing.assert_array_equal(x, y)
+
+
 @pytest.mark.parametrize("grid", [(4, 4, 3), (40, 40, 16), (64, 64, 5), (60, 28, 9), (64, 2, 4)])
 def test_pack_of_many_and_of_few_worlds_agree(lib, grid):
     """Uploads of more than 256 worlds and of fewer take different pack kernels: same rows, tops and material bytes where
