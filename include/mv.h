@@ -91,8 +91,8 @@ void mv_default_config(mv_config* cfg);
 /* Create a batch on cfg->device (paper Sec. 3.2: N environments x M agents per instance).
  * Allocates all device memory the batch will ever use: material grids N*X*Y*Z bytes,
  * occupancy bits, per-environment shaded colour tables, camera records.  *out is written only
- * on success.  Grids up to 64x64 voxels in x and y take the fast row-scan traversal; wider grids
- * are rendered with a plain per-cell DDA.  Errors: MV_ERR_ARG (bad field), MV_ERR_CAPACITY (the
+ * on success.  Grids up to 64x64 voxels in x and y take the row-scan traversal; wider grids
+ * scan their rows through windows of 32 cells, or cell by cell where their x and y rows do not both fit on chip.  Errors: MV_ERR_ARG (bad field), MV_ERR_CAPACITY (the
  * occupancy bits of one grid do not fit in the 160 KiB of LDS of a compute unit), MV_ERR_HIP. */
 int mv_create_batch(const mv_config* cfg, mv_batch** out);
 
