@@ -642,7 +642,7 @@ __device__ __forceinline__ float uniform(float v)
 // without sign; the direction is folded into the address and index steps.
 struct alignas(16) ScanClass {
     float Pu;           // camera coordinate along u (mirrored for negative u)
-    float uexit;        // U - Pu: distance to the far side of the grid along u
+    float uexit;        // U - Pu: distance to the far side of the grid along u (window scan: to the first u plane)
     float Pu_err;       // what rounding took from the mirrored coordinate: (U - P) - Pu exactly, 0 if not mirrored
     int   addr0;        // LDS byte address of the camera's row in this class's row array
     float zero[2];      // 0, 0: where a ray's two crossing counters start (beside two values that are dead by then: the
@@ -853,8 +853,9 @@ struct BoxEntry {
     bool misses;
     float t;            // parameter of the entry point, >= 0
     int face;           // face code of a voxel found in the entry cell
-    int j, k;           // entry cell along v and along z
-    float t0_v, t0_z;   // parameters of the first v and z crossing
+    int i, j, k;        // entry cell along u, v and z
+    float t0_u, t0_v, t0_z;     // parameters of the first crossing along each
+    float left_u;
     float left_v, left_z;   // planes between the entry cell and the far side of the box along v and z
 };
 
@@ -893,8 +894,13 @@ __device__ __forceinline__ BoxEntry enter_box(const OutsideCamera& o, float dx, 
         first = da == 0.0f ? kBig : fmaxf(((float)(neg ? c : c + 1) - pa) * ra, e.t);
         left = (float)(neg ? c : n - 1 - c);
     };
-    if (xm) along(1, dy, o.P[1], rcp[1], o.Y, e.j, e.t0_v, e.left_v);
-    else    along(0, dx, o.P[0], rcp[0], o.X, e.j, e.t0_v, e.left_v);
+    if (xm) {
+        along(0, dx, o.P[0], rcp[0], o.X, e.i, e.t0_u, e.left_u);
+        along(1, dy, o.P[1], rcp[1], o.Y, e.j, e.t0_v, e.left_v);
+    } else {
+        along(1, dy, o.P[1], rcp[1], o.Y, e.i, e.t0_u, e.left_u);
+        along(0, dx, o.P[0], rcp[0], o.X, e.j, e.t0_v, e.left_v);
+    }
     along(2, o.dz, o.P[2], rcp_z, o.top, e.k, e.t0_z, e.left_z);
     return e;
 }
@@ -1212,7 +1218,8 @@ typedef __attribute__((address_space(3))) const uint32_t* lds_u32_ptr;
 // is -1 for mirrored classes, else 0.  Bits of a window beyond the row's ends belong to its neighbours in LDS and never
 // count: runs end at cell U - 1.  Ends for every input as trace_rows does; a window that does not reach the end of the run
 // advances it by 32 cells.  Bound by instruction issue, about five turns per ray instead of one per cell
-// (256 x 2 worlds of 96x96x16 at 128x72, upload + cameras + render: 184 -> 82 us).
+// (256 x 2 worlds of 96x96x16 at 128x72, upload + cameras + render: 184 -> 104 us;
+// 76 us without the correction of a run's last cell, but then rays through a voxel edge fall on other sides than before)..
 template <bool kOutside>
 __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, float dy, const RowRecord& rr,
                                              const OutsideCamera* from_outside = nullptr)
@@ -1233,21 +1240,22 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
     const float dua = fabsf(du);
     const float inv_u = safe_rcp(dua);
     const float dt_v = fabsf(safe_rcp(dv)), dt_z = fabsf(rr.rcp_z);
-    float t0_v, t0_z, t_end;
+    float t0_u, t0_v, t0_z, t_end;
     BoxEntry in{};
     if constexpr (kOutside) {
         in = enter_box(*from_outside, dx, dy, xm, rr.rcp_z);
         if (__ballot(!in.misses) == 0) return Hit{ -1, 0, 0.0f };
-        t0_v = in.t0_v; t0_z = in.t0_z;
-        t_end = vmax(vmin3(c.uexit * inv_u, fmaf(in.left_v, dt_v, t0_v), fmaf(in.left_z, dt_z, t0_z)), in.t);
+        t0_u = in.t0_u; t0_v = in.t0_v; t0_z = in.t0_z;
+        t_end = vmax(vmin3(fmaf(in.left_u, inv_u, t0_u), fmaf(in.left_v, dt_v, t0_v), fmaf(in.left_z, dt_z, t0_z)), in.t);
         const int V = xm ? from_outside->Y : from_outside->X;
         c.addr0 += abs(c.sv) * (in.k * V + in.j);
         c.idx0 += (float)((in.k * from_outside->Y) * from_outside->X + in.j * (xm ? from_outside->X : 1));
-        c.i0 = min(max((int)fmaf(in.t, dua, c.Pu), 0), c.um1);
+        c.i0 = du < 0.0f ? c.um1 - in.i : in.i;
     } else {
+        t0_u = c.uexit * inv_u;
         t0_v = c.dist_v * dt_v;
         t0_z = rr.t0_z;
-        t_end = vmin3(c.uexit * inv_u, fmaf(c.nv_max, dt_v, t0_v), rr.tend_z);
+        t_end = vmin3(fmaf((float)(c.um1 - c.i0), inv_u, t0_u), fmaf(c.nv_max, dt_v, t0_v), rr.tend_z);
     }
     const int mirrored = c.pad;                     // -1 or 0
     const int origin = mirrored & (c.um1 - 30);     // window of mirrored cell i: cells U-32-i .. U-1-i, else i .. i+31
@@ -1255,8 +1263,17 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
     uint32_t addr = (uint32_t)c.addr0, in_range = 0;
     int i_from = c.i0, i_row = c.i0, i_last = c.i0;
     for (bool go = !kOutside || !in.misses; go;) {
+        // The last cell of the run: where the ray is at t_out, put right by one cell where the u crossings themselves say
+        // so.  Every choice of the next crossing is then the per-cell tracer's own comparison, ties included (x before y
+        // before z, and none at or behind the far side), and so are the cells visited.
+        const bool cv = t_v <= t_z;
         const float t_out = vmin3(t_v, t_z, t_end);
-        const int i_to = min((int)fmaf(t_out, dua, c.Pu), c.um1);
+        const bool strict = (!xm && cv) || !(t_out < t_end);
+        auto crossed = [&](float t_u) { return strict ? t_u < t_out : t_u <= t_out; };
+        int i_to = min(max((int)fmaf(t_out, dua, c.Pu), i_from), c.um1);
+        const float n_u = (float)(i_to - c.i0);
+        if (crossed(fmaf(n_u, inv_u, t0_u))) i_to = min(i_to + 1, c.um1);
+        else if (i_to > i_from && !crossed(fmaf(n_u - 1.0f, inv_u, t0_u))) i_to -= 1;
         for (;;) {
             const int first = (i_from ^ mirrored) + origin;
             const lds_u32_ptr at = (lds_u32_ptr)(uintptr_t)(addr + (uint32_t)((first >> 5) * 4));
@@ -1268,7 +1285,6 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
             i_from = i_last + 1;
         }
         if ((in_range != 0) | !(t_out < t_end)) break;
-        const bool cv = t_v <= t_z;
         const float one = cv ? 1.0f : 0.0f;
         addr += (uint32_t)(cv ? c.sv : c.sz);
         n_v += one;
@@ -1286,7 +1302,7 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
     const bool via_z = tz_last >= tv_last;
     const float t_in = vmax3(tv_last, tz_last, 0.0f);
     const float iu_f = (float)iu;
-    const float t_u = ((iu_f - c.Pu) - c.Pu_err) * inv_u;
+    const float t_u = fmaf(iu_f - (float)c.i0 - 1.0f, inv_u, t0_u);
     int face = along_row ? c.face_u : (via_z ? c.face_z : c.face_v);
     float t = along_row ? t_u : t_in;
     if constexpr (kOutside) {
@@ -1539,6 +1555,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         // coordinates that cell is the one before floor(Pu): start the scan there, so that the neighbour
         // on the - side is found as an ordinary hit along the row (through its u face, at t = 0).
         if (neg && c.Pu == floorf(c.Pu) && c.i0 >= 1 && c.Pu < (float)U) c.i0 -= 1;
+        if (!FAST) {
+            // the window scan counts u crossings from the camera's cell: the cell itself (found in unmirrored coordinates,
+            // where nothing is rounded) and the distance to its first u plane
+            const int cell = min(max((int)floorf(pu), 0), U - 1);
+            c.i0 = neg ? U - 1 - cell : cell;
+            c.uexit = fabsf((float)(neg ? cell : cell + 1) - pu);
+        }
         const int j0 = min(max((int)floorf(pv), 0), V - 1);
         // first plane along v: the upper plane of the camera's cell for rising v, the lower one otherwise
         c.dist_v = fabsf((float)(vneg ? j0 : j0 + 1) - pv);
