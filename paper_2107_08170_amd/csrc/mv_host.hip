@@ -305,7 +305,7 @@ static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::Gri
         // faster than whole observations or 6 strips).  Grids that leave room for only two workgroups per
         // CU render whole observations: every strip would re-stage the rows with nothing to hide it.
         const int waves = p.threads / 64;
-        // The window scan's workgroups stage more and are half as many per CU: half the number is enough (96x96x16 x 256, 2
+        // The window scan's workgroups stage more and are half as many per CU: half the number is enough (before the correction of a run's last cell: 96x96x16 x 256, 2
         // agents, 128x72: step 80.3 -> 76.7 us, at 256x144 156 -> 148 us; 2048 workgroups 75.4 and 159, 4096 79.2 and 146).
         const long long target_blocks = plan.window ? 256ll * 12 : 256ll * 24;
         long long strips = (target_blocks + num_obs - 1) / num_obs;

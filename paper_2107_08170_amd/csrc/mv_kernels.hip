@@ -1219,7 +1219,7 @@ typedef __attribute__((address_space(3))) const uint32_t* lds_u32_ptr;
 // count: runs end at cell U - 1.  Ends for every input as trace_rows does; a window that does not reach the end of the run
 // advances it by 32 cells.  Bound by instruction issue, about five turns per ray instead of one per cell
 // (256 x 2 worlds of 96x96x16 at 128x72, upload + cameras + render: 184 -> 104 us;
-// 76 us without the correction of a run's last cell, but then rays through a voxel edge fall on other sides than before)..
+// 76 us without the correction of a run's last cell, but then rays through a voxel edge fall on other sides than before).
 template <bool kOutside>
 __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, float dy, const RowRecord& rr,
                                              const OutsideCamera* from_outside = nullptr)
