@@ -28,10 +28,18 @@
  * the calling thread.  Work is enqueued on the caller's HIP stream and the calls return without
  * synchronising; ordering between calls is stream order.  A batch must not be used from two
  * threads at once, and calls that touch the same batch from different streams must be ordered
- * by the caller (events or synchronisation): the batch's device buffers carry no locks.  Calls
- * that take host memory (src_is_device == 0) validate it, copy it and wait for the copy, so
- * they return only when the stream has passed them; the device-memory forms never wait and
- * allocate nothing, which makes a step built from them capturable in a HIP graph.
+ * by the caller (events or synchronisation): the batch's device buffers carry no locks.
+ *
+ * Calls that take host memory (src_is_device == 0) validate it, make a copy of it and wait until the
+ * stream has passed everything that was enqueued on it before the call, whatever the size of the
+ * arrays: on return the arrays may be reused, and all earlier work of that stream is over (images
+ * fetched into pinned memory may be read, device arrays given to earlier calls may be changed).  What
+ * the call itself enqueues may still run then and is ordered like any other work of the stream.  The
+ * copy of up to 1 MiB is made in pinned memory that the batch allocates when it first needs it.  A
+ * stream that is being captured cannot be waited for: MV_ERR_HIP.
+ *
+ * The device-memory forms never wait and allocate nothing, which makes a step built from them
+ * capturable in a HIP graph.
  */
 #ifndef MV_H
 #define MV_H

@@ -55,55 +55,43 @@ private:
 
 }  // namespace
 
-// Host inputs of a call on their way to the GPU: they are copied into one of a batch's few pinned buffers, and the kernels
-// read them from there.  The call then neither waits for the stream nor makes copies of its own, which cost about 10 us
-// each, more than such a kernel takes to read its inputs over the link (64 x 2 cameras, an eighth of the worlds, moves and
-// cameras from host arrays and images fetched: a step 317 -> 249 us, of which the images take 150).  A buffer is taken again only when the launches of its
-// last use are over.
+// Host inputs of a call on their way to the GPU: they are copied into the batch's pinned buffer, and the kernels read them
+// from there over the link.  That replaces a copy of the runtime's own for every array, which costs about 10 us each, more
+// than such a kernel takes to read its inputs (64 x 2 cameras, an eighth of the worlds, moves and cameras from host arrays,
+// images fetched: a step 321 -> 248 us, of which the images take 150; a new batch's first step 371 -> 297).  The call still
+// waits, before it launches anything, until its stream has passed all earlier work: callers rely on that (see the head of
+// mv.h; without the wait the step took 241 us).
 class HostStaging {
 public:
-    // four buffers each of 64 KiB, 256 KiB and 1 MiB, made when first needed (pinning memory costs time by the page);
-    // above 1 MiB the copy engine's rate counts for more
-    static constexpr int kClasses = 3, kSlots = 4;
-    static constexpr size_t class_bytes(int c) { return (size_t)65536 << (2 * c); }
+    // The buffer is made when first needed and grows by these steps (pinning memory costs time by the page).  Larger inputs
+    // are copied to device memory: up to 1 MiB reading over the link is the faster way for every kind of input, beyond it
+    // depends on the kernel (copied -> staged, us, each call waited for: 2 cameras 35 -> 20, 40 000 cameras of 24 bytes
+    // 119 -> 102, 120 000 283 -> 289; 64 edits 41 -> 25, 78 000 of 9 bytes 115 -> 106, 200 000 214 -> 226; worlds of
+    // 40x40x16, 200 KiB 49 -> 30, 977 KiB 87 -> 67, 4 MiB 218 -> 238).
+    static constexpr size_t kSizes[] = { 64u << 10, 256u << 10, 1024u << 10 };
     struct Part { const void* src; size_t bytes; const void* on_device; };      // on_device: out
 
-    // True: the parts are staged and may be reused by the caller; launch what reads them and call used().  False (too
-    // large, a stream that is being captured, no pinned memory): nothing happened, the caller copies and waits itself.
+    // True: `stream` has passed what was enqueued before, and the parts are staged (unless *err says otherwise); launch what
+    // reads them and call used().  False (too large, no pinned memory): nothing is staged, the caller copies and waits itself.
     bool stage(Part* parts, int count, hipStream_t stream, hipError_t* err)
     {
         *err = hipSuccess;
         size_t total = 0;
         for (int i = 0; i < count; ++i) total += padded(parts[i].bytes);
-        int c = 0;
-        while (c < kClasses && total > class_bytes(c)) ++c;
-        if (c == kClasses) return false;
-        if (stream) {
-            hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-            if (hipStreamIsCapturing(stream, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
-            if (status != hipStreamCaptureStatusNone) return false;
-        }
-        // a buffer that is free, else a new one, else the one used longest ago
-        Slot* free_slot = nullptr;
-        for (int i = 0; i < kSlots && !free_slot; ++i) {
-            Slot& s = slots_[c][i];
-            if (!s.memory) { if (!s.create(class_bytes(c))) return false; free_slot = &s; }
-            else if (!s.in_use || hipEventQuery(s.over) == hipSuccess) free_slot = &s;
-        }
-        (void)hipGetLastError();            // (a query's "not ready")
-        if (!free_slot) {
-            for (Slot& s : slots_[c])
-                if (!free_slot || s.order < free_slot->order) free_slot = &s;
-            *err = hipEventSynchronize(free_slot->over);
-            if (*err != hipSuccess) return true;
-        }
-        Slot& s = *free_slot;
-        s.in_use = false;
-        current_ = &s;
+        size_t size = 0;
+        for (size_t s : kSizes)
+            if (size == 0 && total <= s) size = s;
+        if (size == 0) return false;
+        *err = hipStreamSynchronize(stream);        // (an error while the stream is being captured, as it always was)
+        // the last call's kernels have read the buffer by now, or will have: they may have run on another stream
+        if (*err == hipSuccess && in_use_) *err = hipEventSynchronize(over_);
+        if (*err != hipSuccess) return true;
+        in_use_ = false;
+        if (capacity_ < size && !grow(size)) return false;
         size_t at = 0;
         for (int i = 0; i < count; ++i) {
-            std::memcpy(s.memory + at, parts[i].src, parts[i].bytes);
-            parts[i].on_device = s.device + at;
+            std::memcpy(memory_ + at, parts[i].src, parts[i].bytes);
+            parts[i].on_device = device_ + at;
             at += padded(parts[i].bytes);
         }
         return true;
@@ -111,48 +99,39 @@ public:
     // after the launches that read the parts staged last
     hipError_t used(hipStream_t stream)
     {
-        Slot& s = *current_;
-        s.order = ++uses_;
-        const hipError_t e = hipEventRecord(s.over, stream);
+        const hipError_t e = hipEventRecord(over_, stream);
         if (e != hipSuccess) (void)hipStreamSynchronize(stream);
-        else s.in_use = true;
+        else in_use_ = true;
         return e;
     }
     void release()
     {
-        for (auto& row : slots_)
-            for (Slot& s : row) s.destroy();
+        if (over_) (void)hipEventDestroy(over_);
+        if (memory_) (void)hipHostFree(memory_);
+        over_ = nullptr; memory_ = nullptr; capacity_ = 0; in_use_ = false;
     }
 
 private:
-    struct Slot {
-        uint8_t* memory = nullptr;
-        uint8_t* device = nullptr;
-        hipEvent_t over = nullptr;
-        bool in_use = false;
-        uint64_t order = 0;
-        bool create(size_t bytes)
-        {
-            if (hipHostMalloc((void**)&memory, bytes, hipHostMallocMapped) != hipSuccess) memory = nullptr;
-            if (memory && hipHostGetDevicePointer((void**)&device, memory, 0) == hipSuccess &&
-                hipEventCreateWithFlags(&over, hipEventDisableTiming) == hipSuccess)
-                return true;
-            (void)hipGetLastError();
-            over = nullptr;
-            destroy();
-            return false;
+    bool grow(size_t bytes)
+    {
+        release();
+        if (hipHostMalloc((void**)&memory_, bytes, hipHostMallocMapped) != hipSuccess) memory_ = nullptr;
+        if (memory_ && hipHostGetDevicePointer((void**)&device_, memory_, 0) == hipSuccess &&
+            hipEventCreateWithFlags(&over_, hipEventDisableTiming) == hipSuccess) {
+            capacity_ = bytes;
+            return true;
         }
-        void destroy()
-        {
-            if (over) (void)hipEventDestroy(over);
-            if (memory) (void)hipHostFree(memory);
-            over = nullptr; memory = nullptr; in_use = false;
-        }
-    };
+        (void)hipGetLastError();
+        over_ = nullptr;
+        release();
+        return false;
+    }
     static size_t padded(size_t n) { return (n + 63) & ~(size_t)63; }
-    Slot slots_[kClasses][kSlots];
-    Slot* current_ = nullptr;
-    uint64_t uses_ = 0;
+    uint8_t* memory_ = nullptr;
+    uint8_t* device_ = nullptr;
+    size_t capacity_ = 0;
+    hipEvent_t over_ = nullptr;
+    bool in_use_ = false;
 };
 
 struct mv_batch {
@@ -520,8 +499,8 @@ int mv_upload_worlds(mv_batch* b, int32_t first_env, int32_t count, const uint8_
     return MV_OK;
 }
 
-// The host arrays of an edit list, where the kernels can read them: staged, or (too many, or a stream that is being
-// captured) in the batch's device buffer, which only ever grows.  The parts' sizes are multiples of 4 n but for the last.
+// The host arrays of an edit list, where the kernels can read them: staged, or (too many) in the batch's device buffer,
+// which only ever grows.  The parts' sizes are multiples of 4 n but for the last.
 static int edits_to_device(mv_batch* b, HostStaging::Part* parts, int count, size_t n, hipStream_t stream, bool* staged)
 {
     hipError_t e = hipSuccess;

@@ -1542,6 +1542,54 @@ def test_pack_kernel_bit_exact(lib, grid):
         check(vox2)
 
 
+HOST_CALLS = ("upload", "upload with palette", "edits", "moves", "cameras", "cameras and bodies", "active", "bars", "overlay")
+
+
+@pytest.mark.parametrize("size", ["small", "large"])
+@pytest.mark.parametrize("call", HOST_CALLS)
+def test_host_forms_return_when_the_stream_has_passed_earlier_work(lib, call, size):
+    """Every call with host arrays, below and above the size up to which they are staged in pinned memory, waits for what
+    its stream was given before: an event recorded behind a long kernel has completed on return, so images fetched into
+    pinned memory before the call may be read, and device arrays given to an earlier upload be overwritten."""
+    rng = np.random.default_rng(8)
+    N, grid, M, W, H = (4, (24, 16, 8), 5, 32, 24) if size == "small" else (64, (40, 40, 16), 5, 32, 24)
+    V = grid[0] * grid[1] * grid[2]
+    A = 1 if size == "small" else 1024 if call.startswith("cameras") else 8
+    vox, pal = synth.random_world(rng, N, grid, 0.1, M)
+    batch = binding.Batch(N, A, grid, M, W, H)
+    batch.upload_worlds(torch.from_numpy(vox).cuda(), torch.from_numpy(pal).cuda(), stream=_stream())
+    cams = np.tile(synth.random_cameras(rng, N, grid), (A, 1))
+    batch.set_cameras(torch.from_numpy(cams).cuda(), stream=_stream())
+    rgb = torch.zeros((N * A, H, W, 3), dtype=torch.uint8, device="cuda")
+    n = 16 if size == "small" else 120000
+    env, cell = rng.integers(0, N, n).astype(np.int32), rng.integers(0, V, n).astype(np.int32)
+    mat, frm = rng.integers(0, M + 1, n).astype(np.uint8), rng.integers(-1, V, n).astype(np.int32)
+    body, share = rng.integers(-1, V, N * A).astype(np.int32), rng.random((N * A, 2)).astype(np.float32)
+    rects = [(1, 1, 9, 3, (1, 2, 3), binding.RECT_GAUGE_RIGHT, (4, 5, 6), 1)]
+    calls = {
+        "upload": lambda s: batch.upload_worlds(vox, stream=s),
+        "upload with palette": lambda s: batch.upload_worlds(vox, pal, stream=s),
+        "edits": lambda s: batch.update_voxels(env, cell, mat, stream=s),
+        "moves": lambda s: batch.move_voxels(env, frm, cell, mat, stream=s),
+        "cameras": lambda s: batch.set_cameras(cams, stream=s),
+        "cameras and bodies": lambda s: batch.set_cameras(cams, body, stream=s),
+        "active": lambda s: batch.set_active(np.ones(N, np.uint8), stream=s),
+        "bars": lambda s: batch.draw_bars(rgb, share[:, 0].copy(), 1, 1, 9, 3, (9, 9, 9), (1, 1, 1), stream=s),
+        "overlay": lambda s: batch.draw_overlay(rgb, rects, share, stream=s),
+    }
+    torch.cuda.synchronize()
+    for stream in (torch.cuda.current_stream(), torch.cuda.Stream()):
+        for _ in range(3):                                  # (the first call makes buffers, which may wait by itself)
+            with torch.cuda.stream(stream):
+                torch.cuda._sleep(20_000_000)               # about ten milliseconds
+                behind = torch.cuda.Event()
+                behind.record()
+            assert not behind.query()
+            calls[call](stream.cuda_stream)
+            assert behind.query(), f"{call} ({size}) returned before its stream had passed earlier work"
+            torch.cuda.synchronize()
+
+
 def test_host_arrays_may_be_reused_on_return(lib):
     """Host inputs of every size class (up to 64 KiB, 256 KiB, 1 MiB and beyond), more calls in flight than there are
     buffers, the caller's arrays overwritten straight after each call, two streams: the GPU's state is that of the same
