@@ -1590,47 +1590,63 @@ def test_host_forms_return_when_the_stream_has_passed_earlier_work(lib, call, si
             torch.cuda.synchronize()
 
 
-def test_host_arrays_may_be_reused_on_return(lib):
-    """Host inputs of every size class (up to 64 KiB, 256 KiB, 1 MiB and beyond), more calls in flight than there are
-    buffers, the caller's arrays overwritten straight after each call, two streams: the GPU's state is that of the same
-    calls with device arrays."""
+@pytest.mark.parametrize("part", [600, 4000, 30000, 130000])
+def test_host_arrays_may_be_reused_on_return(lib, part):
+    """Host inputs of every size a staging buffer has (64 KiB, 256 KiB, 1 MiB) and beyond: runs of calls with inputs that
+    nothing overwrites later, each behind a long kernel of its stream, the caller's arrays overwritten straight after each
+    call.  The GPU's state afterwards is that of the same calls with device arrays: a buffer written again before its
+    kernels have read it would leave the worlds, edits or cameras of a later call behind."""
     rng = np.random.default_rng(5)
-    grid, M = (40, 40, 16), 9
+    grid, M, N, runs_of = (40, 40, 16), 9, 96, 8
     V = grid[0] * grid[1] * grid[2]
+    vox, pal = synth.random_world(rng, N, grid, 0.1, M)
+    batches = [binding.Batch(N, 1, grid, M, 32, 24) for _ in range(2)]
     side = torch.cuda.Stream()
-    for N in (2, 8, 30, 60):
-        vox, pal = synth.random_world(rng, N, grid, 0.1, M)
-        batches = [binding.Batch(N, 1, grid, M, 32, 24) for _ in range(2)]
-        runs = [GpuRender(b, 32, 24) for b in batches]
-        for b in batches:
-            b.upload_worlds(torch.from_numpy(vox).cuda(), torch.from_numpy(pal).cuda(), stream=_stream())
+    for b in batches:
+        b.upload_worlds(torch.from_numpy(vox).cuda(), torch.from_numpy(pal).cuda(), stream=_stream())
+    torch.cuda.synchronize()
+    count = {600: 2, 4000: 8}.get(part, 12)                      # worlds of 25.6 KB in one upload
+    worlds, colours = synth.random_world(rng, count * runs_of, grid, 0.06, M)
+    edited = np.arange(count * runs_of, N, dtype=np.int32)  # environments no upload below touches
+    free = edited if edited.size else np.arange(N, dtype=np.int32)
+    voxel = rng.permutation(free.size * V)[:min(part * runs_of, free.size * V)].astype(np.int64)
+    edits = [(free[v // V].astype(np.int32), (v % V).astype(np.int32), rng.integers(0, M + 1, v.size).astype(np.uint8))
+             for v in np.array_split(voxel, runs_of)]
+    cams, body = synth.random_cameras(rng, N, grid), rng.integers(-1, V // 2, N).astype(np.int32)
+
+    def call(b, method, arrays, device, **kw):
+        arrays = [torch.from_numpy(a).cuda() if device else a.copy() for a in arrays]
+        torch.cuda.synchronize() if device else torch.cuda._sleep(2_000_000)
+        getattr(b, method)(*arrays, stream=torch.cuda.current_stream().cuda_stream, **kw)
+        if device:
+            torch.cuda.synchronize()
+        else:
+            for a in arrays:
+                a[:] = 1
+
+    for i, b in enumerate(batches):
+        for k in range(runs_of):
+            at = slice(k * count, (k + 1) * count)
+            call(b, "upload_worlds", (worlds[at], colours[at]), i, first_env=k * count, count=count)
+        for e in edits:                                     # (disjoint voxels)
+            call(b, "update_voxels", e, i)
+        for k in range(runs_of):                            # objects that appear in voxels the edits left alone
+            spot = (np.arange(40) + 40 * k).astype(np.int32)
+            there = np.full(40, int(free[-1]), np.int32)
+            call(b, "move_voxels", (there, np.full(40, -1, np.int32), spot, np.full(40, 1 + k % M, np.uint8)), i)
         torch.cuda.synchronize()
-        for rep in range(7):
-            stream = _stream() if rep % 2 else side.cuda_stream
-            worlds, colours = synth.random_world(rng, N, grid, 0.02 * (rep + 1), M)
-            cells = np.stack([rng.permutation(V)[:3000 // N + 8] for _ in range(N)]).astype(np.int32)
-            env = np.repeat(np.arange(N, dtype=np.int32), cells.shape[1])
-            cells, mat = cells.reshape(-1), rng.integers(0, M + 1, cells.size).astype(np.uint8)
-            cams = synth.random_cameras(rng, N, grid)
-            body = rng.integers(-1, V // 2, N).astype(np.int32)
-            for i, b in enumerate(batches):
-                arrays = [a.copy() for a in (worlds, colours, env, cells, mat, cams, body)]
-                if i:
-                    arrays = [torch.from_numpy(a).cuda() for a in arrays]
-                    torch.cuda.synchronize()
-                w, c, e, v, m, k, s = arrays
-                for _ in range(3):
-                    b.upload_worlds(w, c, stream=stream)
-                b.update_voxels(e, v, m, stream=stream)
-                b.set_cameras(k, s, stream=stream)
-                for a in arrays if not i else ():
-                    a[:] = 1
-                torch.cuda.synchronize()
-        for r in runs:
-            r.render()
-        a, b = runs[0].numpy(), runs[1].numpy()
-        for x, y in ((a.rgb, b.rgb), (a.depth, b.depth), (a.hit_index, b.hit_index), (a.material, b.material)):
-            np.testing.assert_array_equal(x, y)
+        with torch.cuda.stream(side):
+            call(b, "set_cameras", (cams, body), i)
+        torch.cuda.synchronize()
+    runs = [GpuRender(b, 32, 24) for b in batches]
+    for r in runs:
+        r.render()
+    a, b = runs[0].numpy(), runs[1].numpy()
+    for x, y in ((a.rgb, b.rgb), (a.depth, b.depth), (a.hit_index, b.hit_index), (a.material, b.material)):
+        np.testing.assert_array_equal(x, y)
+    xp, xw, yp, yw, _ = batches[0].debug_occupancy(0)
+    words = N * (grid[2] * grid[1] * xw + grid[2] * grid[0] * yw) * 8
+    np.testing.assert_array_equal(_read_device(xp, words), _read_device(batches[1].debug_occupancy(0)[0], words))
 
 
 @pytest.mark.parametrize("grid", [(4, 4, 3), (40, 40, 16), (64, 64, 5), (60, 28, 9), (64, 2, 4)])
