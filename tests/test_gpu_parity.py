@@ -861,6 +861,32 @@ def test_wide_grids_with_bodies_tall_worlds_and_rows_that_do_not_fit(lib, orc, g
     assert (ref.face == 6).any() and (ref.hit_index >= 0).any()
 
 
+@pytest.mark.parametrize("grid", [(40, 40, 16), (96, 96, 16)])
+def test_workgroups_that_fall_back_do_not_wait_for_the_host(lib, grid):
+    """A render whose worlds are taller than the layers it reserved costs the slower tracer, a small multiple of the plain
+    render, and not a serialised trip to host memory for each of its thousands of workgroups (45 times as long on wide grids,
+    170 times on narrow ones, when each asked for an atomic on the host's word)."""
+    rng = np.random.default_rng(4)
+    N, A = 128, 2
+    vox, pal = synth.random_world(rng, 4, grid, 0.02, 5)
+    vox[:, 0] = 3
+    run = _gpu_for(_mini_spec(N, A, grid, 128, 72, 5), np.tile(vox, (N // 4, 1, 1, 1)), np.tile(pal, (N // 4, 1, 1)),
+                   synth.random_cameras(rng, N * A, grid), aux=False)
+    took = {}
+    for layers in (0, 4):
+        run.batch.debug_set_staged_layers(layers)
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            run.batch.render(run.rgb, run.depth, stream=_stream())
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        took[layers] = min(times)
+    assert took[4] < 15 * took[0], took
+
+
 def test_largest_grid_the_lds_plan_takes(lib, orc):
     grid = (128, 128, 32)                   # 64 KiB of occupancy bits
     rng = np.random.default_rng(8)
