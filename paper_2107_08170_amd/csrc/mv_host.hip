@@ -666,8 +666,8 @@ int mv_render_batch(mv_batch* b, uint8_t* rgb, float* depth, uint8_t* aux_materi
 
     // How many layers to stage: as many as the tallest world the kernels have reported
     // so far (read without synchronising: a value that is out of date costs speed, never correctness -- a
-    // workgroup whose world is taller than what was staged traces through global memory and reports it),
-    // all of them before the first report.
+    // workgroup whose world is taller than what was staged traces through global memory), all of them before
+    // the first report.
     // A launch that is being captured into a HIP graph will be replayed later, over worlds this call cannot
     // know: it stages every layer (unless the caller fixed the number), so that a replay never falls back to the
     // slow path because the worlds grew after the capture.
@@ -701,7 +701,6 @@ int mv_render_batch(mv_batch* b, uint8_t* rgb, float* depth, uint8_t* aux_materi
     mv::RenderParams p = b->shape;
     p.staged_layers = staged;
     p.coarse_after = b->cfg.coarse_level != 0 ? mv::kCoarseAfterTurns : -1;
-    p.heights = mv::HeightFeedback{ b->d_height, b->h_height_dev };
     p.active = b->all_active ? nullptr : b->d_active;
     p.bits = b->d_bits; p.ztop = b->d_ztop; p.vox = b->borrowed_vox ? b->borrowed_vox : b->d_vox; p.lut = b->d_lut; p.rec = b->d_rec; p.sx = b->d_sx; p.sy = b->d_sy;
     p.rgb = rgb; p.depth = depth; p.aux_material = aux_material; p.aux_hit = aux_hit_index; p.aux_face = aux_face;
@@ -1052,7 +1051,6 @@ extern "C" int mv_render_worlds_noalloc(const mv_config* cfg, const uint8_t* vox
     mv::RenderParams p{};
     p.staged_layers = cfg->grid_z;            // no height feedback without a batch object: stage every layer
     p.coarse_after = cfg->coarse_level != 0 ? mv::kCoarseAfterTurns : -1;
-    p.heights = no_feedback;
     p.active = nullptr;
     p.bits = d_bits; p.ztop = d_ztop; p.vox = voxels; p.lut = d_lut; p.rec = d_rec; p.sx = d_sx; p.sy = d_sy;
     p.rgb = rgb; p.depth = depth;

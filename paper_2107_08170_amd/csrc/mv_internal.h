@@ -52,7 +52,7 @@ struct GridLayout {
 // lowered): `device_max` is exact; `host_max` is a word of pinned host memory that kernels update when the
 // device word rises and that the host reads WITHOUT synchronising to decide how many layers the next
 // render stages in LDS.  A stale value costs speed only: workgroups that need more layers than were staged
-// trace through the rows in global memory instead, and report what they needed.
+// trace through the rows in global memory instead.
 struct HeightFeedback {
     int32_t* device_max;
     int32_t* host_max;      // device-visible address of the pinned host word
@@ -109,7 +109,6 @@ struct RenderParams {
     int32_t staged_layers;                // layers 0 .. staged_layers-1 of the bit rows go to LDS
     int32_t window;                       // grids wider than 64 voxels: x and y rows are staged for the window scan
     int32_t coarse_after;                 // < 0: no coarse level; else the ordinary turns a ray makes before it uses it
-    HeightFeedback heights;
 };
 
 GridLayout make_layout(int X, int Y, int Z);

@@ -1403,8 +1403,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     const int kc = min(k0, ztop);
     const int zlim = kc + 1 > ztop ? kc + 1 : ztop;
     // Row scan: only if the launch reserved LDS for those layers (as many as the tallest world the host has heard of
-    // needs).  A taller world is traced through the rows in global memory, cell by cell, and says so, so that the next
-    // launch reserves enough.
+    // needs).  A taller world is traced through the rows in global memory, cell by cell; the pack or the edit that made it
+    // tall has told the host, so that a later launch reserves enough.
     const bool scans = FAST || p.window != 0;
     const bool use_rows = scans && origin_in_grid && zlim <= p.staged_layers;
     // A camera outside the grid scans rows from where its rays enter it; far outside, and for positions that are not
@@ -1420,9 +1420,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     const bool stage_rows = use_rows || outside_rows;
     const int wx = FAST ? 1 : g.rowwords_x, wy = FAST ? 1 : g.rowwords_y;
     const int sxw = staged * Y * wx, syw = staged * X * wy;        // words of one staged x / y row array
-    // (the pack and the edits have reported this world already: an atomic on the host's word from every workgroup of the
-    // launch, unasked, serialises on the link: 256 x 2 of 96x96x16 with four of sixteen layers reserved 4100 us)
-    if (scans && origin_in_grid && !use_rows && threadIdx.x == 0) report_height(p.heights, ztop);
 
     {   // a3: stage pixel scalars, colour table and this environment's bit rows.
         // The first loads of every stream are issued before any of them is consumed (clamped indices
