@@ -77,6 +77,10 @@ inline Divider make_divider(uint32_t d)
     return Divider{ (uint32_t)(((1ull << (31 + s)) + d - 1) / d), 31 + s };
 }
 
+// How a render traces the rays of cameras in and near the grid: the row scan (grids up to 64x64), the window scan (wider
+// grids whose x and y rows fit into LDS), cell by cell (the others).
+enum class Scan { kRows, kWindows, kCells };
+
 struct RenderParams {
     const uint64_t*     bits;             // [N][env_words]
     const int32_t*      ztop;             // [N] 1 + highest solid layer (0 = empty world)

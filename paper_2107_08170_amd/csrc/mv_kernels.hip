@@ -1323,10 +1323,14 @@ __device__ __forceinline__ uint32_t next_in_quad(uint32_t v)
     return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xF9, 0xF, 0xF, true);
 }
 
+// SCAN: which tracer a launch is for.  Each has a kernel of its own: in a kernel with the window scan the per-cell tracer kept
+// 115 values in spill registers instead of 2 (256 x 2 of 128x128x40, full height:
+// render 362 us in the shared kernel, 306 in its own), the window scan 115 instead of 32 (96x96x16: 108 -> 101 us).
 // COARSE: with the optional second occupancy level (pairs of rows), row-scan grids only
-template <bool AUX, bool PACKED, bool FAST, bool COARSE = false>
+template <bool AUX, bool PACKED, Scan SCAN, bool COARSE = false>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void render_kernel(RenderParams p)
 {
+    constexpr bool FAST = SCAN == Scan::kRows, scans = SCAN != Scan::kCells;
     extern __shared__ __align__(16) uint8_t lds[];
     // A workgroup that has just arrived runs its staging at a raised wave priority (the tile loop returns to the
     // default): its few instructions are issued ahead of the tracing waves it shares the SIMDs with, so its
@@ -1405,7 +1409,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     // Row scan: only if the launch reserved LDS for those layers (as many as the tallest world the host has heard of
     // needs).  A taller world is traced through the rows in global memory, cell by cell; the pack or the edit that made it
     // tall has told the host, so that a later launch reserves enough.
-    const bool scans = FAST || p.window != 0;
     const bool use_rows = scans && origin_in_grid && zlim <= p.staged_layers;
     // A camera outside the grid scans rows from where its rays enter it; far outside, and for positions that are not
     // numbers, cell by cell.
@@ -1423,7 +1426,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     // Ends the basic block here: otherwise the compiler moves the address arithmetic of the staging into the wait for the
     // camera and the staging's loads start later (4096 x 2 of 40x40x16: render 259 -> 263 us, 2048 x 4 of 64x64x32 983 -> 998).
     if (scans && origin_in_grid && !use_rows) asm volatile("");
-
     {   // a3: stage pixel scalars, colour table and this environment's bit rows.
         // The first loads of every stream are issued before any of them is consumed (clamped indices
         // instead of branches keep them in one straight run, and a trip of the row loop fetches four
@@ -1709,7 +1711,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         float Pc[3] = { 0.0f, 0.0f, 0.0f }, Fcz = 0.0f, Ucz = 0.0f;
         int body_lo = -1, body_hi = -1, top = 0;
         bool inside = true;
-        if constexpr (!kRowsOnly || kOutside) {
+        if constexpr (!scans) {
+            // (one tile loop: nothing to keep out of another's registers)
+            Pc[0] = P[0]; Pc[1] = P[1]; Pc[2] = P[2];
+            Fcz = Fz; Ucz = Uz;
+            inside = origin_in_grid;
+        } else if constexpr (!kRowsOnly || kOutside) {
             const CameraRecord* again = p.rec + obs;
             const int32_t* tops = p.ztop;
             asm volatile("" : "+s"(again), "+s"(tops));
@@ -1791,12 +1798,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         }
     };
     __builtin_amdgcn_s_setprio(0);
-    if (use_rows && cam_idx < 0) {
+    if (scans && use_rows && cam_idx < 0) {
         if (FAST && X < 64 && Y < 64) run_tiles(std::true_type{}, std::true_type{}, std::false_type{});
         else run_tiles(std::true_type{}, std::false_type{}, std::false_type{});
         return;
     }
-    if (!use_rows && stage_rows) { run_tiles(std::true_type{}, std::false_type{}, std::true_type{}); return; }
+    if (scans && !use_rows && stage_rows) { run_tiles(std::true_type{}, std::false_type{}, std::true_type{}); return; }
     run_tiles(std::false_type{}, std::false_type{}, std::false_type{});
 }
 
@@ -1872,10 +1879,10 @@ hipError_t launch_overlay(uint8_t* rgb, const float* values, int values_per_obs,
     return hipGetLastError();
 }
 
-template <bool AUX, bool PACKED, bool FAST, bool COARSE = false>
+template <bool AUX, bool PACKED, Scan SCAN, bool COARSE = false>
 static hipError_t set_lds_limit()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&render_kernel<AUX, PACKED, FAST, COARSE>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&render_kernel<AUX, PACKED, SCAN, COARSE>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBudget);
 }
 
@@ -1891,12 +1898,12 @@ hipError_t prepare_kernels()
     hipError_t e = hipGetDevice(&device);
     if (e != hipSuccess) return e;
     if (device >= 0 && device < kMaxDevices && done[device].load(std::memory_order_acquire)) return hipSuccess;
-#define MV_SET(A, P, F) if (e == hipSuccess) e = set_lds_limit<A, P, F>()
-    MV_SET(false, false, false); MV_SET(false, false, true); MV_SET(false, true, false); MV_SET(false, true, true);
-    MV_SET(true, false, false);  MV_SET(true, false, true);  MV_SET(true, true, false);  MV_SET(true, true, true);
-#undef MV_SET
-#define MV_SET(A, P) if (e == hipSuccess) e = set_lds_limit<A, P, true, true>()
-    MV_SET(false, false); MV_SET(false, true); MV_SET(true, false); MV_SET(true, true);
+#define MV_SET(...)                                                          \
+    if (e == hipSuccess) e = set_lds_limit<false, false, __VA_ARGS__>();     \
+    if (e == hipSuccess) e = set_lds_limit<false, true, __VA_ARGS__>();      \
+    if (e == hipSuccess) e = set_lds_limit<true, false, __VA_ARGS__>();      \
+    if (e == hipSuccess) e = set_lds_limit<true, true, __VA_ARGS__>()
+    MV_SET(Scan::kRows); MV_SET(Scan::kWindows); MV_SET(Scan::kCells); MV_SET(Scan::kRows, true);
 #undef MV_SET
     // the pack kernel also has a few static words of LDS: its dynamic share must leave room for them
     const int pack_limit = (int)(kLdsBudget - kPackStaticLds);
@@ -1914,21 +1921,21 @@ hipError_t launch_render(const RenderParams& p, size_t lds_bytes, hipStream_t st
     const bool aux = p.aux_material || p.aux_hit || p.aux_face;
     // dword colour stores and unclamped tiles need whole 8x8 tiles and a 4-byte aligned colour tensor
     const bool packed = (p.W % kTileW == 0) && (p.H % kTileH == 0) && ((reinterpret_cast<uintptr_t>(p.rgb) & 3) == 0);
-    const bool fast = p.g.fast != 0;
     dim3 grid(p.blocks_per_xcd * kXcds), block(p.threads);
-#define MV_LAUNCH(A, P, F) hipLaunchKernelGGL((render_kernel<A, P, F>), grid, block, lds_bytes, stream, p)
-#define MV_LAUNCH_COARSE(A, P) hipLaunchKernelGGL((render_kernel<A, P, true, true>), grid, block, lds_bytes, stream, p)
-    if (fast && p.coarse_after >= 0) {
-        if (aux) { if (packed) MV_LAUNCH_COARSE(true, true); else MV_LAUNCH_COARSE(true, false); }
-        else     { if (packed) MV_LAUNCH_COARSE(false, true); else MV_LAUNCH_COARSE(false, false); }
-    } else if (aux) {
-        if (packed) { if (fast) MV_LAUNCH(true, true, true); else MV_LAUNCH(true, true, false); }
-        else        { if (fast) MV_LAUNCH(true, false, true); else MV_LAUNCH(true, false, false); }
-    } else {
-        if (packed) { if (fast) MV_LAUNCH(false, true, true); else MV_LAUNCH(false, true, false); }
-        else        { if (fast) MV_LAUNCH(false, false, true); else MV_LAUNCH(false, false, false); }
-    }
-#undef MV_LAUNCH_COARSE
+#define MV_LAUNCH(...)                                                                                                       \
+    do {                                                                                                                     \
+        if (aux) {                                                                                                           \
+            if (packed) hipLaunchKernelGGL((render_kernel<true, true, __VA_ARGS__>), grid, block, lds_bytes, stream, p);       \
+            else hipLaunchKernelGGL((render_kernel<true, false, __VA_ARGS__>), grid, block, lds_bytes, stream, p);             \
+        } else {                                                                                                             \
+            if (packed) hipLaunchKernelGGL((render_kernel<false, true, __VA_ARGS__>), grid, block, lds_bytes, stream, p);      \
+            else hipLaunchKernelGGL((render_kernel<false, false, __VA_ARGS__>), grid, block, lds_bytes, stream, p);            \
+        }                                                                                                                    \
+    } while (0)
+    if (p.g.fast && p.coarse_after >= 0) MV_LAUNCH(Scan::kRows, true);
+    else if (p.g.fast) MV_LAUNCH(Scan::kRows);
+    else if (p.window) MV_LAUNCH(Scan::kWindows);
+    else MV_LAUNCH(Scan::kCells);
 #undef MV_LAUNCH
     return hipGetLastError();
 }

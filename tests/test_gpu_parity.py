@@ -861,6 +861,26 @@ def test_wide_grids_with_bodies_tall_worlds_and_rows_that_do_not_fit(lib, orc, g
     assert (ref.face == 6).any() and (ref.hit_index >= 0).any()
 
 
+@pytest.mark.parametrize("grid", [(70, 20, 5), (128, 128, 48)])
+@pytest.mark.parametrize("image", [(48, 32), (45, 29)])
+@pytest.mark.parametrize("aux", [True, False])
+def test_wide_grids_in_every_kernel_variant(lib, orc, grid, image, aux):
+    """The window scan and the per-cell tracer have kernels of their own: each with and without auxiliary outputs, for
+    images of whole tiles and ragged ones, with cameras inside and outside the grid."""
+    rng = np.random.default_rng(sum(grid) + image[0])
+    N, A, M = 2, 6, 9
+    spec = _mini_spec(N, A, grid, image[0], image[1], M)
+    vox, pal = synth.random_world(rng, N, grid, 0.02, M)
+    cams = synth.random_cameras(rng, N * A, grid)
+    cams[::3, 0] = -4.5
+    cams[::3, 3:] = rng.uniform(-0.4, 0.4, cams[::3, 3:].shape)
+    ref = _oracle_for(orc, spec, vox, pal, cams).render(threads=4)
+    run = _gpu_for(spec, vox, pal, cams, aux=aux)
+    run.render()
+    parity.compare(run.numpy(), ref, label=f"grid {grid}, image {image}, aux {aux}")
+    assert (ref.hit_index >= 0).any()
+
+
 @pytest.mark.parametrize("grid", [(40, 40, 16), (96, 96, 16)])
 def test_workgroups_that_fall_back_do_not_wait_for_the_host(lib, grid):
     """A render whose worlds are taller than the layers it reserved costs the slower tracer, a small multiple of the plain
