@@ -159,9 +159,9 @@ hipError_t launch_side(const SideWork& side, hipStream_t stream)
 
 // ------------------------------------------------------------------------------------------
 // pack: one workgroup per environment, whole z layers per wave.  Two kernels, chosen by the host (launch_pack):
-//   pack_kernel      grids of one word per row whose layers are whole 16-byte pieces at aligned addresses: a layer is
-//                    prefetched into registers one layer ahead, goes through LDS and leaves again as the batch's
-//                    own copy; lane j turns x row j into bits dword by dword.
+//   pack_kernel      grids of one word per row whose layers are whole 16-byte pieces at aligned addresses, or whole dwords
+//                    and small: a layer is prefetched into registers one layer ahead, goes through LDS and leaves again
+//                    as the batch's own copy; lane j turns x row j into bits dword by dword.
 //   pack_any_kernel  every other size and alignment: a layer becomes a plain bit string in LDS (bit c = cell c of the
 //                    layer) as it arrives, and the rows are cut out of that string at any bit offset.
 // In both the y rows are the 64x64 bit transposes of the x rows, done across lanes without memory, and rows leave as
@@ -262,12 +262,15 @@ __device__ __forceinline__ void report_height(const HeightFeedback& fb, int top)
     if (top > old) __hip_atomic_fetch_max(fb.host_max, top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// kPackPrefetch = dwords of the next layer each lane keeps in flight: 8 covers layers up to 2 KiB (40x40), 16
-// layers up to 4 KiB (64x64); the deeper variant costs registers, so small layers keep the shallow one.  (Two
-// layers in flight per wave change nothing, four are slower: the kernel moves its bytes at the rate of a plain
+// Piece = what a lane moves at once: 16 bytes, or a dword where layers are not whole 16-byte pieces or start off their
+// boundary.  kPieces = pieces of the next layer each lane keeps in flight, 2 KiB (40x40) or 4 KiB (64x64) of it in all: the
+// deeper variant costs registers, so small layers keep the shallow one.  (Two layers in flight per wave change nothing, four are slower: the kernel moves its bytes at the rate of a plain
 // device copy as it is.)  Other sizes and alignments have a kernel of their own: with their code in this one it
 // needed a third more registers, and lost two of its eight waves per SIMD.
-template <int kPackPrefetch, bool kSide>
+__device__ __forceinline__ uint32_t all_bits(uint32_t v) { return v; }
+__device__ __forceinline__ uint32_t all_bits(u32x4 v) { return v.x | v.y | v.z | v.w; }
+
+template <typename Piece, int kPieces, bool kSide>
 __global__ __launch_bounds__(kPackThreads) void pack_kernel(const uint8_t* __restrict__ src, uint8_t* __restrict__ vox_dst,
                                                             uint64_t* __restrict__ bits_dst, int32_t* __restrict__ ztop_dst,
                                                             GridLayout g, const uint8_t* __restrict__ pal_src,
@@ -292,14 +295,14 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(const uint8_t* __res
     uint64_t* xrows = bits_dst + (size_t)env * g.env_words;
     uint64_t* yrows = xrows + g.xrow_words;
     int top = 0;
-    const int n16 = XY >> 4;
-    u32x4 pre[kPackPrefetch / 4];
+    const int pieces = XY / (int)sizeof(Piece);
+    Piece pre[kPieces];
     auto fetch_layer = [&](int k) {
-        const u32x4* s16 = reinterpret_cast<const u32x4*>(src + env_vox + (size_t)k * XY);
+        const Piece* layer = reinterpret_cast<const Piece*>(src + env_vox + (size_t)k * XY);
 #pragma unroll
-        for (int u = 0; u < kPackPrefetch / 4; ++u) {
-            u32x4 v = { 0u, 0u, 0u, 0u };
-            if (u * 64 + lane < n16) v = __builtin_nontemporal_load(&s16[u * 64 + lane]);
+        for (int u = 0; u < kPieces; ++u) {
+            Piece v = {};
+            if (u * 64 + lane < pieces) v = __builtin_nontemporal_load(&layer[u * 64 + lane]);
             pre[u] = v;
         }
     };
@@ -316,7 +319,7 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(const uint8_t* __res
         // bits that are all zero.
         uint32_t any = 0;
 #pragma unroll
-        for (int u = 0; u < kPackPrefetch / 4; ++u) any |= pre[u].x | pre[u].y | pre[u].z | pre[u].w;
+        for (int u = 0; u < kPieces; ++u) any |= all_bits(pre[u]);
         if (__ballot(any != 0) == 0) {
             // a layer of air: its rows are zero words, and neither LDS nor the transpose is needed for that
             if (k + waves < Z) fetch_layer(k + waves);
@@ -325,14 +328,14 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(const uint8_t* __res
             continue;
         }
         top = k + 1;
-        u32x4* d16 = reinterpret_cast<u32x4*>(vox_dst + env_vox + (size_t)k * XY);
-        u32x4* m16 = reinterpret_cast<u32x4*>(mine);
+        Piece* own_copy = reinterpret_cast<Piece*>(vox_dst + env_vox + (size_t)k * XY);
+        Piece* in_lds = reinterpret_cast<Piece*>(mine);
 #pragma unroll
-        for (int u = 0; u < kPackPrefetch / 4; ++u) {
+        for (int u = 0; u < kPieces; ++u) {
             const int b = u * 64 + lane;
-            if (b < n16) {
-                m16[b] = pre[u];
-                if (copy) __builtin_nontemporal_store(pre[u], &d16[b]);
+            if (b < pieces) {
+                in_lds[b] = pre[u];
+                if (copy) __builtin_nontemporal_store(pre[u], &own_copy[b]);
             }
         }
         // the next layer is requested as soon as the registers are free, and arrives while this one is packed
@@ -440,14 +443,10 @@ __global__ __launch_bounds__(kPackAnyWaves * 64) __attribute__((amdgpu_waves_per
                 }
             }
         } else {
-            uint32_t bits = 0;
-            for (int c = 0; c < XY; ++c) {
-                const uint8_t m = layer[c];
-                bits |= (m != 0 ? 1u : 0u) << c;
-                if (copy && lane == 0) dst[c] = m;
-            }
-            seen = bits;
-            if (lane == 0) string16[0] = (uint16_t)bits;
+            const uint8_t m = lane < XY ? layer[lane] : (uint8_t)0;
+            seen = __ballot(m != 0);
+            if (copy && lane < XY) dst[lane] = m;
+            if (lane == 0) string16[0] = (uint16_t)seen;
         }
         if (seen == 0) {
             for (int r = lane; r < Y * wx; r += 64) xrows[(size_t)k * Y * wx + r] = 0ull;
@@ -495,20 +494,34 @@ hipError_t launch_pack(const uint8_t* src, uint8_t* vox_dst, uint64_t* bits_dst,
     Intensities I;
     for (int f = 0; f < kNumFaces; ++f) I.v[f] = intensity[f];
     const size_t XY = (size_t)g.X * g.Y;
-    const bool aligned = XY % 16 == 0 && ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(vox_dst)) & 15) == 0;
-    // (fast grids hold at most 64 x 64 cells, 4 KiB, per layer: sixteen dwords per lane; rows are read as dwords)
+    const uintptr_t addresses = reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(vox_dst);
+    // (fast grids hold at most 64 x 64 cells, 4 KiB, per layer; rows are read as dwords)
     // Few worlds leave most of the chip idle: there the general kernel, a wave per layer instead of four layers one after
     // the other per wave, is the faster one (40x40x16, us: 64 worlds 6.8 -> 5.2, 256 7.2 -> 5.9, 512 8.3 and 7.9, 1024 11.7
     // and 14.3; 64x64x32: 64 worlds 11.8 -> 9.6, 256 13.7 -> 13.0, 512 21.5 and 21.9; 16x16x8 the same up to 512).
     const bool few = count <= 256;
-    if (g.fast && aligned && (g.X & 3) == 0 && !few) {
+    // Layers that are whole dwords but not whole 16-byte pieces, or start off a 16-byte boundary, move dword by dword while
+    // that keeps eight waves per SIMD, up to 2 KiB (many worlds, general kernel -> dwords, us: 28x26x12 x 1024 10.6 -> 7.8, x
+    // 4096 36.5 -> 20.0; 8x9x12 x 4096 31.4 -> 13.8; 36x30x16 x 4096 43.5 -> 29.6; 40x40x16 x 4096 at an odd dword 44.2 -> 35.3;
+    // but 44x63x32, sixteen dwords per lane, x 300 12.3 -> 15.6, x 2048 54.7 -> 60.8).
+    const bool whole = XY % 16 == 0 && (addresses & 15) == 0;
+    const bool dwords = (addresses & 3) == 0 && XY <= 8 * 64 * 4;
+    if (g.fast && (g.X & 3) == 0 && (whole || dwords) && !few) {
         const size_t lds = pack_lds_bytes(g);
-#define MV_LAUNCH_PACK(PREFETCH, SIDE)                                                                                    \
-    hipLaunchKernelGGL((pack_kernel<PREFETCH, SIDE>), dim3(blocks), dim3(kPackThreads), lds, stream, src, vox_dst,         \
-                       bits_dst, ztop_dst, g, pal_src, pal_dst, lut_dst, materials_plus_one, I, heights, count,             \
-                       side ? *side : no_side)
-        if (XY / 4 <= 8 * 64) { if (side) MV_LAUNCH_PACK(8, true); else MV_LAUNCH_PACK(8, false); }
-        else                  { if (side) MV_LAUNCH_PACK(16, true); else MV_LAUNCH_PACK(16, false); }
+#define MV_LAUNCH_PACK(PIECE, PIECES)                                                                                     \
+    do {                                                                                                                  \
+        if (side)                                                                                                         \
+            hipLaunchKernelGGL((pack_kernel<PIECE, PIECES, true>), dim3(blocks), dim3(kPackThreads), lds, stream, src,      \
+                               vox_dst, bits_dst, ztop_dst, g, pal_src, pal_dst, lut_dst, materials_plus_one, I, heights,  \
+                               count, *side);                                                                             \
+        else                                                                                                              \
+            hipLaunchKernelGGL((pack_kernel<PIECE, PIECES, false>), dim3(blocks), dim3(kPackThreads), lds, stream, src,     \
+                               vox_dst, bits_dst, ztop_dst, g, pal_src, pal_dst, lut_dst, materials_plus_one, I, heights,  \
+                               count, no_side);                                                                           \
+    } while (0)
+        if (!whole) MV_LAUNCH_PACK(uint32_t, 8);
+        else if (XY <= 2 * 64 * 16) MV_LAUNCH_PACK(u32x4, 2);
+        else MV_LAUNCH_PACK(u32x4, 4);
 #undef MV_LAUNCH_PACK
     } else {
         // (at least kSideThreads threads: what a workgroup takes of the side work)
@@ -1907,8 +1920,9 @@ hipError_t prepare_kernels()
 #undef MV_SET
     // the pack kernel also has a few static words of LDS: its dynamic share must leave room for them
     const int pack_limit = (int)(kLdsBudget - kPackStaticLds);
-    const void* pack_kernels[] = { reinterpret_cast<const void*>(&pack_kernel<8, false>), reinterpret_cast<const void*>(&pack_kernel<8, true>),
-                                   reinterpret_cast<const void*>(&pack_kernel<16, false>), reinterpret_cast<const void*>(&pack_kernel<16, true>),
+    const void* pack_kernels[] = { reinterpret_cast<const void*>(&pack_kernel<u32x4, 2, false>), reinterpret_cast<const void*>(&pack_kernel<u32x4, 2, true>),
+                                   reinterpret_cast<const void*>(&pack_kernel<u32x4, 4, false>), reinterpret_cast<const void*>(&pack_kernel<u32x4, 4, true>),
+                                   reinterpret_cast<const void*>(&pack_kernel<uint32_t, 8, false>), reinterpret_cast<const void*>(&pack_kernel<uint32_t, 8, true>),
                                    reinterpret_cast<const void*>(&pack_any_kernel<false>), reinterpret_cast<const void*>(&pack_any_kernel<true>) };
     for (const void* k : pack_kernels)
         if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, pack_limit);

@@ -1695,8 +1695,12 @@ def test_host_arrays_may_be_reused_on_return(lib, part):
     np.testing.assert_array_equal(_read_device(xp, words), _read_device(batches[1].debug_occupancy(0)[0], words))
 
 
-@pytest.mark.parametrize("grid", [(4, 4, 3), (40, 40, 16), (64, 64, 5), (60, 28, 9), (64, 2, 4)])
-def test_pack_of_many_and_of_few_worlds_agree(lib, grid):
+@pytest.mark.parametrize("grid,offset", [((4, 4, 3), 0), ((40, 40, 16), 0), ((64, 64, 5), 0), ((60, 28, 9), 0), ((64, 2, 4), 0),
+                                         # layers of whole dwords: not whole 16-byte pieces, off their boundary, the most
+                                         # and more than the dword kernel takes, not even dwords, a part of a piece
+                                         ((4, 5, 3), 0), ((28, 26, 12), 0), ((20, 10, 5), 8), ((40, 40, 5), 4), ((64, 32, 3), 4),
+                                         ((64, 33, 3), 4), ((36, 57, 4), 0), ((40, 40, 5), 2), ((3, 5, 4), 0), ((4, 3, 4), 0)])
+def test_pack_of_many_and_of_few_worlds_agree(lib, grid, offset):
     """Uploads of more than 256 worlds and of fewer take different pack kernels: same rows, tops and material bytes where
     there is a solid voxel, for layers of air between solid ones, empty worlds and full ones."""
     rng = np.random.default_rng(sum(grid))
@@ -1706,7 +1710,9 @@ def test_pack_of_many_and_of_few_worlds_agree(lib, grid):
     vox[::3, Z // 2] = 0
     vox[1::7] = 0
     vox[2::7] = 9
-    vd, pd = torch.from_numpy(vox).cuda(), torch.from_numpy(pal).cuda()
+    vd = torch.zeros(vox.size + 16, dtype=torch.uint8, device="cuda")[offset:offset + vox.size].view(vox.shape)
+    vd.copy_(torch.from_numpy(vox))
+    pd = torch.from_numpy(pal).cuda()
     got = []
     for parts in ((0, N),), ((0, half), (half, N)):
         batch = binding.Batch(N, 1, grid, 9, 16, 8)
