@@ -284,9 +284,11 @@ static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::Gri
         // faster than whole observations or 6 strips).  Grids that leave room for only two workgroups per
         // CU render whole observations: every strip would re-stage the rows with nothing to hide it.
         const int waves = p.threads / 64;
-        // The window scan's workgroups stage more and are half as many per CU: half the number is enough (before the correction of a run's last cell: 96x96x16 x 256, 2
-        // agents, 128x72: step 80.3 -> 76.7 us, at 256x144 156 -> 148 us; 2048 workgroups 75.4 and 159, 4096 79.2 and 146).
-        const long long target_blocks = plan.window ? 256ll * 12 : 256ll * 24;
+        // Where the window scan's rows leave room for fewer than six workgroups per CU, half the number is enough (render of
+        // 256 x 2, 3072 -> 4096 -> 6144 workgroups, us: 96x96x16, four per CU, 128x72 79.8, 77.8, 77.6, 256x144 196, 187, 192, four
+        // agents at 64x64 82, 86, 86; 128x128x16, three per CU, 85, 98, 89 and 210, 200, 212; with more room it costs: 80x64x10,
+        // seven per CU, 76.8, 70.7, 71.4 and 234, 197, 183; 70x40x8, eleven per CU, 66.5, 61.4, 59.4 and 193, 180, 165).
+        const long long target_blocks = plan.window && mv::kLdsBudget / plan.bytes < 6 ? 256ll * 12 : 256ll * 24;
         long long strips = (target_blocks + num_obs - 1) / num_obs;
         if (mv::kLdsBudget / plan.bytes >= 4 && strips < 3) strips = 3;
         if (strips < 1) strips = 1;

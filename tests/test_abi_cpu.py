@@ -223,3 +223,13 @@ def test_launch_shape_follows_the_staged_layers_and_rejects_what_create_rejects(
     with pytest.raises(binding.MvError) as e:
         binding.launch_shape(huge)
     assert e.value.code == binding.MV_ERR_CAPACITY
+
+
+@pytest.mark.parametrize("grid,layers,strips", [((40, 40, 16), 10, 12), ((70, 40, 8), 8, 12), ((80, 64, 10), 9, 12),
+                                                ((96, 96, 16), 10, 6), ((128, 128, 16), 10, 6)])
+def test_strips_follow_the_workgroups_a_compute_unit_holds(lib, grid, layers, strips):
+    """About 6144 workgroups for 512 observations, half as many where a wide grid's rows leave room for fewer than six per
+    compute unit."""
+    shape = binding.launch_shape(binding.make_config(256, 2, grid, 16, 128, 72), layers)
+    assert (163840 // shape.lds_bytes < 6) == (strips == 6)
+    assert shape.blocks_per_obs == strips
