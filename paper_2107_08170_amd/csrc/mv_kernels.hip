@@ -77,6 +77,12 @@ LdsPlan plan_lds(const GridLayout& g, int W, int H, int materials_plus_one, int 
     LdsPlan plan{};
     plan.window = !g.fast;
     LdsMap m = lds_map(g, W, H, materials_plus_one, staged_layers, coarse, plan.window);
+    // x and y rows are taken wherever they fit, also where they leave one workgroup per CU and x rows alone would leave two.
+    // With the same reserve, per-cell -> window, us, 5 % of the columns filled to the top and, in brackets, worlds of four
+    // layers: 128x128x24, 8 x 1 at 128x72 30 -> 21 (50 -> 22), 64 x 2 at 256x144 162 -> 148 (233 -> 89), 256 x 2 at 128x72
+    // 181 -> 211 (233 -> 117); 128x128x36 35 -> 24 (50 -> 14), 173 -> 160 (239 -> 86), 224 -> 228 (296 -> 113); 200x200x12 48 -> 29,
+    // 216 -> 148, 197 -> 192.  So large batches of worlds that are dense up there lose up to a sixth, at images of a few
+    // tiles (17x17 pixels) up to a third, all others gain; the launch knows the tallest world only, not how many are.
     if (plan.window && m.total > kLdsBudget) {
         plan.window = false;
         m = lds_map(g, W, H, materials_plus_one, staged_layers, coarse, false);
