@@ -639,6 +639,8 @@ struct Hit {
 };
 
 constexpr float kBig = 3.0e38f;            // stands in for 1/0: keeps every product finite or +inf, never NaN
+constexpr float kNever = 0.5f * kBig;      // first crossing of an axis along which a ray does not move (below kBig, the
+                                           // distance between two crossings: the one before the first lies behind the camera)
 
 __device__ __forceinline__ float safe_rcp(float d)
 {
@@ -1271,8 +1273,10 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
         c.idx0 += (float)((in.k * from_outside->Y) * from_outside->X + in.j * (xm ? from_outside->X : 1));
         c.i0 = du < 0.0f ? c.um1 - in.i : in.i;
     } else {
-        t0_u = c.uexit * inv_u;
-        t0_v = c.dist_v * dt_v;
+        // (an axis along which the ray does not move at all: its first plane is never reached, also from a camera exactly
+        // on the far side of the grid, whose distance to it is 0)
+        t0_u = du == 0.0f ? kNever : c.uexit * inv_u;
+        t0_v = dv == 0.0f ? kNever : c.dist_v * dt_v;
         t0_z = rr.t0_z;
         t_end = vmin3(fmaf((float)(c.um1 - c.i0), inv_u, t0_u), fmaf(c.nv_max, dt_v, t0_v), rr.tend_z);
     }
@@ -1506,7 +1510,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             // distance will do, the top of its real cell is one)
             const float dist_z = fabsf((float)(zneg ? kc : k0 + 1) - P[2]);
             const float nz_max = (float)(zneg ? kc : zlim - 1 - kc);
-            rr.t0_z = dist_z * dt_z;
+            rr.t0_z = !FAST && dz == 0.0f ? kNever : dist_z * dt_z;     // (see trace_windows)
             rr.tend_z = fmaf(nz_max, dt_z, rr.t0_z);
             return rr;
         };

@@ -861,6 +861,28 @@ def test_wide_grids_with_bodies_tall_worlds_and_rows_that_do_not_fit(lib, orc, g
     assert (ref.face == 6).any() and (ref.hit_index >= 0).any()
 
 
+@pytest.mark.parametrize("grid,yaw,pitch", [((96, 80, 8), 0.7, 0.0), ((96, 80, 8), 0.0, 0.3), ((70, 20, 5), 0.7, 0.0),
+                                            ((70, 20, 5), 0.0, 0.3), ((70, 20, 5), 0.0, -np.pi / 2), ((70, 20, 5), np.pi, 0.0)])
+def test_rays_in_the_far_sides_of_wide_grids(lib, orc, grid, yaw, pitch):
+    """Cameras exactly on the sides and corners of a wide grid, views whose middle row or column runs exactly along them:
+    such a ray stays in the cells behind the side, like the oracle's, and does not leave the grid where it starts."""
+    rng = np.random.default_rng(1)
+    X, Y, Z = grid
+    A, M = 24, 7
+    spec = _mini_spec(1, A, grid, 25, 17, M)
+    vox = (rng.random((1, Z, Y, X)) < 0.02).astype(np.uint8) * 3
+    vox[:, Z - 1, ::3, ::5] = 2
+    vox[:, 0] = 1
+    pal = rng.integers(0, 256, (1, M + 1, 3)).astype(np.uint8)
+    cams = np.array([(x, y, z, yaw, pitch) for x in (0, 3.5, 7, X) for y in (0, 5.5, Y) for z in (2.5, Z)], np.float32)
+    ref = _oracle_for(orc, spec, vox, pal, cams).render()
+    run = _gpu_for(spec, vox, pal, cams)
+    run.render()
+    got = run.numpy()
+    np.testing.assert_array_equal(got.hit_index, ref.hit_index)
+    np.testing.assert_array_equal(got.face, ref.face)
+
+
 @pytest.mark.parametrize("grid", [(70, 20, 5), (128, 128, 48)])
 @pytest.mark.parametrize("image", [(48, 32), (45, 29)])
 @pytest.mark.parametrize("aux", [True, False])
