@@ -1288,7 +1288,10 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
     for (bool go = !kOutside || !in.misses; go;) {
         // The last cell of the run: where the ray is at t_out, put right by one cell where the u crossings themselves say
         // so.  Every choice of the next crossing is then the per-cell tracer's own comparison, ties included (x before y
-        // before z, and none at or behind the far side), and so are the cells visited.
+        // before z, and none at or behind the far side), and so are the cells visited, for cameras inside the grid and no
+        // higher than the solids.  From higher up the z crossings are counted from the top of the solids and not from the
+        // camera's own layer (depths differ in the last bit), and a ray that leaves the solids' top plane exactly through
+        // a voxel edge does not look at the voxel beside that edge, as one that leaves the grid.
         const bool cv = t_v <= t_z;
         const float t_out = vmin3(t_v, t_z, t_end);
         const bool strict = (!xm && cv) || !(t_out < t_end);
@@ -1322,7 +1325,8 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
     const bool along_row = iu != i_row;
     const float tv_last = fmaf(n_v - 1.0f, dt_v, t0_v);
     const float tz_last = fmaf(n_z - 1.0f, dt_z, t0_z);
-    const bool via_z = tz_last >= tv_last;
+    // (from a camera exactly on a z plane a rising ray has that plane one crossing behind it, at parameter 0)
+    const bool via_z = tz_last >= tv_last && n_z > 0.0f;
     const float t_in = vmax3(tv_last, tz_last, 0.0f);
     const float iu_f = (float)iu;
     const float t_u = fmaf(iu_f - (float)c.i0 - 1.0f, inv_u, t0_u);

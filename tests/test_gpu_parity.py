@@ -861,6 +861,36 @@ def test_wide_grids_with_bodies_tall_worlds_and_rows_that_do_not_fit(lib, orc, g
     assert (ref.face == 6).any() and (ref.hit_index >= 0).any()
 
 
+@pytest.mark.parametrize("grid", [(96, 80, 8), (70, 20, 5), (128, 128, 16), (65, 90, 12)])
+@pytest.mark.parametrize("where", ["anywhere", "in the middle of cells", "on voxel corners"])
+def test_window_scan_and_per_cell_tracer_agree_bit_for_bit(lib, grid, where):
+    """Inside the grid and no higher than the solids the window scan visits the per-cell tracer's cells, ties included: the
+    same voxel, face and depth in every pixel as from a launch that reserved too few layers and traces cell by cell.  Views
+    at whole multiples of 45 degrees from cell middles and corners meet voxel edges in thousands of pixels."""
+    rng = np.random.default_rng(sum(grid))
+    X, Y, Z = grid
+    N, A, M = 3, 24, 7
+    spec = _mini_spec(N, A, grid, 97, 61, M)
+    vox, pal = synth.random_world(rng, N, grid, 0.01, M)
+    vox[:, 0] = 1
+    vox[:, Z - 1, ::3, ::7] = 4                                     # solids up to the top: nothing is cut off
+    cams = np.zeros((N * A, 5), np.float32)
+    cams[:, :3] = rng.uniform(0.1, np.array(grid) - 0.1, (N * A, 3))
+    cams[:, 3:] = rng.uniform(-3, 3, (N * A, 2)) * (1, 0.3)
+    if where != "anywhere":
+        cams[:, :3] = np.floor(cams[:, :3]) + (0.5 if where == "in the middle of cells" else 0.0)
+        cams[:, 3:] = np.stack([rng.integers(0, 8, N * A), rng.integers(-1, 2, N * A)], 1) * (np.pi / 4)
+    run = _gpu_for(spec, vox, pal, cams)
+    out = []
+    for layers in (0, 1):
+        run.batch.debug_set_staged_layers(layers)
+        run.render()
+        out.append(run.numpy())
+    for name in ("hit_index", "face", "material", "rgb", "depth"):          # (by value: a depth of 0 may carry either sign)
+        np.testing.assert_array_equal(getattr(out[0], name), getattr(out[1], name), err_msg=name)
+    assert (out[0].hit_index >= 0).any() and (out[0].hit_index < 0).any()
+
+
 @pytest.mark.parametrize("grid,yaw,pitch", [((96, 80, 8), 0.7, 0.0), ((96, 80, 8), 0.0, 0.3), ((70, 20, 5), 0.7, 0.0),
                                             ((70, 20, 5), 0.0, 0.3), ((70, 20, 5), 0.0, -np.pi / 2), ((70, 20, 5), np.pi, 0.0)])
 def test_rays_in_the_far_sides_of_wide_grids(lib, orc, grid, yaw, pitch):
