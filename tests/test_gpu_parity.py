@@ -824,6 +824,44 @@ def test_cameras_outside_scan_rows_from_where_rays_enter(lib, orc, grid):
             _pixelwise_rule(run.numpy(), ref, f"outside, grid {grid}, fov {hfov}, layers {layers}")
 
 
+@pytest.mark.parametrize("grid", [(40, 40, 16), (64, 64, 32), (96, 96, 16)])
+@pytest.mark.parametrize("reach", [150.0, 400.0, 1000.0, 2000.0, 4096.0, 4097.0])
+def test_cameras_far_outside_and_on_both_sides_of_the_switch(lib, orc, grid, reach):
+    """Cameras whose largest coordinate is `reach`, up to and beyond 4096 where rays are traced cell by cell, looking at the
+    grid through a narrow lens.  A crossing's parameter t is at most about the distance r and carries two roundings, so its
+    point is good to r * 2^-22 voxels along each axis: a pixel may differ from the oracle only where the oracle's ray passes
+    a voxel edge within that (or within the usual 1e-4, up to r = 420)."""
+    rng = np.random.default_rng(int(reach) + grid[0])
+    N, A, M, W, H = 6, 10, 7, 64, 48
+    spec = _mini_spec(N, A, grid, W, H, M)
+    vox, pal = synth.random_world(rng, N, grid, 0.1, M)
+    vox[:, 0] = 3
+    vox[3:, (grid[2] + 1) // 2:] = 0
+    dim = np.array(grid, np.float64)
+    cams = np.zeros((N * A, 5), np.float32)
+    for o in range(N * A):
+        aim, d = rng.uniform(0.2, 0.8, 3) * dim, rng.normal(size=3)
+        axis = int(np.abs(d).argmax())
+        d *= (reach - np.sign(d[axis]) * aim[axis]) / abs(d[axis])
+        pos = (aim + d).astype(np.float32)
+        pos[axis] = np.sign(d[axis]) * reach
+        v = aim - pos
+        cams[o] = (*pos, np.arctan2(v[1], v[0]), np.arctan2(v[2], np.hypot(v[0], v[1])))
+    hfov = float(np.float32(1.2 * max(grid) / reach))
+    ref = _oracle_for(orc, spec, vox, pal, cams, hfov_rad=hfov).render(threads=8)
+    run = _gpu_for(spec, vox, pal, cams, hfov_rad=hfov)
+    run.render()
+    g = run.numpy()
+    away = np.linalg.norm(cams[:, :3].astype(np.float64) - dim / 2, axis=1).max()
+    margin = max(parity.EDGE_MARGIN, away * 2.0 ** -22)
+    differ = (g.hit_index != ref.hit_index) | (g.material != ref.material) | (g.face != ref.face)
+    assert not (differ & ~(ref.edge_margin < margin)).any(), (int(differ.sum()), float(ref.edge_margin[differ].max()), margin)
+    assert differ.mean() < 5e-4
+    hit = ~differ & (ref.hit_index >= 0)
+    assert (np.abs(g.depth[hit].astype(np.float64) - ref.depth[hit]) <= 4 * 2.0 ** -23 * ref.depth[hit]).all()
+    assert hit.mean() > 0.2 and (ref.hit_index < 0).any()
+
+
 @pytest.mark.parametrize("grid", [(65, 9, 4), (9, 65, 4), (95, 33, 3), (96, 96, 5), (97, 64, 4), (64, 127, 4), (128, 128, 4),
                                   (129, 31, 3), (31, 191, 3), (300, 5, 2)])
 def test_windows_of_wide_rows(lib, orc, grid):
