@@ -100,8 +100,10 @@ void mv_default_config(mv_config* cfg);
  * Allocates all device memory the batch will ever use: material grids N*X*Y*Z bytes,
  * occupancy bits, per-environment shaded colour tables, camera records.  *out is written only
  * on success.  Grids up to 64x64 voxels in x and y take the row-scan traversal; wider grids
- * scan their rows through windows of 32 cells, or cell by cell where their x and y rows do not both fit on chip.  Errors: MV_ERR_ARG (bad field), MV_ERR_CAPACITY (the
- * occupancy bits of one grid do not fit in the 160 KiB of LDS of a compute unit), MV_ERR_HIP. */
+ * scan their rows through windows of 32 cells, or are traced cell by cell where their x and y rows do
+ * not both fit on chip.  Errors: MV_ERR_ARG (bad field), MV_ERR_CAPACITY (the occupancy bits of one
+ * grid do not fit in the 160 KiB of LDS of a compute unit, or a layer has more than 40 704 cells),
+ * MV_ERR_HIP. */
 int mv_create_batch(const mv_config* cfg, mv_batch** out);
 
 /* Replace the voxel grids of environments first_env .. first_env+count-1 (paper Sec. 3.1: the
@@ -180,10 +182,12 @@ int mv_set_cameras(mv_batch* batch, const float* cams, const int32_t* self_voxel
  * grid on chip, as many as the tallest world uploaded so far needs (learnt from earlier kernels without
  * synchronising); the first launch after taller worlds arrive renders them through device memory (slower,
  * same accuracy, not necessarily the same bits at exact ties), later launches adapt.  While `stream` is being
- * captured into a HIP graph that choice would be frozen into the graph, so a captured launch keeps ALL layers
- * on chip instead (a few per cent slower than the adaptive choice on low worlds, never the slow path on a
- * replay over taller ones); a caller who knows the tallest world the graph will ever see can fix a smaller
- * number with mv_debug_set_staged_layers before capturing.
+ * captured into a HIP graph that choice would be frozen into the graph, so a captured launch makes room for ALL
+ * layers on chip instead, and a replay over taller worlds never takes the slow path.  On low worlds that costs a few
+ * per cent against the adaptive choice on grids up to 64x64 in x and y, up to a factor of two on wide and tall ones
+ * (128x128x24); where the x and y rows of all layers of a wide grid do not both fit (128x128x40) the captured launch
+ * traces cell by cell (a factor of six), as mv_render_worlds_noalloc does there.  A caller who knows the tallest world
+ * the graph will ever see can fix a smaller number with mv_debug_set_staged_layers before capturing.
  * Errors: MV_ERR_ARG, MV_ERR_STATE (some environment or the cameras never supplied), MV_ERR_HIP. */
 int mv_render_batch(mv_batch* batch, uint8_t* rgb, float* depth, uint8_t* aux_material,
                     int32_t* aux_hit_index, uint8_t* aux_face, void* hip_stream);
@@ -341,7 +345,8 @@ const char* mv_last_error(void);
  *                        is voxel (i,j,k); *top_layer points to one int32: 1 + the highest layer k
  *                        that holds a solid voxel (0 for an empty grid).
  *   mv_debug_camera_records : device pointer to the [N*A] 64-byte camera records
- *                        (float P[3], F[3], R[3], U[3]; int32 self_lo, self_hi; 8 bytes pad).
+ *                        (float P[3], F[3], R[3], U[3]; int32 self_lo, self_hi; int32 place: 0 in the grid, 1
+ *                        outside, 2 far outside or not a number; int32 layer: floor(P_z) clamped to the grid).
  *   mv_debug_set_staged_layers : the render kernel keeps only the lowest layers of a grid on chip, as many
  *                        as the tallest world uploaded so far needs (it learns that number from its own
  *                        kernels, without synchronising); an environment that needs more is traced

@@ -225,9 +225,10 @@ static int check_config(const mv_config* cfg, const char* who, mv::GridLayout* l
         return fail(MV_ERR_CAPACITY, "%s: the occupancy bit rows of one %dx%dx%d grid do not fit in %zu bytes of LDS", who,
                     cfg->grid_x, cfg->grid_y, cfg->grid_z, mv::kLdsBudget);
 
-    // the pack kernel keeps one whole z layer per wave in LDS
+    // the limit of a layer, 40 704 cells: four copies of its bytes in LDS.  (Grids that reach it are packed from their
+    // bits, which would fit; nothing larger is tested.)
     if (mv::pack_lds_bytes(layout) + mv::kPackStaticLds > mv::kLdsBudget)
-        return fail(MV_ERR_CAPACITY, "%s: one %dx%d layer (x4 waves) does not fit in %zu bytes of LDS while packing", who,
+        return fail(MV_ERR_CAPACITY, "%s: a %dx%d layer has more cells than fit four times in %zu bytes of LDS", who,
                     cfg->grid_x, cfg->grid_y, mv::kLdsBudget);
     *layout_out = layout;
     *plan_out = plan;

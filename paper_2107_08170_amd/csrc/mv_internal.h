@@ -20,7 +20,9 @@ constexpr int kPlaceInGrid = 0;           // inside the grid's box or on its bou
 constexpr int kPlaceOutside = 1;          // outside it, no coordinate beyond kNearOutside
 constexpr int kPlaceFarOutside = 2;       // further away, or a position that is not a number
 // So near, the point where a ray enters the grid is good to a small fraction of a voxel in float32 (the spacing of
-// float32 numbers at 4096 is 5e-4), which the row scan from that point relies on.
+// float32 numbers at 4096 is 5e-4), which the row scan from that point relies on.  (Against the float64 oracle it is no
+// further off than the per-cell tracer at any distance: at 4000 voxels around 40x40x16 it differs in 12 of 184 320 pixels,
+// whose rays pass a voxel edge within 1.5e-4 voxels, the per-cell tracer in 14, within 3.8e-4.)
 constexpr float kNearOutside = 4096.0f;
 static_assert(sizeof(CameraRecord) == 64, "camera record must be 64 bytes");
 
@@ -174,7 +176,8 @@ hipError_t launch_overlay(uint8_t* rgb, const float* values, int values_per_obs,
                           int W, int H, const OverlayParams& overlay, hipStream_t stream);
 // raises the dynamic-LDS limit of the render and pack kernels on the current device (cheap after the first call)
 hipError_t prepare_kernels();
-// dynamic LDS the pack kernel asks for: one z layer per wave
+// dynamic LDS of the pack kernel that keeps the bytes of one z layer per wave (the general one, which takes the wide
+// grids, needs at most half of it); also the measure by which a configuration's layers are limited
 size_t pack_lds_bytes(const GridLayout& g);
 hipError_t launch_render(const RenderParams& p, size_t lds_bytes, hipStream_t stream);
 

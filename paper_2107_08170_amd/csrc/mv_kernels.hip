@@ -374,6 +374,8 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(const uint8_t* __res
 
 // 16 bytes at any address (one unaligned vector access)
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+// a dword of a bit string that is written 16 bits at a time
+typedef uint32_t string_dword __attribute__((may_alias));
 
 // Any grid size, any alignment.  What bounds it is memory, as for pack_kernel; a wave keeps 3 KiB in flight and the
 // workgroup holds as many waves as the world has layers (up to 16), so that a CU with a single environment still has
@@ -400,7 +402,7 @@ __global__ __launch_bounds__(kPackAnyWaves * 64) __attribute__((amdgpu_waves_per
     const int X = g.X, Y = g.Y, Z = g.Z;
     const int XY = X * Y, wx = g.rowwords_x, wy = g.rowwords_y;
     uint16_t* string16 = reinterpret_cast<uint16_t*>(bits_lds + (size_t)wave * bits_bytes);
-    const uint32_t* string32 = reinterpret_cast<const uint32_t*>(string16);
+    const string_dword* string32 = reinterpret_cast<const string_dword*>(string16);
     const size_t env_vox = (size_t)env * XY * Z;
     const bool copy = (src != vox_dst);
     uint64_t* xrows = bits_dst + (size_t)env * g.env_words;
@@ -710,8 +712,8 @@ struct alignas(16) PairClass {
 static_assert(sizeof(ScanClass) + sizeof(PairClass) <= kClassStride, "class slot too small");
 
 // Plain 3D-DDA through the x rows (any row width), in LDS or in global memory.  Used for grids whose x and y rows do not
-// both fit into LDS, for cameras far outside the grid, and for workgroups whose world is taller than the layers staged.  Crossing parameters are t = n*|1/d| + t_first (one fused op, error relative
-// to t itself) rather than accumulated.
+// both fit into LDS, for cameras far outside the grid, and for workgroups whose world is taller than the layers staged.
+// Crossing parameters are t = n*|1/d| + t_first (one fused op, error relative to t itself) rather than accumulated.
 // self_lo / self_hi: voxels this camera must not see (-1 = none); callers that have already removed the body
 // from their copy of the rows pass -1.
 __device__ __forceinline__ Hit trace_generic(const uint32_t* __restrict__ xrows32, int rowdwords, const float P[3],
@@ -942,7 +944,9 @@ __device__ __forceinline__ BoxEntry enter_box(const OutsideCamera& o, float dx, 
 // point, so the runs of cells are monotone here as well.  Bound by instruction issue like the inside scan (about ninety
 // instructions more per ray, for the entry); the per-cell tracer over rows in device memory, which took these cameras
 // before and still takes far ones, spends a dependent memory access per cell (256 x 4 cameras around 40x40x16 worlds at
-// 128x72, upload + cameras + render: 286 -> 82 us).
+// 128x72, upload + cameras + render: 286 -> 80 us).  The last cell of a run is taken from the ray's position, as for
+// cameras inside: a ray that passes exactly through a voxel edge may fall on the other side of it than with the per-cell
+// tracer (45-degree views along cell middles: 6 of 10 000 pixels; views at random: one of 13 million).
 template <bool kNarrow, bool kCoarse, bool kOutside = false>
 __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float dy, const RowRecord& rr, int fine_turns,
                                           const OutsideCamera* from_outside = nullptr)
@@ -1239,8 +1243,8 @@ typedef __attribute__((address_space(3))) const uint32_t* lds_u32_ptr;
 // is -1 for mirrored classes, else 0.  Bits of a window beyond the row's ends belong to its neighbours in LDS and never
 // count: runs end at cell U - 1.  Ends for every input as trace_rows does; a window that does not reach the end of the run
 // advances it by 32 cells.  Bound by instruction issue, about five turns per ray instead of one per cell
-// (256 x 2 worlds of 96x96x16 at 128x72, upload + cameras + render: 184 -> 104 us;
-// 76 us without the correction of a run's last cell, but then rays through a voxel edge fall on other sides than before).
+// (256 x 2 worlds of 96x96x16 at 128x72, upload + cameras + render: 184 -> 98 us; the correction of a run's last cell took
+// it from 76 to 104 us when it was added, but without it rays through a voxel edge fall on other sides than before).
 template <bool kOutside>
 __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, float dy, const RowRecord& rr,
                                              const OutsideCamera* from_outside = nullptr)
