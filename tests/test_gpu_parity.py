@@ -1408,6 +1408,44 @@ def test_slow_paths_on_mid_size_batches(lib, orc, name):
         assert (run.depth > 0).float().mean().item() > 0.2          # the cameras do look at their arenas
 
 
+@pytest.mark.parametrize("grid", [(96, 96, 16), (128, 128, 48)])
+def test_wide_step_captured_over_low_worlds_replays_over_taller_ones(lib, orc, grid):
+    """A captured step of wide worlds makes room for all layers, for the window scan or, where the x and y rows of all of
+    them do not both fit, cell by cell: replays over low and then over taller worlds against the oracle, each replay after
+    eager calls of the same batch (whose own launches adapt to the worlds)."""
+    rng = np.random.default_rng(grid[0])
+    N, A, M = 4, 3, 6
+    spec = _mini_spec(N, A, grid, 64, 40, M)
+    tall, pal = synth.random_world(rng, N, grid, 0.01, M)
+    tall[:, 0] = 2
+    low = tall.copy()
+    low[:, 3:] = 0
+    cams = synth.random_cameras(rng, N * A, grid)
+    cams[:, 2] = 1.5
+    run = _gpu_for(spec, low, pal, cams, aux=False)
+    cams_d, pal_d = torch.from_numpy(cams).cuda(), torch.from_numpy(pal).cuda()
+    run.render()
+    run.render()                                                    # the host has heard: worlds are 3 layers tall
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            run.batch.step(cams_d, run.rgb, run.depth, stream=torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    for worlds in (low, tall, low):
+        worlds_d = torch.from_numpy(worlds).cuda()
+        run.batch.upload_worlds(worlds_d, pal_d, stream=_stream())
+        ref = _oracle_for(orc, spec, worlds, pal, cams).render(threads=8)
+        for _ in range(2):
+            run.render()
+            parity.compare(run.numpy(), ref, label=f"eager, grid {grid}")
+            run.rgb.fill_(7); run.depth.fill_(-1.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            parity.compare(run.numpy(), ref, label=f"replay, grid {grid}")
+
+
 def test_step_captured_over_low_worlds_replays_over_taller_ones(lib, orc):
     """A graph captured while every world is two layers tall must still render at full speed, and correctly,
     when taller worlds are uploaded afterwards: the captured launch reserves room for all layers instead of the
