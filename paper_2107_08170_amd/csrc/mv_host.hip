@@ -228,8 +228,8 @@ static int check_config(const mv_config* cfg, const char* who, mv::GridLayout* l
     // the limit of a layer, 40 704 cells: four copies of its bytes in LDS.  (Grids that reach it are packed from their
     // bits, which would fit; nothing larger is tested.)
     if (mv::pack_lds_bytes(layout) + mv::kPackStaticLds > mv::kLdsBudget)
-        return fail(MV_ERR_CAPACITY, "%s: the bytes of a %dx%d layer do not fit four times in %zu bytes of LDS, the limit for packing", who,
-                    cfg->grid_x, cfg->grid_y, mv::kLdsBudget);
+        return fail(MV_ERR_CAPACITY, "%s: the bytes of a %dx%d layer do not fit four times in %zu bytes of LDS, the limit for "
+                    "packing", who, cfg->grid_x, cfg->grid_y, mv::kLdsBudget);
     *layout_out = layout;
     *plan_out = plan;
     return MV_OK;

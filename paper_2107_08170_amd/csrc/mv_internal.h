@@ -20,7 +20,7 @@ constexpr int kPlaceInGrid = 0;           // inside the grid's box or on its bou
 constexpr int kPlaceOutside = 1;          // outside it, no coordinate beyond kNearOutside
 constexpr int kPlaceFarOutside = 2;       // further away, or a position that is not a number
 // So near, the point where a ray enters the grid is good to a small fraction of a voxel in float32 (the spacing of
-// float32 numbers at 4096 is 5e-4), which the row scan from that point relies on.  (Against the float64 oracle it is no
+// float32 numbers at 4096 is 5e-4), which the row scan from that point relies on.  (Against a trace in float64 it is no
 // further off than the per-cell tracer at any distance: at 4000 voxels around 40x40x16 it differs in 12 of 184 320 pixels,
 // whose rays pass a voxel edge within 1.5e-4 voxels, the per-cell tracer in 14, within 3.8e-4.)
 constexpr float kNearOutside = 4096.0f;
