@@ -635,12 +635,13 @@ hipError_t launch_move_voxels(const int32_t* env, const int32_t* from_voxel, con
 // render
 // ------------------------------------------------------------------------------------------
 struct Hit {
-    int   idx;      // linear voxel index, -1 = miss
-    int   face;     // 0..6, 255 = miss
+    int   idx;      // linear voxel index, negative = miss
+    int   face;     // from trace_rows and trace_windows as FaceRows has it, from trace_generic 0..6, 255 = miss
     float t;        // planar depth
 };
 
 constexpr float kBig = 3.0e38f;            // stands in for 1/0: keeps every product finite or +inf, never NaN
+constexpr float kSmallest = 0x1p-126f;      // smallest normal number
 constexpr float kNever = 0.5f * kBig;      // first crossing of an axis along which a ray does not move (below kBig, the
                                            // distance between two crossings: the one before the first lies behind the camera)
 
@@ -650,11 +651,37 @@ __device__ __forceinline__ float safe_rcp(float d)
     return __builtin_amdgcn_fmed3f(__builtin_amdgcn_rcpf(d), -kBig, kBig);
 }
 
+// Small whole numbers as floats whose bits are the number (denormals): adding two of them, or multiplying one by a whole
+// number, is integer arithmetic as long as the result stays below 2^23 (bits go on counting up to 2^24), exact and with any
+// rounding.  The point is the instruction: a float add, multiply or fused multiply-add with its operands in vector registers
+// issues in the shadow of the comparisons, selects, conversions and shifts other waves keep the vector pipeline busy with
+// (0.5 cycles beside such an instruction, 4.4 for an integer add, shift or multiply-add, or for any operand in a scalar
+// register; measured with streams of two instruction kinds).
+__device__ __forceinline__ float tiny_int(uint32_t v) { return __uint_as_float(v); }
+__device__ __forceinline__ float tiny_to_float(float t) { return (t * 0x1p127f) * 0x1p22f; }        // the number as a float
+__device__ __forceinline__ float float_to_tiny(float v) { return (v * 0x1p-127f) * 0x1p-22f; }      // and back (whole numbers below 2^24)
+
+// a value all lanes share, held in a vector register
+__device__ __forceinline__ float in_vector(float v)
+{
+    float r;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "s"(v));
+    return r;
+}
+
 // a value all lanes share, as a scalar
 __device__ __forceinline__ float uniform(float v)
 {
     return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v)));
 }
+
+// What a tracer reports of the face a ray entered its voxel through: base + code * stride.  Launches with auxiliary outputs
+// take the face code itself (0, 1); the others the LDS address of the face's row of the colour table, so that the colour of a
+// pixel is one multiply-add away from its material.
+struct FaceRows {
+    int base, stride;
+    __device__ __forceinline__ int of(int code) const { return base + code * stride; }
+};
 
 // Constants of one scan class of one camera.  A class is (dominant horizontal axis, direction along it,
 // direction along the other horizontal axis, vertical direction): class = 8*(y dominant) + 4*(u negative) +
@@ -668,8 +695,8 @@ struct alignas(16) ScanClass {
     float uexit;        // U - Pu: distance to the far side of the grid along u (window scan: to the first u plane)
     float Pu_err;       // what rounding took from the mirrored coordinate: (U - P) - Pu exactly, 0 if not mirrored
     int   addr0;        // LDS byte address of the camera's row in this class's row array
-    float zero[2];      // 0, 0: where a ray's two crossing counters start (beside two values that are dead by then: the
-                        // counters keep the registers they were loaded into)
+    float row_step_v;   // the row-address steps per v and z crossing as floats whose bits are the number of bytes (denormals;
+    float row_step_z;   // a sign bit for steps back): see the row loop
     float dist_v;       // distance from the camera to the first v plane in this direction (>= 0)
     float nv_max;       // v planes between the camera cell and the grid boundary in this direction
                         // (the z counterparts of these two depend on the image row: RowRecord holds them)
@@ -683,9 +710,9 @@ struct alignas(16) ScanClass {
     float stride_z;     // voxel-index step per z crossing: +-X*Y
     int   sv;           // row-address step per v crossing: +-8 bytes
     int   sz;           // row-address step per z crossing: +-8*V bytes
-    int   face_u;       // face code of a voxel found while scanning along the row
-    int   face_v;       // face code of a voxel entered through a v crossing
-    int   face_z;       // face code of a voxel entered through a z crossing
+    int   face_u;       // face (see FaceRows) of a voxel found while scanning along the row
+    int   face_v;       // of a voxel entered through a v crossing
+    int   face_z;       // of a voxel entered through a z crossing
     int   pad;
 };
 static_assert(sizeof(ScanClass) == 80, "scan class record must be 80 bytes");
@@ -835,7 +862,7 @@ __device__ __forceinline__ int ctz64_nonzero(uint64_t v)
     asm("v_ffbl_b32 %0, %1" : "=v"(flo) : "v"(lo));
     asm("v_ffbl_b32 %0, %1" : "=v"(fhi) : "v"(hi));
     // v_ffbl_b32 returns 0xffffffff for 0, so the unsigned minimum picks the low word whenever it has a bit
-    return (int)min(flo, 32u + fhi);
+    return (int)min(flo, __float_as_uint(tiny_int(fhi) + tiny_int(32u)));      // (0xffffffff + 32 stays a NaN: all ones or nearly)
 }
 
 // v & 1 as a 32-bit operation of its own (the compiler otherwise widens the test back to the 64-bit row)
@@ -846,17 +873,12 @@ __device__ __forceinline__ uint32_t low_bit(uint32_t v)
     return b;
 }
 
+typedef __attribute__((address_space(3))) const uint32_t* lds_u32_ptr;
 typedef __attribute__((address_space(3))) const uint64_t* lds_u64_ptr;
 typedef __attribute__((address_space(3))) const u32x4* lds_u32x4_ptr;
 
-// a*b + c on the 24-bit multiplier (full rate); every product on this path fits 24 x 24 bits.
-// mad24s takes the multiplier b from a scalar register (a wave-uniform value such as a grid dimension).
-__device__ __forceinline__ int mad24(int a, int b, int c)
-{
-    int r;
-    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
+// a*b + c on the 24-bit multiplier, the multiplier b from a scalar register (a wave-uniform value such as a grid dimension);
+// every product on this path fits 24 x 24 bits.
 __device__ __forceinline__ int mad24s(int a, int b_uniform, int c)
 {
     int r;
@@ -866,6 +888,7 @@ __device__ __forceinline__ int mad24s(int a, int b_uniform, int c)
 
 // A camera outside the grid, for the tracers below: its rays start where they enter the box [0,X]x[0,Y]x[0,top].
 struct OutsideCamera {
+    FaceRows faces;
     float P[3];
     float dz;           // vertical component of the ray
     int X, Y, top;      // top: layers that may hold a solid voxel, at least 1
@@ -906,7 +929,7 @@ __device__ __forceinline__ BoxEntry enter_box(const OutsideCamera& o, float dx, 
     e.t = fmaxf(t_near, 0.0f);
     if (!(t_near > 0.0f)) axis = -1;
     const float d_axis = axis == 0 ? dx : (axis == 1 ? dy : o.dz);
-    e.face = axis < 0 ? 6 : 2 * axis + (d_axis > 0.0f ? 0 : 1);
+    e.face = o.faces.of(axis < 0 ? 6 : 2 * axis + (d_axis > 0.0f ? 0 : 1));
     auto along = [&](int a, float da, float pa, float ra, int n, int& cell, float& first, float& left) {
         const bool neg = da < 0.0f;
         int c = (int)fminf(fmaxf(floorf(fmaf(e.t, da, pa)), 0.0f), (float)(n - 1));
@@ -958,22 +981,25 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     // class = 8*(y dominant) + 4*(u negative) + 2*(v negative) + (z negative): each funnel shift moves the
     // index up one bit and brings in the sign bit of the next component.  Along v and z a component
     // of -0 counts as positive (the ray never crosses a plane of that axis, and the distance to the
-    // upper plane is never 0 inside the cell): adding +0 turns -0 into +0 and changes nothing else.
+    // upper plane is never 0 inside the cell): adding the smallest normal number makes it positive and changes no other.
     uint32_t q = xm ? 0u : 1u;
     q = __builtin_amdgcn_alignbit(q, __float_as_uint(du), 31);
-    q = __builtin_amdgcn_alignbit(q, __float_as_uint(dv + 0.0f), 31);
+    const float dv_ = dv + kSmallest;
+    q = __builtin_amdgcn_alignbit(q, __float_as_uint(dv_), 31);
     q = __builtin_amdgcn_alignbit(q, __float_as_uint(rr.rcp_z), 31);        // the sign of 1/d_z is the sign of d_z
-    const uint32_t qoff = q * (uint32_t)kClassStride;
+    const uint32_t record = __float_as_uint(tiny_int(q) * (float)kClassStride + tiny_int(classes_addr));
     ScanClass c;
     {
-        lds_u32x4_ptr rec = (lds_u32x4_ptr)(uintptr_t)(classes_addr + qoff);
+        lds_u32x4_ptr rec = (lds_u32x4_ptr)(uintptr_t)record;
         u32x4* dst = reinterpret_cast<u32x4*>(&c);
         dst[0] = rec[0]; dst[1] = rec[1]; dst[2] = rec[2]; dst[3] = rec[3]; dst[4] = rec[4];
     }
 
+    // 1 / d of a component that may be 0: adding the smallest normal number changes no other component and keeps the
+    // reciprocal finite (8.5e37), for -0 as for +0 on the positive side
     const float dua = fabsf(du);
-    const float inv_u = safe_rcp(dua);
-    const float rcp_v = safe_rcp(dv), rcp_z = rr.rcp_z;
+    const float inv_u = __builtin_amdgcn_rcpf(fabsf(du + kSmallest));
+    const float rcp_v = kOutside ? safe_rcp(dv) : __builtin_amdgcn_rcpf(dv_), rcp_z = rr.rcp_z;      // (as enter_box has it)
     const float dt_v = fabsf(rcp_v), dt_z = fabsf(rcp_z);
     // first crossing on an axis: the distance to the first plane in the ray's direction times |1/d| (along z: from
     // the image row's record, see RowRecord)
@@ -1000,7 +1026,7 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     // crossings made so far along v and z (without sign; the directions sit in the class), and the parameters
     // of the next ones: t_v = n_v*dt_v + t0_v, t_z likewise
     // (the counters start from the two zero words of the record: registers the load has filled anyway)
-    float t_v, t_z, n_v = c.zero[0], n_z = c.zero[1];
+    float t_v, t_z, n_v = 0.0f, n_z = 0.0f;
     uint32_t addr = (uint32_t)c.addr0;
     uint64_t r, in_range;
     int i_last;
@@ -1025,7 +1051,7 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
         // state they would arrive in); otherwise it takes one ordinary turn.  Every decision uses the same
         // crossing parameters as the ordinary scan: the result is the same bit for bit.
         PairClass pc;
-        *reinterpret_cast<u32x4*>(&pc) = *(lds_u32x4_ptr)(uintptr_t)(classes_addr + qoff + (uint32_t)sizeof(ScanClass));
+        *reinterpret_cast<u32x4*>(&pc) = *(lds_u32x4_ptr)(uintptr_t)(record + (uint32_t)sizeof(ScanClass));
         t_v = t0_v; t_z = t0_z;
         uint32_t addr_p = (uint32_t)pc.addr0;
         int inner = pc.inner0;                  // the next v plane lies inside the current pair
@@ -1093,112 +1119,122 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     // on lane masks (two breaks per trip); written out, a turn needs one, the branch: the two comparisons that
     // decide whether a lane goes on write the execution mask themselves.  Lanes that are done simply leave
     // the execution mask (it only ever shrinks; restored after the loop), so every register of a finished lane
-    // keeps the values of its last turn.  The cell index alternates between i_a and i_b from turn to turn; a
-    // turn that writes i_a copies it to i_b, so that i_b holds the last cell of a lane whichever turn it left in.
-    // The first turn is peeled: it reads the first crossings straight from t0_v / t0_z and starts the crossing
-    // counters instead of incrementing them; the loop proper holds four turns per backward branch.  The v-or-z
-    // decision of a turn is taken at its top (VCC), well ahead of the selects that read it (a vector instruction may
-    // not read a lane mask within two instructions of the one that wrote it).  Every kind of instruction costs this
-    // kernel about the same issue time, so what counts is how many there are (measured: the mask-writing
-    // comparisons and the longer unrolling together -1.3 %).
+    // keeps the values of its last turn.  The cell index alternates between i_a and i_b from turn to turn; the later cell
+    // of a finished lane is the larger of the two.
+    // The v-or-z decision of a turn is taken at its top (VCC), well ahead of the select that reads it (a vector instruction
+    // may not read a lane mask within two instructions of the one that wrote it).
+    // What bounds the loop is the issue of comparisons, selects, conversions and shifts, of which other waves' float adds and
+    // multiply-adds run beside (see tiny_int); so the counters and the row address are float arithmetic with one select per
+    // turn (two and an integer add before; 4096 x 2 of 40x40x16: step 304 -> 301 us, 2048 x 4 of 64x64x32 1085 -> 1074): the
+    // row address as a number of bytes in a denormal, and for the first 13 turns, written out one by one, the z crossings as
+    // the turns that are not v crossings.  A multiply-add whose three vector registers all have even or all odd numbers
+    // takes twice the time: the temporaries and counters have registers of their own (v48 to v53) that rule it out.
     {
         uint64_t exec_save, m_go, m_empty;
-        float t_out, tmp;
         int sh;
+        float inc;
         // the run of cells [IFROM, ITO] of the current row: ITO from the parameter at which the ray leaves the row
         // (TOUT, NARROW: capped at the grid exit; else the cell is clamped to U - 1), then the two shifts
-#define MV_ASM_TEST(TV, TZ, IFROM, ITO, TOUT_AND_CELL, WAIT)                            \
+#define MV_ASM_TEST(TV, TZ, IFROM, ITO, CELL, WAIT)                                     \
             "v_cmp_le_f32_e32 vcc, " TV ", " TZ "\n\t"                                   \
-            TOUT_AND_CELL(TV, TZ, ITO)                                                   \
+            CELL(TV, TZ, ITO)                                                           \
             WAIT                                                                        \
             "v_lshrrev_b64 %[r], " IFROM ", %[row]\n\t"                                 \
             "v_xad_u32 %[sh], " ITO ", -1, " IFROM "\n\t"                               \
             "v_lshlrev_b64 %[inr], %[sh], %[r]\n\t"
 #define MV_ASM_CELL_NARROW(TV, TZ, ITO)                                                 \
-            "v_min3_f32 %[tout], " TV ", " TZ ", %[tend]\n\t"                            \
-            "v_fma_f32 %[tmp], %[tout], |%[du]|, %[pu]\n\t"                             \
-            "v_cvt_i32_f32_e32 " ITO ", %[tmp]\n\t"
+            "v_min3_f32 v51, " TV ", " TZ ", %[tend]\n\t"                                \
+            "v_fma_f32 v53, v51, |%[du]|, %[pu]\n\t"                                    \
+            "v_cvt_i32_f32_e32 " ITO ", v53\n\t"
 #define MV_ASM_CELL_WIDE(TV, TZ, ITO)                                                   \
-            "v_min_f32_e32 %[tout], " TV ", " TZ "\n\t"                                  \
-            "v_fma_f32 %[tmp], %[tout], |%[du]|, %[pu]\n\t"                             \
-            "v_cvt_i32_f32_e32 %[tmp], %[tmp]\n\t"                                      \
-            "v_min_i32_e32 " ITO ", %[tmp], %[um1]\n\t"
+            "v_min_f32_e32 v51, " TV ", " TZ "\n\t"                                      \
+            "v_fma_f32 v53, v51, |%[du]|, %[pu]\n\t"                                    \
+            "v_cvt_i32_f32_e32 v53, v53\n\t"                                            \
+            "v_min_i32_e32 " ITO ", v53, %[um1]\n\t"
         // lanes that found a solid cell leave first (their in_range stays non-zero), then the lanes whose ray leaves
         // the grid in this row (theirs is zero): each comparison writes the execution mask itself
 #define MV_ASM_LEAVE                                                                    \
             "v_cmpx_eq_u64_e64 %[mempty], 0, %[inr]\n\t"                                \
-            "v_cmpx_lt_f32_e64 %[mgo], %[tout], %[tend]\n\t"                            \
+            "v_cmpx_lt_f32_e64 %[mgo], v51, %[tend]\n\t"                                \
             "s_cbranch_execz 2f\n\t"
 #define MV_ASM_NEXT_ROW                                                                 \
-            "v_cndmask_b32_e32 %[tmp], %[sz], %[sv], vcc\n\t"                           \
-            "v_add_u32_e32 %[addr], %[addr], %[tmp]\n\t"                                \
-            "ds_read_b64 %[row], %[addr]\n\t"
+            "v_fma_f32 v53, %[nz], %[szd], %[base]\n\t"                                 \
+            "v_fma_f32 %[addr], %[nv], %[svd], v53\n\t"                                 \
+            "ds_read_b64 %[row], %[addr]\n\t"                                           \
+            "v_fma_f32 %[tv], %[nv], |%[rv]|, %[t0v]\n\t"                               \
+            "v_fma_f32 %[tz], %[nz], |%[rz]|, %[t0z]\n\t"
 #define MV_ASM_FIRST_ADVANCE                                                            \
-            MV_ASM_NEXT_ROW                                                             \
             "v_cndmask_b32_e64 %[nv], 0, 1.0, vcc\n\t"                                  \
             "v_sub_f32_e32 %[nz], 1.0, %[nv]\n\t"                                       \
-            "v_fma_f32 %[tv], %[nv], |%[rv]|, %[t0v]\n\t"                               \
-            "v_fma_f32 %[tz], %[nz], |%[rz]|, %[t0z]\n\t"
-#define MV_ASM_ADVANCE                                                                  \
-            MV_ASM_NEXT_ROW                                                             \
-            "v_cndmask_b32_e64 %[tmp], 0, 1.0, vcc\n\t"                                 \
-            "v_add_f32_e32 %[nv], %[nv], %[tmp]\n\t"                                    \
-            "v_sub_f32_e32 %[tmp], 1.0, %[tmp]\n\t"                                     \
-            "v_add_f32_e32 %[nz], %[nz], %[tmp]\n\t"                                    \
-            "v_fma_f32 %[tv], %[nv], |%[rv]|, %[t0v]\n\t"                               \
-            "v_fma_f32 %[tz], %[nz], |%[rz]|, %[t0z]\n\t"
+            MV_ASM_NEXT_ROW
+        // (after N turns the crossings along v and z add up to N)
+#define MV_ASM_ADVANCE(N)                                                               \
+            "v_cndmask_b32_e64 %[inc], 0, 1.0, vcc\n\t"                                 \
+            "v_add_f32_e32 %[nv], %[nv], %[inc]\n\t"                                    \
+            "v_sub_f32_e32 %[nz], " N ", %[nv]\n\t"                                     \
+            MV_ASM_NEXT_ROW
+#define MV_ASM_ADVANCE_ANY                                                              \
+            "v_cndmask_b32_e64 %[inc], 0, 1.0, vcc\n\t"                                 \
+            "v_add_f32_e32 %[nv], %[nv], %[inc]\n\t"                                    \
+            "v_sub_f32_e32 %[inc], 1.0, %[inc]\n\t"                                     \
+            "v_add_f32_e32 %[nz], %[nz], %[inc]\n\t"                                    \
+            MV_ASM_NEXT_ROW
 #define MV_ASM_WAIT "s_waitcnt lgkmcnt(0)\n\t"
-#define MV_ASM_TURN_TO_A(CELL)                                                          \
-            MV_ASM_TEST("%[tv]", "%[tz]", "%[ib]", "%[ia]", CELL, MV_ASM_WAIT)           \
-            "v_mov_b32_e32 %[ib], %[ia]\n\t"                                            \
-            MV_ASM_LEAVE                                                                \
-            MV_ASM_ADVANCE
-#define MV_ASM_TURN_TO_B(CELL)                                                          \
-            MV_ASM_TEST("%[tv]", "%[tz]", "%[ia]", "%[ib]", CELL, MV_ASM_WAIT)           \
-            MV_ASM_LEAVE                                                                \
-            MV_ASM_ADVANCE
+#define MV_ASM_TO_A(CELL) MV_ASM_TEST("%[tv]", "%[tz]", "%[ib]", "%[ia]", CELL, MV_ASM_WAIT) MV_ASM_LEAVE
+#define MV_ASM_TO_B(CELL) MV_ASM_TEST("%[tv]", "%[tz]", "%[ia]", "%[ib]", CELL, MV_ASM_WAIT) MV_ASM_LEAVE
+#define MV_ASM_TWO(CELL, M, N) MV_ASM_TO_A(CELL) MV_ASM_ADVANCE(M) MV_ASM_TO_B(CELL) MV_ASM_ADVANCE(N)
         // (the first row has arrived when the statement starts: it is one of its inputs)
 #define MV_ASM_LOOP(CELL)                                                               \
             "s_mov_b64 %[save], exec\n\t"                                               \
+            "v_mov_b32_e32 %[nv], 0\n\t"                                                \
+            "v_mov_b32_e32 %[nz], 0\n\t"                                                \
             MV_ASM_TEST("%[t0v]", "%[t0z]", "%[ia]", "%[ib]", CELL, "")                  \
             MV_ASM_LEAVE                                                                \
             MV_ASM_FIRST_ADVANCE                                                        \
+            MV_ASM_TWO(CELL, "2.0", "0x40400000")                                       \
+            MV_ASM_TWO(CELL, "4.0", "0x40a00000")                                       \
+            MV_ASM_TWO(CELL, "0x40c00000", "0x40e00000")                                \
+            MV_ASM_TWO(CELL, "0x41000000", "0x41100000")                                \
+            MV_ASM_TWO(CELL, "0x41200000", "0x41300000")                                \
+            MV_ASM_TWO(CELL, "0x41400000", "0x41500000")                                \
             "1:\n\t"                                                                    \
-            MV_ASM_TURN_TO_A(CELL)                                                      \
-            MV_ASM_TURN_TO_B(CELL)                                                      \
-            MV_ASM_TURN_TO_A(CELL)                                                      \
-            MV_ASM_TURN_TO_B(CELL)                                                      \
+            MV_ASM_TO_A(CELL) MV_ASM_ADVANCE_ANY                                        \
+            MV_ASM_TO_B(CELL) MV_ASM_ADVANCE_ANY                                        \
             "s_branch 1b\n"                                                             \
             "2:\n\t"                                                                    \
             "s_mov_b64 exec, %[save]\n\t"
 #define MV_ASM_OPERANDS                                                                                              \
-                : [save] "=&s"(exec_save), [mgo] "=&s"(m_go), [mempty] "=&s"(m_empty), [tout] "=&v"(t_out),            \
-                  [tmp] "=&v"(tmp), [sh] "=&v"(sh), [r] "=&v"(r), [inr] "=&v"(in_range), [ib] "=&v"(i_b),             \
-                  [tv] "=&v"(t_v), [tz] "=&v"(t_z), [ia] "+v"(i_a), [row] "+v"(row), [addr] "+v"(addr),               \
-                  [nv] "+v"(n_v), [nz] "+v"(n_z)                                                                      \
-                : [tend] "v"(t_end), [du] "v"(du), [pu] "v"(c.Pu), [sv] "v"(c.sv), [sz] "v"(c.sz), [rv] "v"(rcp_v),  \
-                  [rz] "v"(rcp_z), [t0v] "v"(t0_v), [t0z] "v"(t0_z), [um1] "v"(c.um1)                                 \
-                : "vcc", "scc", "memory"
+                : [save] "=&s"(exec_save), [mgo] "=&s"(m_go), [mempty] "=&s"(m_empty),                                \
+                  [inc] "=&v"(inc), [sh] "=&v"(sh), [r] "=&v"(r), [inr] "=&v"(in_range), [ib] "=&v"(i_b),             \
+                  [tv] "=&v"(t_v), [tz] "=&v"(t_z), [ia] "+v"(i_a), [row] "+v"(row), [addr] "=&v"(addr),              \
+                  [nv] "=&{v49}"(n_v), [nz] "=&{v48}"(n_z)                                                            \
+                : [tend] "v"(t_end), [du] "v"(du), [pu] "v"(c.Pu), [svd] "v"(c.row_step_v), [szd] "v"(c.row_step_z),  \
+                  [base] "v"(c.addr0), [rv] "v"(rcp_v),                                                               \
+                  [rz] "v"(rcp_z), [t0v] "{v50}"(t0_v), [t0z] "v"(t0_z), [um1] "v"(c.um1)                             \
+                : "vcc", "scc", "memory", "v51", "v53"
         if (kNarrow) asm volatile(MV_ASM_LOOP(MV_ASM_CELL_NARROW) MV_ASM_OPERANDS);
         else         asm volatile(MV_ASM_LOOP(MV_ASM_CELL_WIDE) MV_ASM_OPERANDS);
 #undef MV_ASM_OPERANDS
 #undef MV_ASM_LOOP
+#undef MV_ASM_TWO
+#undef MV_ASM_ADVANCE_ANY
 #undef MV_ASM_ADVANCE
 #undef MV_ASM_FIRST_ADVANCE
 #undef MV_ASM_NEXT_ROW
 #undef MV_ASM_WAIT
-#undef MV_ASM_TURN_TO_A
-#undef MV_ASM_TURN_TO_B
+#undef MV_ASM_TO_A
+#undef MV_ASM_TO_B
 #undef MV_ASM_LEAVE
 #undef MV_ASM_CELL_WIDE
 #undef MV_ASM_CELL_NARROW
 #undef MV_ASM_TEST
-        i_last = i_b;
+        i_last = max(i_a, i_b);
     }
     const bool found = in_range != 0;
 
     // in_range is r moved up so that cell i_last sits at bit 63: its lowest set bit p is cell i_last - (63 - p)
-    const int iu = i_last - 63 + ctz64_nonzero(in_range);                        // mirrored cell along u
+    // mirrored cell along u
+    const float iu_f = tiny_to_float(tiny_int((uint32_t)i_last) + tiny_int((uint32_t)ctz64_nonzero(in_range))) - 63.0f;
     const bool along_row = low_bit((uint32_t)r) == 0u;                          // not the row's entry cell
     // the row was entered at the later of the last v crossing and the last z crossing (n-1; for n = 0
     // the expression is <= 0 because the first plane is at most one cell away).  Recomputed with one
@@ -1213,7 +1249,6 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     const float t_in = vmax3(tv_last, tz_last, 0.0f);
     // distance along u to the near face of the hit cell: the mirrored camera coordinate was rounded once,
     // which matters when the camera almost touches that face; its exact rounding error comes with the class
-    const float iu_f = (float)iu;
     const float t_u = ((iu_f - c.Pu) - c.Pu_err) * inv_u;
     const int face_vz = via_z ? c.face_z : c.face_v;
     int face = along_row ? c.face_u : face_vz;
@@ -1226,15 +1261,15 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     }
     // voxel index: the class record holds the index of (mirrored cell 0, camera's v cell, camera's layer)
     // and the signed index steps per cell along u and per crossing along v and z
-    const int idx = (int)fmaf(n_z, c.stride_z, fmaf(n_v, c.stride_v, fmaf(iu_f, c.stride_u, c.idx0)));
+    const float idx_f = fmaf(n_z, c.stride_z, fmaf(n_v, c.stride_v, fmaf(iu_f, c.stride_u, c.idx0)));
     Hit h;
-    h.idx = found ? idx : -1;       // face and t are only meaningful for idx >= 0; the caller substitutes the miss values
+    // face and t are only meaningful for idx >= 0 (-1.0f becomes a negative number other than -1); the caller substitutes the
+    // miss values
+    h.idx = __float_as_int(float_to_tiny(found ? idx_f : -1.0f));
     h.face = face;
     h.t = t;
     return h;
 }
-
-typedef __attribute__((address_space(3))) const uint32_t* lds_u32_ptr;
 
 // Row scan for grids of any width: the traversal of trace_rows, but a row is looked at through a window of 32 cells that
 // starts wherever the ray is (two dwords of the row and one funnel shift); a run of more than 32 cells takes several
@@ -1345,6 +1380,16 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
     return Hit{ found ? idx : -1, face, t };
 }
 
+// one dword or byte per lane at a scalar address plus a 32-bit offset of the lane
+__device__ __forceinline__ void store_dword(uint32_t lane_offset, uint32_t v, const void* at)
+{
+    asm volatile("global_store_dword %0, %1, %2" :: "v"(lane_offset), "v"(v), "s"(at) : "memory");
+}
+__device__ __forceinline__ void store_byte(uint32_t lane_offset, uint32_t v, const void* at)
+{
+    asm volatile("global_store_byte %0, %1, %2" :: "v"(lane_offset), "v"(v), "s"(at) : "memory");
+}
+
 // colour of lane+1 within each group of four lanes (lane 3 of the group keeps its own): DPP
 // quad_perm [1,2,3,3]
 __device__ __forceinline__ uint32_t next_in_quad(uint32_t v)
@@ -1418,6 +1463,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     float* lds_sx = reinterpret_cast<float*>(lds + off_scalars);
     RowRecord* lds_rowrec = reinterpret_cast<RowRecord*>(lds + off_rowrec);
     uint64_t* lds_rows = reinterpret_cast<uint64_t*>(lds + off_rows);
+
+    const FaceRows faces = AUX ? FaceRows{ 0, 1 } : FaceRows{ (int)(lds_base + off_lut), 4 * p.materials_plus_one };
 
     // the camera: uniform for the whole workgroup, read once
     const CameraRecord* __restrict__ recp = p.rec + obs;
@@ -1598,7 +1645,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         // first plane along v: the upper plane of the camera's cell for rising v, the lower one otherwise
         c.dist_v = fabsf((float)(vneg ? j0 : j0 + 1) - pv);
         c.nv_max = (float)(vneg ? j0 : V - 1 - j0);
-        c.zero[0] = c.zero[1] = 0.0f;
         const uint32_t array_off = off_rows + 8u * (uint32_t)(FAST ? (xmaj ? (neg ? sxw : 0) : 2 * sxw + (neg ? syw : 0))
                                                                    : (xmaj ? 0 : sxw));
         const int row_bytes = 8 * (xmaj ? wx : wy);
@@ -1607,10 +1653,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         c.addr0 = (int)(lds_base + array_off) + row_bytes * (k_row * V + j_row);
         c.sv = vneg ? -row_bytes : row_bytes;
         c.sz = zneg ? -row_bytes * V : row_bytes * V;
+        c.row_step_v = copysignf(__uint_as_float((uint32_t)row_bytes), vneg ? -1.0f : 1.0f);
+        c.row_step_z = copysignf(__uint_as_float((uint32_t)(row_bytes * V)), zneg ? -1.0f : 1.0f);
         c.um1 = U - 1;
-        c.face_u = 2 * (xmaj ? 0 : 1) + (neg ? 1 : 0);
-        c.face_v = 2 * (xmaj ? 1 : 0) + (vneg ? 1 : 0);
-        c.face_z = zneg ? 5 : 4;
+        c.face_u = faces.of(2 * (xmaj ? 0 : 1) + (neg ? 1 : 0));
+        c.face_v = faces.of(2 * (xmaj ? 1 : 0) + (vneg ? 1 : 0));
+        c.face_z = faces.of(zneg ? 5 : 4);
         const int su = xmaj ? 1 : X;                       // voxel-index step per original u cell
         const int sv_idx = xmaj ? X : 1;                   // and per v cell
         c.stride_u = (float)(neg ? -su : su);
@@ -1682,45 +1730,50 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     int32_t* __restrict__ auxh_obs = AUX && p.aux_hit ? p.aux_hit + obs_pix : nullptr;
     uint8_t* __restrict__ auxf_obs = AUX && p.aux_face ? p.aux_face + obs_pix : nullptr;
     const uint8_t* __restrict__ vox_env = p.vox + (size_t)env * p.voxels_per_env;
-    const uint32_t* lut_lds = reinterpret_cast<const uint32_t*>(lds + off_lut);
     const uint32_t last_voxel = (uint32_t)p.voxels_per_env - 1u;
     const int last_material = p.materials_plus_one - 1;
 
     // a6 + a7 of a finished tile: material -> colour, then the stores.
-    // (PACKED launches without auxiliary outputs: `pix` is the wave-uniform pixel offset of the tile, and the two
-    // store offsets are a per-lane constant plus a scalar multiple of it)
+    // Branch-free: lanes that found nothing look up a valid entry as well and then take the miss values.
+    // (PACKED launches: `pix` is the wave-uniform pixel offset of the tile; the addresses of the stores are scalar, with a
+    // per-lane constant.  The store instructions are written out: the compiler adds the tile's offset per lane, in 64 bits)
     const uint32_t lane_depth_off = 4u * (uint32_t)lane_pix, lane_rgb_off = 3u * (uint32_t)lane_pix + (uint32_t)quad;
-    auto shade_and_store = [&](int idx, int hit_face, float t, int material, uint32_t pix, bool active, auto trusted_face) {
-        // branch-free: lanes that found nothing look up a valid entry as well and then take the miss values
+    // constants in vector registers (see tiny_int) where there are registers left for them
+    constexpr bool kVectors = FAST && PACKED && !AUX;
+    const uint64_t three_of_four = 0x7777777777777777ull;
+    // four consecutive lanes hold four consecutive pixels of one row = 12 bytes = three aligned dwords, written by the first
+    // three lanes of the quad: dword m holds the upper 3-m bytes of pixel m and the lower m+1 bytes of pixel m+1, one byte
+    // permutation of the two (byte selectors 0..2: own pixel, 4..6: the next one)
+    const uint32_t word_bytes = quad == 0 ? 0x04020100u : (quad == 1 ? 0x05040201u : 0x06050402u);
+    const uint32_t sky = kVectors ? __float_as_uint(in_vector(__uint_as_float(p.sky_packed))) : p.sky_packed;
+    auto shade_and_store = [&](int idx, int face, float t, uint32_t material, uint32_t pix, bool active) {
         const bool hit = idx >= 0;
-        // (the row scan takes its face codes from the scan-class records: nothing to clamp)
-        const int face_row = decltype(trusted_face)::value ? hit_face : min(hit_face, kNumFaces - 1);
-        const uint32_t shaded = lut_lds[mad24s(face_row, p.materials_plus_one, min(material, last_material))];
-        const uint32_t colour = hit ? shaded : p.sky_packed;
+        asm volatile("" : "+v"(material));          // (a whole register, not its low byte: no sub-dword operand below)
+        material = min(material, (uint32_t)last_material);
+        uint32_t shaded;
+        if (AUX) {
+            const float row = fmaf(tiny_int((uint32_t)face), (float)(4 * p.materials_plus_one), tiny_int(lds_base + off_lut));
+            shaded = *(lds_u32_ptr)(uintptr_t)__float_as_uint(fmaf(tiny_int(material), 4.0f, row));
+        } else shaded = *(lds_u32_ptr)(uintptr_t)__float_as_uint(fmaf(tiny_int(material), 4.0f, tiny_int((uint32_t)face)));
+        asm volatile("" : "+v"(shaded));            // (read for every lane: a select costs less than a branch around the read)
+        const uint32_t colour = hit ? shaded : sky;
         const float depth = hit ? t : 0.0f;
-        const int face = hit ? hit_face : 255;
-        material = hit ? material : 0;
-        if (PACKED && !AUX) {
-            *reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(depth_obs) + (lane_depth_off + 4u * pix)) = depth;
+        if (PACKED) {
+            store_dword(lane_depth_off, __float_as_uint(depth), reinterpret_cast<const uint8_t*>(depth_obs) + 4u * pix);
+            if (AUX && auxm_obs) store_byte((uint32_t)lane_pix, hit ? material : 0u, auxm_obs + pix);
+            if (AUX && auxh_obs) store_dword(lane_depth_off, (uint32_t)max(idx, -1), reinterpret_cast<const uint8_t*>(auxh_obs) + 4u * pix);
+            if (AUX && auxf_obs) store_byte((uint32_t)lane_pix, (uint32_t)(hit ? face : 255), auxf_obs + pix);
+            const uint32_t word = __builtin_amdgcn_perm(next_in_quad(colour), colour, word_bytes);
+            // (all lanes of a wave are in the tile loop: the mask is set and reset without being read)
+            asm volatile("s_mov_b64 exec, %0\n\tglobal_store_dword %1, %2, %3\n\ts_mov_b64 exec, -1"
+                         :: "s"(three_of_four), "v"(lane_rgb_off), "v"(word), "s"(rgb_obs + 3u * pix) : "memory");
         } else if (active) {
             depth_obs[pix] = depth;
             if (AUX) {
-                if (auxm_obs) auxm_obs[pix] = (uint8_t)material;
-                if (auxh_obs) auxh_obs[pix] = idx;
-                if (auxf_obs) auxf_obs[pix] = (uint8_t)face;
+                if (auxm_obs) auxm_obs[pix] = (uint8_t)(hit ? material : 0u);
+                if (auxh_obs) auxh_obs[pix] = max(idx, -1);
+                if (auxf_obs) auxf_obs[pix] = (uint8_t)(hit ? face : 255);
             }
-        }
-        if (PACKED) {
-            // four consecutive lanes hold four consecutive pixels of one row = 12 bytes = three aligned
-            // dwords, written by the first three lanes of the quad: dword m holds the upper 4-m bytes'
-            // worth of pixel m and the lower m+1 bytes of pixel m+1.
-            const uint32_t next = next_in_quad(colour);
-            const uint32_t word = (colour >> (8 * quad)) | (next << (24 - 8 * quad));
-            if (quad < 3) {
-                if (!AUX) *reinterpret_cast<uint32_t*>(rgb_obs + (lane_rgb_off + 3u * pix)) = word;
-                else *reinterpret_cast<uint32_t*>(rgb_obs + (3u * pix + (uint32_t)quad)) = word;
-            }
-        } else if (active) {
             uint8_t* out = rgb_obs + 3u * pix;
             out[0] = (uint8_t)colour;
             out[1] = (uint8_t)(colour >> 8);
@@ -1758,18 +1811,24 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             inside = __builtin_amdgcn_readfirstlane(again->place) == kPlaceInGrid;
         }
         constexpr bool kNarrow = decltype(narrow_tag)::value;
-        int pend_idx = -1, pend_face = 255;
+        int pend_idx = -1, pend_face = faces.base;
         float pend_t = 0.0f;
         uint32_t pend_pix = 0;
         bool pend_active = false, pending = false;
+        // (in vector registers: see tiny_int)
+        const float vFx = kVectors ? in_vector(Fx) : Fx, vFy = kVectors ? in_vector(Fy) : Fy, vRx = kVectors ? in_vector(Rx) : Rx, vRy = kVectors ? in_vector(Ry) : Ry,
+                    vUx = kVectors ? in_vector(Ux) : Ux, vUy = kVectors ? in_vector(Uy) : Uy;
         // tile coordinates are carried along instead of divided out of the tile index every trip
         int ty = (int)p.by_tiles_x.quotient((uint32_t)(tile_begin + wave)), tx = (tile_begin + wave) - ty * p.tiles_x - waves;
+        uint32_t tile_pix = (uint32_t)(ty * kTileH * p.W + tx * kTileW);
+        const uint32_t pix_step = (uint32_t)(waves * kTileW), pix_wrap = (uint32_t)(kTileH * p.W - p.tiles_x * kTileW);
         for (int tile = tile_begin + wave; tile < tile_end; tile += waves) {
             // lanes without a hit (idx -1 = 0xffffffff) read the last voxel and drop it later: no branch
-            const uint8_t pend_material = vox_env[min((uint32_t)pend_idx, last_voxel)];
+            const uint32_t pend_material = vox_env[min((uint32_t)pend_idx, last_voxel)];
 
             tx += waves;
-            while (tx >= p.tiles_x) { tx -= p.tiles_x; ++ty; }
+            tile_pix += pix_step;
+            while (tx >= p.tiles_x) { tx -= p.tiles_x; ++ty; tile_pix += pix_wrap; }
             // PACKED launches have W and H multiples of the tile size: every lane owns a pixel, and its
             // addresses are a per-lane constant plus a per-tile (wave-uniform) offset
             bool active = true;
@@ -1779,7 +1838,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             if (PACKED) {
                 sx = sx_lane[tx * kTileW];
                 rr = rowrec_lane[ty * kTileH];
-                pix = AUX ? (uint32_t)(lane_pix + ty * kTileH * p.W + tx * kTileW) : (uint32_t)(ty * kTileH * p.W + tx * kTileW);
+                pix = tile_pix;
             } else {
                 const int col = tx * kTileW + lx, row = ty * kTileH + ly;
                 active = col < p.W && row < p.H;
@@ -1792,40 +1851,42 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             // a4: ray through the pixel centre, two fused multiply-adds per axis (the row scan takes what it needs of
             // the vertical component from the row record)
             float d[3];
-            d[0] = fmaf(rr.sy, Ux, fmaf(sx, Rx, Fx));
-            d[1] = fmaf(rr.sy, Uy, fmaf(sx, Ry, Fy));
+            d[0] = fmaf(rr.sy, vUx, fmaf(sx, vRx, vFx));
+            d[1] = fmaf(rr.sy, vUy, fmaf(sx, vRy, vFy));
             if (!kRowsOnly || kOutside) d[2] = fmaf(rr.sy, Ucz, Fcz);
 
             // a5: traversal
             Hit h;
             if constexpr (kOutside) {
-                const OutsideCamera from{ { Pc[0], Pc[1], Pc[2] }, d[2], X, Y, max(top, 1) };
+                const OutsideCamera from{ faces, { Pc[0], Pc[1], Pc[2] }, d[2], X, Y, max(top, 1) };
                 if constexpr (FAST) h = trace_rows<kNarrow, false, true>(lds_base + off_classes, d[0], d[1], rr, -1, &from);
                 else h = trace_windows<true>(lds_base + off_classes, d[0], d[1], rr, &from);
             } else if constexpr (kRowsOnly) {
                 if constexpr (FAST) h = trace_rows<kNarrow, COARSE>(lds_base + off_classes, d[0], d[1], rr, p.coarse_after);
                 else h = trace_windows<false>(lds_base + off_classes, d[0], d[1], rr);
             } else if (use_rows) {
-                h.idx = cam_idx; h.face = 6; h.t = 0.0f;
+                h.idx = cam_idx; h.face = faces.of(6); h.t = 0.0f;
             } else if (scans) {
                 // cameras far outside the grid, and worlds taller than the staged layers: the x rows in global
                 // memory, own body skipped by index
                 h = trace_generic(reinterpret_cast<const uint32_t*>(p.bits + (size_t)env * g.env_words), 2 * g.rowwords_x,
                                   Pc, d, X, Y, Z, inside, p.max_steps, body_lo, body_hi);
+                h.face = faces.of(min(h.face, kNumFaces - 1));
             } else {
                 h = trace_generic(reinterpret_cast<const uint32_t*>(lds_rows), 2 * g.rowwords_x, Pc, d, X, Y, Z,
                                   inside, p.max_steps, -1, -1);
+                h.face = faces.of(min(h.face, kNumFaces - 1));
             }
 
-            if (pending) shade_and_store(pend_idx, pend_face, pend_t, pend_material, pend_pix, pend_active, rows_only_tag);
+            if (pending) shade_and_store(pend_idx, pend_face, pend_t, pend_material, pend_pix, pend_active);
             pend_idx = h.idx; pend_face = h.face; pend_t = h.t;
             pend_pix = pix;
             pend_active = active;
             pending = true;
         }
         if (pending) {
-            const uint8_t pend_material = vox_env[min((uint32_t)pend_idx, last_voxel)];
-            shade_and_store(pend_idx, pend_face, pend_t, pend_material, pend_pix, pend_active, rows_only_tag);
+            const uint32_t pend_material = vox_env[min((uint32_t)pend_idx, last_voxel)];
+            shade_and_store(pend_idx, pend_face, pend_t, pend_material, pend_pix, pend_active);
         }
     };
     __builtin_amdgcn_s_setprio(0);

@@ -778,6 +778,44 @@ def test_rays_that_reach_the_far_end_of_a_row(lib, orc, grid):
     assert (ref.hit_index >= 0).any() and (ref.hit_index < 0).any()
 
 
+@pytest.mark.parametrize("grid,image,aux", [((48, 44, 6), (48, 16), True), ((48, 44, 6), (48, 16), False), ((64, 64, 6), (40, 24), True),
+                                            ((63, 64, 5), (40, 24), False), ((48, 44, 6), (33, 17), False), ((64, 40, 6), (33, 17), True)])
+def test_rays_that_pass_many_rows(lib, orc, grid, image, aux):
+    """The row loop counts its first 13 turns by their number and the rest by adding: rays that pass up to about fifty rows
+    along v and z (diagonal views over an empty floor to solids at the rim), found in every turn and lost in every turn."""
+    X, Y, Z = grid
+    rng = np.random.default_rng(X * 1000 + Y + image[0])
+    N, A, M = 4, 8, 7
+    spec = _mini_spec(N, A, grid, image[0], image[1], M)
+    vox = np.zeros((N, Z, Y, X), np.uint8)
+    vox[:, 0] = np.where(rng.random((N, Y, X)) < 0.3, rng.integers(1, M + 1, (N, Y, X)), 0)
+    for e in range(N):
+        rim = np.ones((Y, X), bool)
+        rim[2:-2, 2:-2] = False
+        fill = rng.random((Z, Y, X)) < (0.5, 0.1, 0.0, 0.9)[e]
+        vox[e] = np.where(fill & rim, rng.integers(1, M + 1, (Z, Y, X)), vox[e])
+    pal = rng.integers(0, 256, (N, M + 1, 3)).astype(np.uint8)
+    cams = np.zeros((N * A, 5), np.float32)
+    for o in range(N * A):
+        corner = o % 4
+        at = (rng.uniform(0.5, 6) if corner & 1 else X - rng.uniform(0.5, 6), rng.uniform(0.5, 6) if corner & 2 else Y - rng.uniform(0.5, 6))
+        cams[o] = (at[0], at[1], rng.uniform(1.2, Z - 0.5), np.arctan2(Y / 2 - at[1], X / 2 - at[0]) + rng.uniform(-0.2, 0.2), rng.uniform(-0.1, 0.02))
+    ob = _oracle_for(orc, spec, vox, pal, cams, hfov_rad=0.9)
+    run = _gpu_for(spec, vox, pal, cams, aux=aux, hfov_rad=0.9)
+    run.render()
+    g, ref = run.numpy(), ob.render()
+    idx = ref.hit_index
+    rows = np.abs(idx // X % Y - cams[:, 1].astype(int).reshape(-1, 1, 1)), np.abs(idx % X - cams[:, 0].astype(int).reshape(-1, 1, 1))
+    passed = np.where(idx >= 0, np.minimum(*rows), 0)
+    assert all((passed == n).any() for n in range(1, 30)), "rays found after every number of crossings"
+    if aux:
+        _pixelwise_rule(g, ref, f"many rows, grid {grid}")
+    else:
+        clear = ref.edge_margin >= parity.EDGE_MARGIN
+        assert (np.abs(g.rgb.astype(int) - ref.rgb.astype(int)).max(axis=-1)[clear] <= 1).all()
+        assert (np.abs(g.depth - ref.depth)[clear] <= 1e-4 * np.abs(ref.depth)[clear]).all()
+
+
 @pytest.mark.parametrize("grid", [(1, 1, 1), (5, 7, 3), (63, 20, 9), (64, 64, 8), (20, 64, 12), (40, 40, 16),
                                   (65, 9, 4), (9, 65, 4), (96, 96, 6), (70, 129, 3), (1, 200, 5)])
 def test_cameras_outside_scan_rows_from_where_rays_enter(lib, orc, grid):
