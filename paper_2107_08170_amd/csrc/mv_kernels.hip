@@ -1206,7 +1206,7 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
 #define MV_ASM_OPERANDS                                                                                              \
                 : [save] "=&s"(exec_save), [mgo] "=&s"(m_go), [mempty] "=&s"(m_empty),                                \
                   [inc] "=&v"(inc), [sh] "=&v"(sh), [r] "=&v"(r), [inr] "=&v"(in_range), [ib] "=&v"(i_b),             \
-                  [tv] "=&v"(t_v), [tz] "=&v"(t_z), [ia] "+v"(i_a), [row] "+v"(row), [addr] "=&v"(addr),              \
+                  [tv] "=&v"(t_v), [tz] "=&v"(t_z), [ia] "+&v"(i_a), [row] "+&v"(row), [addr] "=&v"(addr),              \
                   [nv] "=&{v49}"(n_v), [nz] "=&{v48}"(n_z)                                                            \
                 : [tend] "v"(t_end), [du] "v"(du), [pu] "v"(c.Pu), [svd] "v"(c.row_step_v), [szd] "v"(c.row_step_z),  \
                   [base] "v"(c.addr0), [rv] "v"(rcp_v),                                                               \
@@ -1273,15 +1273,15 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
 
 // Row scan for grids of any width: the traversal of trace_rows, but a row is looked at through a window of 32 cells that
 // starts wherever the ray is (two dwords of the row and one funnel shift); a run of more than 32 cells takes several
-// windows.  There is one copy of the rows for both directions: for a ray that runs towards lower cells the window ends
-// where the ray is and is bit-reversed.  The record's address and index steps are those of rows of several words; `pad`
-// is -1 for mirrored classes, else 0.  Bits of a window beyond the row's ends belong to its neighbours in LDS and never
-// count: runs end at cell U - 1.  Ends for every input as trace_rows does; a window that does not reach the end of the run
-// advances it by 32 cells.  Bound by instruction issue, about five turns per ray instead of one per cell
-// (256 x 2 worlds of 96x96x16 at 128x72, upload + cameras + render: 184 -> 98 us; the correction of a run's last cell took
-// it from 76 to 104 us when it was added, but without it rays through a voxel edge fall on other sides than before).
+// windows.  There is one copy of the rows for both directions: for a ray that runs towards lower cells the window starts
+// where its run ends, and the first cell it meets is the highest one.  The record's address and index steps are those of rows
+// of several words; `pad` is -1 for mirrored classes, else 0.  Bits beyond a row's end belong to its neighbour in LDS and
+// never count: runs end at cell U - 1.  Ends for every input as trace_rows does; a window that does not reach the end of the
+// run advances it by 32 cells.  Bound by instruction issue (256 x 2 worlds of 96x96x16 at 128x72, upload + cameras + render:
+// 184 us cell by cell; 97 us with the loop made by the compiler, a lane mask for every way out of it and every run's last cell
+// checked against the u crossings; 69 us written out, with that check only where the position cannot tell the cell).
 template <bool kOutside>
-__device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, float dy, const RowRecord& rr,
+__device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, float dy, const RowRecord& rr, float edge,
                                              const OutsideCamera* from_outside = nullptr)
 {
     const bool xm = fabsf(dx) >= fabsf(dy);
@@ -1299,7 +1299,8 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
     }
     const float dua = fabsf(du);
     const float inv_u = safe_rcp(dua);
-    const float dt_v = fabsf(safe_rcp(dv)), dt_z = fabsf(rr.rcp_z);
+    const float rcp_v = safe_rcp(dv);
+    const float dt_v = fabsf(rcp_v), dt_z = fabsf(rr.rcp_z);
     float t0_u, t0_v, t0_z, t_end;
     BoxEntry in{};
     if constexpr (kOutside) {
@@ -1320,47 +1321,140 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
         t_end = vmin3(fmaf((float)(c.um1 - c.i0), inv_u, t0_u), fmaf(c.nv_max, dt_v, t0_v), rr.tend_z);
     }
     const int mirrored = c.pad;                     // -1 or 0
-    const int origin = mirrored & (c.um1 - 30);     // window of mirrored cell i: cells U-32-i .. U-1-i, else i .. i+31
-    float t_v = t0_v, t_z = t0_z, n_v = 0.0f, n_z = 0.0f;
-    uint32_t addr = (uint32_t)c.addr0, in_range = 0;
-    int i_from = c.i0, i_row = c.i0, i_last = c.i0;
-    for (bool go = !kOutside || !in.misses; go;) {
-        // The last cell of the run: where the ray is at t_out, put right by one cell where the u crossings themselves say
-        // so.  Every choice of the next crossing is then the per-cell tracer's own comparison, ties included (x before y
-        // before z, and none at or behind the far side), and so are the cells visited, for cameras inside the grid and no
-        // higher than the solids.  From higher up the z crossings are counted from the top of the solids and not from the
-        // camera's own layer (depths differ in the last bit), and a ray that leaves the solids' top plane exactly through
-        // a voxel edge does not look at the voxel beside that edge, as one that leaves the grid.
-        const bool cv = t_v <= t_z;
-        const float t_out = vmin3(t_v, t_z, t_end);
-        const bool strict = (!xm && cv) || !(t_out < t_end);
-        auto crossed = [&](float t_u) { return strict ? t_u < t_out : t_u <= t_out; };
-        int i_to = min(max((int)fmaf(t_out, dua, c.Pu), i_from), c.um1);
-        const float n_u = (float)(i_to - c.i0);
-        if (crossed(fmaf(n_u, inv_u, t0_u))) i_to = min(i_to + 1, c.um1);
-        else if (i_to > i_from && !crossed(fmaf(n_u - 1.0f, inv_u, t0_u))) i_to -= 1;
-        for (;;) {
-            const int first = (i_from ^ mirrored) + origin;
-            const lds_u32_ptr at = (lds_u32_ptr)(uintptr_t)(addr + (uint32_t)((first >> 5) * 4));
-            uint32_t cells = __builtin_amdgcn_alignbit(at[1], at[0], (uint32_t)first);
-            cells = mirrored ? __builtin_bitreverse32(cells) : cells;
-            i_last = min(i_to, i_from + 31);
-            in_range = cells << ((~i_last + i_from) & 31);
-            if ((in_range != 0) | (i_last == i_to)) break;
-            i_from = i_last + 1;
-        }
-        if ((in_range != 0) | !(t_out < t_end)) break;
-        const float one = cv ? 1.0f : 0.0f;
-        addr += (uint32_t)(cv ? c.sv : c.sz);
-        n_v += one;
-        n_z += 1.0f - one;
-        t_v = fmaf(n_v, dt_v, t0_v);
-        t_z = fmaf(n_z, dt_z, t0_z);
-        i_from = i_row = i_to;
+    const int origin = mirrored & (c.um1 + 1);      // mirrored cell i is cell ~i + U
+    const uint64_t is_mirrored = __ballot(mirrored != 0), y_scan = __ballot(!xm);
+    const uint64_t live = kOutside ? __ballot(!in.misses) : ~0ull;
+    float t_v = t0_v, t_z = t0_z, n_v, n_z;
+    uint32_t in_range = 0;
+    int i_row = c.i0, i_win = c.i0, i_last;
+    // A turn: the run of cells the ray covers in its row ends where the ray is at t_out; the window that starts (for a
+    // mirrored class: ends) there is shifted so that only the cells of the run are left.
+    // The last cell of the run is put right by the u crossings themselves wherever the ray's position is too close to a
+    // voxel edge to tell: every choice of the next crossing is then the per-cell tracer's own comparison, ties included (x
+    // before y before z, and none at or behind the far side), and so are the cells visited, for cameras inside the grid and
+    // no higher than the solids.  From higher up the z crossings are counted from the top of the solids and not from the
+    // camera's own layer (depths differ in the last bit), and a ray that leaves the solids' top plane exactly through
+    // a voxel edge does not look at the voxel beside that edge, as one that leaves the grid.
+    // How close is too close: the parameter of a u crossing has three roundings of at most 2^-23 and one reciprocal of one
+    // unit (2^-23) in it, the position two roundings and the mirrored camera coordinate one, each relative to the largest
+    // distance to a plane, D (the grid's size, for cameras outside plus theirs): less than 2^-20 D together.  `edge` is half
+    // a voxel minus that.  Such a turn, about one in fifty, and one whose run is longer than a window, takes a path of its own
+    // for the whole wave (3 below).
+    // Registers: see trace_rows; lanes that are done leave the execution mask.  v40/v41 hold the two dwords of the window.
+    {
+        uint64_t exec_save, exec_turn, cv, m_a, m_b, m_c, strict;
+        float t_out, u_out, u_prev = (float)c.i0, addr = tiny_int((uint32_t)c.addr0), tmp;
+        int x, sh;
+        asm volatile(
+            "s_mov_b64 %[save], exec\n\t"
+            "s_and_b64 exec, exec, %[live]\n\t"
+            "v_mov_b32_e32 %[nv], 0\n\t"
+            "v_mov_b32_e32 %[nz], 0\n"
+            "1:\n\t"
+            "v_cmp_le_f32_e64 %[cv], %[tv], %[tz]\n\t"
+            "v_min3_f32 %[tout], %[tv], %[tz], %[tend]\n\t"
+            "v_fma_f32 %[uout], %[tout], |%[du]|, %[pu]\n\t"
+            "v_fract_f32_e32 %[tmp], %[uout]\n\t"
+            "v_sub_f32_e32 %[up], %[uout], %[up]\n\t"
+            "v_cvt_i32_f32_e32 %[ito], %[uout]\n\t"
+            "v_add_f32_e32 %[tmp], -0.5, %[tmp]\n\t"
+            "v_cmp_ngt_f32_e32 vcc, 0x41f00000, %[up]\n\t"                 // 30: a run of more than 31 cells, to be sure
+            "v_cmp_nlt_f32_e64 %[ma], |%[tmp]|, %[edge]\n\t"
+            "s_or_b64 vcc, vcc, %[ma]\n\t"
+            "s_cbranch_vccnz 3f\n\t"
+            "v_cndmask_b32_e64 %[x], %[irow], %[ito], %[mir]\n\t"
+            "v_xad_u32 %[x], %[x], %[m], %[org]\n\t"
+            "v_lshrrev_b32_e32 %[sh], 5, %[x]\n\t"
+            "v_lshl_add_u32 %[sh], %[sh], 2, %[addr]\n\t"
+            "ds_read2_b32 v[40:41], %[sh] offset1:1\n\t"
+            "v_xad_u32 %[sh], %[ito], -1, %[irow]\n\t"
+            "s_waitcnt lgkmcnt(0)\n\t"
+            "v_alignbit_b32 %[inr], v41, v40, %[x]\n\t"
+            "v_lshlrev_b32_e32 %[inr], %[sh], %[inr]\n"
+            "2:\n\t"
+            "v_cmpx_eq_u32_e64 %[ma], 0, %[inr]\n\t"
+            "v_cmpx_lt_f32_e64 %[mb], %[tout], %[tend]\n\t"
+            "s_cbranch_execz 9f\n\t"
+            "v_cndmask_b32_e64 %[tmp], 0, 1.0, %[cv]\n\t"
+            "v_add_f32_e32 %[nv], %[nv], %[tmp]\n\t"
+            "v_sub_f32_e32 %[tmp], 1.0, %[tmp]\n\t"
+            "v_add_f32_e32 %[nz], %[nz], %[tmp]\n\t"
+            "v_fma_f32 %[tv], %[nv], |%[rv]|, %[t0v]\n\t"
+            "v_fma_f32 %[tz], %[nz], |%[rz]|, %[t0z]\n\t"
+            "v_fma_f32 %[tmp], %[nz], %[szd], %[base]\n\t"
+            "v_fma_f32 %[addr], %[nv], %[svd], %[tmp]\n\t"
+            "v_mov_b32_e32 %[irow], %[ito]\n\t"
+            "v_mov_b32_e32 %[iwin], %[ito]\n\t"
+            "v_mov_b32_e32 %[up], %[uout]\n\t"
+            "s_branch 1b\n"
+            "3:\n\t"
+            // the crossing that ends the run comes before (strict) or not after a u crossing at the same parameter
+            "v_cmp_nlt_f32_e64 %[strict], %[tout], %[tend]\n\t"
+            "s_and_b64 %[ma], %[yscan], %[cv]\n\t"
+            "s_or_b64 %[strict], %[strict], %[ma]\n\t"
+            "v_max_i32_e32 %[ito], %[ito], %[irow]\n\t"
+            "v_min_i32_e32 %[ito], %[ito], %[um1]\n\t"
+            "v_sub_u32_e32 %[tmp], %[ito], %[i0]\n\t"
+            "v_cvt_f32_i32_e32 %[tmp], %[tmp]\n\t"
+            "v_fma_f32 %[up], %[tmp], %[invu], %[t0u]\n\t"
+            "v_cmp_lt_f32_e64 %[ma], %[up], %[tout]\n\t"
+            "v_cmp_le_f32_e64 %[mb], %[up], %[tout]\n\t"
+            "s_andn2_b64 %[mb], %[mb], %[strict]\n\t"
+            "s_or_b64 %[ma], %[ma], %[mb]\n\t"                              // one cell further
+            "v_add_f32_e32 %[tmp], -1.0, %[tmp]\n\t"
+            "v_fma_f32 %[up], %[tmp], %[invu], %[t0u]\n\t"
+            "v_cmp_lt_f32_e64 %[mc], %[up], %[tout]\n\t"
+            "v_cmp_le_f32_e64 %[mb], %[up], %[tout]\n\t"
+            "s_andn2_b64 %[mb], %[mb], %[strict]\n\t"
+            "s_or_b64 %[mc], %[mc], %[mb]\n\t"
+            "s_or_b64 %[mc], %[mc], %[ma]\n\t"
+            "v_cmp_gt_i32_e64 %[mb], %[ito], %[irow]\n\t"
+            "s_andn2_b64 %[mb], %[mb], %[mc]\n\t"                           // one cell less
+            "v_cndmask_b32_e64 %[tmp], 0, 1, %[ma]\n\t"
+            "v_add_u32_e32 %[tmp], %[tmp], %[ito]\n\t"
+            "v_min_i32_e32 %[ito], %[tmp], %[um1]\n\t"
+            "v_cndmask_b32_e64 %[tmp], 0, -1, %[mb]\n\t"
+            "v_add_u32_e32 %[up], %[ito], %[tmp]\n\t"                       // the run's last cell
+            "s_mov_b64 %[turn], exec\n"
+            "4:\n\t"
+            "v_add_u32_e32 %[ito], 31, %[iwin]\n\t"
+            "v_min_i32_e32 %[ito], %[ito], %[up]\n\t"
+            "v_cndmask_b32_e64 %[x], %[iwin], %[ito], %[mir]\n\t"
+            "v_xad_u32 %[x], %[x], %[m], %[org]\n\t"
+            "v_lshrrev_b32_e32 %[sh], 5, %[x]\n\t"
+            "v_lshl_add_u32 %[sh], %[sh], 2, %[addr]\n\t"
+            "ds_read2_b32 v[40:41], %[sh] offset1:1\n\t"
+            "v_xad_u32 %[sh], %[ito], -1, %[iwin]\n\t"
+            "s_waitcnt lgkmcnt(0)\n\t"
+            "v_alignbit_b32 %[inr], v41, v40, %[x]\n\t"
+            "v_lshlrev_b32_e32 %[inr], %[sh], %[inr]\n\t"
+            "v_cmpx_eq_u32_e64 %[ma], 0, %[inr]\n\t"
+            "v_cmpx_lt_i32_e64 %[ma], %[ito], %[up]\n\t"
+            "s_cbranch_execz 5f\n\t"
+            "v_add_u32_e32 %[iwin], 1, %[ito]\n\t"
+            "s_branch 4b\n"
+            "5:\n\t"
+            "s_mov_b64 exec, %[turn]\n\t"
+            "s_branch 2b\n"
+            "9:\n\t"
+            "s_mov_b64 exec, %[save]\n\t"
+            : [save] "=&s"(exec_save), [turn] "=&s"(exec_turn), [cv] "=&s"(cv), [ma] "=&s"(m_a), [mb] "=&s"(m_b), [mc] "=&s"(m_c),
+              [strict] "=&s"(strict), [tout] "=&v"(t_out), [uout] "=&v"(u_out), [tmp] "=&v"(tmp), [x] "=&v"(x), [sh] "=&v"(sh),
+              [inr] "+&v"(in_range), [ito] "=&v"(i_last), [irow] "+&v"(i_row), [iwin] "+&v"(i_win), [up] "+&v"(u_prev),
+              [tv] "+&v"(t_v), [tz] "+&v"(t_z), [addr] "+&v"(addr), [nv] "=&{v43}"(n_v), [nz] "=&{v42}"(n_z)
+            : [live] "s"(live), [tend] "v"(t_end), [du] "v"(du), [pu] "v"(c.Pu), [edge] "s"(edge), [mir] "s"(is_mirrored), [yscan] "s"(y_scan),
+              [m] "v"(mirrored), [org] "v"(origin), [rv] "v"(rcp_v), [rz] "v"(rr.rcp_z), [t0v] "v"(t0_v), [t0z] "v"(t0_z),
+              [szd] "v"(c.row_step_z), [svd] "v"(c.row_step_v), [base] "v"(c.addr0), [um1] "v"(c.um1), [i0] "v"(c.i0),
+              [invu] "v"(inv_u), [t0u] "v"(t0_u)
+            : "vcc", "scc", "memory", "v40", "v41");
     }
-    // as in trace_rows; the hit cell is i_last - (31 - lowest bit)
+    // as in trace_rows.  The first solid cell the ray meets: bit 31 of in_range is cell i_last and the lowest bit counts, for
+    // mirrored classes bit 31 is the window's first cell and the highest one counts.
     const bool found = in_range != 0;
-    const int iu = i_last - 31 + (found ? __builtin_ctz(in_range) : 0);
+    uint32_t lowest, highest;
+    asm("v_ffbl_b32 %0, %1" : "=v"(lowest) : "v"(in_range));
+    asm("v_ffbh_u32 %0, %1" : "=v"(highest) : "v"(in_range));
+    const int iu = mirrored ? i_win + (int)highest : i_last - 31 + (int)lowest;
     const bool along_row = iu != i_row;
     const float tv_last = fmaf(n_v - 1.0f, dt_v, t0_v);
     const float tz_last = fmaf(n_z - 1.0f, dt_z, t0_z);
@@ -1811,6 +1905,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             inside = __builtin_amdgcn_readfirstlane(again->place) == kPlaceInGrid;
         }
         constexpr bool kNarrow = decltype(narrow_tag)::value;
+        // (window scan) how far from the middle of a cell a position may be to tell the cell: see trace_windows
+        const float edge = uniform(0.5f - 0x1p-20f * ((float)max(X, Y) + (kOutside ? fmaxf(fabsf(Pc[0]), fabsf(Pc[1])) : 0.0f)));
         int pend_idx = -1, pend_face = faces.base;
         float pend_t = 0.0f;
         uint32_t pend_pix = 0;
@@ -1860,10 +1956,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             if constexpr (kOutside) {
                 const OutsideCamera from{ faces, { Pc[0], Pc[1], Pc[2] }, d[2], X, Y, max(top, 1) };
                 if constexpr (FAST) h = trace_rows<kNarrow, false, true>(lds_base + off_classes, d[0], d[1], rr, -1, &from);
-                else h = trace_windows<true>(lds_base + off_classes, d[0], d[1], rr, &from);
+                else h = trace_windows<true>(lds_base + off_classes, d[0], d[1], rr, edge, &from);
             } else if constexpr (kRowsOnly) {
                 if constexpr (FAST) h = trace_rows<kNarrow, COARSE>(lds_base + off_classes, d[0], d[1], rr, p.coarse_after);
-                else h = trace_windows<false>(lds_base + off_classes, d[0], d[1], rr);
+                else h = trace_windows<false>(lds_base + off_classes, d[0], d[1], rr, edge);
             } else if (use_rows) {
                 h.idx = cam_idx; h.face = faces.of(6); h.t = 0.0f;
             } else if (scans) {

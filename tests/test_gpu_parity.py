@@ -778,6 +778,37 @@ def test_rays_that_reach_the_far_end_of_a_row(lib, orc, grid):
     assert (ref.hit_index >= 0).any() and (ref.hit_index < 0).any()
 
 
+@pytest.mark.parametrize("grid", [(65, 9, 4), (97, 40, 5), (129, 66, 4), (40, 200, 3), (160, 33, 3)])
+def test_runs_longer_than_a_window(lib, orc, grid):
+    """The window scan looks at 32 cells of a row at a time and takes its other path for a run of 31 and more: rays nearly
+    along the rows, in all four directions, that meet a solid in any cell of the first three windows and in the last cell."""
+    X, Y, Z = grid
+    rng = np.random.default_rng(X * 1000 + Y)
+    N, A, M = 8, 8, 5
+    spec = _mini_spec(N, A, grid, 32, 16, M)
+    vox = np.zeros((N, Z, Y, X), np.uint8)
+    for e in range(N):
+        share = (0.002, 0.005, 0.01, 0.02, 0.03, 0.05, 0.0, 0.0)[e]
+        vox[e] = np.where(rng.random((Z, Y, X)) < share, rng.integers(1, M + 1, (Z, Y, X)), 0)
+        if e == 7:
+            vox[e, :, :, (0, -1)] = 1
+            vox[e, :, (0, -1)] = 2
+    pal = rng.integers(0, 256, (N, M + 1, 3)).astype(np.uint8)
+    cams = np.zeros((N * A, 5), np.float32)
+    for o in range(N * A):
+        towards = o % 4
+        pos = [rng.uniform(0.1, X - 0.1), rng.uniform(0.1, Y - 0.1), rng.uniform(0.1, Z - 0.1)]
+        pos[towards // 2] = rng.uniform(0.1, 3) if towards % 2 == 0 else (X, Y)[towards // 2] - rng.uniform(0.1, 3)
+        cams[o] = (*pos, (0.0, np.pi, np.pi / 2, -np.pi / 2)[towards] + rng.uniform(-0.01, 0.01), rng.uniform(-0.01, 0.01))
+    ob = _oracle_for(orc, spec, vox, pal, cams, hfov_rad=0.1)
+    run = _gpu_for(spec, vox, pal, cams, hfov_rad=0.1)
+    run.render()
+    g, ref = run.numpy(), ob.render()
+    _pixelwise_rule(g, ref, f"long runs, grid {grid}")
+    far = ref.depth[ref.hit_index >= 0]
+    assert all(((far >= 32 * k) & (far < 32 * (k + 1))).any() for k in range(min(max(X, Y) // 32, 4)))
+
+
 @pytest.mark.parametrize("grid,image,aux", [((48, 44, 6), (48, 16), True), ((48, 44, 6), (48, 16), False), ((64, 64, 6), (40, 24), True),
                                             ((63, 64, 5), (40, 24), False), ((48, 44, 6), (33, 17), False), ((64, 40, 6), (33, 17), True)])
 def test_rays_that_pass_many_rows(lib, orc, grid, image, aux):
