@@ -695,8 +695,8 @@ struct alignas(16) ScanClass {
     float uexit;        // U - Pu: distance to the far side of the grid along u (window scan: to the first u plane)
     float Pu_err;       // what rounding took from the mirrored coordinate: (U - P) - Pu exactly, 0 if not mirrored
     int   addr0;        // LDS byte address of the camera's row in this class's row array
-    float row_step_v;   // the row-address steps per v and z crossing as floats whose bits are the number of bytes (denormals;
-    float row_step_z;   // a sign bit for steps back): see the row loop
+    float row_step_vz;  // row-address step of a v crossing minus that of a z crossing, and that of a z crossing, as floats
+    float row_step_z;   // whose bits are the number of bytes (denormals; a sign bit for steps back): see the row loop
     float dist_v;       // distance from the camera to the first v plane in this direction (>= 0)
     float nv_max;       // v planes between the camera cell and the grid boundary in this direction
                         // (the z counterparts of these two depend on the image row: RowRecord holds them)
@@ -1125,14 +1125,15 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     // may not read a lane mask within two instructions of the one that wrote it).
     // What bounds the loop is the issue of comparisons, selects, conversions and shifts, of which other waves' float adds and
     // multiply-adds run beside (see tiny_int); so the counters and the row address are float arithmetic with one select per
-    // turn (two and an integer add before; 4096 x 2 of 40x40x16: step 304 -> 301 us, 2048 x 4 of 64x64x32 1085 -> 1074): the
+    // turn (two and an integer add before; 4096 x 2 of 40x40x16: step 304 -> 301 us, 2048 x 4 of 64x64x32 1085 -> 1070): the
     // row address as a number of bytes in a denormal, and for the first 13 turns, written out one by one, the z crossings as
-    // the turns that are not v crossings.  A multiply-add whose three vector registers all have even or all odd numbers
-    // takes twice the time: the temporaries and counters have registers of their own (v48 to v53) that rule it out.
+    // the turns that are not v crossings (five turns written out: 64x64x32 +1.2 %).  A multiply-add whose three vector
+    // registers all have even or all odd numbers takes twice the time: the temporaries, the counters and the address have
+    // registers of their own (v48 to v55) that rule it out.
     {
         uint64_t exec_save, m_go, m_empty;
         int sh;
-        float inc;
+        float inc, row_addr = tiny_int(addr);
         // the run of cells [IFROM, ITO] of the current row: ITO from the parameter at which the ray leaves the row
         // (TOUT, NARROW: capped at the grid exit; else the cell is clamped to U - 1), then the two shifts
 #define MV_ASM_TEST(TV, TZ, IFROM, ITO, CELL, WAIT)                                     \
@@ -1158,23 +1159,25 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
             "v_cmpx_lt_f32_e64 %[mgo], v51, %[tend]\n\t"                                \
             "s_cbranch_execz 2f\n\t"
 #define MV_ASM_NEXT_ROW                                                                 \
-            "v_fma_f32 v53, %[nz], %[szd], %[base]\n\t"                                 \
-            "v_fma_f32 %[addr], %[nv], %[svd], v53\n\t"                                 \
-            "ds_read_b64 %[row], %[addr]\n\t"                                           \
             "v_fma_f32 %[tv], %[nv], |%[rv]|, %[t0v]\n\t"                               \
             "v_fma_f32 %[tz], %[nz], |%[rz]|, %[t0z]\n\t"
+#define MV_ASM_READ(INC)                                                                \
+            "v_add_f32_e32 v55, v55, %[szd]\n\t"                                       \
+            "v_cndmask_b32_e64 " INC ", 0, 1.0, vcc\n\t"                               \
+            "v_fma_f32 v55, " INC ", %[svz], v55\n\t"                                  \
+            "ds_read_b64 %[row], v55\n\t"
 #define MV_ASM_FIRST_ADVANCE                                                            \
-            "v_cndmask_b32_e64 %[nv], 0, 1.0, vcc\n\t"                                  \
+            MV_ASM_READ("%[nv]")                                                        \
             "v_sub_f32_e32 %[nz], 1.0, %[nv]\n\t"                                       \
             MV_ASM_NEXT_ROW
         // (after N turns the crossings along v and z add up to N)
 #define MV_ASM_ADVANCE(N)                                                               \
-            "v_cndmask_b32_e64 %[inc], 0, 1.0, vcc\n\t"                                 \
+            MV_ASM_READ("%[inc]")                                                       \
             "v_add_f32_e32 %[nv], %[nv], %[inc]\n\t"                                    \
             "v_sub_f32_e32 %[nz], " N ", %[nv]\n\t"                                     \
             MV_ASM_NEXT_ROW
 #define MV_ASM_ADVANCE_ANY                                                              \
-            "v_cndmask_b32_e64 %[inc], 0, 1.0, vcc\n\t"                                 \
+            MV_ASM_READ("%[inc]")                                                       \
             "v_add_f32_e32 %[nv], %[nv], %[inc]\n\t"                                    \
             "v_sub_f32_e32 %[inc], 1.0, %[inc]\n\t"                                     \
             "v_add_f32_e32 %[nz], %[nz], %[inc]\n\t"                                    \
@@ -1206,10 +1209,10 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
 #define MV_ASM_OPERANDS                                                                                              \
                 : [save] "=&s"(exec_save), [mgo] "=&s"(m_go), [mempty] "=&s"(m_empty),                                \
                   [inc] "=&v"(inc), [sh] "=&v"(sh), [r] "=&v"(r), [inr] "=&v"(in_range), [ib] "=&v"(i_b),             \
-                  [tv] "=&v"(t_v), [tz] "=&v"(t_z), [ia] "+&v"(i_a), [row] "+&v"(row), [addr] "=&v"(addr),              \
+                  [tv] "=&v"(t_v), [tz] "=&v"(t_z), [ia] "+&v"(i_a), [row] "+&v"(row), "+&{v55}"(row_addr),             \
                   [nv] "=&{v49}"(n_v), [nz] "=&{v48}"(n_z)                                                            \
-                : [tend] "v"(t_end), [du] "v"(du), [pu] "v"(c.Pu), [svd] "v"(c.row_step_v), [szd] "v"(c.row_step_z),  \
-                  [base] "v"(c.addr0), [rv] "v"(rcp_v),                                                               \
+                : [tend] "v"(t_end), [du] "v"(du), [pu] "v"(c.Pu), [svz] "v"(c.row_step_vz), [szd] "v"(c.row_step_z), \
+                  [rv] "v"(rcp_v),                                                                                    \
                   [rz] "v"(rcp_z), [t0v] "{v50}"(t0_v), [t0z] "v"(t0_z), [um1] "v"(c.um1)                             \
                 : "vcc", "scc", "memory", "v51", "v53"
         if (kNarrow) asm volatile(MV_ASM_LOOP(MV_ASM_CELL_NARROW) MV_ASM_OPERANDS);
@@ -1220,6 +1223,7 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
 #undef MV_ASM_ADVANCE_ANY
 #undef MV_ASM_ADVANCE
 #undef MV_ASM_FIRST_ADVANCE
+#undef MV_ASM_READ
 #undef MV_ASM_NEXT_ROW
 #undef MV_ASM_WAIT
 #undef MV_ASM_TO_A
@@ -1365,7 +1369,7 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
             "v_cndmask_b32_e64 %[x], %[irow], %[ito], %[mir]\n\t"
             "v_xad_u32 %[x], %[x], %[m], %[org]\n\t"
             "v_lshrrev_b32_e32 %[sh], 5, %[x]\n\t"
-            "v_lshl_add_u32 %[sh], %[sh], 2, %[addr]\n\t"
+            "v_lshl_add_u32 %[sh], %[sh], 2, v45\n\t"
             "ds_read2_b32 v[40:41], %[sh] offset1:1\n\t"
             "v_xad_u32 %[sh], %[ito], -1, %[irow]\n\t"
             "s_waitcnt lgkmcnt(0)\n\t"
@@ -1375,14 +1379,14 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
             "v_cmpx_eq_u32_e64 %[ma], 0, %[inr]\n\t"
             "v_cmpx_lt_f32_e64 %[mb], %[tout], %[tend]\n\t"
             "s_cbranch_execz 9f\n\t"
+            "v_add_f32_e32 v45, v45, %[szd]\n\t"
             "v_cndmask_b32_e64 %[tmp], 0, 1.0, %[cv]\n\t"
+            "v_fma_f32 v45, %[tmp], %[svz], v45\n\t"
             "v_add_f32_e32 %[nv], %[nv], %[tmp]\n\t"
             "v_sub_f32_e32 %[tmp], 1.0, %[tmp]\n\t"
             "v_add_f32_e32 %[nz], %[nz], %[tmp]\n\t"
             "v_fma_f32 %[tv], %[nv], |%[rv]|, %[t0v]\n\t"
             "v_fma_f32 %[tz], %[nz], |%[rz]|, %[t0z]\n\t"
-            "v_fma_f32 %[tmp], %[nz], %[szd], %[base]\n\t"
-            "v_fma_f32 %[addr], %[nv], %[svd], %[tmp]\n\t"
             "v_mov_b32_e32 %[irow], %[ito]\n\t"
             "v_mov_b32_e32 %[iwin], %[ito]\n\t"
             "v_mov_b32_e32 %[up], %[uout]\n\t"
@@ -1422,7 +1426,7 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
             "v_cndmask_b32_e64 %[x], %[iwin], %[ito], %[mir]\n\t"
             "v_xad_u32 %[x], %[x], %[m], %[org]\n\t"
             "v_lshrrev_b32_e32 %[sh], 5, %[x]\n\t"
-            "v_lshl_add_u32 %[sh], %[sh], 2, %[addr]\n\t"
+            "v_lshl_add_u32 %[sh], %[sh], 2, v45\n\t"
             "ds_read2_b32 v[40:41], %[sh] offset1:1\n\t"
             "v_xad_u32 %[sh], %[ito], -1, %[iwin]\n\t"
             "s_waitcnt lgkmcnt(0)\n\t"
@@ -1441,10 +1445,10 @@ __device__ __forceinline__ Hit trace_windows(uint32_t classes_addr, float dx, fl
             : [save] "=&s"(exec_save), [turn] "=&s"(exec_turn), [cv] "=&s"(cv), [ma] "=&s"(m_a), [mb] "=&s"(m_b), [mc] "=&s"(m_c),
               [strict] "=&s"(strict), [tout] "=&v"(t_out), [uout] "=&v"(u_out), [tmp] "=&v"(tmp), [x] "=&v"(x), [sh] "=&v"(sh),
               [inr] "+&v"(in_range), [ito] "=&v"(i_last), [irow] "+&v"(i_row), [iwin] "+&v"(i_win), [up] "+&v"(u_prev),
-              [tv] "+&v"(t_v), [tz] "+&v"(t_z), [addr] "+&v"(addr), [nv] "=&{v43}"(n_v), [nz] "=&{v42}"(n_z)
+              [tv] "+&v"(t_v), [tz] "+&v"(t_z), "+&{v45}"(addr), [nv] "=&{v43}"(n_v), [nz] "=&{v42}"(n_z)
             : [live] "s"(live), [tend] "v"(t_end), [du] "v"(du), [pu] "v"(c.Pu), [edge] "s"(edge), [mir] "s"(is_mirrored), [yscan] "s"(y_scan),
               [m] "v"(mirrored), [org] "v"(origin), [rv] "v"(rcp_v), [rz] "v"(rr.rcp_z), [t0v] "v"(t0_v), [t0z] "v"(t0_z),
-              [szd] "v"(c.row_step_z), [svd] "v"(c.row_step_v), [base] "v"(c.addr0), [um1] "v"(c.um1), [i0] "v"(c.i0),
+              [szd] "v"(c.row_step_z), [svz] "v"(c.row_step_vz), [um1] "v"(c.um1), [i0] "v"(c.i0),
               [invu] "v"(inv_u), [t0u] "v"(t0_u)
             : "vcc", "scc", "memory", "v40", "v41");
     }
@@ -1747,8 +1751,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         c.addr0 = (int)(lds_base + array_off) + row_bytes * (k_row * V + j_row);
         c.sv = vneg ? -row_bytes : row_bytes;
         c.sz = zneg ? -row_bytes * V : row_bytes * V;
-        c.row_step_v = copysignf(__uint_as_float((uint32_t)row_bytes), vneg ? -1.0f : 1.0f);
-        c.row_step_z = copysignf(__uint_as_float((uint32_t)(row_bytes * V)), zneg ? -1.0f : 1.0f);
+        c.row_step_z = copysignf(tiny_int((uint32_t)(row_bytes * V)), zneg ? -1.0f : 1.0f);
+        c.row_step_vz = copysignf(tiny_int((uint32_t)row_bytes), vneg ? -1.0f : 1.0f) - c.row_step_z;
         c.um1 = U - 1;
         c.face_u = faces.of(2 * (xmaj ? 0 : 1) + (neg ? 1 : 0));
         c.face_v = faces.of(2 * (xmaj ? 1 : 0) + (vneg ? 1 : 0));
