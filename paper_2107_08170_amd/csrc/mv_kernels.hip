@@ -36,9 +36,9 @@ GridLayout make_layout(int X, int Y, int Z)
 }
 
 constexpr int kScanClasses = 16;        // (dominant axis) x (direction along u, v, z)
-// bytes between scan-class records in LDS (80 used, 16 more with the coarse level): 28 dwords, so that the sixteen
-// records start in sixteen different banks (a tile whose rays fall into several classes reads several records at
-// once; 128 bytes apart they collided: render +0.6 %)
+// bytes between scan-class records in LDS (80 used, 16 more with the coarse level, 32 more for cameras outside): 28 dwords, so
+// that the sixteen records start in sixteen different banks (a tile whose rays fall into several classes reads several records
+// at once; 128 bytes apart they collided: render +0.6 %)
 constexpr int kClassStride = 112;
 
 static size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
@@ -642,6 +642,7 @@ struct Hit {
 
 constexpr float kBig = 3.0e38f;            // stands in for 1/0: keeps every product finite or +inf, never NaN
 constexpr float kSmallest = 0x1p-126f;      // smallest normal number
+constexpr float kTinyDistance = 1e-30f;     // to a plane a camera is exactly on: nothing times |1/d|, or never if d is 0
 constexpr float kNever = 0.5f * kBig;      // first crossing of an axis along which a ray does not move (below kBig, the
                                            // distance between two crossings: the one before the first lies behind the camera)
 
@@ -737,6 +738,18 @@ struct alignas(16) PairClass {
     int inner0;         // 1 if the first v plane ahead of the camera lies inside its pair, 0 if it bounds it
 };
 static_assert(sizeof(ScanClass) + sizeof(PairClass) <= kClassStride, "class slot too small");
+
+// Where the rays of a camera outside the grid enter the box [0,X]x[0,Y]x[0,top] (row scan): these constants of a class sit
+// behind its record, and in four words of the record that such cameras have no other use for (near_v: dist_v, far_v: nv_max,
+// Pv: i0, last_v: pad).  Distances along u and v are those a ray has to go, so that times |1/d| they are its parameters.
+struct alignas(16) EntryClass {
+    float near_u, far_u;                    // to the near and to the far side of the box along u; near_v, far_v along v
+                                            // Pv: camera coordinate along v, as it is; last_v: V - 1
+    float ahead_v, ahead_z;                 // 0 or 1: from a cell's number to that of the plane a ray leaves it through
+    float per_cell_v, per_cell_z;           // planes left behind a cell's = planes + per_cell * cell
+    float planes_v, planes_z;
+};
+static_assert(sizeof(EntryClass) == 32 && sizeof(ScanClass) + sizeof(EntryClass) <= kClassStride, "class slot too small");
 
 // Plain 3D-DDA through the x rows (any row width), in LDS or in global memory.  Used for grids whose x and y rows do not
 // both fit into LDS, for cameras far outside the grid, and for workgroups whose world is taller than the layers staged.
@@ -847,6 +860,12 @@ __device__ __forceinline__ float vmax3(float a, float b, float c)
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
 }
+__device__ __forceinline__ float vmed3(float a, float b, float c)
+{
+    float r;
+    asm("v_med3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
 __device__ __forceinline__ float vmin3(float a, float b, float c)
 {
     float r;
@@ -889,12 +908,14 @@ __device__ __forceinline__ int mad24s(int a, int b_uniform, int c)
 // A camera outside the grid, for the tracers below: its rays start where they enter the box [0,X]x[0,Y]x[0,top].
 struct OutsideCamera {
     FaceRows faces;
+    bool finite;        // the camera's directions are numbers (all rays of others miss)
     float P[3];
     float dz;           // vertical component of the ray
     int X, Y, top;      // top: layers that may hold a solid voxel, at least 1
 };
 
-// Where such a ray enters the box: the same slab test, entry cells and first crossings as trace_generic.
+// Where such a ray enters the box: the same slab test, entry cells and first crossings as trace_generic (window scan; the row
+// scan gets the same values from an EntryClass).
 struct BoxEntry {
     bool misses;
     float t;            // parameter of the entry point, >= 0
@@ -961,15 +982,15 @@ __device__ __forceinline__ BoxEntry enter_box(const OutsideCamera& o, float dx, 
 // t_end, which puts the last cell of the run at U at most (U only through rounding at the far boundary);
 // with U <= 63 that still is a valid bit position of an always-empty cell, and the clamp to U - 1 that
 // 64-cell rows need is left out.
-// kOutside: the ray starts where it enters the grid's box instead of in the camera's cell (see enter_box), and the
+// kOutside: the ray starts where it enters the grid's box instead of in the camera's cell (see EntryClass), and the
 // class records hold row and voxel index of cell (0,0,0) of the class's array instead of the camera's.  The row loop
 // is the same one; a ray that misses the box leaves it in its first turn.  No crossing parameter lies before the entry
-// point, so the runs of cells are monotone here as well.  Bound by instruction issue like the inside scan (about ninety
-// instructions more per ray, for the entry); the per-cell tracer over rows in device memory, which took these cameras
-// before and still takes far ones, spends a dependent memory access per cell (256 x 4 cameras around 40x40x16 worlds at
-// 128x72, upload + cameras + render: 286 -> 80 us).  The last cell of a run is taken from the ray's position, as for
-// cameras inside: a ray that passes exactly through a voxel edge may fall on the other side of it than with the per-cell
-// tracer (45-degree views along cell middles: 6 of 10 000 pixels; views at random: one of 13 million).
+// point, so the runs of cells are monotone here as well.  Bound by instruction issue like the inside scan (256 x 4 cameras
+// around 40x40x16 worlds at 128x72, upload + cameras + render: 286 us with the per-cell tracer over rows in device memory,
+// which still takes far ones; 77 us with the slab test worked out per ray and axis; 63 us with what a class and an image row
+// know of it ready-made, and one reciprocal per ray and axis instead of two).  The last cell of a run is taken from the ray's
+// position, as for cameras inside: a ray that passes exactly through a voxel edge may fall on the other side of it than with
+// the per-cell tracer (45-degree views along cell middles: 6 of 10 000 pixels; views at random: one of 13 million).
 template <bool kNarrow, bool kCoarse, bool kOutside = false>
 __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float dy, const RowRecord& rr, int fine_turns,
                                           const OutsideCamera* from_outside = nullptr)
@@ -999,23 +1020,49 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     // reciprocal finite (8.5e37), for -0 as for +0 on the positive side
     const float dua = fabsf(du);
     const float inv_u = __builtin_amdgcn_rcpf(fabsf(du + kSmallest));
-    const float rcp_v = kOutside ? safe_rcp(dv) : __builtin_amdgcn_rcpf(dv_), rcp_z = rr.rcp_z;      // (as enter_box has it)
+    const float rcp_v = __builtin_amdgcn_rcpf(dv_), rcp_z = rr.rcp_z;
     const float dt_v = fabsf(rcp_v), dt_z = fabsf(rcp_z);
     // first crossing on an axis: the distance to the first plane in the ray's direction times |1/d| (along z: from
     // the image row's record, see RowRecord)
     float t0_v, t0_z, t_end;
-    BoxEntry in{};
+    float t_in_box = 0.0f;
+    int entry_face = 0;
+    bool misses = false;
     if constexpr (kOutside) {
-        in = enter_box(*from_outside, dx, dy, xm, rcp_z);
-        if (__ballot(!in.misses) == 0) return Hit{ -1, 0, 0.0f };        // no ray of the tile meets the box
-        t0_v = in.t0_v; t0_z = in.t0_z;
-        t_end = vmax(vmin3(c.uexit * inv_u, fmaf(in.left_v, dt_v, t0_v), fmaf(in.left_z, dt_z, t0_z)), in.t);
+        // the slab test, the entry cell along v and z and the first crossings from there (see EntryClass; the row record holds
+        // the parameters of the box's sides along z): the values of enter_box, in the order a class knows them
+        EntryClass e;
+        {
+            lds_u32x4_ptr rec = (lds_u32x4_ptr)(uintptr_t)(record + (uint32_t)sizeof(ScanClass));
+            u32x4* dst = reinterpret_cast<u32x4*>(&e);
+            dst[0] = rec[0]; dst[1] = rec[1];
+        }
+        const float Pv = __int_as_float(c.i0), last_v = __int_as_float(c.pad);
+        const float near_u = e.near_u * inv_u, near_v = c.dist_v * dt_v, near_z = rr.t0_z;
+        const float t_far = vmin3(e.far_u * inv_u, c.nv_max * dt_v, rr.tend_z);
+        const float t_near = vmax3(near_u, near_v, near_z);
+        misses = !(t_near <= t_far) || !(t_far >= 0.0f) || !from_outside->finite;
+        if (__ballot(!misses) == 0) return Hit{ -1, 0, 0.0f };               // no ray of the tile meets the box
+        t_in_box = vmax(t_near, 0.0f);
+        const bool by_v = xm ? near_v > near_u : near_v >= near_u;          // (x before y before z)
+        const bool by_z = near_z > (by_v ? near_v : near_u);
+        entry_face = by_z ? c.face_z : (by_v ? c.face_v : c.face_u);
+        if (!(t_near > 0.0f)) entry_face = from_outside->faces.of(6);
+        // (a cell number below 0 only from rounding; a ray that enters through a side of the axis stands in its first cell)
+        const float dz = from_outside->dz, top_1 = (float)(from_outside->top - 1);
+        float j = vmed3(floorf(fmaf(t_in_box, dv, Pv)), 0.0f, last_v), k = vmed3(floorf(fmaf(t_in_box, dz, from_outside->P[2])), 0.0f, top_1);
+        const bool stands = t_near > 0.0f;
+        if (stands && by_v && !by_z) j = last_v - e.planes_v;
+        if (stands && by_z) k = top_1 - e.planes_z;
+        // (the tiny distance stands for "never" where a component is 0 and the camera is exactly on the plane ahead)
+        t0_v = vmax(((j + e.ahead_v) - Pv + kTinyDistance) * rcp_v, t_in_box);
+        t0_z = vmax(((k + e.ahead_z) - from_outside->P[2] + kTinyDistance) * rcp_z, t_in_box);
+        t_end = vmax(vmin3(c.uexit * inv_u, fmaf(fmaf(e.per_cell_v, j, e.planes_v), dt_v, t0_v), fmaf(fmaf(e.per_cell_z, k, e.planes_z), dt_z, t0_z)), t_in_box);
         // the record's address and index are those of cell (0,0,0)
-        const int V = xm ? from_outside->Y : from_outside->X;
-        c.addr0 += 8 * (in.k * V + in.j);
-        c.idx0 += (float)((in.k * from_outside->Y) * from_outside->X + in.j * (xm ? from_outside->X : 1));
-        c.i0 = min(max((int)fmaf(in.t, dua, c.Pu), 0), c.um1);
-        if (in.misses) t0_v = t0_z = t_end = 0.0f;
+        c.addr0 = __float_as_int(fmaf(k, fabsf(c.row_step_z), fmaf(j, tiny_int(8u), tiny_int((uint32_t)c.addr0))));
+        c.idx0 = fmaf(k, fabsf(c.stride_z), fmaf(j, fabsf(c.stride_v), c.idx0));
+        c.i0 = min(max((int)fmaf(t_in_box, dua, c.Pu), 0), c.um1);
+        if (misses) t0_v = t0_z = t_end = 0.0f;
     } else {
         t0_v = c.dist_v * dt_v;
         t0_z = rr.t0_z;
@@ -1041,7 +1088,7 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     // The next row is requested as soon as its address is known, at the end of the turn before (render -1 %).
     uint64_t row = 0;
     if constexpr (!kCoarse) row = *(lds_u64_ptr)(uintptr_t)addr;
-    if constexpr (kOutside) row = in.misses ? 0ull : row;
+    if constexpr (kOutside) row = misses ? 0ull : row;
     int i_a = c.i0, i_b;
     if constexpr (kCoarse) {
         // Coarse level: after `fine_turns` ordinary turns a ray first looks at the PAIR of rows it is in (the OR of
@@ -1260,8 +1307,8 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     if constexpr (kOutside) {
         // the voxel the ray meets as it enters the box
         const bool at_entry = !along_row && n_v + n_z == 0.0f;
-        face = at_entry ? in.face : face;
-        t = at_entry ? in.t : t;
+        face = at_entry ? entry_face : face;
+        t = at_entry ? t_in_box : t;
     }
     // voxel index: the class record holds the index of (mirrored cell 0, camera's v cell, camera's layer)
     // and the signed index steps per cell along u and per crossing along v and z
@@ -1776,6 +1823,36 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             *reinterpret_cast<PairClass*>(lds + off_classes + q * kClassStride + sizeof(ScanClass)) = pc;
         }
     }
+    if (FAST && outside_rows) {
+        // what cameras outside know of the box (see EntryClass), by the threads that wrote the records
+        for (int i = threadIdx.x; i < p.H; i += threads) {
+            RowRecord& rr = lds_rowrec[i];
+            const float dt_z = fabsf(rr.rcp_z);
+            const bool zneg = rr.rcp_z < 0.0f;
+            rr.t0_z = (zneg ? P[2] - (float)solid_layers : 0.0f - P[2]) * dt_z;
+            rr.tend_z = ((zneg ? P[2] : (float)solid_layers - P[2]) + kTinyDistance) * dt_z;
+        }
+        if (threadIdx.x >= 64 && threadIdx.x < 64 + kScanClasses) {
+            const int q = threadIdx.x - 64;
+            const bool xmaj = q < 8, neg = q & 4, vneg = q & 2, zneg = q & 1;
+            const float U = (float)(xmaj ? X : Y), V = (float)(xmaj ? Y : X), pu = xmaj ? P[0] : P[1], pv = xmaj ? P[1] : P[0];
+            ScanClass& c = *reinterpret_cast<ScanClass*>(lds + off_classes + q * kClassStride);
+            c.dist_v = vneg ? pv - V : 0.0f - pv;
+            c.nv_max = (vneg ? pv : V - pv) + kTinyDistance;
+            c.i0 = __float_as_int(pv);
+            c.pad = __float_as_int(V - 1.0f);
+            EntryClass e;
+            e.near_u = neg ? pu - U : 0.0f - pu;
+            e.far_u = (neg ? pu : U - pu) + kTinyDistance;
+            e.ahead_v = vneg ? 0.0f : 1.0f;
+            e.ahead_z = zneg ? 0.0f : 1.0f;
+            e.per_cell_v = vneg ? 1.0f : -1.0f;
+            e.per_cell_z = zneg ? 1.0f : -1.0f;
+            e.planes_v = vneg ? 0.0f : V - 1.0f;
+            e.planes_z = zneg ? 0.0f : (float)(solid_layers - 1);
+            *reinterpret_cast<EntryClass*>(lds + off_classes + q * kClassStride + sizeof(ScanClass)) = e;
+        }
+    }
     __syncthreads();
 
     if (COARSE && use_rows) {
@@ -1892,7 +1969,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         // match with the first read): kept in scalar registers from the prologue on, it costs the common loop spills.
         float Pc[3] = { 0.0f, 0.0f, 0.0f }, Fcz = 0.0f, Ucz = 0.0f;
         int body_lo = -1, body_hi = -1, top = 0;
-        bool inside = true;
+        bool inside = true, finite = true;
         if constexpr (!scans) {
             // (one tile loop: nothing to keep out of another's registers)
             Pc[0] = P[0]; Pc[1] = P[1]; Pc[2] = P[2];
@@ -1907,6 +1984,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             body_lo = __builtin_amdgcn_readfirstlane(again->self_lo); body_hi = __builtin_amdgcn_readfirstlane(again->self_hi);
             top = __builtin_amdgcn_readfirstlane(tops[env]);
             inside = __builtin_amdgcn_readfirstlane(again->place) == kPlaceInGrid;
+            float sum = 0.0f;           // (R_z is 0)
+            for (int a = 0; a < 3; ++a) sum += fabsf(again->F[a]) + fabsf(again->R[a]) + fabsf(again->U[a]);
+            finite = __builtin_amdgcn_readfirstlane(sum < kBig) != 0;
         }
         constexpr bool kNarrow = decltype(narrow_tag)::value;
         // (window scan) how far from the middle of a cell a position may be to tell the cell: see trace_windows
@@ -1958,7 +2038,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             // a5: traversal
             Hit h;
             if constexpr (kOutside) {
-                const OutsideCamera from{ faces, { Pc[0], Pc[1], Pc[2] }, d[2], X, Y, max(top, 1) };
+                const OutsideCamera from{ faces, finite, { Pc[0], Pc[1], Pc[2] }, d[2], X, Y, max(top, 1) };
                 if constexpr (FAST) h = trace_rows<kNarrow, false, true>(lds_base + off_classes, d[0], d[1], rr, -1, &from);
                 else h = trace_windows<true>(lds_base + off_classes, d[0], d[1], rr, edge, &from);
             } else if constexpr (kRowsOnly) {

@@ -809,6 +809,36 @@ def test_runs_longer_than_a_window(lib, orc, grid):
     assert all(((far >= 32 * k) & (far < 32 * (k + 1))).any() for k in range(min(max(X, Y) // 32, 4)))
 
 
+@pytest.mark.parametrize("grid", [(12, 9, 5), (40, 40, 6), (64, 20, 4)])
+def test_outside_rays_with_zero_components_in_the_planes_of_the_grid(lib, grid):
+    """Cameras outside, exactly on planes of the grid (its sides among them) and looking along an axis: two components of the
+    middle pixel's ray are exactly 0, it never crosses a plane of those axes, and hits what the per-cell tracer says it hits
+    (which takes over when fewer layers are reserved than the world has)."""
+    X, Y, Z = grid
+    rng = np.random.default_rng(X)
+    W, H, M = 15, 9, 6
+    views = []
+    for yaw, side in ((0.0, 0), (np.float32(np.pi), 0), (np.float32(np.pi / 2), 1), (np.float32(-np.pi / 2), 1)):
+        for across in (0.0, 1.0, 3.5, float((Y, X)[side]), -1.0, (Y, X)[side] + 1.0):
+            for z in (0.0, 1.0, 2.5, float(Z), -2.0, Z + 2.0):
+                along = -4.5 if np.cos(yaw - side * np.pi / 2) > 0 else (X, Y)[side] + 4.5
+                views.append(((along, across) if side == 0 else (across, along)) + (z, yaw, 0.0))
+    cams = np.array(views, np.float32)
+    vox, pal = synth.random_world(rng, 1, grid, 0.15, M)
+    vox[:, Z - 1, ::3, ::2] = 1
+    spec = _mini_spec(1, len(cams), grid, W, H, M)
+    scan, cells = _gpu_for(spec, vox, pal, cams), _gpu_for(spec, vox, pal, cams)
+    cells.batch.debug_set_staged_layers(1)
+    scan.render()
+    cells.render()
+    a, b = scan.numpy(), cells.numpy()
+    # (yaw 0: the components of the other views' middle pixels are only tiny)
+    middle = (np.abs(cams[:, 3]) < 1e-6)
+    assert (a.hit_index[middle, H // 2, W // 2] == b.hit_index[middle, H // 2, W // 2]).all()
+    assert (a.depth[middle, H // 2, W // 2] == b.depth[middle, H // 2, W // 2]).all()
+    assert (a.hit_index[middle, H // 2, W // 2] >= 0).any() and (a.hit_index[middle, H // 2, W // 2] < 0).any()
+
+
 @pytest.mark.parametrize("grid,image,aux", [((48, 44, 6), (48, 16), True), ((48, 44, 6), (48, 16), False), ((64, 64, 6), (40, 24), True),
                                             ((63, 64, 5), (40, 24), False), ((48, 44, 6), (33, 17), False), ((64, 40, 6), (33, 17), True)])
 def test_rays_that_pass_many_rows(lib, orc, grid, image, aux):
