@@ -892,18 +892,10 @@ __device__ __forceinline__ uint32_t low_bit(uint32_t v)
     return b;
 }
 
+typedef __attribute__((address_space(3))) const float* lds_f32_ptr;
 typedef __attribute__((address_space(3))) const uint32_t* lds_u32_ptr;
 typedef __attribute__((address_space(3))) const uint64_t* lds_u64_ptr;
 typedef __attribute__((address_space(3))) const u32x4* lds_u32x4_ptr;
-
-// a*b + c on the 24-bit multiplier, the multiplier b from a scalar register (a wave-uniform value such as a grid dimension);
-// every product on this path fits 24 x 24 bits.
-__device__ __forceinline__ int mad24s(int a, int b_uniform, int c)
-{
-    int r;
-    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b_uniform), "v"(c));
-    return r;
-}
 
 // A camera outside the grid, for the tracers below: its rays start where they enter the box [0,X]x[0,Y]x[0,top].
 struct OutsideCamera {
@@ -1910,18 +1902,21 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
 
     // a6 + a7 of a finished tile: material -> colour, then the stores.
     // Branch-free: lanes that found nothing look up a valid entry as well and then take the miss values.
-    // (PACKED launches: `pix` is the wave-uniform pixel offset of the tile; the addresses of the stores are scalar, with a
-    // per-lane constant.  The store instructions are written out: the compiler adds the tile's offset per lane, in 64 bits)
+    // `pix` is the wave-uniform pixel offset of the tile: the addresses of the stores are scalar, with a per-lane constant.
+    // The store instructions are written out: the compiler adds the tile's offset per lane, in 64 bits.  Tiles that reach
+    // beyond the image (PACKED launches have none) store what they have of it, colours byte by byte (256 x 4 cameras of 130x70
+    // pixels: step 55.3 us when all tiles of such images did, 53.5 now).
     const uint32_t lane_depth_off = 4u * (uint32_t)lane_pix, lane_rgb_off = 3u * (uint32_t)lane_pix + (uint32_t)quad;
-    // constants in vector registers (see tiny_int) where there are registers left for them
+    // constants in vector registers (see tiny_int) where there are registers left for them (with the code of the tiles that
+    // reach beyond the image they cost small images 1 % and gain large ones nothing)
     constexpr bool kVectors = FAST && PACKED && !AUX;
     const uint64_t three_of_four = 0x7777777777777777ull;
-    // four consecutive lanes hold four consecutive pixels of one row = 12 bytes = three aligned dwords, written by the first
+    // four consecutive lanes hold four consecutive pixels of one row = 12 bytes = three dwords, written by the first
     // three lanes of the quad: dword m holds the upper 3-m bytes of pixel m and the lower m+1 bytes of pixel m+1, one byte
     // permutation of the two (byte selectors 0..2: own pixel, 4..6: the next one)
     const uint32_t word_bytes = quad == 0 ? 0x04020100u : (quad == 1 ? 0x05040201u : 0x06050402u);
     const uint32_t sky = kVectors ? __float_as_uint(in_vector(__uint_as_float(p.sky_packed))) : p.sky_packed;
-    auto shade_and_store = [&](int idx, int face, float t, uint32_t material, uint32_t pix, bool active) {
+    auto shade_and_store = [&](int idx, int face, float t, uint32_t material, uint32_t pix, int columns_left, int rows_left) {
         const bool hit = idx >= 0;
         asm volatile("" : "+v"(material));          // (a whole register, not its low byte: no sub-dword operand below)
         material = min(material, (uint32_t)last_material);
@@ -1933,7 +1928,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         asm volatile("" : "+v"(shaded));            // (read for every lane: a select costs less than a branch around the read)
         const uint32_t colour = hit ? shaded : sky;
         const float depth = hit ? t : 0.0f;
-        if (PACKED) {
+        if (PACKED || __builtin_expect(columns_left >= kTileW && rows_left >= kTileH, 1)) {
             store_dword(lane_depth_off, __float_as_uint(depth), reinterpret_cast<const uint8_t*>(depth_obs) + 4u * pix);
             if (AUX && auxm_obs) store_byte((uint32_t)lane_pix, hit ? material : 0u, auxm_obs + pix);
             if (AUX && auxh_obs) store_dword(lane_depth_off, (uint32_t)max(idx, -1), reinterpret_cast<const uint8_t*>(auxh_obs) + 4u * pix);
@@ -1942,14 +1937,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             // (all lanes of a wave are in the tile loop: the mask is set and reset without being read)
             asm volatile("s_mov_b64 exec, %0\n\tglobal_store_dword %1, %2, %3\n\ts_mov_b64 exec, -1"
                          :: "s"(three_of_four), "v"(lane_rgb_off), "v"(word), "s"(rgb_obs + 3u * pix) : "memory");
-        } else if (active) {
-            depth_obs[pix] = depth;
-            if (AUX) {
-                if (auxm_obs) auxm_obs[pix] = (uint8_t)(hit ? material : 0u);
-                if (auxh_obs) auxh_obs[pix] = max(idx, -1);
-                if (auxf_obs) auxf_obs[pix] = (uint8_t)(hit ? face : 255);
-            }
-            uint8_t* out = rgb_obs + 3u * pix;
+        } else {
+            // (the lane's column and row are worked out again here: kept through the tile loop they cost it registers)
+            const int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), row = l / kTileW, column = l % kTileW;
+            if (column >= columns_left || row >= rows_left) return;
+            const int lane_pix = row * p.W + column;
+            const uint32_t lane_depth_off = 4u * (uint32_t)lane_pix;
+            store_dword(lane_depth_off, __float_as_uint(depth), reinterpret_cast<const uint8_t*>(depth_obs) + 4u * pix);
+            if (AUX && auxm_obs) store_byte((uint32_t)lane_pix, hit ? material : 0u, auxm_obs + pix);
+            if (AUX && auxh_obs) store_dword(lane_depth_off, (uint32_t)max(idx, -1), reinterpret_cast<const uint8_t*>(auxh_obs) + 4u * pix);
+            if (AUX && auxf_obs) store_byte((uint32_t)lane_pix, (uint32_t)(hit ? face : 255), auxf_obs + pix);
+            uint8_t* out = rgb_obs + 3u * pix + 3u * (uint32_t)lane_pix;
             out[0] = (uint8_t)colour;
             out[1] = (uint8_t)(colour >> 8);
             out[2] = (uint8_t)(colour >> 16);
@@ -1994,7 +1992,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         int pend_idx = -1, pend_face = faces.base;
         float pend_t = 0.0f;
         uint32_t pend_pix = 0;
-        bool pend_active = false, pending = false;
+        int pend_columns = 0, pend_rows = 0;
+        bool pending = false;
         // (in vector registers: see tiny_int)
         const float vFx = kVectors ? in_vector(Fx) : Fx, vFy = kVectors ? in_vector(Fy) : Fy, vRx = kVectors ? in_vector(Rx) : Rx, vRy = kVectors ? in_vector(Ry) : Ry,
                     vUx = kVectors ? in_vector(Ux) : Ux, vUy = kVectors ? in_vector(Uy) : Uy;
@@ -2009,23 +2008,18 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             tx += waves;
             tile_pix += pix_step;
             while (tx >= p.tiles_x) { tx -= p.tiles_x; ++ty; tile_pix += pix_wrap; }
-            // PACKED launches have W and H multiples of the tile size: every lane owns a pixel, and its
-            // addresses are a per-lane constant plus a per-tile (wave-uniform) offset
-            bool active = true;
             float sx;
             RowRecord rr;
-            uint32_t pix;
-            if (PACKED) {
+            if constexpr (PACKED) {
                 sx = sx_lane[tx * kTileW];
                 rr = rowrec_lane[ty * kTileH];
-                pix = tile_pix;
             } else {
-                const int col = tx * kTileW + lx, row = ty * kTileH + ly;
-                active = col < p.W && row < p.H;
-                const int ccol = min(col, p.W - 1), crow = min(row, p.H - 1);
-                sx = lds_sx[ccol];
-                rr = lds_rowrec[crow];
-                pix = (uint32_t)mad24s(crow, p.W, ccol);
+                // (columns and rows of the last tiles that the image does not have repeat its last ones)
+                const uint32_t first_sx = lds_base + off_scalars, first_row = lds_base + off_rowrec;
+                const uint32_t at_sx = min(first_sx + 4u * (uint32_t)(tx * kTileW + lx), first_sx + 4u * (uint32_t)(p.W - 1));
+                const uint32_t at_row = min(first_row + 16u * (uint32_t)(ty * kTileH + ly), first_row + 16u * (uint32_t)(p.H - 1));
+                sx = *(lds_f32_ptr)(uintptr_t)at_sx;
+                *reinterpret_cast<u32x4*>(&rr) = *(lds_u32x4_ptr)(uintptr_t)at_row;
             }
 
             // a4: ray through the pixel centre, two fused multiply-adds per axis (the row scan takes what it needs of
@@ -2058,15 +2052,15 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
                 h.face = faces.of(min(h.face, kNumFaces - 1));
             }
 
-            if (pending) shade_and_store(pend_idx, pend_face, pend_t, pend_material, pend_pix, pend_active);
+            if (pending) shade_and_store(pend_idx, pend_face, pend_t, pend_material, pend_pix, pend_columns, pend_rows);
             pend_idx = h.idx; pend_face = h.face; pend_t = h.t;
-            pend_pix = pix;
-            pend_active = active;
+            pend_pix = tile_pix;
+            pend_columns = p.W - tx * kTileW; pend_rows = p.H - ty * kTileH;
             pending = true;
         }
         if (pending) {
             const uint32_t pend_material = vox_env[min((uint32_t)pend_idx, last_voxel)];
-            shade_and_store(pend_idx, pend_face, pend_t, pend_material, pend_pix, pend_active);
+            shade_and_store(pend_idx, pend_face, pend_t, pend_material, pend_pix, pend_columns, pend_rows);
         }
     };
     __builtin_amdgcn_s_setprio(0);
@@ -2192,7 +2186,7 @@ hipError_t prepare_kernels()
 hipError_t launch_render(const RenderParams& p, size_t lds_bytes, hipStream_t stream)
 {
     const bool aux = p.aux_material || p.aux_hit || p.aux_face;
-    // dword colour stores and unclamped tiles need whole 8x8 tiles and a 4-byte aligned colour tensor
+    // (images of whole 8x8 tiles whose colours start on a dword: no tile needs a second look, and no dword is split)
     const bool packed = (p.W % kTileW == 0) && (p.H % kTileH == 0) && ((reinterpret_cast<uintptr_t>(p.rgb) & 3) == 0);
     dim3 grid(p.blocks_per_xcd * kXcds), block(p.threads);
 #define MV_LAUNCH(...)                                                                                                       \

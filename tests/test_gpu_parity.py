@@ -809,6 +809,39 @@ def test_runs_longer_than_a_window(lib, orc, grid):
     assert all(((far >= 32 * k) & (far < 32 * (k + 1))).any() for k in range(min(max(X, Y) // 32, 4)))
 
 
+@pytest.mark.parametrize("aux", [False, True])
+@pytest.mark.parametrize("grid", [(14, 11, 5), (70, 12, 4)])
+@pytest.mark.parametrize("image", [(1, 1), (7, 8), (8, 7), (8, 8), (9, 9), (16, 12), (15, 16), (17, 23), (24, 8)])
+def test_ragged_images_and_unaligned_colours(lib, orc, grid, image, aux):
+    """Whole tiles of any image store dwords, those that reach beyond it single bytes: image sizes around the tile, colours
+    that start at any byte, and nothing written beside the image."""
+    W, H = image
+    rng = np.random.default_rng(W * 100 + H)
+    N, A, M = 2, 2, 6
+    spec = _mini_spec(N, A, grid, W, H, M)
+    vox, pal = synth.random_world(rng, N, grid, 0.15, M)
+    cams = synth.random_cameras(rng, N * A, grid, margin=0.0)
+    ref = _oracle_for(orc, spec, vox, pal, cams).render()
+    run = _gpu_for(spec, vox, pal, cams, aux=aux)
+    clear = ref.edge_margin >= parity.EDGE_MARGIN
+    size = N * A * H * W * 3
+    for offset in range(4):
+        block = torch.full((size + 64,), 171, dtype=torch.uint8, device="cuda")
+        depth = torch.full((N * A * H * W + 16,), -5.0, device="cuda")
+        at = (-block.data_ptr()) % 4 + 16 + offset
+        rgb, d = block[at:at + size].view(N * A, H, W, 3), depth[8:8 + N * A * H * W].view(N * A, H, W)
+        extra = (run.material.fill_(254), run.hit.fill_(-7), run.face.fill_(9)) if aux else ()
+        run.batch.render(rgb, d, *extra, stream=_stream())
+        torch.cuda.synchronize()
+        assert (block[:at] == 171).all() and (block[at + size:] == 171).all()
+        assert (depth[:8] == -5.0).all() and (depth[8 + N * A * H * W:] == -5.0).all()
+        assert (np.abs(rgb.cpu().numpy().astype(int) - ref.rgb.astype(int)).max(axis=-1)[clear] <= 1).all()
+        assert (np.abs(d.cpu().numpy() - ref.depth)[clear] <= 1e-4 * np.abs(ref.depth)[clear]).all()
+        if aux:
+            assert (run.hit.cpu().numpy()[clear] == ref.hit_index[clear]).all()
+            assert (run.face.cpu().numpy()[clear] == ref.face[clear]).all() and (run.material.cpu().numpy()[clear] == ref.material[clear]).all()
+
+
 @pytest.mark.parametrize("grid", [(12, 9, 5), (40, 40, 6), (64, 20, 4)])
 def test_outside_rays_with_zero_components_in_the_planes_of_the_grid(lib, grid):
     """Cameras outside, exactly on planes of the grid (its sides among them) and looking along an axis: two components of the
