@@ -169,7 +169,7 @@ struct mv_batch {
     HostStaging staging;
     int forced_layers = 0;                // debug override (0 = automatic)
     // the render's launch shape for `shaped_layers` staged layers: it follows from the configuration and that number
-    mv::RenderParams shape{};
+    mv::RenderParams shape[2];            // without and with auxiliary outputs
     size_t shape_lds_bytes = 0;
     int shaped_layers = -1;
 
@@ -259,9 +259,10 @@ static mv::SideWork camera_work(const mv_batch* b, const float* cams, const int3
     return s;
 }
 
-// Launch shape of the render kernel: image tiling, strips of tiles per workgroup, the work list per XCD.
+// Launch shape of the render kernel: image tiling, strips of tiles per workgroup, the work list per XCD.  `aux`: for launches
+// with auxiliary outputs.
 static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::GridLayout& layout, const mv::LdsPlan& plan,
-                        const char* who)
+                        const char* who, bool aux = false)
 {
     const int num_obs = cfg.num_envs * cfg.agents_per_env;
     p.g = layout;
@@ -275,6 +276,11 @@ static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::Gri
     p.tiles_per_obs = p.tiles_x * tiles_y;
     int tpb = cfg.tiles_per_block;
     int tpb_tail = 0;                                   // 0: no shorter strips at the end of an XCD's work
+    // workgroups the chip holds at a time
+    long long per_cu = (long long)(mv::kLdsBudget / plan.bytes);
+    if (per_cu > 32 / (p.threads / 64)) per_cu = 32 / (p.threads / 64);
+    if (per_cu < 1) per_cu = 1;
+    const long long resident = 256 * per_cu;
     if (tpb <= 0) {
         // Strips of an observation per workgroup.  Two pulls: (1) enough workgroups to fill 256 CUs a few
         // times over (about 6144: on 1024 observations of 40x40x16 worlds, 6 strips per observation render
@@ -293,6 +299,21 @@ static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::Gri
         long long strips = (target_blocks + num_obs - 1) / num_obs;
         if (mv::kLdsBudget / plan.bytes >= 4 && strips < 3) strips = 3;
         if (strips < 1) strips = 1;
+        // Row-scan grids.  Where three strips per observation already fill the chip one and a quarter times over, more would
+        // only stage more (1024 observations of 40x40x16 at 128x72, 6 -> 4 -> 3 strips, the last quarter cut into thirds: step
+        // 48.7, 47.7, 46.6 us; at 130x70 53.6, 52.2, 50.4; 962 of 60x63x28 58.7, 56.3, 53.2; 1012 of 16x16x26 at 64x64 33.6, 31.6,
+        // 30.3).  Launches that write auxiliary outputs as well gain nothing from it (59.8, 60.7, 61.2).  Below that, a strip has
+        // a tile for every 1100 bytes of rows that its workgroup stages, as long as there are enough strips to fill the chip
+        // (378 observations of 26x63x29 with 23 KB of rows, 16 -> 6 strips: step 40.5 -> 33.4 us).
+        if (layout.fast && !aux) {
+            if (12 * num_obs >= 5 * resident) strips = strips < 3 ? strips : 3;
+            else if (strips * num_obs > resident) {
+                long long most = (long long)p.tiles_per_obs * 1100 / (long long)plan.row_bytes;
+                const long long fill = (resident + num_obs - 1) / num_obs;
+                if (most < fill) most = fill;
+                if (strips > most) strips = most;
+            }
+        }
         tpb = (int)((p.tiles_per_obs + strips - 1) / strips);
         // Two tiles per wave at least, or one where even that leaves compute units without a workgroup (4 observations of
         // 128x72: 5.2 -> 4.4 us; 64 observations, 1152 workgroups of two tiles per wave: 8.6 us, of one 9.6).
@@ -313,13 +334,12 @@ static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::Gri
     p.num_obs = num_obs;
     p.obs_per_xcd = (num_obs + mv::kXcds - 1) / mv::kXcds;
     // how much of the range: a twentieth when the launch runs a dozen or more rounds of workgroups through the
-    // chip, up to a tenth when it runs only a few (measured optimum on 1024 and 4096 observations: a tenth)
-    long long per_cu = (long long)(mv::kLdsBudget / plan.bytes);
-    if (per_cu > 32 / (p.threads / 64)) per_cu = 32 / (p.threads / 64);
-    if (per_cu < 1) per_cu = 1;
-    const long long rounds = (long long)p.blocks_per_obs * num_obs / (256 * per_cu);
-    int tail_den = (int)(rounds * 5 / 3);
-    if (tail_den < 10) tail_den = 10;
+    // chip, up to a tenth when it runs only a few (measured optimum on 4096 observations: a tenth), and up to a quarter of
+    // row-scan launches of hardly more than one (1024 observations, 3 strips: a tenth 50.0 us, a fifth 48.3, a quarter 46.6, a
+    // third 47.0)
+    const int least = layout.fast && !aux ? 4 : 10;
+    int tail_den = (int)((long long)p.blocks_per_obs * num_obs * 5 / (3 * resident));
+    if (tail_den < least) tail_den = least;
     if (tail_den > 20) tail_den = 20;
     const int tail_obs = tpb_tail > 0 ? p.obs_per_xcd / tail_den : 0;
     p.obs_body_per_xcd = p.obs_per_xcd - tail_obs;
@@ -696,12 +716,14 @@ int mv_render_batch(mv_batch* b, uint8_t* rgb, float* depth, uint8_t* aux_materi
         b->shaped_layers = -1;
         const mv::LdsPlan plan = mv::plan_lds(b->layout, b->cfg.width, b->cfg.height, b->materials_plus_one, staged,
                                               b->cfg.coarse_level != 0);
-        const int rc = shape_render(b->shape, b->cfg, b->layout, plan, "mv_render_batch");
-        if (rc != MV_OK) return rc;
+        for (int aux = 0; aux < 2; ++aux) {
+            const int rc = shape_render(b->shape[aux], b->cfg, b->layout, plan, "mv_render_batch", aux != 0);
+            if (rc != MV_OK) return rc;
+        }
         b->shape_lds_bytes = plan.bytes;
         b->shaped_layers = staged;
     }
-    mv::RenderParams p = b->shape;
+    mv::RenderParams p = b->shape[aux_material || aux_hit_index || aux_face ? 1 : 0];
     p.staged_layers = staged;
     p.coarse_after = b->cfg.coarse_level != 0 ? mv::kCoarseAfterTurns : -1;
     p.active = b->all_active ? nullptr : b->d_active;

@@ -233,3 +233,17 @@ def test_strips_follow_the_workgroups_a_compute_unit_holds(lib, grid, layers, st
     shape = binding.launch_shape(binding.make_config(256, 2, grid, 16, 128, 72), layers)
     assert (163840 // shape.lds_bytes < 6) == (strips == 6)
     assert shape.blocks_per_obs == strips
+
+
+@pytest.mark.parametrize("obs,grid,image,layers,strips", [
+    (854, (40, 40, 16), (128, 72), 10, 3), (853, (40, 40, 16), (128, 72), 10, 8), (1024, (40, 40, 16), (128, 72), 16, 3),
+    (378, (26, 63, 29), (128, 72), 16, 6), (48, (26, 63, 29), (128, 72), 16, 18), (100, (64, 64, 32), (16, 16), 32, 1),
+    (4096, (40, 40, 16), (128, 72), 10, 3), (1024, (96, 96, 16), (128, 72), 10, 3)])
+def test_strips_of_row_scan_launches_that_fill_the_chip_once(lib, obs, grid, image, layers, strips):
+    """Three strips per observation as soon as those fill the chip one and a quarter times over; below that a tile for every
+    1100 bytes of staged rows, while there are enough strips to fill it once; launches that do not fill it are not changed."""
+    shape = binding.launch_shape(binding.make_config(obs, 1, grid, 16, image[0], image[1]), layers)
+    assert shape.blocks_per_obs == strips
+    resident = 256 * min(163840 // shape.lds_bytes, 2048 // shape.threads)
+    if grid[0] <= 64 and obs * strips > resident and strips > 3:
+        assert shape.tiles_per_block * 1100 >= 16 * layers * (grid[0] + grid[1]) - 1100 or obs * (strips - 1) <= resident
