@@ -169,7 +169,7 @@ struct mv_batch {
     HostStaging staging;
     int forced_layers = 0;                // debug override (0 = automatic)
     // the render's launch shape for `shaped_layers` staged layers: it follows from the configuration and that number
-    mv::RenderParams shape[2];            // without and with auxiliary outputs
+    mv::RenderParams shape[2]{};          // without and with auxiliary outputs
     size_t shape_lds_bytes = 0;
     int shaped_layers = -1;
 
