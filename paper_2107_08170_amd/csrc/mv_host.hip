@@ -674,8 +674,9 @@ int mv_set_cameras(mv_batch* b, const float* cams, const int32_t* self_voxel, in
     return MV_OK;
 }
 
-int mv_render_batch(mv_batch* b, uint8_t* rgb, float* depth, uint8_t* aux_material, int32_t* aux_hit_index,
-                    uint8_t* aux_face, void* hip_stream)
+// mv_render_batch, with an indicator bar (of device fractions) painted over the colours if `bar` is given
+static int render_batch(mv_batch* b, uint8_t* rgb, float* depth, uint8_t* aux_material, int32_t* aux_hit_index,
+                        uint8_t* aux_face, const mv::BarParams* bar, const float* bar_fraction, void* hip_stream)
 {
     if (!b || !rgb || !depth) return fail(MV_ERR_ARG, "mv_render_batch: null argument");
     if ((reinterpret_cast<uintptr_t>(depth) & 3) || (aux_hit_index && (reinterpret_cast<uintptr_t>(aux_hit_index) & 3)))
@@ -729,8 +730,16 @@ int mv_render_batch(mv_batch* b, uint8_t* rgb, float* depth, uint8_t* aux_materi
     p.active = b->all_active ? nullptr : b->d_active;
     p.bits = b->d_bits; p.ztop = b->d_ztop; p.vox = b->borrowed_vox ? b->borrowed_vox : b->d_vox; p.lut = b->d_lut; p.rec = b->d_rec; p.sx = b->d_sx; p.sy = b->d_sy;
     p.rgb = rgb; p.depth = depth; p.aux_material = aux_material; p.aux_hit = aux_hit_index; p.aux_face = aux_face;
+    p.bar_fraction = bar ? bar_fraction : nullptr;
+    if (bar) p.bar = *bar;
     MV_HIP(mv::launch_render(p, b->shape_lds_bytes, (hipStream_t)hip_stream));
     return MV_OK;
+}
+
+int mv_render_batch(mv_batch* b, uint8_t* rgb, float* depth, uint8_t* aux_material, int32_t* aux_hit_index,
+                    uint8_t* aux_face, void* hip_stream)
+{
+    return render_batch(b, rgb, depth, aux_material, aux_hit_index, aux_face, nullptr, nullptr, hip_stream);
 }
 
 int mv_set_active(mv_batch* b, const uint8_t* active, int32_t src_is_device, void* hip_stream)
@@ -747,15 +756,26 @@ int mv_set_active(mv_batch* b, const uint8_t* active, int32_t src_is_device, voi
     return MV_OK;
 }
 
-int mv_draw_bars(mv_batch* b, uint8_t* rgb, const float* fraction, const mv_bar* bar, int32_t src_is_device,
-                 void* hip_stream)
+static int bar_params(const mv_batch* b, const mv_bar* bar, mv::BarParams& bp)
 {
-    if (!b || !rgb || !fraction || !bar) return fail(MV_ERR_ARG, "mv_draw_bars: null argument");
     if (bar->reserved[0] || bar->reserved[1]) return fail(MV_ERR_ARG, "mv_draw_bars: reserved bytes must be 0");
     if (bar->width <= 0 || bar->height <= 0 || bar->x < 0 || bar->y < 0 || bar->x > b->cfg.width - bar->width ||
         bar->y > b->cfg.height - bar->height)
         return fail(MV_ERR_ARG, "mv_draw_bars: bar %dx%d at (%d,%d) does not fit the %dx%d image", bar->width,
                     bar->height, bar->x, bar->y, b->cfg.width, b->cfg.height);
+    bp.x = bar->x; bp.y = bar->y; bp.width = bar->width; bp.height = bar->height;
+    bp.fill_packed = (uint32_t)bar->fill_rgb[0] | ((uint32_t)bar->fill_rgb[1] << 8) | ((uint32_t)bar->fill_rgb[2] << 16);
+    bp.empty_packed = (uint32_t)bar->empty_rgb[0] | ((uint32_t)bar->empty_rgb[1] << 8) | ((uint32_t)bar->empty_rgb[2] << 16);
+    return MV_OK;
+}
+
+int mv_draw_bars(mv_batch* b, uint8_t* rgb, const float* fraction, const mv_bar* bar, int32_t src_is_device,
+                 void* hip_stream)
+{
+    if (!b || !rgb || !fraction || !bar) return fail(MV_ERR_ARG, "mv_draw_bars: null argument");
+    mv::BarParams bp{};
+    const int rc = bar_params(b, bar, bp);
+    if (rc != MV_OK) return rc;
     DeviceScope scope(b->cfg.device);
     if (!scope.ok()) return fail(MV_ERR_HIP, "mv_draw_bars: cannot select device %d", b->cfg.device);
     hipStream_t stream = (hipStream_t)hip_stream;
@@ -767,10 +787,6 @@ int mv_draw_bars(mv_batch* b, uint8_t* rgb, const float* fraction, const mv_bar*
         MV_HIP(hipStreamSynchronize(stream));
         d_fraction = b->d_fraction;
     }
-    mv::BarParams bp{};
-    bp.x = bar->x; bp.y = bar->y; bp.width = bar->width; bp.height = bar->height;
-    bp.fill_packed = (uint32_t)bar->fill_rgb[0] | ((uint32_t)bar->fill_rgb[1] << 8) | ((uint32_t)bar->fill_rgb[2] << 16);
-    bp.empty_packed = (uint32_t)bar->empty_rgb[0] | ((uint32_t)bar->empty_rgb[1] << 8) | ((uint32_t)bar->empty_rgb[2] << 16);
     MV_HIP(mv::launch_bars(rgb, d_fraction, b->all_active ? nullptr : b->d_active, b->num_obs, b->cfg.agents_per_env,
                            b->cfg.width, b->cfg.height, bp, stream));
     return MV_OK;
@@ -854,9 +870,14 @@ int mv_step(mv_batch* b, const mv_step_inputs* in, uint8_t* rgb, float* depth, v
         b->cameras_set = true;
         b->all_active = in->done == nullptr;
     }
-    int rc = MV_OK;
-    if (rc == MV_OK) rc = mv_render_batch(b, rgb, depth, nullptr, nullptr, nullptr, hip_stream);
-    if (rc == MV_OK && in->bar_fraction) rc = mv_draw_bars(b, rgb, in->bar_fraction, in->bar, 1, hip_stream);
+    // A small bar is painted by the render's own waves, a larger one by a launch of its own: every wave looks at all pixels of the
+    // bar in its strip, and the launch saved is worth about two such looks (1024 x 4 cameras of 128x72, painted by the render
+    // or apart, us a step: 27 pixels 133.4 or 134.3, 128 pixels 134.5 or 135.0, 512 pixels 141.8 or 136.5, 2304 pixels 179.5 or
+    // 144.6).  An invalid bar fails in mv_draw_bars, behind the render.
+    mv::BarParams bar{};
+    const bool with_render = in->bar_fraction && (long long)in->bar->width * in->bar->height <= 128 && bar_params(b, in->bar, bar) == MV_OK;
+    int rc = render_batch(b, rgb, depth, nullptr, nullptr, nullptr, with_render ? &bar : nullptr, in->bar_fraction, hip_stream);
+    if (rc == MV_OK && in->bar_fraction && !with_render) rc = mv_draw_bars(b, rgb, in->bar_fraction, in->bar, 1, hip_stream);
     if (rc == MV_OK && in->num_overlay > 0)
         rc = mv_draw_overlay(b, rgb, in->overlay, in->num_overlay, in->overlay_values, in->overlay_values_per_obs, 1,
                              hip_stream);

@@ -83,6 +83,12 @@ inline Divider make_divider(uint32_t d)
 // grids whose x and y rows fit into LDS), cell by cell (the others).
 enum class Scan { kRows, kWindows, kCells };
 
+// indicator bar
+struct BarParams {
+    int32_t x, y, width, height;
+    uint32_t fill_packed, empty_packed;   // r | g<<8 | b<<16
+};
+
 struct RenderParams {
     const uint64_t*     bits;             // [N][env_words]
     const int32_t*      ztop;             // [N] 1 + highest solid layer (0 = empty world)
@@ -115,6 +121,8 @@ struct RenderParams {
     int32_t staged_layers;                // layers 0 .. staged_layers-1 of the bit rows go to LDS
     int32_t window;                       // grids wider than 64 voxels: x and y rows are staged for the window scan
     int32_t coarse_after;                 // < 0: no coarse level; else the ordinary turns a ray makes before it uses it
+    const float* bar_fraction;            // [N*A] filled share of a bar to paint over the colours, or nullptr
+    BarParams bar;
 };
 
 GridLayout make_layout(int X, int Y, int Z);
@@ -156,10 +164,6 @@ hipError_t launch_move_voxels(const int32_t* env, const int32_t* from_voxel, con
                               const uint8_t* material, int count, uint8_t* vox, uint64_t* bits, int32_t* ztop,
                               int num_envs, int voxels_per_env, int num_materials, const GridLayout& g,
                               const HeightFeedback& heights, hipStream_t stream);
-struct BarParams {
-    int32_t x, y, width, height;
-    uint32_t fill_packed, empty_packed;   // r | g<<8 | b<<16
-};
 hipError_t launch_bars(uint8_t* rgb, const float* fraction, const uint8_t* active, int num_obs, int A, int W, int H,
                        const BarParams& bar, hipStream_t stream);
 // overlay primitives, passed to the kernel by value (kind: 0 solid, 1 gauge to the right, 2 gauge upwards)

@@ -1528,6 +1528,13 @@ __device__ __forceinline__ void store_byte(uint32_t lane_offset, uint32_t v, con
     asm volatile("global_store_byte %0, %1, %2" :: "v"(lane_offset), "v"(v), "s"(at) : "memory");
 }
 
+// filled columns of an indicator bar: one float32 multiply, one float32 add, floor, clamp
+__device__ __forceinline__ int bar_columns(float fraction, int width)
+{
+    const float columns = floorf(__fadd_rn(__fmul_rn(fraction, (float)width), 0.5f));
+    return (int)fminf(fmaxf(columns, 0.0f), (float)width);              // NaN falls to 0
+}
+
 // colour of lane+1 within each group of four lanes (lane 3 of the group keeps its own): DPP
 // quad_perm [1,2,3,3]
 __device__ __forceinline__ uint32_t next_in_quad(uint32_t v)
@@ -2068,24 +2075,50 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     if (scans && use_rows && cam_idx < 0) {
         if (FAST && X < 64 && Y < 64) run_tiles(std::true_type{}, std::true_type{}, std::false_type{});
         else run_tiles(std::true_type{}, std::false_type{}, std::false_type{});
-        return;
+    } else if (scans && !use_rows && stage_rows) {
+        run_tiles(std::true_type{}, std::false_type{}, std::true_type{});
+    } else {
+        run_tiles(std::false_type{}, std::false_type{}, std::false_type{});
     }
-    if (scans && !use_rows && stage_rows) { run_tiles(std::true_type{}, std::false_type{}, std::true_type{}); return; }
-    run_tiles(std::false_type{}, std::false_type{}, std::false_type{});
+
+    // The indicator bar over the colours: each wave paints the bar's pixels in the tiles that it has rendered itself, behind
+    // its own stores and without waiting for them (a wave's stores to one address keep their order).  1024 x 4 cameras of 128x72
+    // with bars of 9x3: step 145.0 us with a launch of its own for the bars, 141.7 so.
+    // (The bar is read here, through a pointer that the compiler cannot match with the argument: held in scalar registers through
+    // the tile loop it costs spills.)
+    typedef __attribute__((address_space(4))) const RenderParams* params_ptr;
+    params_ptr again = (params_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(again));
+    if (!AUX && again->bar_fraction) {
+        const BarParams bar{ again->bar.x, again->bar.y, again->bar.width, again->bar.height, again->bar.fill_packed, again->bar.empty_packed };
+        const float* fractions = again->bar_fraction;
+        const int filled = bar_columns(fractions[obs], bar.width);
+        const int first_row = max(bar.y, (int)p.by_tiles_x.quotient((uint32_t)tile_begin) * kTileH);
+        const int end_row = min(bar.y + bar.height, ((int)p.by_tiles_x.quotient((uint32_t)(tile_end - 1)) + 1) * kTileH);
+        const int pixels = max(end_row - first_row, 0) * bar.width;
+        for (int i = (int)__lane_id(); i < pixels; i += 64) {
+            const int r = i / bar.width, c = i - r * bar.width;
+            const int y = first_row + r, x = bar.x + c;
+            const int tile = (y / kTileH) * p.tiles_x + x / kTileW - tile_begin;
+            if (tile < 0 || tile >= tile_end - tile_begin || tile % waves != wave) continue;
+            const uint32_t colour = c < filled ? bar.fill_packed : bar.empty_packed;
+            uint8_t* out = rgb_obs + 3u * (uint32_t)(y * p.W + x);
+            out[0] = (uint8_t)colour;
+            out[1] = (uint8_t)(colour >> 8);
+            out[2] = (uint8_t)(colour >> 16);
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------
-// bars: one workgroup per observation paints the indicator bar over the rendered colours.
+// bars: one workgroup per observation paints the indicator bar over the rendered colours (small bars of mv_step: render_kernel).
 // ------------------------------------------------------------------------------------------
 __global__ void bars_kernel(uint8_t* __restrict__ rgb, const float* __restrict__ fraction,
                             const uint8_t* __restrict__ active, int A, int W, int H, BarParams bar)
 {
     const int obs = blockIdx.x;
     if (active && active[obs / A] == 0) return;
-    // number of filled columns: one float32 multiply, one float32 add, floor, clamp
-    float cols = floorf(__fadd_rn(__fmul_rn(fraction[obs], (float)bar.width), 0.5f));
-    cols = fminf(fmaxf(cols, 0.0f), (float)bar.width);      // NaN falls to 0
-    const int filled = (int)cols;
+    const int filled = bar_columns(fraction[obs], bar.width);
     uint8_t* img = rgb + (size_t)obs * H * W * 3;
     for (int p = threadIdx.x; p < bar.width * bar.height; p += blockDim.x) {
         const int r = p / bar.width, c = p - r * bar.width;

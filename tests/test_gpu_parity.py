@@ -1446,6 +1446,44 @@ def test_single_call_step_against_the_oracle(lib, orc):
     assert e.value.code == binding.MV_ERR_ARG
 
 
+@pytest.mark.parametrize("tiles_per_block", [0, 1, 5])
+@pytest.mark.parametrize("grid", [(14, 11, 5), (70, 12, 4), (200, 190, 8)])
+@pytest.mark.parametrize("image,bars", [((128, 72), [(4, 2, 9, 3), (0, 9, 128, 1), (0, 9, 43, 3), (7, 7, 2, 2), (120, 64, 8, 8), (3, 5, 4, 30), (60, 0, 1, 72), (0, 0, 128, 72)]),
+                                        ((33, 17), [(0, 0, 33, 1), (31, 15, 2, 2), (6, 7, 11, 3), (32, 0, 1, 17), (0, 0, 33, 17)])])
+def test_bar_of_a_step_is_the_bar_painted_afterwards(lib, grid, image, bars, tiles_per_block):
+    """Bars of up to 128 pixels are painted by the waves that rendered the tiles, others by a launch: the same
+    pixels as mv_draw_bars behind a step without one, wherever the bar lies across tiles and strips, and finished
+    environments keep their frames."""
+    W, H = image
+    rng = np.random.default_rng(W + grid[0])
+    N, A, M = 5, 3, 6
+    spec = _mini_spec(N, A, grid, W, H, M)
+    vox, pal = synth.random_world(rng, N, grid, 0.1, M)
+    cams = torch.from_numpy(synth.random_cameras(rng, N * A, grid, margin=0.0)).cuda()
+    cams[1, :3] = torch.tensor([-3.0, 4.0, 2.0])                       # outside
+    cams[2, :3] = torch.tensor([1e5, 4.0, 2.0])                        # far outside
+    done = torch.tensor([0, 0, 1, 0, 0], dtype=torch.uint8, device="cuda")
+    fraction = torch.from_numpy(rng.uniform(-0.2, 1.2, N * A).astype(np.float32)).cuda()
+    fraction[0], fraction[3], fraction[4] = float("nan"), 0.0, 1.0
+    run = _gpu_for(spec, vox, pal, cams.cpu().numpy(), aux=False, tiles_per_block=tiles_per_block)
+    for x, y, width, height in bars:
+        bar = dict(x=x, y=y, width=width, height=height, fill_rgb=(220, 40, 41), empty_rgb=(1, 2, 3))
+        frames = []
+        for together in (True, False):
+            rgb = torch.full((N * A, H, W, 3), 9, dtype=torch.uint8, device="cuda")
+            depth = torch.full((N * A, H, W), -1.0, device="cuda")
+            extra = dict(bar_fraction=fraction, bar=bar) if together else {}
+            run.batch.step(cams, rgb, depth, done=done, stream=_stream(), **extra)
+            if not together:
+                before = rgb.clone()
+                run.batch.draw_bars(rgb, fraction, stream=_stream(), **bar)
+            torch.cuda.synchronize()
+            frames.append((rgb, depth))
+        assert torch.equal(frames[0][0], frames[1][0]) and torch.equal(frames[0][1], frames[1][1])
+        assert not torch.equal(before, frames[0][0])
+        assert (frames[0][0].view(N, A, H, W, 3)[2] == 9).all()
+
+
 def test_step_replays_from_a_hip_graph(lib, orc):
     """The device-source calls enqueue kernels only (no allocation, no synchronisation, no memset), so a
     step can be captured once into a HIP graph and replayed: every replay, with fresh cameras and
