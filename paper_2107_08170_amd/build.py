@@ -14,6 +14,12 @@ ROOT = os.path.dirname(PKG_DIR)
 LIB_PATH = os.path.join(PKG_DIR, "libmv.so")
 SOURCES = ("csrc/mv_host.hip", "csrc/mv_kernels.hip")
 HEADERS = ("csrc/mv_internal.h", "../include/mv.h")
+COMPILE_FLAGS = ("-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
+                 # packed-FP32 instructions are kept out of the generated code on purpose
+                 "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                 "-ffp-contract=off", "-fno-fast-math",
+                 "-Wall", "-Wno-unused-command-line-argument",
+                 "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG_DIR, "csrc"))
 
 
 def _hipcc() -> str:
@@ -32,13 +38,7 @@ def is_stale() -> bool:
 
 def build(verbose: bool = False) -> str:
     """Compile every HIP source for gfx950 into libmv.so (always recompiles)."""
-    cmd = [_hipcc(), "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
-           # packed-FP32 instructions are kept out of the generated code on purpose
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-ffp-contract=off", "-fno-fast-math",
-           "-Wall", "-Wno-unused-command-line-argument",
-           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG_DIR, "csrc"),
-           "-o", LIB_PATH] + [os.path.join(PKG_DIR, s) for s in SOURCES]
+    cmd = [_hipcc(), *COMPILE_FLAGS, "-shared", "-o", LIB_PATH] + [os.path.join(PKG_DIR, s) for s in SOURCES]
     if verbose:
         print(" ".join(cmd), flush=True)
     proc = subprocess.run(cmd, capture_output=True, text=True)
@@ -48,6 +48,14 @@ def build(verbose: bool = False) -> str:
     if verbose and proc.stderr:
         sys.stderr.write(proc.stderr)
     return LIB_PATH
+
+
+def assembly(source: str, path: str) -> str:
+    """Write the gfx950 assembly that build() makes of one of SOURCES to `path` and return it."""
+    subprocess.run([_hipcc(), *COMPILE_FLAGS, "--cuda-device-only", "-S", "-o", path, os.path.join(PKG_DIR, source)],
+                   check=True, capture_output=True, text=True)
+    with open(path) as f:
+        return f.read()
 
 
 if __name__ == "__main__":

@@ -663,11 +663,12 @@ __device__ __forceinline__ float tiny_int(uint32_t v) { return __uint_as_float(v
 __device__ __forceinline__ float tiny_to_float(float t) { return (t * 0x1p127f) * 0x1p22f; }        // the number as a float
 __device__ __forceinline__ float float_to_tiny(float v) { return (v * 0x1p-127f) * 0x1p-22f; }      // and back (whole numbers below 2^24)
 
-// a value all lanes share, held in a vector register
+// a value all lanes share, held in a vector register.  (The compiler often brings the scalar back from a spill with a
+// v_readlane straight before, which needs two wait states between; it puts them in only in front of instructions of its own.)
 __device__ __forceinline__ float in_vector(float v)
 {
     float r;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "s"(v));
+    asm volatile("s_nop 1\n\tv_mov_b32 %0, %1" : "=v"(r) : "s"(v));
     return r;
 }
 
