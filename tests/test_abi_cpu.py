@@ -247,3 +247,10 @@ def test_strips_of_row_scan_launches_that_fill_the_chip_once(lib, obs, grid, ima
     resident = 256 * min(163840 // shape.lds_bytes, 2048 // shape.threads)
     if grid[0] <= 64 and obs * strips > resident and strips > 3:
         assert shape.tiles_per_block * 1100 >= 16 * layers * (grid[0] + grid[1]) - 1100 or obs * (strips - 1) <= resident
+
+
+def test_every_file_beside_the_sources_is_built(lib):
+    """No leftover copy of a source stands beside the sources."""
+    from paper_2107_08170_amd import build
+    csrc = os.path.join(build.PKG_DIR, "csrc")
+    assert sorted(os.listdir(csrc)) == sorted(os.path.basename(p) for p in build.SOURCES + build.HEADERS if p.startswith("csrc/"))
