@@ -996,10 +996,10 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
     // class = 8*(y dominant) + 4*(u negative) + 2*(v negative) + (z negative): each funnel shift moves the
     // index up one bit and brings in the sign bit of the next component.  Along v and z a component
     // of -0 counts as positive (the ray never crosses a plane of that axis, and the distance to the
-    // upper plane is never 0 inside the cell): adding the smallest normal number makes it positive and changes no other.
+    // upper plane is never 0 inside the cell): adding +0 turns -0 into +0 and changes nothing else.
     uint32_t q = xm ? 0u : 1u;
     q = __builtin_amdgcn_alignbit(q, __float_as_uint(du), 31);
-    const float dv_ = dv + kSmallest;
+    const float dv_ = dv + 0.0f;
     q = __builtin_amdgcn_alignbit(q, __float_as_uint(dv_), 31);
     q = __builtin_amdgcn_alignbit(q, __float_as_uint(rr.rcp_z), 31);        // the sign of 1/d_z is the sign of d_z
     const uint32_t record = __float_as_uint(tiny_int(q) * (float)kClassStride + tiny_int(classes_addr));
@@ -1010,12 +1010,12 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
         dst[0] = rec[0]; dst[1] = rec[1]; dst[2] = rec[2]; dst[3] = rec[3]; dst[4] = rec[4];
     }
 
-    // 1 / d of a component that may be 0: adding the smallest normal number changes no other component and keeps the
-    // reciprocal finite (8.5e37), for -0 as for +0 on the positive side
+    // 1 / |d| of a component that may be 0: adding the smallest normal number to the magnitude keeps the reciprocal finite (at
+    // most 8.5e37) and changes no component of 2^-101 or more.  (Added to the signed component it would take those just below
+    // 0 to 0 or to a denormal number, whose reciprocal is infinite.)
     const float dua = fabsf(du);
-    const float inv_u = __builtin_amdgcn_rcpf(fabsf(du + kSmallest));
-    const float rcp_v = __builtin_amdgcn_rcpf(dv_), rcp_z = rr.rcp_z;
-    const float dt_v = fabsf(rcp_v), dt_z = fabsf(rcp_z);
+    const float inv_u = __builtin_amdgcn_rcpf(dua + kSmallest);
+    const float dt_v = __builtin_amdgcn_rcpf(fabsf(dv) + kSmallest), rcp_z = rr.rcp_z, dt_z = fabsf(rcp_z);
     // first crossing on an axis: the distance to the first plane in the ray's direction times |1/d| (along z: from
     // the image row's record, see RowRecord)
     float t0_v, t0_z, t_end;
@@ -1031,7 +1031,7 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
             u32x4* dst = reinterpret_cast<u32x4*>(&e);
             dst[0] = rec[0]; dst[1] = rec[1];
         }
-        const float Pv = __int_as_float(c.i0), last_v = __int_as_float(c.pad);
+        const float Pv = __int_as_float(c.i0), last_v = __int_as_float(c.pad), rcp_v = copysignf(dt_v, dv_);
         const float near_u = e.near_u * inv_u, near_v = c.dist_v * dt_v, near_z = rr.t0_z;
         const float t_far = vmin3(e.far_u * inv_u, c.nv_max * dt_v, rr.tend_z);
         const float t_near = vmax3(near_u, near_v, near_z);
@@ -1200,7 +1200,7 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
             "v_cmpx_lt_f32_e64 %[mgo], v51, %[tend]\n\t"                                \
             "s_cbranch_execz 2f\n\t"
 #define MV_ASM_NEXT_ROW                                                                 \
-            "v_fma_f32 %[tv], %[nv], |%[rv]|, %[t0v]\n\t"                               \
+            "v_fma_f32 %[tv], %[nv], %[dtv], %[t0v]\n\t"                                \
             "v_fma_f32 %[tz], %[nz], |%[rz]|, %[t0z]\n\t"
 #define MV_ASM_READ(INC)                                                                \
             "v_add_f32_e32 v55, v55, %[szd]\n\t"                                       \
@@ -1253,7 +1253,7 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
                   [tv] "=&v"(t_v), [tz] "=&v"(t_z), [ia] "+&v"(i_a), [row] "+&v"(row), "+&{v55}"(row_addr),             \
                   [nv] "=&{v49}"(n_v), [nz] "=&{v48}"(n_z)                                                            \
                 : [tend] "v"(t_end), [du] "v"(du), [pu] "v"(c.Pu), [svz] "v"(c.row_step_vz), [szd] "v"(c.row_step_z), \
-                  [rv] "v"(rcp_v),                                                                                    \
+                  [dtv] "v"(dt_v),                                                                                    \
                   [rz] "v"(rcp_z), [t0v] "{v50}"(t0_v), [t0z] "v"(t0_z), [um1] "v"(c.um1)                             \
                 : "vcc", "scc", "memory", "v51", "v53"
         if (kNarrow) asm volatile(MV_ASM_LOOP(MV_ASM_CELL_NARROW) MV_ASM_OPERANDS);

@@ -872,6 +872,29 @@ def test_outside_rays_with_zero_components_in_the_planes_of_the_grid(lib, grid):
     assert (a.hit_index[middle, H // 2, W // 2] >= 0).any() and (a.hit_index[middle, H // 2, W // 2] < 0).any()
 
 
+@pytest.mark.parametrize("outside", [False, True])
+@pytest.mark.parametrize("grid", [(24, 11, 6), (64, 11, 6), (70, 11, 6)])
+def test_direction_components_next_to_zero(lib, orc, grid, outside):
+    """Yaws of which the smallest float32 numbers are left (a turn that has died away), denormal ones and those around the
+    smallest normal one among them: in an image of odd width the middle column's ray has such a y component."""
+    X, Y, Z = grid
+    rng = np.random.default_rng(X)
+    W, H, M = 9, 25, 6
+    tiny = [s * v for v in (1e-45, 5e-39, 1.1754942e-38, 2.0 ** -126, 1.2e-38, 2e-38, 2.0 ** -125, 3e-38, 1e-36, 1e-30, 1e-20, 0.0) for s in (-1, 1)]
+    cams = np.array([(-3.5 if outside else 2.5, y, 4.3, yaw, pitch) for yaw in tiny for y in (3.3, 7.75) for pitch in (-0.4, 0.1)], np.float32)
+    vox, pal = synth.random_world(rng, 1, grid, 0.02, M)
+    vox[:, 0] = np.where(rng.random((1, Y, X)) < 0.9, 1, 0)
+    vox[:, 1:, :, :6] = 0
+    vox[:, :, :, -1] = 2
+    spec = _mini_spec(1, len(cams), grid, W, H, M)
+    run = _gpu_for(spec, vox, pal, cams)
+    run.render()
+    g, ref = run.numpy(), _oracle_for(orc, spec, vox, pal, cams).render()
+    _pixelwise_rule(g, ref, f"components next to zero, grid {grid}")
+    middle = ref.face[:, :, W // 2]
+    assert (middle == 5).any() and (middle == 0).any() and (ref.edge_margin[:, :, W // 2] >= parity.EDGE_MARGIN).any()
+
+
 @pytest.mark.parametrize("grid,image,aux", [((48, 44, 6), (48, 16), True), ((48, 44, 6), (48, 16), False), ((64, 64, 6), (40, 24), True),
                                             ((63, 64, 5), (40, 24), False), ((48, 44, 6), (33, 17), False), ((64, 40, 6), (33, 17), True)])
 def test_rays_that_pass_many_rows(lib, orc, grid, image, aux):
