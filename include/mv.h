@@ -346,7 +346,7 @@ const char* mv_last_error(void);
  *                        that holds a solid voxel (0 for an empty grid).
  *   mv_debug_camera_records : device pointer to the [N*A] 64-byte camera records
  *                        (float P[3], F[3], R[3], U[3]; int32 self_lo, self_hi; int32 place: 0 in the grid, 1
- *                        outside, 2 far outside or not a number; int32 layer: floor(P_z) clamped to the grid).
+ *                        outside, 2 far outside, outside by less than 1e-28 or not a number; int32 layer: floor(P_z) clamped to the grid).
  *   mv_debug_set_staged_layers : the render kernel keeps only the lowest layers of a grid on chip, as many
  *                        as the tallest world uploaded so far needs (it learns that number from its own
  *                        kernels, without synchronising); an environment that needs more is traced

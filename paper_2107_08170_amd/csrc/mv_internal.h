@@ -18,12 +18,16 @@ struct alignas(64) CameraRecord {
 };
 constexpr int kPlaceInGrid = 0;           // inside the grid's box or on its boundary
 constexpr int kPlaceOutside = 1;          // outside it, no coordinate beyond kNearOutside
-constexpr int kPlaceFarOutside = 2;       // further away, or a position that is not a number
+constexpr int kPlaceFarOutside = 2;       // further away, outside by less than kHair, or a position that is not a number
 // So near, the point where a ray enters the grid is good to a small fraction of a voxel in float32 (the spacing of
 // float32 numbers at 4096 is 5e-4), which the row scan from that point relies on.  (Against a trace in float64 it is no
 // further off than the per-cell tracer at any distance: at 4000 voxels around 40x40x16 it differs in 12 of 184 320 pixels,
 // whose rays pass a voxel edge within 1.5e-4 voxels, the per-cell tracer in 14, within 3.8e-4.)
 constexpr float kNearOutside = 4096.0f;
+// Negative coordinates nearer to 0 than this (they are what is left of a value that has died away) are left to the per-cell
+// tracer as well: the row scan has a finite 1/d for a ray that does not move along an axis, and such a distance times it is
+// small enough to pass for a way into the grid.  (On the far sides float32 numbers are 1e-7 apart.)
+constexpr float kHair = 1e-28f;
 static_assert(sizeof(CameraRecord) == 64, "camera record must be 64 bytes");
 
 // A wave renders a tile of kTileW x kTileH = 64 pixels.  8 x 8 keeps the rays of a wave most alike; 16 x 4 would

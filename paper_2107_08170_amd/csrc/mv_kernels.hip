@@ -132,7 +132,8 @@ __device__ __forceinline__ void write_camera(const SideWork& s, int o)
     const bool in_grid = r.P[0] >= 0.0f && r.P[0] <= (float)s.X && r.P[1] >= 0.0f && r.P[1] <= (float)s.Y &&
                          r.P[2] >= 0.0f && r.P[2] <= (float)s.Z;
     const bool near = fabsf(r.P[0]) <= kNearOutside && fabsf(r.P[1]) <= kNearOutside && fabsf(r.P[2]) <= kNearOutside;
-    r.place = in_grid ? kPlaceInGrid : (near ? kPlaceOutside : kPlaceFarOutside);
+    const bool hair = (r.P[0] < 0.0f && r.P[0] > -kHair) || (r.P[1] < 0.0f && r.P[1] > -kHair) || (r.P[2] < 0.0f && r.P[2] > -kHair);
+    r.place = in_grid ? kPlaceInGrid : (near && !hair ? kPlaceOutside : kPlaceFarOutside);
     r.layer = min(max((int)floorf(r.P[2]), 0), s.Z - 1);
     s.rec[o] = r;
 }
@@ -1634,7 +1635,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     // needs).  A taller world is traced through the rows in global memory, cell by cell; the pack or the edit that made it
     // tall has told the host, so that a later launch reserves enough.
     const bool use_rows = scans && origin_in_grid && zlim <= p.staged_layers;
-    // A camera outside the grid scans rows from where its rays enter it; far outside, and for positions that are not
+    // A camera outside the grid scans rows from where its rays enter it; far outside, by a hair, and for positions that are not
     // numbers, cell by cell.
     const int solid_layers = max(ztop, 1);
     const bool outside_rows = scans && place == kPlaceOutside && solid_layers <= p.staged_layers;

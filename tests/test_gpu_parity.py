@@ -872,6 +872,47 @@ def test_outside_rays_with_zero_components_in_the_planes_of_the_grid(lib, grid):
     assert (a.hit_index[middle, H // 2, W // 2] >= 0).any() and (a.hit_index[middle, H // 2, W // 2] < 0).any()
 
 
+@pytest.mark.parametrize("grid", [(12, 9, 5), (64, 20, 4), (70, 9, 5)])
+def test_outside_by_a_hair(lib, orc, grid):
+    """Cameras outside the grid by less than any distance that matters, solid voxels straight behind the side they are at:
+    looking away they see nothing at all; looking along that side, the pixels whose ray stays in its plane (a component
+    of exactly 0) see nothing; looking in they see what the oracle sees."""
+    X, Y, Z = grid
+    rng = np.random.default_rng(X)
+    W, H, M = 15, 9, 6
+    hairs = (-1e-38, -3e-37, -1e-33, -2e-31, -1e-28, -1e-12)
+    mid = (X / 2 + 0.25, Y / 2 - 0.25, Z / 2 + 0.25)
+    views, away, along = [], [], []
+    for hair in hairs:
+        for axis, yaws, pitches in ((0, (np.pi, 0.0, np.pi / 2), (0.0, 0.0, 0.0)), (1, (-np.pi / 2, np.pi / 2, 0.0), (0.0, 0.0, 0.0)),
+                                    (2, (0.3, 0.3, 0.0), (-1.4, 1.4, 0.0))):
+            for kind in range(3):
+                at = list(mid)
+                at[axis] = hair
+                views.append((*at, yaws[kind], pitches[kind]))
+                away.append(kind == 0)
+                along.append((kind == 2) * axis)                # (yaw pi/2: the x component is tiny, not 0)
+    cams, away, along = np.array(views, np.float32), np.array(away), np.array(along)
+    assert (cams[:, :3].min(axis=1) < 0).all()
+    vox, pal = synth.random_world(rng, 1, grid, 0.1, M)
+    vox[:, :, :, 0] = np.where(rng.random((1, Z, Y)) < 0.7, 1, 0)
+    vox[:, :, 0] = np.where(rng.random((1, Z, X)) < 0.7, 2, 0)
+    vox[:, 0] = np.where(rng.random((1, Y, X)) < 0.7, 3, 0)
+    spec = _mini_spec(1, len(cams), grid, W, H, M)
+    run = _gpu_for(spec, vox, pal, cams, hfov_rad=0.4)
+    run.render()
+    g, ref = run.numpy(), _oracle_for(orc, spec, vox, pal, cams, hfov_rad=0.4).render()
+    assert (ref.hit_index[away] == -1).all()
+    assert (g.hit_index[away] == -1).all(), [tuple(cams[o]) for o in np.flatnonzero(away) if (g.hit_index[o] >= 0).any()]
+    assert (g.hit_index[along == 1][:, :, W // 2] == -1).all() and (g.hit_index[along == 2][:, H // 2] == -1).all()
+    looking_in = ~away & (along == 0)
+    keep = lambda out: parity.GpuOut(*(getattr(out, f)[looking_in] for f in ("rgb", "depth", "material", "hit_index", "face")))
+    ref_in = keep(ref)
+    ref_in.edge_margin = ref.edge_margin[looking_in]
+    _pixelwise_rule(keep(g), ref_in, f"a hair outside, grid {grid}")
+    assert (ref_in.hit_index >= 0).any()
+
+
 @pytest.mark.parametrize("outside", [False, True])
 @pytest.mark.parametrize("grid", [(24, 11, 6), (64, 11, 6), (70, 11, 6)])
 def test_direction_components_next_to_zero(lib, orc, grid, outside):
