@@ -338,7 +338,9 @@ static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::Gri
     // row-scan launches of hardly more than one (1024 observations, 3 strips: a tenth 50.0 us, a fifth 48.3, a quarter 46.6, a
     // third 47.0)
     const int least = layout.fast && !aux ? 4 : 10;
-    int tail_den = (int)((long long)p.blocks_per_obs * num_obs * 5 / (3 * resident));
+    // (row-scan launches without auxiliary outputs by their rounds and parts of one, the others by whole rounds)
+    const long long workgroups = (long long)p.blocks_per_obs * num_obs;
+    int tail_den = layout.fast && !aux ? (int)(workgroups * 5 / (3 * resident)) : (int)(workgroups / resident * 5 / 3);
     if (tail_den < least) tail_den = least;
     if (tail_den > 20) tail_den = 20;
     const int tail_obs = tpb_tail > 0 ? p.obs_per_xcd / tail_den : 0;

@@ -249,6 +249,20 @@ def test_strips_of_row_scan_launches_that_fill_the_chip_once(lib, obs, grid, ima
         assert shape.tiles_per_block * 1100 >= 16 * layers * (grid[0] + grid[1]) - 1100 or obs * (strips - 1) <= resident
 
 
+@pytest.mark.parametrize("grid,image", [((96, 96, 16), (128, 72)), ((96, 96, 16), (256, 144)), ((70, 40, 8), (130, 70)), ((200, 190, 8), (128, 72)),
+                                        ((128, 128, 40), (128, 72))])
+def test_short_strips_at_the_end_of_wide_launches(lib, grid, image):
+    """Window-scan and per-cell launches: a tenth of the observations, less by the whole rounds of workgroups, down to a
+    twentieth."""
+    for obs in (100, 300, 512, 700, 1000, 1024, 1500, 2000, 3000, 4096, 8192):
+        shape = binding.launch_shape(binding.make_config(obs, 1, grid, 16, image[0], image[1]), 0)
+        resident = 256 * max(1, min(163840 // shape.lds_bytes, 2048 // shape.threads))
+        rounds = shape.blocks_per_obs * obs // resident
+        share = min(max(rounds * 5 // 3, 10), 20)
+        tail = shape.obs_per_xcd - shape.obs_body_per_xcd
+        assert tail == shape.obs_per_xcd // share or (tail == 0 and shape.tiles_per_block == shape.tiles_per_block_tail), (obs, tail, share)
+
+
 def test_every_file_beside_the_sources_is_built(lib):
     """No leftover copy of a source stands beside the sources."""
     from paper_2107_08170_amd import build
