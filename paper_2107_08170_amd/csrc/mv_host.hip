@@ -299,20 +299,26 @@ static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::Gri
         long long strips = (target_blocks + num_obs - 1) / num_obs;
         if (mv::kLdsBudget / plan.bytes >= 4 && strips < 3) strips = 3;
         if (strips < 1) strips = 1;
-        // Row-scan grids.  Where three strips per observation already fill the chip one and a quarter times over, more would
-        // only stage more (1024 observations of 40x40x16 at 128x72, 6 -> 4 -> 3 strips, the last quarter cut into thirds: step
-        // 48.7, 47.7, 46.6 us; at 130x70 53.6, 52.2, 50.4; 962 of 60x63x28 58.7, 56.3, 53.2; 1012 of 16x16x26 at 64x64 33.6, 31.6,
-        // 30.3).  Launches that write auxiliary outputs as well gain nothing from it (59.8, 60.7, 61.2).  Below that, a strip has
-        // a tile for every 1100 bytes of rows that its workgroup stages, as long as there are enough strips to fill the chip
-        // (378 observations of 26x63x29 with 23 KB of rows, 16 -> 6 strips: step 40.5 -> 33.4 us).
+        // Row-scan grids, without auxiliary outputs: fewer strips than that where fewer fill the chip, because every strip stages
+        // the rows again.  One round of workgroups is enough as long as it takes five strips per observation or more; with
+        // fewer, longer ones an uneven last part of a round weighs more, and it takes a round and a quarter.  At least three
+        // strips (see above) and as many as leave none with more than 64 tiles.
+        // Steps of 40x40x16, us, 24 workgroups per CU -> so many strips -> other numbers of strips.  128x72: 200 observations 25.3
+        // (18 strips) -> 23.0 (11) -> 24.7 (6); 378 35.5 (16) -> 31.4 (6) -> 32.3 (8); 600 44.9 (11) -> 41.5 (5) -> 42.1 (8); 750
+        // 48.6 (9) -> 45.9 (4) -> 48.3 (3); 853 53.9 (8) -> 50.8 (4) -> 51.3 (3); 950 55.2 (7) -> 52.1 (3) -> 52.9 (4).  256x144:
+        // 378 61.7 (17) -> 60.1 (8; 9 are taken) -> 68.5 (5); 854 112.1 (8) -> 112.0 (8) -> 124.7 (3).  Over 3207 launches drawn from 8 to 64
+        // voxels a side, 48x48 to 512x288 pixels and 20 to 4000 observations, against 24 workgroups per CU with a tenth as tail: a
+        // step 6 % faster in the mean, 4 in 1000 more than 4 % slower.  Launches with auxiliary outputs gain nothing (1024
+        // observations, 6 -> 4 -> 3 strips: 59.8, 60.7, 61.2).
         if (layout.fast && !aux) {
-            if (12 * num_obs >= 5 * resident) strips = strips < 3 ? strips : 3;
-            else if (strips * num_obs > resident) {
-                long long most = (long long)p.tiles_per_obs * 1100 / (long long)plan.row_bytes;
-                const long long fill = (resident + num_obs - 1) / num_obs;
-                if (most < fill) most = fill;
-                if (strips > most) strips = most;
+            long long fill = (resident + num_obs - 1) / num_obs;
+            if (fill < 5) {
+                fill = (5 * resident + 4 * num_obs - 1) / (4 * num_obs);
+                if (fill > 5) fill = 5;
             }
+            if (fill < 3) fill = 3;
+            if (fill < (p.tiles_per_obs + 63) / 64) fill = (p.tiles_per_obs + 63) / 64;
+            if (strips > fill) strips = fill;
         }
         tpb = (int)((p.tiles_per_obs + strips - 1) / strips);
         // Two tiles per wave at least, or one where even that leaves compute units without a workgroup (4 observations of
@@ -320,7 +326,7 @@ static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::Gri
         const long long two_each = (long long)num_obs * ((p.tiles_per_obs + 2 * waves - 1) / (2 * waves));
         const int min_tpb = two_each <= 256 ? waves : waves * 2;
         if (tpb < min_tpb) tpb = min_tpb;
-        // The last twentieth (to tenth, see below) of every XCD's observations is cut into strips a third as long: the XCD's
+        // The last observations of every XCD (a twentieth to a quarter of them, see below) are cut into strips a third as long: the XCD's
         // work then ends with short workgroups (4096 x 2 observations, 3 strips of 48 tiles: tail strips of
         // 16 tiles render 1 % faster than none, strips of 24 or 12 tiles gain less; 1024 x 4 observations:
         // 3.6 % faster).
@@ -334,15 +340,15 @@ static int shape_render(mv::RenderParams& p, const mv_config& cfg, const mv::Gri
     p.num_obs = num_obs;
     p.obs_per_xcd = (num_obs + mv::kXcds - 1) / mv::kXcds;
     // how much of the range: a twentieth when the launch runs a dozen or more rounds of workgroups through the
-    // chip, up to a tenth when it runs only a few (measured optimum on 4096 observations: a tenth), and up to a quarter of
-    // row-scan launches of hardly more than one (1024 observations, 3 strips: a tenth 50.0 us, a fifth 48.3, a quarter 46.6, a
-    // third 47.0)
-    const int least = layout.fast && !aux ? 4 : 10;
-    // (row-scan launches without auxiliary outputs by their rounds and parts of one, the others by whole rounds)
+    // chip, up to a tenth when it runs only a few (measured optimum on 4096 observations: a tenth).  A quarter of row-scan
+    // launches without auxiliary outputs that run less than three rounds (128x72, three strips of 40x40x16, a tenth -> a quarter,
+    // us: 1024 observations, one round and a half, 50.0 -> 46.6 with a fifth at 48.3 and a third at 47.0; 1500, 2.2 rounds, 74.1 ->
+    // 72.6; 2048, three rounds, 92.8 -> 93.8; 3000 125.4 -> 128.9).
     const long long workgroups = (long long)p.blocks_per_obs * num_obs;
-    int tail_den = layout.fast && !aux ? (int)(workgroups * 5 / (3 * resident)) : (int)(workgroups / resident * 5 / 3);
-    if (tail_den < least) tail_den = least;
+    int tail_den = (int)(workgroups / resident * 5 / 3);
+    if (tail_den < 10) tail_den = 10;
     if (tail_den > 20) tail_den = 20;
+    if (layout.fast && !aux && workgroups < 3 * resident) tail_den = 4;
     const int tail_obs = tpb_tail > 0 ? p.obs_per_xcd / tail_den : 0;
     p.obs_body_per_xcd = p.obs_per_xcd - tail_obs;
     p.tiles_per_block_tail = tail_obs > 0 ? tpb_tail : tpb;

@@ -134,7 +134,6 @@ GridLayout make_layout(int X, int Y, int Z);
 // LDS plan of the render kernel for a batch; returns 0 if the grid cannot be staged at all.
 struct LdsPlan {
     size_t bytes;         // dynamic LDS per workgroup
-    size_t row_bytes;     // of which rows
     int    threads;       // workgroup size that keeps a CU busy with that much LDS
     bool   window;        // a grid wider than 64 voxels whose x and y rows fit (else: all x rows, traced cell by cell)
 };

@@ -89,7 +89,6 @@ LdsPlan plan_lds(const GridLayout& g, int W, int H, int materials_plus_one, int 
     }
     if (m.total > kLdsBudget) return LdsPlan{};                             // bytes == 0: does not fit
     plan.bytes = m.total;
-    plan.row_bytes = m.total - m.rows;
     // as many waves per workgroup as fill the CU's wave slots with the workgroups its LDS can hold
     // (measured: 64x64x32 grids, two workgroups per CU: 1024 threads render 9 % faster than 512)
     size_t per_cu = kLdsBudget / plan.bytes;

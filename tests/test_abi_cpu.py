@@ -225,28 +225,42 @@ def test_launch_shape_follows_the_staged_layers_and_rejects_what_create_rejects(
     assert e.value.code == binding.MV_ERR_CAPACITY
 
 
-@pytest.mark.parametrize("grid,layers,strips", [((40, 40, 16), 10, 12), ((70, 40, 8), 8, 12), ((80, 64, 10), 9, 12),
+@pytest.mark.parametrize("grid,layers,strips", [((40, 40, 16), 10, 5), ((70, 40, 8), 8, 12), ((80, 64, 10), 9, 12),
                                                 ((96, 96, 16), 10, 6), ((128, 128, 16), 10, 6)])
 def test_strips_follow_the_workgroups_a_compute_unit_holds(lib, grid, layers, strips):
     """About 6144 workgroups for 512 observations, half as many where a wide grid's rows leave room for fewer than six per
-    compute unit."""
+    compute unit.  (A row-scan launch takes a round and a quarter: 520 observations, 12 strips 41.4 us a step, 5 strips 38.5.)"""
     shape = binding.launch_shape(binding.make_config(256, 2, grid, 16, 128, 72), layers)
     assert (163840 // shape.lds_bytes < 6) == (strips == 6)
     assert shape.blocks_per_obs == strips
 
 
-@pytest.mark.parametrize("obs,grid,image,layers,strips", [
-    (854, (40, 40, 16), (128, 72), 10, 3), (853, (40, 40, 16), (128, 72), 10, 8), (1024, (40, 40, 16), (128, 72), 16, 3),
-    (378, (26, 63, 29), (128, 72), 16, 6), (48, (26, 63, 29), (128, 72), 16, 18), (100, (64, 64, 32), (16, 16), 32, 1),
-    (4096, (40, 40, 16), (128, 72), 10, 3), (1024, (96, 96, 16), (128, 72), 10, 3)])
-def test_strips_of_row_scan_launches_that_fill_the_chip_once(lib, obs, grid, image, layers, strips):
-    """Three strips per observation as soon as those fill the chip one and a quarter times over; below that a tile for every
-    1100 bytes of staged rows, while there are enough strips to fill it once; launches that do not fill it are not changed."""
+@pytest.mark.parametrize("obs,grid,image,layers,strips,quarter", [
+    (48, (26, 63, 29), (128, 72), 16, 18, False), (200, (40, 40, 16), (128, 72), 10, 11, True), (378, (40, 40, 16), (128, 72), 10, 6, True),
+    (378, (26, 63, 29), (128, 72), 16, 5, True), (600, (40, 40, 16), (128, 72), 10, 5, True), (750, (40, 40, 16), (128, 72), 10, 4, True),
+    (853, (40, 40, 16), (128, 72), 10, 4, True), (854, (40, 40, 16), (128, 72), 10, 3, True), (1024, (40, 40, 16), (128, 72), 16, 3, True),
+    (2048, (40, 40, 16), (128, 72), 10, 3, False), (4096, (40, 40, 16), (128, 72), 10, 3, False), (854, (40, 40, 16), (256, 144), 10, 8, False),
+    (8192, (64, 64, 32), (256, 144), 16, 3, False), (100, (64, 64, 32), (16, 16), 32, 1, False), (1024, (96, 96, 16), (128, 72), 10, 3, False)])
+def test_strips_of_row_scan_launches(lib, obs, grid, image, layers, strips, quarter):
+    """One round of workgroups where that takes five strips per observation or more, a round and a quarter below, three strips
+    at least and none of more than 64 tiles, never more of them than about 6144 workgroups need; the last quarter in short
+    strips below three rounds."""
     shape = binding.launch_shape(binding.make_config(obs, 1, grid, 16, image[0], image[1]), layers)
     assert shape.blocks_per_obs == strips
-    resident = 256 * min(163840 // shape.lds_bytes, 2048 // shape.threads)
-    if grid[0] <= 64 and obs * strips > resident and strips > 3:
-        assert shape.tiles_per_block * 1100 >= 16 * layers * (grid[0] + grid[1]) - 1100 or obs * (strips - 1) <= resident
+    tail = shape.obs_per_xcd - shape.obs_body_per_xcd
+    assert (tail == shape.obs_per_xcd // 4) == quarter or shape.tiles_per_block_tail == shape.tiles_per_block
+
+
+@pytest.mark.parametrize("grid,layers", [((16, 16, 8), 8), ((40, 40, 16), 10), ((60, 63, 28), 16), ((64, 64, 32), 32), ((64, 64, 60), 60)])
+@pytest.mark.parametrize("image", [(64, 64), (128, 72), (130, 70), (256, 144)])
+def test_strips_do_not_jump_between_neighbouring_numbers_of_observations(lib, grid, layers, image):
+    """One observation more changes the strips of an observation by one, from 260 observations on (below, a strip has few
+    tiles and whole tiles make coarser steps)."""
+    before = None
+    for obs in range(260, 2600):
+        shape = binding.launch_shape(binding.make_config(obs, 1, grid, 16, image[0], image[1]), layers)
+        assert before is None or 0 <= before.blocks_per_obs - shape.blocks_per_obs <= 1, obs
+        before = shape
 
 
 @pytest.mark.parametrize("grid,image", [((96, 96, 16), (128, 72)), ((96, 96, 16), (256, 144)), ((70, 40, 8), (130, 70)), ((200, 190, 8), (128, 72)),
