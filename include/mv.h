@@ -332,7 +332,8 @@ int mv_render_worlds_noalloc(const mv_config* cfg, const uint8_t* voxels, const 
                              const float* cams, const int32_t* self_voxel, uint8_t* rgb, float* depth,
                              void* hip_stream);
 
-/* Free the batch and its device memory (synchronises the device first).  NULL is a no-op. */
+/* Free the batch and its device memory (synchronises the device first).  NULL is a no-op.  The capture of a stream that does
+ * not use the batch goes on. */
 void mv_destroy(mv_batch* batch);
 
 /* Description of the last error on this thread ("" if none).  Never NULL. */

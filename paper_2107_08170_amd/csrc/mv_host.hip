@@ -53,6 +53,18 @@ private:
     int prev_, target_ = -1;
 };
 
+// While a stream is being captured anywhere in the process, freeing memory from a thread in the default mode is refused and
+// ends the capture.  It is no part of a capture here: the thread is relaxed for the duration.
+class RelaxedCapture {
+public:
+    RelaxedCapture() { ok_ = hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess; }
+    ~RelaxedCapture() { if (ok_) (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+
+private:
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+    bool ok_;
+};
+
 }  // namespace
 
 // Host inputs of a call on their way to the GPU: they are copied into the batch's pinned buffer, and the kernels read them
@@ -933,7 +945,9 @@ void mv_destroy(mv_batch* b)
 {
     if (!b) return;
     DeviceScope scope(b->cfg.device);
-    if (scope.ok()) (void)hipDeviceSynchronize();
+    RelaxedCapture relaxed;
+    // (hipFree waits until the device has done all work enqueued so far, before it frees; hipDeviceSynchronize would end a
+    // capture whatever the mode)
     free_batch(b);
 }
 

@@ -1,4 +1,3 @@
-import gc
 import os
 import sys
 
@@ -18,10 +17,3 @@ def orc():
     from oracle import oracle
     oracle.build()
     return oracle
-
-
-def pytest_runtest_setup(item):
-    """Batches that earlier tests left in reference cycles (a frame kept by a caught exception) are destroyed now and not
-    whenever the collector runs next: freeing device memory while a stream is being captured invalidates the capture."""
-    if "captur" in item.name or "graph" in item.name:
-        gc.collect()

@@ -1,6 +1,7 @@
 """GPU parity: the HIP library through its C ABI against the CPU oracle, element by element, on the
 same seeded inputs.  Needs a real MI355X; run with ``-m gpu``."""
 import ctypes as C
+import time
 
 import numpy as np
 import pytest
@@ -1678,6 +1679,61 @@ def test_wide_step_captured_over_low_worlds_replays_over_taller_ones(lib, orc, g
             graph.replay()
             torch.cuda.synchronize()
             parity.compare(run.numpy(), ref, label=f"replay, grid {grid}")
+
+
+def test_batch_destroyed_while_a_step_is_captured(lib, orc):
+    """A batch that is destroyed during another one's capture (by the garbage collector, say) does not end the capture: its
+    memory is freed, after work of other streams, and the graph replays what the oracle renders."""
+    N, A, grid, M, W, H = 3, 2, (16, 12, 5), 6, 40, 24
+    rng = np.random.default_rng(77)
+    vox, pal = synth.random_world(rng, N, grid, 0.1, M)
+    spec = _mini_spec(N, A, grid, W, H, M)
+    views = [synth.random_cameras(rng, N * A, grid, margin=0.0) for _ in range(4)]
+    run = _gpu_for(spec, vox, pal, views[0], aux=False)
+    other = _gpu_for(_mini_spec(64, 2, (40, 40, 16), W, H, M), *synth.random_world(rng, 64, (40, 40, 16), 0.1, M),
+                     synth.random_cameras(rng, 128, (40, 40, 16), margin=0.0), device_src=False)
+    other.render()
+    large = binding.Batch(4096, 1, (64, 64, 32), M, W, H)                           # 800 MB of worlds and rows
+    cams = torch.from_numpy(views[0]).cuda()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    run.batch.step(cams, run.rgb, run.depth, stream=_stream())
+    torch.cuda.synchronize()
+    elsewhere, a = torch.cuda.Stream(), torch.randn(4096, 4096, device="cuda")
+    out = torch.empty_like(a)
+
+    def work(count):
+        with torch.cuda.stream(elsewhere):
+            for _ in range(count):
+                torch.mm(a, a, out=out)
+
+    work(5)
+    torch.cuda.synchronize()
+    start = time.perf_counter()
+    work(40)
+    torch.cuda.synchronize()
+    duration = time.perf_counter() - start
+    before = torch.cuda.mem_get_info()[0]
+    work(200)
+    with torch.cuda.stream(side):
+        graph.capture_begin()
+        start = time.perf_counter()
+        other.batch.close()
+        waited = time.perf_counter() - start
+        large.close()
+        run.batch.step(cams, run.rgb, run.depth, stream=side.cuda_stream)
+        graph.capture_end()
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] > before + (400 << 20)
+    assert waited > duration, (waited, duration)
+    for view in views[1:]:
+        cams.copy_(torch.from_numpy(view))
+        run.rgb.fill_(7)
+        graph.replay()
+        torch.cuda.synchronize()
+        ref = _oracle_for(orc, spec, vox, pal, view).render()
+        clear = ref.edge_margin >= parity.EDGE_MARGIN
+        assert (np.abs(run.numpy().rgb.astype(int) - ref.rgb.astype(int)).max(axis=-1)[clear] <= 1).all()
 
 
 def test_step_captured_over_low_worlds_replays_over_taller_ones(lib, orc):
