@@ -355,8 +355,9 @@ const char* mv_last_error(void);
  *                        (1..Z) so that tests can reach that path; 0 returns to the automatic choice.
  *                        Errors: MV_ERR_ARG, MV_ERR_RANGE.
  *   mv_debug_launch_shape : how a render of this configuration with `staged_layers` layers on chip (0 = all Z)
- *                        is laid out, computed on the host without touching a GPU: *shape receives the LDS bytes and
- *                        threads of a workgroup and the work list (workgroup b of the launch belongs to XCD b mod 8
+ *                        and without auxiliary outputs (with them, strips may be shorter) is laid out, computed on
+ *                        the host without touching a GPU: *shape receives the LDS bytes and threads of a workgroup
+ *                        and the work list (workgroup b of the launch belongs to XCD b mod 8
  *                        and is number s = b div 8 there; an XCD renders the observations x*obs_per_xcd ..
  *                        (x+1)*obs_per_xcd-1 that exist; s < obs_body_per_xcd*blocks_per_obs: observation
  *                        s div blocks_per_obs of the range, strip s mod blocks_per_obs of tiles_per_block tiles;

@@ -891,9 +891,10 @@ int mv_step(mv_batch* b, const mv_step_inputs* in, uint8_t* rgb, float* depth, v
         b->all_active = in->done == nullptr;
     }
     // A small bar is painted by the render's own waves, a larger one by a launch of its own: every wave looks at all pixels of the
-    // bar in its strip, and the launch saved is worth about two such looks (1024 x 4 cameras of 128x72, painted by the render
-    // or apart, us a step: 27 pixels 133.4 or 134.3, 128 pixels 134.5 or 135.0, 512 pixels 141.8 or 136.5, 2304 pixels 179.5 or
-    // 144.6).  An invalid bar fails in mv_draw_bars, behind the render.
+    // bar in its strip, which costs what the launch saves at about 200 pixels (painted by the render or apart, us a step, in turn
+    // on one machine: 1024 x 4 cameras of 128x72 with edits, 27 pixels 135.0 or 136.4, 128 136.3 or 137.1, 256 138.9 or 137.6, 512
+    // 144.5 or 139.3, 2304 180.2 or 146.7; 64 x 2 without edits, 27 pixels 16.2 or 18.0, 128 16.3 or 18.0, 512 17.7 or 18.4, 2304
+    // 24.3 or 19.8).  An invalid bar fails in mv_draw_bars, behind the render.
     mv::BarParams bar{};
     const bool with_render = in->bar_fraction && (long long)in->bar->width * in->bar->height <= 128 && bar_params(b, in->bar, bar) == MV_OK;
     int rc = render_batch(b, rgb, depth, nullptr, nullptr, nullptr, with_render ? &bar : nullptr, in->bar_fraction, hip_stream);

@@ -1066,7 +1066,6 @@ __device__ __forceinline__ Hit trace_rows(uint32_t classes_addr, float dx, float
 
     // crossings made so far along v and z (without sign; the directions sit in the class), and the parameters
     // of the next ones: t_v = n_v*dt_v + t0_v, t_z likewise
-    // (the counters start from the two zero words of the record: registers the load has filled anyway)
     float t_v, t_z, n_v = 0.0f, n_z = 0.0f;
     uint32_t addr = (uint32_t)c.addr0;
     uint64_t r, in_range;
@@ -2083,8 +2082,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     }
 
     // The indicator bar over the colours: each wave paints the bar's pixels in the tiles that it has rendered itself, behind
-    // its own stores and without waiting for them (a wave's stores to one address keep their order).  1024 x 4 cameras of 128x72
-    // with bars of 9x3: step 145.0 us with a launch of its own for the bars, 141.7 so.
+    // its own stores and without waiting for them (a wave's stores to one address keep their order).  Steps with bars of 9x3, us,
+    // with a launch of its own -> so, in turn on one machine: 1024 x 4 cameras of 128x72 with edits 136.4 -> 135.0, 256 x 4 47.8 ->
+    // 46.1, 64 x 2 20.9 -> 19.0.  The look for a bar costs launches without one nothing that stands out from the differences
+    // between two builds: without this block 48.3 / 48.5 (256 x 4), 298.9 / 300.0 (4096 x 2), 51.3 / 51.2 (130x70 pixels), 47.0 /
+    // 47.3 (no batch object), 62.6 / 63.2 (cameras outside), where builds that differ elsewhere only read 48.0 to 49.0 for the first.
     // (The bar is read here, through a pointer that the compiler cannot match with the argument: held in scalar registers through
     // the tile loop it costs spills.)
     typedef __attribute__((address_space(4))) const RenderParams* params_ptr;
