@@ -70,7 +70,7 @@ private:
 // Host inputs of a call on their way to the GPU: they are copied into the batch's pinned buffer, and the kernels read them
 // from there over the link.  That replaces a copy of the runtime's own for every array, which costs about 10 us each, more
 // than such a kernel takes to read its inputs (64 x 2 cameras, an eighth of the worlds, moves and cameras from host arrays,
-// images fetched: a step 321 -> 248 us, of which the images take 150; a new batch's first step 371 -> 297).  The call still
+// images fetched: a step 321 -> 248 us, of which the images take 163; a new batch's first step 371 -> 297).  The call still
 // waits, before it launches anything, until its stream has passed all earlier work: callers rely on that (see the head of
 // mv.h; without the wait the step took 241 us).
 class HostStaging {

@@ -941,7 +941,7 @@ def test_direction_components_next_to_zero(lib, orc, grid, outside):
                                             ((63, 64, 5), (40, 24), False), ((48, 44, 6), (33, 17), False), ((64, 40, 6), (33, 17), True)])
 def test_rays_that_pass_many_rows(lib, orc, grid, image, aux):
     """The row loop counts its first 13 turns by their number and the rest by adding: rays that pass up to about fifty rows
-    along v and z (diagonal views over an empty floor to solids at the rim), found in every turn and lost in every turn."""
+    along v and z (diagonal views over an empty floor to solids at the rim), with a hit after every number of rows up to 29."""
     X, Y, Z = grid
     rng = np.random.default_rng(X * 1000 + Y + image[0])
     N, A, M = 4, 8, 7
@@ -1931,6 +1931,9 @@ def test_coarse_level_gives_the_same_bits(lib, orc):
         vox, pal = synth.random_world(rng, N, grid, 0.04, M)
         cams = synth.random_cameras(rng, N * A, grid, margin=0.0, max_pitch=1.2)
         cases.append((spec, vox, pal, cams, None))
+    # cameras around the grid (theirs is the plain row scan, from a record in the place of the coarse level's)
+    spec = _mini_spec(6, 3, (39, 41, 7), 72, 40, 5)
+    cases.append((spec, *synth.random_world(rng, 6, spec.grid, 0.04, 5), synth.random_cameras(rng, 18, spec.grid, margin=9.0), None))
     for spec, vox, pal, cams, selfv in cases:
         plain = _gpu_for(spec, vox, pal, cams, selfv)
         coarse = _gpu_for(spec, vox, pal, cams, selfv, coarse_level=1)
