@@ -758,6 +758,11 @@ static_assert(sizeof(EntryClass) == 32 && sizeof(ScanClass) + sizeof(EntryClass)
 // Crossing parameters are t = n*|1/d| + t_first (one fused op, error relative to t itself) rather than accumulated.
 // self_lo / self_hi: voxels this camera must not see (-1 = none); callers that have already removed the body
 // from their copy of the rows pass -1.
+// Every cell it looks at lies in the grid, whatever the camera: no first crossing is NaN and every distance between two is
+// finite, so an axis steps only while its parameter is the least of the three and below t_exit, which is at most that same
+// expression at the axis's last plane.  A component below the smallest normal number counts as 0 (its reciprocal is infinite,
+// and 0 times that not a number), and an axis whose first crossing is not a number (unchecked cameras) is never crossed: with
+// NaN among them the comparisons fail one after the other, and z went on for ever.
 __device__ __forceinline__ Hit trace_generic(const uint32_t* __restrict__ xrows32, int rowdwords, const float P[3],
                                              const float d[3], int X, int Y, int Z, bool origin_in_grid, int max_steps,
                                              int self_lo, int self_hi)
@@ -769,7 +774,7 @@ __device__ __forceinline__ Hit trace_generic(const uint32_t* __restrict__ xrows3
     bool pos[3], zero[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        zero[a] = d[a] == 0.0f;
+        zero[a] = fabsf(d[a]) < kSmallest;
         pos[a] = d[a] > 0.0f;
         inv[a] = zero[a] ? 0.0f : __builtin_amdgcn_rcpf(d[a]);
     }
@@ -805,6 +810,7 @@ __device__ __forceinline__ Hit trace_generic(const uint32_t* __restrict__ xrows3
         float plane = (float)(c + (pos[a] ? 1 : 0));
         t_first[a] = zero[a] ? kInf : (plane - P[a]) * inv[a];
         dt[a] = fabsf(inv[a]);
+        if (!(t_first[a] == t_first[a])) { t_first[a] = kInf; dt[a] = 0.0f; }
         n[a] = 0.0f;
         t_next[a] = t_first[a];
         float planes_left = (float)(pos[a] ? dim[a] - 1 - c : c);

@@ -937,6 +937,37 @@ def test_direction_components_next_to_zero(lib, orc, grid, outside):
     assert (middle == 5).any() and (middle == 0).any() and (ref.edge_margin[:, :, W // 2] >= parity.EDGE_MARGIN).any()
 
 
+@pytest.mark.parametrize("grid,staged", [((24, 11, 6), 1), ((24, 11, 6), 0), ((70, 11, 6), 1), ((128, 128, 40), 0)])
+def test_per_cell_tracer_stays_in_the_grid(lib, orc, grid, staged):
+    """The per-cell tracer over rows in device memory (more layers than reserved, cameras outside by a hair or far outside) and
+    on chip (128x128x40), with direction components around the smallest float32 numbers: what the oracle sees.  Positions
+    that are not numbers, in any coordinate, give some image and leave the others' alone."""
+    X, Y, Z = grid
+    rng = np.random.default_rng(X + Z)
+    W, H, M = 9, 13, 6
+    tiny = [s * v for v in (1e-45, 5e-39, 2.0 ** -126, 2e-38, 1e-36, 1e-20, 0.0) for s in (-1, 1)]
+    views = [(x, y, 4.3, yaw, pitch) for x in (2.5, -1e-31) for y in (3.3, 7.0) for yaw in tiny for pitch in (-0.3, 0.2, tiny[1], tiny[2])]
+    far = [(-5000.0, y, z, yaw, pitch) for y in (3.3, 7.0) for z in (2.0, 4.3) for yaw in tiny for pitch in (0.0, tiny[0], tiny[2])]
+    nan = float("nan")
+    wild = [(*p, yaw, 0.2) for p in ((nan, 5.0, 3.0), (5.0, nan, 3.0), (5.0, 5.0, nan), (nan, nan, nan), (5.0, float("inf"), 3.0), (5.0, 5.0, -float("inf")))
+            for yaw in (0.0, 0.7, 2.0)] + [(5.0, 5.0, 3.0, nan, 0.2), (-1e-31, 5.0, 3.0, nan, 0.2)]
+    vox, pal = synth.random_world(rng, 1, grid, 0.03, M)
+    vox[:, 0] = np.where(rng.random((1, Y, X)) < 0.9, 1, 0)
+    vox[:, 1:, :, :6] = 0
+    cams = np.array(views + far + wild, np.float32)
+    spec = _mini_spec(1, len(cams), grid, W, H, M)
+    run = _gpu_for(spec, vox, pal, cams)
+    run.batch.debug_set_staged_layers(staged)
+    run.render()
+    g = run.numpy()
+    assert ((g.hit_index >= -1) & (g.hit_index < X * Y * Z)).all()
+    n = len(views)
+    spec = _mini_spec(1, n, grid, W, H, M)
+    ref = _oracle_for(orc, spec, vox, pal, cams[:n]).render()
+    _pixelwise_rule(run.numpy(np.arange(n)), ref, f"per cell, grid {grid}")
+    assert (ref.hit_index >= 0).any() and (ref.edge_margin[:, :, W // 2] >= parity.EDGE_MARGIN).any()
+
+
 @pytest.mark.parametrize("grid,image,aux", [((48, 44, 6), (48, 16), True), ((48, 44, 6), (48, 16), False), ((64, 64, 6), (40, 24), True),
                                             ((63, 64, 5), (40, 24), False), ((48, 44, 6), (33, 17), False), ((64, 40, 6), (33, 17), True)])
 def test_rays_that_pass_many_rows(lib, orc, grid, image, aux):
